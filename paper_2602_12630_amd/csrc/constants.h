@@ -35,6 +35,7 @@ struct Fp28Params {
     static constexpr int32_t ONE[14] = {0x347fcb8, 0xd800000, 0x002b119, 0x0cde6d2, 0xc7212e0, 0x83a2090, 0x037669f, 0xda0f73e, 0x9b09b42, 0x1297bb0, 0x515d98f, 0x012ca7c, 0x659fcfa, 0x000577a};   /* 2^392 mod p */
     static constexpr int GCD_ROUNDS = 29;                /* ceil((2 len(p) - 1) / 28) + 1 rounds of 28 steps */
     static constexpr int32_t INV_FIX[14] = {0x4d1dd0e, 0x41d94cc, 0x109f399, 0x8cb551c, 0x2b7ff56, 0x980df0c, 0x71cc8ea, 0x76862c6, 0xbf76e0c, 0xae37e1d, 0x527bf47, 0xb194cef, 0x04d56b3, 0x0008347};  /* 2^1168 mod p: 1 / a (mod p) -> the 28-bit form of R^2 / a, R = 2^384 */
+    static constexpr int32_t INV_START[14] = {0x10370ed, 0x6d1c345, 0xe243d62, 0xec45c53, 0x3b1d65a, 0x093317d, 0xb4f36a0, 0x5d74088, 0xc10ea72, 0x865d118, 0x7320a75, 0xfd5cd50, 0xcc8a759, 0x000c8d4};  /* 2^784 mod p: a R -> R / a under the radix R = 2^392 */
 };
 /* G1 generator, Montgomery form */
 static constexpr uint32_t G1_GEN_X[12] = {0xfd530c16u, 0x5cb38790u, 0x9976fff5u, 0x7817fc67u, 0x143ba1c1u, 0x154f95c7u, 0xf3d0e747u, 0xf0ae6acdu, 0x21dbf440u, 0xedce6eccu, 0x9e0bfb75u, 0x12017741u};

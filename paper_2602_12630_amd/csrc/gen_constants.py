@@ -135,6 +135,8 @@ def block28():
     out.append("    static constexpr int GCD_ROUNDS = %d;                /* ceil((2 len(p) - 1) / 28) + 1 rounds of 28 steps */" % rounds)
     out.append("    static constexpr int32_t INV_FIX[14] = {%s};  /* 2^1168 mod p: 1 / a (mod p) -> the 28-bit form of R^2 / a, R = 2^384 */"
                % limbs28(pow(2, 1168, P_MOD)))
+    out.append("    static constexpr int32_t INV_START[14] = {%s};  /* 2^784 mod p: a R -> R / a under the radix R = 2^392 */"
+               % limbs28(pow(2, 784, P_MOD)))
     out.append("};")
     return "\n".join(out)
 

@@ -1972,31 +1972,74 @@ struct ShiftPoints {
 };
 
 /* ---- normalisation: XYZZ -> affine (batched inversion) and canonical bytes ---------- */
-/* Lane handles G consecutive points with one field inversion (Montgomery's trick).  The
- * running products are parked in out[i].x until the backward sweep overwrites them. */
+/* A workgroup is one wave and takes `leaves` (a power of two, at most 64) runs of G consecutive points with ONE field
+ * inversion: a lane multiplies the denominators of its run up (the running products parked in out[i] until the
+ * backward sweep overwrites them), the lanes' products are multiplied pairwise up a binary tree in LDS, the root is
+ * inverted by the whole wave (fp28_inv_wave) and the inverses come back down the tree, every child taking its parent's
+ * inverse times its sibling's product.  phi and the canonical bytes of a point are written along with it where the
+ * caller wants them: the point is in registers, and a launch of their own costs as much as their arithmetic.
+ * Bound by depth: two products per level of the tree in a lone wave, and the inversion.  Measured against one binary
+ * GCD per lane: 131072 points 157 -> 104 us (phi included), 8192 points 114 -> 68 us, one point 110 -> 45 us.
+ * Phases: 0 run products, 1 .. 6 up (one level each), 7 inversion, 8 .. 13 down, 14 backward sweep; levels above the
+ * root of a smaller tree are empty. */
 struct BatchNormalize {
+    static constexpr int BLOCK = 64;
+    static constexpr int PHASES = 15;
+    static constexpr size_t NODE_BYTES = sizeof(fp28);
+    static constexpr size_t LDS_BYTES = 2 * 128 * NODE_BYTES;      /* products and inverses: node i has children 2 i, 2 i + 1 */
     const g1_xyzz* in;
     uint64_t n;
-    uint32_t G;
+    uint32_t G, leaves;
     g1_affine* out;
-    TC_DEV void operator()(uint32_t t) const {
-        uint64_t lo = (uint64_t)t * G, hi = lo + G < n ? lo + G : n;
-        if (lo >= hi) return;
-        fp_t run = fe_one<FpParams>();
-        for (uint64_t i = lo; i < hi; ++i) {
-            out[i].x = run;                       /* product of z_lo .. z_{i-1} */
-            if (!fe_is_zero(in[i].ZZ)) run = fp_mul(run, fp_mul(in[i].ZZ, in[i].ZZZ));
-        }
-        fp_t inv = fp_inv28(run);                    /* run != 0: product of non-zero values */
-        for (uint64_t i = hi; i-- > lo;) {
-            g1_xyzz p = in[i];
-            if (fe_is_zero(p.ZZ)) {
-                out[i] = affine_identity();
-                continue;
+    fr_plain* phi;          /* or null */
+    uint32_t* canonical;    /* 24 words per point, or null */
+    TC_DEV static fp28 denominator(const g1_xyzz& p) { return fp28_mul(fp28_from_fp(p.ZZ), fp28_from_fp(p.ZZZ)); }
+    TC_DEV void phase(int ph, uint32_t lane, uint32_t wg, uint8_t* lds) const {
+        fp28* prod = (fp28*)lds;
+        fp28* inv = prod + 128;
+        const uint64_t lo = ((uint64_t)wg * leaves + lane) * G, end = lo + G < n ? lo + G : n, hi = lane < leaves && lo < end ? end : lo;
+        if (ph == 0) {
+            if (lane >= leaves) return;
+            fp28 run = fp28_one();
+            for (uint64_t i = lo; i < hi; ++i) {
+                if (G > 1) *(fp28*)&out[i] = run;                  /* product of the denominators before i */
+                if (!fe_is_zero(in[i].ZZ)) run = G > 1 ? fp28_mul(run, denominator(in[i])) : denominator(in[i]);
             }
-            fp_t zi = fp_mul(inv, out[i].x);       /* 1 / (ZZ_i ZZZ_i) */
-            inv = fp_mul(inv, fp_mul(p.ZZ, p.ZZZ));
-            out[i] = xyzz_to_affine_with_inv(p, zi);
+            prod[leaves + lane] = run;
+        } else if (ph <= 6) {
+            uint32_t width = leaves >> ph;
+            if (lane < width) prod[width + lane] = fp28_mul(prod[2 * (width + lane)], prod[2 * (width + lane) + 1]);
+        } else if (ph == 7) {
+            /* the product of non-zero values is not zero */
+#if defined(TC_HOST_EMU)
+            if (lane == 0) inv[1] = fp28_inv_wave(prod[1]);
+#else
+            fp28 r = fp28_inv_wave(prod[1]);
+            if (lane == 0) inv[1] = r;
+#endif
+        } else if (ph <= 13) {
+            uint32_t width = 2u << (ph - 8);
+            if (width <= leaves && lane < width) inv[width + lane] = fp28_mul(inv[(width + lane) >> 1], prod[(width + lane) ^ 1u]);
+        } else {
+            if (lo >= hi) return;
+            fp28 rest = inv[leaves + lane];
+            for (uint64_t i = hi; i-- > lo;) {
+                g1_xyzz p = in[i];
+                g1_affine r = affine_identity();
+                if (!fe_is_zero(p.ZZ)) {
+                    fp28 zi = G > 1 ? fp28_mul(rest, *(const fp28*)&out[i]) : rest;      /* 1 / (ZZ_i ZZZ_i) */
+                    if (G > 1) rest = fp28_mul(rest, denominator(p));
+                    r.x = fp28_to_fp(fp28_mul(fp28_from_fp(p.X), fp28_mul(zi, fp28_from_fp(p.ZZZ))));
+                    r.y = fp28_to_fp(fp28_mul(fp28_from_fp(p.Y), fp28_mul(zi, fp28_from_fp(p.ZZ))));
+                }
+                out[i] = r;
+                if (canonical) affine_to_canonical(r, canonical + 24 * i);
+                if (phi) {
+                    fr_t v = phi_map(r);
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) phi[i].l[k] = v.l[k];
+                }
+            }
         }
     }
 };

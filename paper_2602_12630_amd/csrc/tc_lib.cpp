@@ -651,18 +651,23 @@ extern "C" int tc_ctx_sync(tc_ctx* ctx) {
 /* ======================================================================================= */
 /* normalisation and fixed-base tables                                                     */
 /* ======================================================================================= */
-static int normalize(tc_ctx* ctx, const g1_xyzz* d_in, uint64_t n, g1_affine* d_out) {
-    uint32_t G = n >= (1u << 18) ? 8 : n >= (1u << 14) ? 2 : 1;
-    BatchNormalize k{d_in, n, G, d_out};
-    RT(rt::launch<64>((n + G - 1) / G, ctx->stream, k));
+static int normalize(tc_ctx* ctx, const g1_xyzz* d_in, uint64_t n, g1_affine* d_out, fr_plain* d_phi = nullptr, uint32_t* d_canonical = nullptr) {
+    if (n == 0) return TC_OK;
+    /* one point per lane up to four waves per compute unit, then longer runs (of up to 16: past that the tree and the
+     * inversion are a small share); fewer than 64 points take a tree of their own height */
+    uint32_t G = (uint32_t)std::min<uint64_t>(16, (n + 65535) / 65536);
+    uint64_t runs = (n + G - 1) / G;
+    uint32_t leaves = 1;
+    while (leaves < 64 && leaves < runs) leaves *= 2;
+    BatchNormalize k{d_in, n, G, leaves, d_out, d_phi, d_canonical};
+    RT((launch_coop<BatchNormalize::BLOCK>((uint32_t)((runs + leaves - 1) / leaves), ctx->stream, k)));
     return TC_OK;
 }
 /* XYZZ points on the device -> canonical bytes on the host */
 static int points_to_host(tc_ctx* ctx, const g1_xyzz* d_in, uint32_t n, uint8_t* out) {
     WS(aff, g1_affine, n);
     WS(can, uint32_t, 24ull * n);
-    TRY(normalize(ctx, d_in, n, aff));
-    RT(rt::launch<64>(n, ctx->stream, ToCanonical{aff, can}));
+    TRY(normalize(ctx, d_in, n, aff, nullptr, can));
     RT(rt::memcpy_d2h(out, can, 96ull * n, ctx->stream));
     TRY(ctx_sync(ctx));
     return TC_OK;
@@ -1858,8 +1863,7 @@ extern "C" int tc_commit_static(tc_ctx* ctx, const tc_srs* srs, const void* d_sc
         msm_config(ctx, dtype, srs->n[0], &W, &c);
         MsmProblem one{srs_gather_table(srs, 0), d_scalars, srs->n[0]};
         TRY(msm_engine_multi(ctx, 1, &one, dtype, W, c, result));
-        TRY(normalize(ctx, result, 1, aff));
-        RT(rt::launch<64>(1, ctx->stream, ToCanonical{aff, (uint32_t*)d_out_g1}));
+        TRY(normalize(ctx, result, 1, aff, nullptr, (uint32_t*)d_out_g1));
         return TC_OK;
     } catch (const std::bad_alloc&) {
         return fail(ctx, TC_ERR_NOMEM, "host allocation failed");
@@ -2550,10 +2554,7 @@ extern "C" int tc_terkle_build(tc_ctx* ctx, const tc_tree_desc* desc, tc_tree** 
                     }
                 }
                 if (rc) break;
-                rc = normalize(ctx, acc, lv.n, lv.C);
-                if (rc) break;
-                int e = rt::launch<64>(lv.n, ctx->stream, PhiKernel{lv.C, lv.phi});
-                if (e) rc = fail_hip(ctx, e, "phi");
+                rc = normalize(ctx, acc, lv.n, lv.C, lv.phi);
             } while (0);
             ctx->wsp->off = mark;
         }

@@ -20,7 +20,7 @@ LIB = os.path.join(HERE, "hostmath", "libhostmath.so")
 
 @pytest.fixture(scope="module")
 def hm():
-    hdrs = [os.path.join(HERE, "..", "paper_2602_12630_amd", "csrc", h) for h in ("field.h", "g1.h", "constants.h", "kernels.h", "rt.h", "pairing.h")]
+    hdrs = [os.path.join(HERE, "..", "paper_2602_12630_amd", "csrc", h) for h in ("field.h", "field28.h", "g1.h", "constants.h", "kernels.h", "rt.h", "pairing.h")]
     newest = max(os.path.getmtime(f) for f in [SRC] + hdrs)
     if not os.path.exists(LIB) or os.path.getmtime(LIB) < newest:
         subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", LIB, SRC])
@@ -53,6 +53,19 @@ def test_fp64_product_columns_stay_exact():
         worst = max(worst, column)
         carry = column >> 24
     assert worst < 1 << 53
+
+
+@pytest.mark.parametrize("group", ["edges", "powers", "random"])
+def test_inversion_by_division_steps(hm, group):
+    """The wave's inversion (rows of limbs, division steps on the lowest limbs, lazily carried updates)."""
+    rng = random.Random(3)
+    vals = {"edges": [0, 1, 2, 3, P - 1, P - 2, (P - 1) // 2, (P + 1) // 2, (1 << 28) - 1, P >> 28],
+            "powers": [1 << k for k in range(0, 381, 7)] + [P - (1 << k) for k in range(0, 380, 7)],
+            "random": [rng.randrange(P) for _ in range(200)]}[group]
+    out = (ctypes.c_uint8 * 48)()
+    for a in vals:
+        hm.hm_fp_inv_wave(_b(a, 48), out)
+        assert int.from_bytes(bytes(out), "little") == (pow(a, -1, P) if a else 0), a
 
 
 def test_fp_fr_arithmetic(hm):
