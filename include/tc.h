@@ -371,16 +371,17 @@ int tc_terkle_update(tc_ctx* ctx, tc_tree* tree, const uint32_t* leaf_index, con
  * 32 bytes, device memory. */
 
 /* d_coeffs = monomial coefficients of the polynomial with f(zeta) = T[zeta] on the grid prod_j {1..d_j}
- * (Sec. 4, Com; one axis at a time in Newton form, App. C: divided differences on the equispaced nodes, then
- * expansion of the nested products).  m <= TC_MAX_INTERP_ORDER axes; the scalars as in tc_commit. */
+ * (Sec. 4, Com; one axis at a time, App. C: in Newton form, divided differences on the equispaced nodes and
+ * expansion of the nested products, or, axes of middle length, in barycentric form over a tree of the nodes).
+ * m <= TC_MAX_INTERP_ORDER axes; the scalars as in tc_commit. */
 #define TC_MAX_INTERP_ORDER 12
 int tc_interpolate(tc_ctx* ctx, int m, const uint32_t* shape, const void* d_scalars, int dtype, void* d_coeffs);
 /* The same coefficients through one of the three interpolation forms of App. C, the comparison of Fig. 1:
- * Newton (divided differences; what tc_interpolate uses), Gregory (forward differences Delta^k T[0] on the
- * equispaced grid, weights binom(X - zeta_0, k)) or barycentric (weights beta_l, the interpolant assembled as
+ * Newton (divided differences; tc_interpolate takes a tree over the nodes of an axis instead where that is
+ * faster), Gregory (forward differences Delta^k T[0] on the equispaced grid, weights binom(X - zeta_0, k)) or barycentric (weights beta_l, the interpolant assembled as
  * sum_l beta_l T_l prod_(r != l) (X - zeta_r) node by node).  All three return the identical array; they differ
  * in their steps and running time.  The barycentric form needs five Fr arrays of the tensor's size as
- * workspace, the others three.  Unknown form: TC_ERR_ARG. */
+ * workspace, the others three (tc_interpolate two and its tables).  Unknown form: TC_ERR_ARG. */
 #define TC_INTERP_NEWTON 0
 #define TC_INTERP_GREGORY 1
 #define TC_INTERP_BARYCENTRIC 2

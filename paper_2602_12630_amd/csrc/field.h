@@ -274,7 +274,7 @@ __device__ __forceinline__ void carry_into(uint32_t& hi, uint64_t carry) {
 /* (volatile keeps the multiply-adds and the carry additions in the order written here; sending the unused
  * carry-out of the addition to VCC instead of an SGPR pair made the accumulation kernels 3 % slower) */
 /* LATE = false adds every carry at once, in an order the compiler is free to choose: the 8-limb products of the
- * interpolation kernel, eight waves to a SIMD, never wait for a carry and ran 6 % faster that way (242 against
+ * line-by-line interpolation kernel, eight waves to a SIMD, never wait for a carry and ran 6 % faster that way (242 against
  * 256 ms for the 512 x 4096 tensor); the 12-limb products of kernels with three waves to a SIMD take it late. */
 template <bool LATE>
 __device__ __forceinline__ void macp_vv(Acc96P& A, uint32_t a, uint32_t b) {
@@ -562,62 +562,65 @@ __device__ fr_t fr_mul(const fr_t& a, const fr_t& b);
 __device__ fp_t fp_mul_lat(const fp_t& a, const fp_t& b);
 __device__ fp_t fp_sqr_lat(const fp_t& a);
 #endif
-/* Host code multiplies in Fp on 64-bit limbs: the same Montgomery representation (R = 2^384; the bytes of an
+/* Host code multiplies on 64-bit limbs: the same Montgomery representation (R = 2^(32 N); the bytes of an
  * element are its little-endian value either way), about four times faster on a CPU than the 32-bit limbs that
  * suit the GPU.  Used by everything the library computes on the host (set-up tables, the pairing verifier) and
  * by the CPU builds of the kernels. */
-inline fp_t fp_mul_host64(const fp_t& a, const fp_t& b) {
+template <class P>
+inline Fe<P> fe_mul_host64(const Fe<P>& a, const Fe<P>& b) {
     typedef unsigned __int128 u128;
-    uint64_t q[6], x[6], y[6], t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int i = 0; i < 6; ++i) q[i] = (uint64_t)FpParams::MOD[2 * i] | ((uint64_t)FpParams::MOD[2 * i + 1] << 32);
+    constexpr int N = P::N / 2;
+    uint64_t q[N], x[N], y[N], t[N + 2] = {};
+    for (int i = 0; i < N; ++i) q[i] = (uint64_t)P::MOD[2 * i] | ((uint64_t)P::MOD[2 * i + 1] << 32);
     uint64_t inv = 1;
     for (int i = 0; i < 6; ++i) inv *= 2 - q[0] * inv;       /* Newton: q[0]^-1 mod 2^64 */
     inv = 0 - inv;
-    memcpy(x, a.l, 48);
-    memcpy(y, b.l, 48);
-    for (int i = 0; i < 6; ++i) {
+    memcpy(x, a.l, 8 * N);
+    memcpy(y, b.l, 8 * N);
+    for (int i = 0; i < N; ++i) {
         u128 c = 0;
-        for (int j = 0; j < 6; ++j) {
+        for (int j = 0; j < N; ++j) {
             c += (u128)x[j] * y[i] + t[j];
             t[j] = (uint64_t)c;
             c >>= 64;
         }
-        c += t[6];
-        t[6] = (uint64_t)c;
-        t[7] = (uint64_t)(c >> 64);
+        c += t[N];
+        t[N] = (uint64_t)c;
+        t[N + 1] = (uint64_t)(c >> 64);
         uint64_t m = t[0] * inv;
         c = ((u128)m * q[0] + t[0]) >> 64;
-        for (int j = 1; j < 6; ++j) {
+        for (int j = 1; j < N; ++j) {
             c += (u128)m * q[j] + t[j];
             t[j - 1] = (uint64_t)c;
             c >>= 64;
         }
-        c += t[6];
-        t[5] = (uint64_t)c;
-        t[6] = t[7] + (uint64_t)(c >> 64);
+        c += t[N];
+        t[N - 1] = (uint64_t)c;
+        t[N] = t[N + 1] + (uint64_t)(c >> 64);
     }
-    uint64_t d[6];
+    uint64_t d[N];
     u128 bw = 0;
-    for (int j = 0; j < 6; ++j) {                            /* t < 2 q: one conditional subtraction */
+    for (int j = 0; j < N; ++j) {                            /* t < 2 q: one conditional subtraction */
         u128 s = (u128)t[j] - q[j] - (uint64_t)bw;
         d[j] = (uint64_t)s;
         bw = (s >> 64) & 1;
     }
-    bool take = t[6] != 0 || bw == 0;
-    fp_t r;
-    memcpy(r.l, take ? d : t, 48);
+    bool take = t[N] != 0 || bw == 0;
+    Fe<P> r;
+    memcpy(r.l, take ? d : t, 8 * N);
     return r;
 }
+inline fp_t fp_mul_host64(const fp_t& a, const fp_t& b) { return fe_mul_host64<FpParams>(a, b); }
 #if defined(__HIPCC__)
 __host__ inline fp_t fp_mul(const fp_t& a, const fp_t& b) { return fp_mul_host64(a, b); }
 __host__ inline fp_t fp_sqr(const fp_t& a) { return fp_mul_host64(a, a); }
-__host__ inline fr_t fr_mul(const fr_t& a, const fr_t& b) { return fe_mul<FrParams>(a, b); }
+__host__ inline fr_t fr_mul(const fr_t& a, const fr_t& b) { return fe_mul_host64<FrParams>(a, b); }
 __host__ inline fp_t fp_mul_lat(const fp_t& a, const fp_t& b) { return fp_mul_host64(a, b); }
 __host__ inline fp_t fp_sqr_lat(const fp_t& a) { return fp_mul_host64(a, a); }
 #else
 inline fp_t fp_mul(const fp_t& a, const fp_t& b) { return fp_mul_host64(a, b); }
 inline fp_t fp_sqr(const fp_t& a) { return fp_mul_host64(a, a); }
-inline fr_t fr_mul(const fr_t& a, const fr_t& b) { return fe_mul<FrParams>(a, b); }
+inline fr_t fr_mul(const fr_t& a, const fr_t& b) { return fe_mul_host64<FrParams>(a, b); }
 inline fp_t fp_mul_lat(const fp_t& a, const fp_t& b) { return fp_mul_host64(a, b); }
 inline fp_t fp_sqr_lat(const fp_t& a) { return fp_mul_host64(a, a); }
 #endif

@@ -113,6 +113,13 @@ def block(name, mod, n):
     out.append("    static constexpr uint32_t GCD_FIX[%d] = {%s}; /* 4^GCD_ROUNDS * R^3 mod q */"
                % (n, limbs(pow(4, rounds, mod) * pow(Rm, 3, mod) % mod, n)))
     out.append("    static constexpr uint32_t HALF[%d] = {%s};  /* (q - 1) / 2 */" % (n, limbs((mod - 1) // 2, n)))
+    if mod == R_MOD:
+        two_adicity = (mod - 1 & -(mod - 1)).bit_length() - 1
+        g = next(g for g in range(2, 100) if pow(g, (mod - 1) // 2, mod) == mod - 1)       # no square: full 2-power order
+        root = pow(g, (mod - 1) >> two_adicity, mod)
+        out.append("    static constexpr int TWO_ADICITY = %d;" % two_adicity)
+        out.append("    static constexpr uint32_t ROOT[%d] = {%s};  /* a root of unity of order 2^TWO_ADICITY, Montgomery form */"
+                   % (n, limbs(root * Rm % mod, n)))
     out.append("};")
     return "\n".join(out)
 

@@ -3099,6 +3099,254 @@ struct InterpAxisBarycentric {
         }
     }
 };
+/* The same interpolation in O(d log^2 d) products per line instead of O(d^2): the barycentric sum
+ * f(X) = sum_l w_l prod_(r != l) (X - zeta_r), w_l = beta_l T_l, over a binary tree of the nodes.  A node of the tree with
+ * children L and R has P = P_L M_R + P_R M_L with M = prod (X - zeta_r) over its leaves, and every polynomial is held by
+ * its values on the roots of unity of the order of its size, in bit-reversed order, where the first half of a parent's
+ * domain is its children's domain and the second half the odd powers: half of P comes from the children's values as they
+ * stand, the other half after an inverse transform, a twist by powers of the parent's root and a transform.  Leaves past
+ * d (n = 2^logn >= d) are zero with M = 1, so any d will do.  M depends on the grid alone: InterpNodesDirect, InterpNodeTables.
+ *
+ * A workgroup owns a tile of whole lines in LDS, in two planes of 16 bytes per element (lanes one element apart then
+ * touch all banks).  At n = 4096 some 100 products per element against 4095.
+ * Bound by the multiply-adds of those products (84 to 95 a nanosecond); 2 097 152 entries: axis of 4096 183 -> 2.43 ms,
+ * axis of 512 56 -> 1.45 ms against the differences line by line, and 0.30 ms for the tables of both axes. */
+struct alignas(16) FrHalf { uint32_t v[4]; };
+struct InterpRoots {           /* lane t: roots[t] = omega_(2 s)^j and twist[t] = roots[t] / s for t = s + j, s = 2^k, j < s */
+    fr_t order[17];            /* order[k]: root of unity of order 2^k */
+    fr_t half_pow[17];         /* 2^-k */
+    fr_t* roots;
+    fr_t* twist;
+    TC_DEV void operator()(uint32_t t) const {
+        if (t == 0) return;
+        int k = 31 - __builtin_clz(t);
+        uint32_t j = t - (1u << k);
+        fr_t v = fe_one<FrParams>();
+        for (int b = 0; b < k; ++b)
+            if (j >> b & 1u) v = fr_mul(v, order[k + 1 - b]);
+        roots[t] = v;
+        twist[t] = fr_mul(v, half_pow[k]);
+    }
+};
+struct InterpWeights {         /* lane l: beta_l / n = (-1)^(d-1-l) / (n l! (d-1-l)!), nodes 1 .. d */
+    const fr_t* inv_fact;
+    uint32_t d;
+    fr_t inv_n;
+    fr_t* weights;
+    TC_DEV void operator()(uint32_t l) const {
+        fr_t v = fr_mul(fr_mul(inv_fact[l], inv_fact[d - 1 - l]), inv_n);
+        weights[l] = ((d - 1 - l) & 1u) ? fr_neg(v) : v;
+    }
+};
+struct InterpTile {            /* elements of a tile in LDS, and the transforms on blocks of them */
+    FrHalf* lo;
+    FrHalf* hi;
+    const fr_t* roots;
+    const fr_t* twist;
+    TC_DEV fr_t get(uint32_t i) const {
+        FrHalf a = lo[i], b = hi[i];
+        fr_t r;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { r.l[k] = a.v[k]; r.l[4 + k] = b.v[k]; }
+        return r;
+    }
+    TC_DEV void put(uint32_t i, const fr_t& r) const {
+        FrHalf a, b;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { a.v[k] = r.l[k]; b.v[k] = r.l[4 + k]; }
+        lo[i] = a;
+        hi[i] = b;
+    }
+    /* x / omega_(2 s)^j up to the sign: omega_(2 s)^(-j) = -omega_(2 s)^(s - j) */
+    TC_DEV void inverse_butterfly(uint32_t s, uint32_t j, fr_t& u, fr_t& v) const {
+        if (s > 1) v = fr_mul(v, roots[j ? 2 * s - j : s]);
+        fr_t a = fr_add(u, v), b = fr_sub(u, v);
+        u = j ? b : a;
+        v = j ? a : b;
+    }
+    TC_DEV void forward_butterfly(uint32_t s, uint32_t j, fr_t& u, fr_t& v) const {
+        fr_t a = fr_add(u, v), b = fr_sub(u, v);
+        u = a;
+        v = s > 1 ? fr_mul(b, roots[s + j]) : b;
+    }
+    TC_DEV void inverse_stage(uint32_t k, uint32_t p) const {
+        uint32_t s = 1u << k, j = p & (s - 1), i = (p >> k << (k + 1)) + j;
+        fr_t u = get(i), v = get(i + s);
+        inverse_butterfly(s, j, u, v);
+        put(i, u);
+        put(i + s, v);
+    }
+    /* stage e (of 2 t - 1) of: values of blocks of 2^t on their domain -> values on the odd powers of the parent's root;
+     * the last stage back, the twist and the first stage forth have the same pairs and share a phase */
+    static TC_HD int extend_stages(int t) { return t ? 2 * t - 1 : 0; }
+    TC_DEV void extend_stage(int t, int e, uint32_t p) const {
+        if (e < t - 1) return inverse_stage((uint32_t)e, p);
+        uint32_t k = (uint32_t)(e == t - 1 ? t - 1 : 2 * t - 2 - e);
+        uint32_t s = 1u << k, j = p & (s - 1), i = (p >> k << (k + 1)) + j;
+        fr_t u = get(i), v = get(i + s);
+        if (e == t - 1) {
+            inverse_butterfly(s, j, u, v);
+            u = fr_mul(u, twist[2 * s + j]);
+            v = fr_mul(v, twist[3 * s + j]);
+        }
+        forward_butterfly(s, j, u, v);
+        put(i, u);
+        put(i + s, v);
+    }
+};
+/* M of all nodes with 2^t leaves of an axis, at t << logn: even[i], odd[i] = values of the node of leaf i on its own
+ * domain and on the odd powers of its parent's root.  All distinct axes of a call in the same launches: a table is a
+ * chain of some hundred dependent products however short the axis. */
+struct InterpTables {
+    fr_t* even;
+    fr_t* odd;
+    uint32_t d;
+    int logn;
+};
+static constexpr int INTERP_MAX_AXES = 12;
+/* The small nodes point by point, at most 2^(LEVELS - 1) products in a row: all of them in one launch and shorter than
+ * level by level (41 against 76 us at LEVELS = 6). */
+struct InterpNodesDirect {
+    static constexpr int LEVELS = 6;
+    InterpTables axis[INTERP_MAX_AXES];
+    uint32_t first[INTERP_MAX_AXES + 1];      /* lanes: axis, then level, then even / odd, then leaf */
+    const fr_t* roots;
+    static uint32_t lanes(const InterpTables& a) { return (uint32_t)(a.logn < LEVELS ? a.logn : LEVELS) << (a.logn + 1); }
+    TC_DEV void operator()(uint32_t lane) const {
+        uint32_t x = 0;
+        while (lane >= first[x + 1]) ++x;
+        const InterpTables& a = axis[x];
+        lane -= first[x];
+        const uint32_t t = lane >> (a.logn + 1), odd = lane >> a.logn & 1u, g = lane & ((1u << a.logn) - 1), h = 1u << t;
+        /* the point: power m of the root of order 2 h */
+        uint32_t j = g & (h - 1), m = odd;
+        for (uint32_t b = 0; b < t; ++b) m |= (j >> b & 1u) << (t - b);
+        fr_t point = roots[h + (m & (h - 1))], v = fe_one<FrParams>();
+        if (m >= h) point = fr_neg(point);
+        const uint32_t lo = g - j, hi = lo + h < a.d ? lo + h : a.d;
+        fr_t zeta = fe_from_u32<FrParams>(lo + 1);
+        for (uint32_t l = lo; l < hi; ++l) {
+            v = fr_mul(v, fr_sub(point, zeta));
+            zeta = fr_add(zeta, fe_one<FrParams>());
+        }
+        (odd ? a.odd : a.even)[((size_t)t << a.logn) + g] = v;
+    }
+};
+/* The larger ones level by level, each from the tables of t - 1; a workgroup takes max(2^t, 256) elements.  M of a full
+ * node is monic of degree 2^t: on its own domain X^(2^t) = 1, on the odd powers -1, so the extension is off by 2. */
+struct InterpNodeTables {
+    static constexpr int BLOCK = 1024;
+    static constexpr uint32_t TILE = 2048, CHUNK = 256;
+    static constexpr size_t LDS_BYTES = TILE * 32;
+    InterpTables axis[INTERP_MAX_AXES];
+    uint32_t first[INTERP_MAX_AXES + 1];      /* workgroups */
+    const fr_t* roots;
+    const fr_t* twist;
+    int t;
+    static uint32_t chunk(const InterpTables& a, int t) {
+        uint32_t n = 1u << a.logn, least = n < CHUNK ? n : CHUNK;
+        return (1u << t) > least ? 1u << t : least;
+    }
+    int phases() const { return InterpTile::extend_stages(t) + 2; }
+    TC_DEV void phase(int ph, uint32_t lane, uint32_t wg, uint8_t* lds) const {
+        uint32_t ax = 0;
+        while (wg >= first[ax + 1]) ++ax;
+        const InterpTables& a = axis[ax];
+        InterpTile x{(FrHalf*)lds, (FrHalf*)lds + TILE, roots, twist};
+        const uint32_t n = 1u << a.logn, h = 1u << t, least = n < CHUNK ? n : CHUNK, elements = h > least ? h : least;
+        const uint32_t base = (wg - first[ax]) * elements;
+        fr_t* even = a.even + ((size_t)t << a.logn);
+        fr_t* odd = a.odd + ((size_t)t << a.logn);
+        if (ph == 0) {
+            for (uint32_t i = lane; i < elements; i += BLOCK) {
+                uint32_t g = base + i, j = g & (h - 1), half = h >> 1, left = g - j + (j & (half - 1));
+                const fr_t* below = (j < half ? even : odd) - n;
+                fr_t v = fr_mul(below[left], below[left + half]);
+                even[g] = v;
+                x.put(i, v);
+            }
+        } else if (ph <= InterpTile::extend_stages(t)) {
+            for (uint32_t p = lane; p < elements / 2; p += BLOCK) x.extend_stage(t, ph - 1, p);
+        } else {
+            const fr_t two = fe_from_u32<FrParams>(2);
+            for (uint32_t i = lane; i < elements; i += BLOCK) {
+                uint32_t g = base + i;
+                fr_t v = x.get(i);
+                odd[g] = ((g >> t) + 1) << t <= a.d ? fr_sub(v, two) : v;
+            }
+        }
+    }
+};
+struct InterpAxisTree {
+    static constexpr int BLOCK = 1024;
+    static constexpr uint32_t TILE = 4096;
+    static constexpr size_t LDS_BYTES = TILE * 32;
+    fr_t* data;                /* (outer, d, inner), in place */
+    fr_t* half;                /* lines_per_wg * n / 2 elements per workgroup: the even half of a level while the odd half is computed */
+    uint64_t outer, inner;
+    uint32_t d, lines_per_wg;
+    int logn;                  /* lines_per_wg << logn <= TILE */
+    const fr_t* weights;
+    const fr_t* roots;
+    const fr_t* twist;
+    const fr_t* even;          /* tables of level t at t << logn */
+    const fr_t* odd;
+    int phases() const {
+        int ph = 2 + logn;
+        for (int t = 0; t < logn; ++t) ph += InterpTile::extend_stages(t) + 2;
+        return ph;
+    }
+    TC_DEV fr_t* element(uint32_t wg, uint32_t local, uint32_t k) const {
+        uint64_t line = (uint64_t)wg * lines_per_wg + local;
+        return line < outer * inner && k < d ? data + ((line / inner) * d + k) * inner + line % inner : nullptr;
+    }
+    TC_DEV void phase(int ph, uint32_t lane, uint32_t wg, uint8_t* lds) const {
+        InterpTile x{(FrHalf*)lds, (FrHalf*)lds + TILE, roots, twist};
+        const uint32_t n = 1u << logn, elements = lines_per_wg << logn, pairs = elements >> 1;
+        if (ph == 0) {
+            /* neighbouring lines first where they are neighbours in memory */
+            for (uint32_t i = lane; i < elements; i += BLOCK) {
+                uint32_t local = inner > 1 ? i % lines_per_wg : i >> logn, k = inner > 1 ? i / lines_per_wg : i & (n - 1);
+                const fr_t* at = element(wg, local, k);
+                x.put((local << logn) + k, at ? fr_mul(*at, weights[k]) : fe_zero<FrParams>());
+            }
+            return;
+        }
+        int r = ph - 1, t = 0;
+        while (t < logn && r >= InterpTile::extend_stages(t) + 2) {
+            r -= InterpTile::extend_stages(t) + 2;
+            ++t;
+        }
+        if (t < logn) {
+            const uint32_t h = 1u << t, odd_phase = (uint32_t)InterpTile::extend_stages(t) + 1;
+            const bool at_odd = (uint32_t)r == odd_phase;
+            if (r == 0 || at_odd) {
+                const fr_t* m = (at_odd ? odd : even) + ((size_t)t << logn);
+                fr_t* keep = half + (size_t)wg * pairs;
+                for (uint32_t p = lane; p < pairs; p += BLOCK) {
+                    uint32_t i = (p >> t << (t + 1)) + (p & (h - 1)), at = i & (n - 1);
+                    fr_t v = fr_add(fr_mul(x.get(i), m[at + h]), fr_mul(x.get(i + h), m[at]));
+                    if (at_odd) {
+                        x.put(i, keep[p]);
+                        x.put(i + h, v);
+                    } else {
+                        keep[p] = v;
+                    }
+                }
+            } else {
+                for (uint32_t p = lane; p < pairs; p += BLOCK) x.extend_stage(t, r - 1, p);
+            }
+        } else if (r < logn) {
+            for (uint32_t p = lane; p < pairs; p += BLOCK) x.inverse_stage((uint32_t)r, p);
+        } else {
+            for (uint32_t i = lane; i < elements; i += BLOCK) {
+                uint32_t local = inner > 1 ? i % lines_per_wg : i >> logn, k = inner > 1 ? i / lines_per_wg : i & (n - 1);
+                fr_t* at = element(wg, local, k);
+                if (at) *at = x.get((local << logn) + k);
+            }
+        }
+    }
+};
 struct ScalarsToFr {           /* any scalar type -> Montgomery Fr */
     const void* scalars;
     int dtype;

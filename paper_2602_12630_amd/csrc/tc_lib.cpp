@@ -363,6 +363,13 @@ __global__ __launch_bounds__(BLOCK) void coop_kernel_n(const F f, int phases) {
 template <int BLOCK, class F>
 static int launch_coop_n(uint32_t groups, rt::stream_t st, const F& f, int phases) {
     if (!groups || phases <= 0) return 0;
+    static std::once_flag attr_once;
+    static int attr_error = 0;
+    std::call_once(attr_once, [] {
+        attr_error = (int)hipFuncSetAttribute(reinterpret_cast<const void*>(&coop_kernel_n<F, BLOCK>),
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)F::LDS_BYTES);
+    });
+    if (attr_error) return attr_error;
     hipLaunchKernelGGL((coop_kernel_n<F, BLOCK>), dim3(groups), dim3(BLOCK), F::LDS_BYTES, st, f, phases);
     return (int)hipGetLastError();
 }
@@ -3161,36 +3168,146 @@ static bool interp_shape_ok(int m, const uint32_t* shape, uint64_t* total) {
     return true;
 }
 
-extern "C" int tc_interpolate_form(tc_ctx* ctx, int m, const uint32_t* shape, const void* d_scalars, int dtype, int form,
-                                   void* d_coeffs) {
+/* What the tree over the nodes of an axis needs of the grid: roots of unity up to the longest axis, and per distinct
+ * axis length the tables of its nodes. */
+struct InterpPlan {
+    InterpRoots roots;
+    fr_t* inv_fact;                   /* 1 / l! up to the longest axis */
+    uint32_t count = 0;
+    InterpTables axis[INTERP_MAX_AXES];
+    const InterpTables* tables(uint32_t d) const {
+        for (uint32_t i = 0; i < count; ++i)
+            if (axis[i].d == d) return &axis[i];
+        return nullptr;
+    }
+};
+static int interp_plan(tc_ctx* ctx, InterpPlan& plan, uint32_t count, const uint32_t* lengths) {
+    InterpRoots& roots = plan.roots;
+    fr_t w;
+    for (int i = 0; i < 8; ++i) w.l[i] = FrParams::ROOT[i];
+    const int top = (int)(sizeof roots.order / sizeof roots.order[0]) - 1;
+    for (int k = FrParams::TWO_ADICITY; k >= 0; --k, w = fr_mul(w, w))
+        if (k <= top) roots.order[k] = w;
+    const fr_t half = fe_inv_fermat<FrParams>(fe_from_u32<FrParams>(2));
+    roots.half_pow[0] = fe_one<FrParams>();
+    for (int k = 1; k <= top; ++k) roots.half_pow[k] = fr_mul(roots.half_pow[k - 1], half);
+    int logmax = 0;
+    for (uint32_t i = 0; i < count; ++i) {
+        if (plan.tables(lengths[i])) continue;
+        InterpTables& a = plan.axis[plan.count];
+        a.d = lengths[i];
+        a.logn = 1;
+        while ((1u << a.logn) < a.d) ++a.logn;
+        logmax = std::max(logmax, a.logn);
+        WS(even, fr_t, (size_t)a.logn << a.logn);
+        WS(odd, fr_t, (size_t)a.logn << a.logn);
+        a.even = even;
+        a.odd = odd;
+        ++plan.count;
+    }
+    WS(d_roots, fr_t, 1u << logmax);
+    WS(d_twist, fr_t, 1u << logmax);
+    roots.roots = d_roots;
+    roots.twist = d_twist;
+    RT(rt::launch<64>(1u << logmax, ctx->stream, roots));
+    InterpNodesDirect direct;
+    direct.roots = d_roots;
+    direct.first[0] = 0;
+    for (uint32_t i = 0; i < plan.count; ++i) {
+        direct.axis[i] = plan.axis[i];
+        direct.first[i + 1] = direct.first[i] + InterpNodesDirect::lanes(plan.axis[i]);
+    }
+    RT(rt::launch<64>(direct.first[plan.count], ctx->stream, direct));
+    for (int t = InterpNodesDirect::LEVELS; t < logmax; ++t) {
+        InterpNodeTables k;
+        k.roots = d_roots; k.twist = d_twist; k.t = t;
+        k.first[0] = 0;
+        uint32_t used = 0;
+        for (uint32_t i = 0; i < plan.count; ++i) {
+            if (plan.axis[i].logn <= t) continue;
+            k.axis[used] = plan.axis[i];
+            k.first[used + 1] = k.first[used] + ((1u << plan.axis[i].logn) / InterpNodeTables::chunk(plan.axis[i], t));
+            ++used;
+        }
+        RT((launch_coop_n<InterpNodeTables::BLOCK>(k.first[used], ctx->stream, k, k.phases())));
+    }
+    return TC_OK;
+}
+/* One axis of an (outer, d, inner) array, in place. */
+static int interpolate_axis_tree(tc_ctx* ctx, const InterpPlan& plan, fr_t* data, uint64_t outer, uint64_t inner, uint32_t d) {
+    const InterpTables& a = *plan.tables(d);
+    WS(d_weights, fr_t, d);
+    RT(rt::launch<64>(d, ctx->stream, InterpWeights{plan.inv_fact, d, plan.roots.half_pow[a.logn], d_weights}));
+    InterpAxisTree k;
+    const uint64_t lines = outer * inner;
+    /* as many lines as fill the tile, fewer while compute units would stand idle */
+    k.lines_per_wg = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(InterpAxisTree::TILE >> a.logn, (lines + 255) / 256));
+    const uint64_t groups = (lines + k.lines_per_wg - 1) / k.lines_per_wg;
+    WS(d_half, fr_t, groups * ((uint64_t)k.lines_per_wg << a.logn) / 2);
+    k.data = data; k.half = d_half;
+    k.outer = outer; k.inner = inner; k.d = d; k.logn = a.logn;
+    k.weights = d_weights; k.roots = plan.roots.roots; k.twist = plan.roots.twist; k.even = a.even; k.odd = a.odd;
+    RT((launch_coop_n<InterpAxisTree::BLOCK>((uint32_t)groups, ctx->stream, k, k.phases())));
+    return TC_OK;
+}
+/* tc_interpolate takes the tree over the nodes where an axis fits a tile; tc_interpolate_form keeps to its form.  The tree's
+ * tables are a chain of launches, so few lines have to be longer before it pays than many: a line of 16 alone 0.11 ms against
+ * 0.08 by its differences, of 33 0.19 against 0.14, of 64 0.19 against 0.25; 16^5 entries 1.2 against 2.0 ms, 9^6 1.3
+ * against 0.95, 8^7 the same 2.8. */
+static const int INTERP_ANY_FORM = -1;
+static bool interp_by_tree(int form, uint64_t n, uint32_t d) {
+    return form == INTERP_ANY_FORM && d >= (n >= 65536 ? 16u : 48u) && d <= InterpAxisTree::TILE;
+}
+static int interpolate(tc_ctx* ctx, int m, const uint32_t* shape, const void* d_scalars, int dtype, int form, void* d_coeffs) {
     try {
         if (!ctx) return TC_ERR_ARG;
         if (!d_scalars || !d_coeffs) return fail(ctx, TC_ERR_ARG, "null argument");
         if (!valid_dtype_scalar(dtype)) return fail(ctx, TC_ERR_ARG, "unsupported scalar dtype");
-        if (form != TC_INTERP_NEWTON && form != TC_INTERP_GREGORY && form != TC_INTERP_BARYCENTRIC)
+        if (form != INTERP_ANY_FORM && form != TC_INTERP_NEWTON && form != TC_INTERP_GREGORY && form != TC_INTERP_BARYCENTRIC)
             return fail(ctx, TC_ERR_ARG, "unknown interpolation form");
         uint64_t n = 0;
         if (!interp_shape_ok(m, shape, &n)) return fail(ctx, TC_ERR_SHAPE, "bad shape");
         RT(rt::set_device(ctx->device));
         TRY(ws_reset(ctx));
-        uint32_t dmax = 1;
-        for (int j = 0; j < m; ++j) dmax = std::max(dmax, shape[j]);
-        /* 1 / l, 1 / l! and zeta_k = k + 1 up to the longest axis */
-        std::vector<fr_t> inv(dmax), zeta(dmax), inv_fact(dmax);
-        for (uint32_t i = 0; i < dmax; ++i) {
-            inv[i] = fe_from_u32<FrParams>(i ? i : 1);
-            zeta[i] = fe_from_u32<FrParams>(i + 1);
+        uint32_t dmax = 1, ntree = 0, by_tree[TC_MAX_INTERP_ORDER];
+        for (int j = 0; j < m; ++j) {
+            dmax = std::max(dmax, shape[j]);
+            if (interp_by_tree(form, n, shape[j])) by_tree[ntree++] = shape[j];
         }
-        fr_batch_inverse(inv);
-        inv_fact[0] = fe_one<FrParams>();
-        for (uint32_t i = 1; i < dmax; ++i) inv_fact[i] = fr_mul(inv_fact[i - 1], inv[i]);
-        WS(d_inv, fr_t, dmax);
-        WS(d_zeta, fr_t, dmax);
-        WS(d_aux, fr_t, dmax);             /* 1 / l! (Gregory) or the weights beta of the current axis (barycentric) */
-        TRY(h2d(ctx, d_inv, inv.data(), sizeof(fr_t) * dmax));
-        TRY(h2d(ctx, d_zeta, zeta.data(), sizeof(fr_t) * dmax));
-        if (form == TC_INTERP_GREGORY) TRY(h2d(ctx, d_aux, inv_fact.data(), sizeof(fr_t) * dmax));
-        const int nbuf = form == TC_INTERP_BARYCENTRIC ? 5 : 3;
+        const bool by_lines = ntree < (uint32_t)m;
+        /* 1 / l, 1 / l! and zeta_k = k + 1 up to the longest axis; (dmax - 1)! from as many factors at a time as fit 32 bits */
+        std::vector<fr_t> inv(dmax), zeta(dmax), inv_fact(dmax);
+        const fr_t one = fe_one<FrParams>();
+        zeta[0] = inv[0] = one;
+        for (uint32_t i = 1; i < dmax; ++i) zeta[i] = fr_add(zeta[i - 1], one);
+        fr_t fact = one;
+        for (uint32_t i = 2; i < dmax;) {
+            uint64_t run = i++;
+            while (i < dmax && run * i >> 32 == 0) run *= i++;
+            fact = fr_mul(fact, fe_from_u32<FrParams>((uint32_t)run));
+        }
+        inv_fact[dmax - 1] = fe_inv_gcd<FrParams>(fact);
+        for (uint32_t i = dmax - 1; i >= 1; --i) inv_fact[i - 1] = fr_mul(inv_fact[i], zeta[i - 1]);
+        WS(d_aux, fr_t, dmax);             /* 1 / l! (Gregory, tree) or the weights beta of the current axis (barycentric) */
+        fr_t* d_inv = nullptr;
+        fr_t* d_zeta = nullptr;
+        if (by_lines) {
+            for (uint32_t i = 1; i < dmax; ++i) {          /* 1 / i = (i - 1)! / i!, and (i - 1)! along the way */
+                if (i == 1) fact = one;
+                inv[i] = fr_mul(inv_fact[i], fact);
+                fact = fr_mul(fact, zeta[i - 1]);
+            }
+            d_inv = ws_array<fr_t>(ctx, dmax);
+            d_zeta = ws_array<fr_t>(ctx, dmax);
+            if (!d_inv || !d_zeta) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
+            TRY(h2d(ctx, d_inv, inv.data(), sizeof(fr_t) * dmax));
+            TRY(h2d(ctx, d_zeta, zeta.data(), sizeof(fr_t) * dmax));
+        }
+        if (form == TC_INTERP_GREGORY || ntree) TRY(h2d(ctx, d_aux, inv_fact.data(), sizeof(fr_t) * dmax));
+        InterpPlan plan;
+        plan.inv_fact = d_aux;
+        if (ntree) TRY(interp_plan(ctx, plan, ntree, by_tree));
+        const int nbuf = form == TC_INTERP_BARYCENTRIC ? 5 : by_lines ? 3 : 1;
         fr_t* buf[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
         for (int i = 0; i < nbuf; ++i) {
             buf[i] = ws_array<fr_t>(ctx, n);
@@ -3205,7 +3322,11 @@ extern "C" int tc_interpolate_form(tc_ctx* ctx, int m, const uint32_t* shape, co
             uint64_t lines = outer * inner;
             uint32_t lines_per_wg = d >= (uint32_t)InterpAxis<false>::BLOCK ? 1u : (uint32_t)InterpAxis<false>::BLOCK / d;
             uint64_t groups = (lines + lines_per_wg - 1) / lines_per_wg;
-            if (d > 1 && form == TC_INTERP_BARYCENTRIC) {
+            if (interp_by_tree(form, n, d)) {
+                size_t mark = ctx->wsp->off;
+                TRY(interpolate_axis_tree(ctx, plan, buf[0], outer, inner, d));
+                ctx->wsp->off = mark;                 /* the next axis is behind this one on the stream */
+            } else if (d > 1 && form == TC_INTERP_BARYCENTRIC) {
                 /* beta_l = (-1)^(d-1-l) / (l! (d-1-l)!) on the nodes 1 .. d */
                 beta.resize(d);
                 for (uint32_t l = 0; l < d; ++l) {
@@ -3248,14 +3369,14 @@ extern "C" int tc_interpolate_form(tc_ctx* ctx, int m, const uint32_t* shape, co
     }
 }
 
+extern "C" int tc_interpolate_form(tc_ctx* ctx, int m, const uint32_t* shape, const void* d_scalars, int dtype, int form,
+                                   void* d_coeffs) {
+    if (form == INTERP_ANY_FORM) return ctx ? fail(ctx, TC_ERR_ARG, "unknown interpolation form") : TC_ERR_ARG;
+    return interpolate(ctx, m, shape, d_scalars, dtype, form, d_coeffs);
+}
+
 extern "C" int tc_interpolate(tc_ctx* ctx, int m, const uint32_t* shape, const void* d_scalars, int dtype, void* d_coeffs) {
-    try {
-        return tc_interpolate_form(ctx, m, shape, d_scalars, dtype, TC_INTERP_NEWTON, d_coeffs);
-    } catch (const std::bad_alloc&) {
-        return fail(ctx, TC_ERR_NOMEM, "host allocation failed");
-    } catch (...) {
-        return fail(ctx, TC_ERR_STATE, "internal: unexpected exception");
-    }
+    return interpolate(ctx, m, shape, d_scalars, dtype, INTERP_ANY_FORM, d_coeffs);
 }
 
 extern "C" int tc_divide_by_linear(tc_ctx* ctx, int m, const uint32_t* shape, const void* d_coeffs, int axis,

@@ -1079,6 +1079,20 @@ def test_coefficient_route(T, ctx):
         lag.close()
 
 
+@pytest.mark.parametrize("shape", [(48,), (64, 33), (15, 16, 17, 17), (3, 512, 5), (511, 7), (7, 513), (2049, 2), (4095,), (4096, 3), (2, 4097)])
+def test_interpolation_by_tree(T, ctx, shape):
+    """The tree over the nodes of an axis against Newton's differences line by line, bit for bit."""
+    import torch
+
+    n = int(np.prod(shape))
+    rng = np.random.default_rng(n)
+    X = to_device(rng.integers(-32768, 32768, size=shape).astype(np.int16))
+    tree, lines = (torch.empty(32 * n, dtype=torch.uint8, device="cuda") for _ in range(2))
+    ctx.interpolate(shape, X, T.TC_I16, tree)
+    ctx.interpolate_form(shape, X, T.TC_I16, T.TC_INTERP_NEWTON, lines)
+    assert torch.equal(tree, lines)
+
+
 def test_coefficient_route_at_the_size_the_bench_times(T, ctx):
     """Interpolation of the whole 512 x 4096 activation, the size bench.py times: the three forms of App. C return
     the same coefficient array, and the polynomial reproduces sampled entries of the tensor (what can be computed

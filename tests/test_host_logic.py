@@ -327,6 +327,24 @@ def _fr_list(buf):
     return [int.from_bytes(raw[32 * i : 32 * (i + 1)], "little") for i in range(len(raw) // 32)]
 
 
+@pytest.mark.parametrize("shape", [(47,), (48,), (2, 49), (63, 1), (4, 64, 3), (2, 65), (48, 50, 2), (257, 11), (1000,), (15, 16, 274), (17, 31, 32, 4)])
+def test_emulated_interpolation_by_tree(emu, shape):
+    """The tree over the nodes of an axis against Newton's differences line by line (axes below, at and past a power
+    of two, alone, innermost and outermost, with axes that keep to the lines), and against the oracle where that is quick."""
+    n = int(np.prod(shape))
+    rng = np.random.default_rng(n)
+    for dtype, X in ((T.TC_I8, rng.integers(-128, 128, size=shape).astype(np.int8)),      # from 65536 entries on: axes of 16
+                     (T.TC_FR, fr_bytes_array([int.from_bytes(rng.bytes(40), "little") % R for _ in range(n)]))):
+        tree, lines = _fr_array(n), _fr_array(n)
+        emu.interpolate(shape, X, dtype, tree)
+        emu.interpolate_form(shape, X, dtype, T.TC_INTERP_NEWTON, lines)
+        assert np.array_equal(tree, lines), shape
+        if n <= 100 and dtype == T.TC_I8:
+            assert _fr_list(tree) == tc.interpolate(X, shape)
+    with pytest.raises(T.TcError):
+        emu.interpolate_form(shape, X, T.TC_FR, -1, tree)
+
+
 def test_emulated_coefficient_route(emu):
     """The literal route of Def. 4.1 through the library: interpolation to monomial coefficients, Algorithm 1 on
     the coefficient array, commitments against the monomial SRS -- each against the oracle's own literal route,
