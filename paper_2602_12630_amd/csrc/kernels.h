@@ -1421,140 +1421,175 @@ struct AccFinal {
  * its fourteen products fall into four levels of independent ones (U1 U2 S1 S2 | PP RR ZZa.ZZb ZZZa.ZZZb |
  * PPP Q ZZ' | T1 T2 ZZZ'), and a wave alone on its SIMD issues products no faster one after the other than four
  * waves do side by side, so an addition costs four product latencies instead of fourteen.  Points and
- * intermediates live in LDS, field by field (lanes of a wave touch consecutive 16-byte pieces); a barrier
- * separates the levels.  Reads of the operands happen in the first two levels, writes of the result (into the
- * slot of the first operand) in the last three, and only when the addition is a regular one; an identity
- * operand, opposite points and equal points are settled by wave 0 in the last level.
+ * intermediates live in LDS in the 28-bit form, whose products a lone wave gets through 1.6 times as fast, field by
+ * field (lanes of a wave touch consecutive 16-byte pieces); a barrier separates the levels.  The points are read in two
+ * halves, the first added pairwise before the second comes in: with 192 points and eight intermediates of 64 pairs,
+ * 71 KB, two workgroups share a compute unit.  Reads of the operands happen in the first two levels, writes of the
+ * result (into the slot of the first operand) in the last three, and only when the addition is a regular one; an
+ * identity operand, opposite points and equal points are settled by wave 0 in the last level.  Bounds of the values
+ * as for acc_add and acc_dbl.
+ * Bound by depth, ten additions of four products.  Against the 32-bit form with all points at once (79 KB): sixteen
+ * bit sums 142 -> 108 us, windows of one to 512 nodes 150 -> 110 us, 768 sums of verification 265 -> 204 us, 144 of them
+ * 138 -> 111 us; the 384 row and column sums, where the second half's load shows, 104 -> 121 us.
  *
  * `Src` says what is summed: count(wg) <= 256 slots, load(wg, i) the point of slot i, store(wg, sum). */
 struct Quad16 { uint32_t v[4]; };
 template <class Src>
 struct CoopReduce {
     static constexpr int BLOCK = 256;
-    static constexpr int NP = 256;
+    static constexpr int NP = 192;
     enum { PX, PY, PZZ, PZZZ, NPF };
-    enum { TU1, TU2, TS1, TS2, TPP, TRR, TZA, TZB, TPPP, TQ, NT };
+    enum { TU1, TU2, TS1, TS2, TPP, TRR, TZA, TZB, NT, TQ = TU1, TPPP = TU2 };     /* the last two follow what their wave has read */
     static constexpr int TP = 64;                                             /* pairs in flight: one per lane of a wave */
-    static constexpr size_t TEMP_BASE = (size_t)NPF * 3 * NP;                 /* in 16-byte pieces */
-    static constexpr size_t FLAG_BASE = (TEMP_BASE + (size_t)NT * 3 * TP) * 16;   /* in bytes */
+    static constexpr size_t FP_BYTES = sizeof(fp28);
+    static constexpr size_t TEMP_BASE = (size_t)NPF * NP * FP_BYTES;
+    static constexpr size_t FLAG_BASE = TEMP_BASE + (size_t)NT * TP * FP_BYTES;
     static constexpr size_t LDS_BYTES = FLAG_BASE + 3 * TP * 4;
-    static constexpr int PHASES = 1 + 9 * 5 + 1;     /* load; the 128 pairs of the first level in two passes, seven more levels; store */
+    static constexpr int PHASES = 6 + 6 + 7 * 5 + 1;     /* twice a load and an addition; seven more levels; store */
+    struct Half8 { int32_t v[2]; };
+    struct Quad { int32_t v[4]; };
     Src src;
 
-    TC_DEV static fp_t ldq(const uint8_t* lds, size_t base, int f, uint32_t n, uint32_t i) {
-        const Quad16* q = (const Quad16*)lds + base;
-        fp_t r;
+    TC_DEV static fp28 ld(const uint8_t* base, int f, uint32_t n, uint32_t i) {
+        const Quad* q = (const Quad*)(base + (size_t)f * n * FP_BYTES);
+        fp28 r;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            Quad16 t = q[(size_t)(f * 3 + k) * n + i];
+            Quad t = q[(size_t)k * n + i];
             r.l[4 * k] = t.v[0]; r.l[4 * k + 1] = t.v[1]; r.l[4 * k + 2] = t.v[2]; r.l[4 * k + 3] = t.v[3];
         }
+        Half8 h = ((const Half8*)(q + (size_t)3 * n))[i];
+        r.l[12] = h.v[0]; r.l[13] = h.v[1];
         return r;
     }
-    TC_DEV static void stq(uint8_t* lds, size_t base, int f, uint32_t n, uint32_t i, const fp_t& x) {
-        Quad16* q = (Quad16*)lds + base;
+    TC_DEV static void st(uint8_t* base, int f, uint32_t n, uint32_t i, const fp28& x) {
+        Quad* q = (Quad*)(base + (size_t)f * n * FP_BYTES);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            Quad16 t;
+            Quad t;
             t.v[0] = x.l[4 * k]; t.v[1] = x.l[4 * k + 1]; t.v[2] = x.l[4 * k + 2]; t.v[3] = x.l[4 * k + 3];
-            q[(size_t)(f * 3 + k) * n + i] = t;
+            q[(size_t)k * n + i] = t;
         }
+        Half8 h;
+        h.v[0] = x.l[12]; h.v[1] = x.l[13];
+        ((Half8*)(q + (size_t)3 * n))[i] = h;
     }
-    TC_DEV static fp_t pt(const uint8_t* lds, int f, uint32_t slot) { return ldq(lds, 0, f, NP, slot); }
-    TC_DEV static void pt_set(uint8_t* lds, int f, uint32_t slot, const fp_t& x) { stq(lds, 0, f, NP, slot, x); }
-    TC_DEV static fp_t tmp(const uint8_t* lds, int f, uint32_t t) { return ldq(lds, TEMP_BASE, f, TP, t); }
-    TC_DEV static void tmp_set(uint8_t* lds, int f, uint32_t t, const fp_t& x) { stq(lds, TEMP_BASE, f, TP, t, x); }
-    TC_DEV static g1_xyzz point(const uint8_t* lds, uint32_t slot) {
-        g1_xyzz r;
-        r.X = pt(lds, PX, slot); r.Y = pt(lds, PY, slot); r.ZZ = pt(lds, PZZ, slot); r.ZZZ = pt(lds, PZZZ, slot);
+    TC_DEV static fp28 pt(const uint8_t* lds, int f, uint32_t slot) { return ld(lds, f, NP, slot); }
+    TC_DEV static void pt_set(uint8_t* lds, int f, uint32_t slot, const fp28& x) { st(lds, f, NP, slot, x); }
+    TC_DEV static fp28 tmp(const uint8_t* lds, int f, uint32_t t) { return ld(lds + TEMP_BASE, f, TP, t); }
+    TC_DEV static void tmp_set(uint8_t* lds, int f, uint32_t t, const fp28& x) { st(lds + TEMP_BASE, f, TP, t, x); }
+    /* ZZ of an identity is written as zero and the ZZ of a finite point is no multiple of p */
+    TC_DEV static bool none(const fp28& ZZ) {
+        int32_t any = 0;
+#pragma unroll
+        for (int j = 0; j < 14; ++j) any |= ZZ.l[j];
+        return any == 0;
+    }
+    TC_DEV static xyzz_acc point(const uint8_t* lds, uint32_t slot) {
+        xyzz_acc r;
+        r.v.X = pt(lds, PX, slot); r.v.Y = pt(lds, PY, slot); r.v.ZZ = pt(lds, PZZ, slot); r.v.ZZZ = pt(lds, PZZZ, slot);
+        r.inf = none(r.v.ZZ);
+        r.lone = false;
         return r;
     }
-    TC_DEV static void point_set(uint8_t* lds, uint32_t slot, const g1_xyzz& p) {
-        pt_set(lds, PX, slot, p.X); pt_set(lds, PY, slot, p.Y); pt_set(lds, PZZ, slot, p.ZZ); pt_set(lds, PZZZ, slot, p.ZZZ);
+    TC_DEV static void point_set(uint8_t* lds, uint32_t slot, const xyzz_acc& p) {
+        const g1_xyzz28 v = p.inf ? acc_identity().v : p.v;
+        pt_set(lds, PX, slot, v.X); pt_set(lds, PY, slot, v.Y); pt_set(lds, PZZ, slot, v.ZZ); pt_set(lds, PZZZ, slot, v.ZZZ);
     }
 
     TC_DEV void phase(int ph, uint32_t lane, uint32_t wg, uint8_t* lds) const {
-        uint32_t count = src.count(wg);
-        if (ph == 0) {
-            point_set(lds, lane, lane < count ? src.load(wg, lane) : xyzz_identity());
+        const uint32_t count = src.count(wg);
+        if (ph == 0 || ph == 6) {                               /* points 0 .. 127 to slots 0 .., then 128 .. 255 to slots 64 .. */
+            uint32_t i = lane + (ph ? 128u : 0u);
+            if (lane >= 128u || (ph && count <= 128u)) return;
+            point_set(lds, lane + (ph ? 64u : 0u), i < count ? acc_from(src.load(wg, i)) : acc_identity());
             return;
         }
         if (ph == PHASES - 1) {
-            if (lane == 0) src.store(wg, point(lds, 0));
+            if (lane == 0) src.store(wg, acc_result(point(lds, 0)));
             return;
         }
-        int q = ph - 1;
-        int lv = q < 10 ? 0 : (q - 10) / 5 + 1, sub = q % 5;
-        uint32_t stride = 1u << lv, npairs = (uint32_t)(NP / 2) >> lv;
-        uint32_t wave = lane >> 6;
+        /* the additions in order: points i and 64 + i, 128 + i and 192 + i, then the two sums, then halves of the 64 sums;
+         * `beyond` is the first point that the second operand holds */
+        const int add = ph < 6 ? 0 : ph < 12 ? 1 : 2 + (ph - 12) / 5, sub = ph < 12 ? (ph - 1) % 6 : (ph - 12) % 5;
+        const uint32_t pr = lane & 63u, wave = lane >> 6;
+        uint32_t a = pr, b = 64u + pr, beyond = 64u + pr;
+        if (add == 1) {
+            a = 64u + pr; b = 128u + pr; beyond = 192u + pr;
+        } else if (add == 2) {
+            beyond = 128u + pr;
+        } else if (add > 2) {
+            const uint32_t half = 32u >> (add - 3);
+            if (pr >= half) return;
+            b = beyond = pr + half;
+        }
+        if (beyond >= count) return;                            /* nothing but identities from there on */
         uint32_t* flag_id = (uint32_t*)(lds + FLAG_BASE);      /* 0 regular, 1 keep a, 2 take b */
         uint32_t* flag_pz = flag_id + TP;                       /* same x */
         uint32_t* flag_rz = flag_pz + TP;                       /* same y */
-        {
-            uint32_t pr = (lane & 63u) + ((q >= 5 && q < 10) ? 64u : 0u);       /* the pair; its temporaries sit at lane & 63 */
-            if (pr >= npairs) return;
-            uint32_t a = pr * 2 * stride, b = a + stride;
-            if (b >= count) return;                             /* nothing but identities from b on */
-            pr &= 63u;
-            if (sub == 0) {
-                if (wave == 0) {
-                    fp_t ZZa = pt(lds, PZZ, a), ZZb = pt(lds, PZZ, b);
-                    flag_id[pr] = fe_is_zero(ZZb) ? 1u : fe_is_zero(ZZa) ? 2u : 0u;
-                    tmp_set(lds, TU1, pr, fp_mul(pt(lds, PX, a), ZZb));
-                } else if (wave == 1) {
-                    tmp_set(lds, TU2, pr, fp_mul(pt(lds, PX, b), pt(lds, PZZ, a)));
-                } else if (wave == 2) {
-                    tmp_set(lds, TS1, pr, fp_mul(pt(lds, PY, a), pt(lds, PZZZ, b)));
-                } else {
-                    tmp_set(lds, TS2, pr, fp_mul(pt(lds, PY, b), pt(lds, PZZZ, a)));
-                }
-            } else if (sub == 1) {
-                if (wave == 0) {
-                    fp_t Pd = fp_sub(tmp(lds, TU2, pr), tmp(lds, TU1, pr));
-                    flag_pz[pr] = fe_is_zero(Pd) ? 1u : 0u;
-                    tmp_set(lds, TU2, pr, Pd);
-                    tmp_set(lds, TPP, pr, fp_sqr(Pd));
-                } else if (wave == 1) {
-                    fp_t Rd = fp_sub(tmp(lds, TS2, pr), tmp(lds, TS1, pr));
-                    flag_rz[pr] = fe_is_zero(Rd) ? 1u : 0u;
-                    tmp_set(lds, TS2, pr, Rd);
-                    tmp_set(lds, TRR, pr, fp_sqr(Rd));
-                } else if (wave == 2) {
-                    tmp_set(lds, TZA, pr, fp_mul(pt(lds, PZZ, a), pt(lds, PZZ, b)));
-                } else {
-                    tmp_set(lds, TZB, pr, fp_mul(pt(lds, PZZZ, a), pt(lds, PZZZ, b)));
-                }
+        if (sub == 0) {
+            if (wave == 0) {
+                fp28 ZZa = pt(lds, PZZ, a), ZZb = pt(lds, PZZ, b);
+                flag_id[pr] = none(ZZb) ? 1u : none(ZZa) ? 2u : 0u;
+                tmp_set(lds, TU1, pr, fp28_mul(pt(lds, PX, a), ZZb));
+            } else if (wave == 1) {
+                tmp_set(lds, TU2, pr, fp28_mul(pt(lds, PX, b), pt(lds, PZZ, a)));
+            } else if (wave == 2) {
+                tmp_set(lds, TS1, pr, fp28_mul(pt(lds, PY, a), pt(lds, PZZZ, b)));
             } else {
-                bool regular = flag_id[pr] == 0u && flag_pz[pr] == 0u;
-                if (sub == 2) {
-                    if (wave == 0) {
-                        tmp_set(lds, TPPP, pr, fp_mul(tmp(lds, TU2, pr), tmp(lds, TPP, pr)));
-                    } else if (wave == 1) {
-                        tmp_set(lds, TQ, pr, fp_mul(tmp(lds, TU1, pr), tmp(lds, TPP, pr)));
-                    } else if (wave == 2) {
-                        fp_t ZZ3 = fp_mul(tmp(lds, TZA, pr), tmp(lds, TPP, pr));
-                        if (regular) pt_set(lds, PZZ, a, ZZ3);
+                tmp_set(lds, TS2, pr, fp28_mul(pt(lds, PY, b), pt(lds, PZZZ, a)));
+            }
+        } else if (sub == 1) {
+            if (wave == 0) {
+                fp28 Pd = fp28_sub(tmp(lds, TU2, pr), tmp(lds, TU1, pr));
+                flag_pz[pr] = fp28_is_zero(Pd, 128u) ? 1u : 0u;
+                tmp_set(lds, TU2, pr, Pd);
+                tmp_set(lds, TPP, pr, fp28_sqr(Pd));
+            } else if (wave == 1) {
+                fp28 Rd = fp28_sub(tmp(lds, TS2, pr), tmp(lds, TS1, pr));
+                flag_rz[pr] = fp28_is_zero(Rd, 128u) ? 1u : 0u;
+                tmp_set(lds, TS2, pr, Rd);
+                tmp_set(lds, TRR, pr, fp28_sqr(Rd));
+            } else if (wave == 2) {
+                tmp_set(lds, TZA, pr, fp28_mul(pt(lds, PZZ, a), pt(lds, PZZ, b)));
+            } else {
+                tmp_set(lds, TZB, pr, fp28_mul(pt(lds, PZZZ, a), pt(lds, PZZZ, b)));
+            }
+        } else {
+            bool regular = flag_id[pr] == 0u && flag_pz[pr] == 0u;
+            if (sub == 2) {
+                if (wave == 0) {
+                    tmp_set(lds, TPPP, pr, fp28_mul(tmp(lds, TU2, pr), tmp(lds, TPP, pr)));
+                } else if (wave == 1) {
+                    tmp_set(lds, TQ, pr, fp28_mul(tmp(lds, TU1, pr), tmp(lds, TPP, pr)));
+                } else if (wave == 2) {
+                    fp28 ZZ3 = fp28_mul(tmp(lds, TZA, pr), tmp(lds, TPP, pr));
+                    if (regular) pt_set(lds, PZZ, a, ZZ3);
+                }
+            } else if (sub == 3) {
+                if (wave == 0) {
+                    fp28 Q = tmp(lds, TQ, pr);
+                    fp28 X3 = fp28_carry(fp28_sub(fp28_sub(fp28_sub(tmp(lds, TRR, pr), tmp(lds, TPPP, pr)), Q), Q));
+                    tmp_set(lds, TRR, pr, fp28_mul(tmp(lds, TS2, pr), fp28_sub(Q, X3)));
+                    if (regular) pt_set(lds, PX, a, X3);
+                } else if (wave == 1) {
+                    tmp_set(lds, TS1, pr, fp28_mul(tmp(lds, TS1, pr), tmp(lds, TPPP, pr)));
+                } else if (wave == 2) {
+                    fp28 ZZZ3 = fp28_mul(tmp(lds, TZB, pr), tmp(lds, TPPP, pr));
+                    if (regular) pt_set(lds, PZZZ, a, ZZZ3);
+                }
+            } else if (wave == 0) {
+                if (regular) {
+                    pt_set(lds, PY, a, fp28_sub(tmp(lds, TRR, pr), tmp(lds, TS1, pr)));
+                } else if (flag_id[pr] == 2u) {
+                    point_set(lds, a, point(lds, b));
+                } else if (flag_id[pr] == 0u) {             /* same x: the same point, or opposite ones */
+                    xyzz_acc p = acc_identity();
+                    if (flag_rz[pr]) {
+                        p = point(lds, a);
+                        acc_dbl(p);
                     }
-                } else if (sub == 3) {
-                    if (wave == 0) {
-                        fp_t Q = tmp(lds, TQ, pr);
-                        fp_t X3 = fp_sub(fp_sub(fp_sub(tmp(lds, TRR, pr), tmp(lds, TPPP, pr)), Q), Q);
-                        tmp_set(lds, TRR, pr, fp_mul(tmp(lds, TS2, pr), fp_sub(Q, X3)));
-                        if (regular) pt_set(lds, PX, a, X3);
-                    } else if (wave == 1) {
-                        tmp_set(lds, TS1, pr, fp_mul(tmp(lds, TS1, pr), tmp(lds, TPPP, pr)));
-                    } else if (wave == 2) {
-                        fp_t ZZZ3 = fp_mul(tmp(lds, TZB, pr), tmp(lds, TPPP, pr));
-                        if (regular) pt_set(lds, PZZZ, a, ZZZ3);
-                    }
-                } else if (wave == 0) {
-                    if (regular) {
-                        pt_set(lds, PY, a, fp_sub(tmp(lds, TRR, pr), tmp(lds, TS1, pr)));
-                    } else if (flag_id[pr] == 2u) {
-                        point_set(lds, a, point(lds, b));
-                    } else if (flag_id[pr] == 0u) {             /* same x: the same point, or opposite ones */
-                        point_set(lds, a, flag_rz[pr] ? xyzz_dbl32(point(lds, a)) : xyzz_identity());
-                    }
+                    point_set(lds, a, p);
                 }
             }
         }
