@@ -1433,7 +1433,34 @@ struct AccFinal {
  * 138 -> 111 us; the 384 row and column sums, where the second half's load shows, 104 -> 121 us.
  *
  * `Src` says what is summed: count(wg) <= 256 slots, load(wg, i) the point of slot i, store(wg, sum). */
-struct Quad16 { uint32_t v[4]; };
+struct Fp28Planes {             /* fields of n elements in LDS: three planes of 16-byte pieces and one of 8 */
+    struct Half8 { int32_t v[2]; };
+    struct Quad { int32_t v[4]; };
+    TC_DEV static fp28 ld(const uint8_t* base, int f, uint32_t n, uint32_t i) {
+        const Quad* q = (const Quad*)(base + (size_t)f * n * sizeof(fp28));
+        fp28 r;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            Quad t = q[(size_t)k * n + i];
+            r.l[4 * k] = t.v[0]; r.l[4 * k + 1] = t.v[1]; r.l[4 * k + 2] = t.v[2]; r.l[4 * k + 3] = t.v[3];
+        }
+        Half8 h = ((const Half8*)(q + (size_t)3 * n))[i];
+        r.l[12] = h.v[0]; r.l[13] = h.v[1];
+        return r;
+    }
+    TC_DEV static void st(uint8_t* base, int f, uint32_t n, uint32_t i, const fp28& x) {
+        Quad* q = (Quad*)(base + (size_t)f * n * sizeof(fp28));
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            Quad t;
+            t.v[0] = x.l[4 * k]; t.v[1] = x.l[4 * k + 1]; t.v[2] = x.l[4 * k + 2]; t.v[3] = x.l[4 * k + 3];
+            q[(size_t)k * n + i] = t;
+        }
+        Half8 h;
+        h.v[0] = x.l[12]; h.v[1] = x.l[13];
+        ((Half8*)(q + (size_t)3 * n))[i] = h;
+    }
+};
 template <class Src>
 struct CoopReduce {
     static constexpr int BLOCK = 256;
@@ -1446,38 +1473,12 @@ struct CoopReduce {
     static constexpr size_t FLAG_BASE = TEMP_BASE + (size_t)NT * TP * FP_BYTES;
     static constexpr size_t LDS_BYTES = FLAG_BASE + 3 * TP * 4;
     static constexpr int PHASES = 6 + 6 + 7 * 5 + 1;     /* twice a load and an addition; seven more levels; store */
-    struct Half8 { int32_t v[2]; };
-    struct Quad { int32_t v[4]; };
     Src src;
 
-    TC_DEV static fp28 ld(const uint8_t* base, int f, uint32_t n, uint32_t i) {
-        const Quad* q = (const Quad*)(base + (size_t)f * n * FP_BYTES);
-        fp28 r;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            Quad t = q[(size_t)k * n + i];
-            r.l[4 * k] = t.v[0]; r.l[4 * k + 1] = t.v[1]; r.l[4 * k + 2] = t.v[2]; r.l[4 * k + 3] = t.v[3];
-        }
-        Half8 h = ((const Half8*)(q + (size_t)3 * n))[i];
-        r.l[12] = h.v[0]; r.l[13] = h.v[1];
-        return r;
-    }
-    TC_DEV static void st(uint8_t* base, int f, uint32_t n, uint32_t i, const fp28& x) {
-        Quad* q = (Quad*)(base + (size_t)f * n * FP_BYTES);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            Quad t;
-            t.v[0] = x.l[4 * k]; t.v[1] = x.l[4 * k + 1]; t.v[2] = x.l[4 * k + 2]; t.v[3] = x.l[4 * k + 3];
-            q[(size_t)k * n + i] = t;
-        }
-        Half8 h;
-        h.v[0] = x.l[12]; h.v[1] = x.l[13];
-        ((Half8*)(q + (size_t)3 * n))[i] = h;
-    }
-    TC_DEV static fp28 pt(const uint8_t* lds, int f, uint32_t slot) { return ld(lds, f, NP, slot); }
-    TC_DEV static void pt_set(uint8_t* lds, int f, uint32_t slot, const fp28& x) { st(lds, f, NP, slot, x); }
-    TC_DEV static fp28 tmp(const uint8_t* lds, int f, uint32_t t) { return ld(lds + TEMP_BASE, f, TP, t); }
-    TC_DEV static void tmp_set(uint8_t* lds, int f, uint32_t t, const fp28& x) { st(lds + TEMP_BASE, f, TP, t, x); }
+    TC_DEV static fp28 pt(const uint8_t* lds, int f, uint32_t slot) { return Fp28Planes::ld(lds, f, NP, slot); }
+    TC_DEV static void pt_set(uint8_t* lds, int f, uint32_t slot, const fp28& x) { Fp28Planes::st(lds, f, NP, slot, x); }
+    TC_DEV static fp28 tmp(const uint8_t* lds, int f, uint32_t t) { return Fp28Planes::ld(lds + TEMP_BASE, f, TP, t); }
+    TC_DEV static void tmp_set(uint8_t* lds, int f, uint32_t t, const fp28& x) { Fp28Planes::st(lds + TEMP_BASE, f, TP, t, x); }
     /* ZZ of an identity is written as zero and the ZZ of a finite point is no multiple of p */
     TC_DEV static bool none(const fp28& ZZ) {
         int32_t any = 0;
@@ -1683,95 +1684,95 @@ struct BitSumSrc {             /* workgroup (w, j): j < 9 the columns with bit j
     }
     TC_DEV void store(uint32_t wg, const g1_xyzz& r) const { out[wg] = r; }
 };
-/* lane (w, j): 2^j X_j for the columns, 2^(8 + j - 9) Y_(j-9) for the rows.  Up to 14 doublings in a row and only
- * 16 chains per window: the nine products of an XYZZ doubling are shared by the four waves of a workgroup in three
- * levels (V = (2Y)^2, A = X^2 | W = 2Y V, S = X V, (3A)^2, V ZZ | 3A (S - X3), W Y, W ZZZ), operands in LDS, a barrier
- * after every level and one more for the subtraction that ends the doubling; a chain that has done its own number
- * of doublings no longer takes the results.  ZZ = 0 (the identity) reproduces itself. */
+/* 2^e X for every bit sum X, e the place value of its bit: chain t of CHAINS per window.  CHAINS = 16: X_j with e = j, then
+ * Y_j with e = 8 + j; otherwise e = t % CHAINS.  Up to 14 doublings in a row and few chains: the nine products of an
+ * XYZZ doubling are shared by the four waves of a workgroup in three levels (V = (2Y)^2, A = X^2 | W = 2Y V, S = X V,
+ * (3A)^2, V ZZ | 3A (S - X3), W Y, W ZZZ), operands in LDS in the 28-bit form, a barrier after every level and one more
+ * for the subtraction that ends the doubling; a chain that has done its own number of doublings no longer takes the
+ * results.  ZZ = 0 (the identity) reproduces itself; bounds as for acc_dbl.
+ * Bound by the chain of products: 14 doublings 91 -> 69 us against the form on the FP64 pipe. */
+template <int CHAINS>
 struct BitSumScale {
     static constexpr int BLOCK = 256;
-    static constexpr int MAX_DOUBLINGS = 14;
+    static constexpr int MAX_DOUBLINGS = CHAINS == 16 ? 14 : CHAINS - 1;
     enum { FX, FY, FZZ, FZZZ, FU, FV, FM, FW, FS, FMM, FT, FWY, FZZN, FZZZN, FX3, NFIELD };
-    static constexpr size_t LDS_BYTES = (size_t)NFIELD * 3 * 64 * 16;
+    static constexpr size_t LDS_BYTES = (size_t)NFIELD * sizeof(fp28) * 64;
     static constexpr int PHASES = 1 + 4 * MAX_DOUBLINGS + 1;
     const g1_xyzz* in;
-    uint32_t n;                /* chains: 16 per window */
+    uint32_t n;                /* chains */
     g1_xyzz* out;
     TC_DEV static uint32_t doublings(uint32_t t) {
-        uint32_t j = t % 16u;
-        return j < 9u ? j : j - 9u + 8u;
+        uint32_t j = t % (uint32_t)CHAINS;
+        return CHAINS == 16 && j >= 9u ? j - 1u : j;
     }
-    TC_DEV static fp_t ld(const uint8_t* lds, int f, uint32_t l) {
-        const Quad16* q = (const Quad16*)lds;
-        fp_t r;
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            Quad16 t = q[(f * 3 + i) * 64 + l];
-            r.l[4 * i] = t.v[0]; r.l[4 * i + 1] = t.v[1]; r.l[4 * i + 2] = t.v[2]; r.l[4 * i + 3] = t.v[3];
-        }
-        return r;
-    }
-    TC_DEV static void st(uint8_t* lds, int f, uint32_t l, const fp_t& x) {
-        Quad16* q = (Quad16*)lds;
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            Quad16 t;
-            t.v[0] = x.l[4 * i]; t.v[1] = x.l[4 * i + 1]; t.v[2] = x.l[4 * i + 2]; t.v[3] = x.l[4 * i + 3];
-            q[(f * 3 + i) * 64 + l] = t;
-        }
-    }
+    TC_DEV static fp28 ld(const uint8_t* lds, int f, uint32_t l) { return Fp28Planes::ld(lds, f, 64, l); }
+    TC_DEV static void st(uint8_t* lds, int f, uint32_t l, const fp28& x) { Fp28Planes::st(lds, f, 64, l, x); }
     TC_DEV void phase(int ph, uint32_t lane, uint32_t wg, uint8_t* lds) const {
         uint32_t wave = lane >> 6, l = lane & 63u;
         uint32_t t = wg * 64u + l;
         bool live = t < n;
         if (ph == 0) {
             if (wave != 0) return;
-            g1_xyzz p = live ? in[t] : xyzz_identity();
+            g1_xyzz28 p = xyzz28_from(live ? in[t] : xyzz_identity());
             st(lds, FX, l, p.X); st(lds, FY, l, p.Y); st(lds, FZZ, l, p.ZZ); st(lds, FZZZ, l, p.ZZZ);
-            st(lds, FU, l, fp_dbl(p.Y));
+            st(lds, FU, l, fp28_add(p.Y, p.Y));
             return;
         }
         if (ph == PHASES - 1) {
             if (wave != 0 || !live) return;
-            g1_xyzz p;
+            g1_xyzz28 p;
             p.X = ld(lds, FX, l); p.Y = ld(lds, FY, l); p.ZZ = ld(lds, FZZ, l); p.ZZZ = ld(lds, FZZZ, l);
-            out[t] = p;
+            out[t] = xyzz28_to(p);
             return;
         }
         uint32_t d = (uint32_t)(ph - 1) / 4u + 1u;          /* the d-th doubling is in the making */
         int level = (ph - 1) % 4;
         if (level == 0) {
             if (wave == 0) {
-                st(lds, FV, l, fp_sqr_lat(ld(lds, FU, l)));
+                st(lds, FV, l, fp28_sqr(ld(lds, FU, l)));
             } else if (wave == 1) {
-                fp_t A = fp_sqr_lat(ld(lds, FX, l));
-                st(lds, FM, l, fp_add(fp_dbl(A), A));
+                fp28 A = fp28_sqr(ld(lds, FX, l));
+                st(lds, FM, l, fp28_carry(fp28_add(fp28_add(A, A), A)));
             }
         } else if (level == 1) {
-            if (wave == 0) st(lds, FW, l, fp_mul_lat(ld(lds, FU, l), ld(lds, FV, l)));
-            else if (wave == 1) st(lds, FS, l, fp_mul_lat(ld(lds, FX, l), ld(lds, FV, l)));
-            else if (wave == 2) st(lds, FMM, l, fp_sqr_lat(ld(lds, FM, l)));
-            else st(lds, FZZN, l, fp_mul_lat(ld(lds, FV, l), ld(lds, FZZ, l)));
+            if (wave == 0) st(lds, FW, l, fp28_mul(ld(lds, FU, l), ld(lds, FV, l)));
+            else if (wave == 1) st(lds, FS, l, fp28_mul(ld(lds, FX, l), ld(lds, FV, l)));
+            else if (wave == 2) st(lds, FMM, l, fp28_sqr(ld(lds, FM, l)));
+            else st(lds, FZZN, l, fp28_mul(ld(lds, FV, l), ld(lds, FZZ, l)));
         } else if (level == 2) {
             if (wave == 0) {
-                fp_t S = ld(lds, FS, l);
-                fp_t X3 = fp_sub(fp_sub(ld(lds, FMM, l), S), S);
+                fp28 S = ld(lds, FS, l);
+                fp28 X3 = fp28_carry(fp28_sub(fp28_sub(ld(lds, FMM, l), S), S));
                 st(lds, FX3, l, X3);
-                st(lds, FT, l, fp_mul_lat(ld(lds, FM, l), fp_sub(S, X3)));
+                st(lds, FT, l, fp28_mul(ld(lds, FM, l), fp28_sub(S, X3)));
             } else if (wave == 1) {
-                st(lds, FWY, l, fp_mul_lat(ld(lds, FW, l), ld(lds, FY, l)));
+                st(lds, FWY, l, fp28_mul(ld(lds, FW, l), ld(lds, FY, l)));
             } else if (wave == 2) {
-                st(lds, FZZZN, l, fp_mul_lat(ld(lds, FW, l), ld(lds, FZZZ, l)));
+                st(lds, FZZZN, l, fp28_mul(ld(lds, FW, l), ld(lds, FZZZ, l)));
             }
         } else if (wave == 0 && live && d <= doublings(t)) {
-            fp_t Y3 = fp_sub(ld(lds, FT, l), ld(lds, FWY, l));
+            fp28 Y3 = fp28_sub(ld(lds, FT, l), ld(lds, FWY, l));
             st(lds, FX, l, ld(lds, FX3, l));
             st(lds, FY, l, Y3);
-            st(lds, FU, l, fp_dbl(Y3));
+            st(lds, FU, l, fp28_add(Y3, Y3));
             st(lds, FZZ, l, ld(lds, FZZN, l));
             st(lds, FZZZ, l, ld(lds, FZZZN, l));
         }
     }
+};
+/* The same bit by bit for a few windows of 128 or 256 buckets: workgroup (w, j) adds the buckets k = 1 .. nb with bit j of k
+ * set, nb / 2 of them for j < log2(nb) and bucket nb alone for the last j. */
+struct SmallBitSumSrc {
+    const g1_xyzz* bucket;     /* windows * nb, bucket k at k - 1 */
+    uint32_t lognb;
+    g1_xyzz* out;              /* windows * (lognb + 1) */
+    TC_DEV uint32_t count(uint32_t wg) const { return wg % (lognb + 1u) == lognb ? 1u : 1u << (lognb - 1u); }
+    TC_DEV g1_xyzz load(uint32_t wg, uint32_t i) const {
+        uint32_t w = wg / (lognb + 1u), j = wg % (lognb + 1u);
+        uint32_t k = (i >> j << (j + 1u)) | (1u << j) | (i & ((1u << j) - 1u));
+        return bucket[((uint64_t)w << lognb) + k - 1u];
+    }
+    TC_DEV void store(uint32_t wg, const g1_xyzz& r) const { out[wg] = r; }
 };
 struct GroupSumSrc {           /* out[g] = sum of in[g * group .. (g + 1) * group), group <= 256 */
     const g1_xyzz* in;

@@ -1272,6 +1272,14 @@ static const int SMALL_WINDOW_REDUCE_MIN = 8;          /* the CPU build of the t
 #else
 static const int SMALL_WINDOW_REDUCE_MIN = 512;
 #endif
+/* up to this many of them the weights are taken bit by bit: at most two workgroups per compute unit, each a sum of half
+ * the window's buckets, against fourteen additions in a row (one window of 128:
+ * 262 -> 175 us in three launches, four: 345 -> 168) */
+#if defined(TC_HOST_EMU)
+static const int SMALL_WINDOW_BITS_MAX = 2;
+#else
+static const int SMALL_WINDOW_BITS_MAX = 56;
+#endif
 /* from this many 32768-bucket windows on, a launch fills the chip with the packed row / column sums */
 static const int ROWCOL_PACKED_WINDOWS = 8;
 
@@ -1292,6 +1300,18 @@ static int reduce_windows(tc_ctx* ctx, const g1_xyzz* bucket, int W, uint32_t nb
         RT(rt::launch<64>(redo_lanes, ctx->stream, StridedRedo<StridedSums>{S, redo_lanes}));
         RT(rt::launch<64>(2ull * (uint32_t)W, ctx->stream, SmallWeighted{sums, S.cols(), (uint32_t)W, parts}));
         RT(rt::launch<64>((uint32_t)W, ctx->stream, SmallFinish{parts, S.cols(), (uint32_t)W, wsum}));
+        return TC_OK;
+    }
+    if ((nb == 128 || nb == 256) && W <= SMALL_WINDOW_BITS_MAX) {
+        typedef CoopReduce<SmallBitSumSrc> BitSum;
+        typedef CoopReduce<GroupSumSrc> GroupSum;
+        const uint32_t lognb = nb == 128 ? 7u : 8u, chains = lognb + 1u, n = chains * (uint32_t)W;
+        WS(bits, g1_xyzz, n);
+        WS(scaled, g1_xyzz, n);
+        RT((launch_coop<BitSum::BLOCK>(n, ctx->stream, BitSum{SmallBitSumSrc{bucket, lognb, bits}})));
+        if (nb == 128) RT((launch_coop<BitSumScale<8>::BLOCK>((n + 63u) / 64u, ctx->stream, BitSumScale<8>{bits, n, scaled})));
+        else RT((launch_coop<BitSumScale<9>::BLOCK>((n + 63u) / 64u, ctx->stream, BitSumScale<9>{bits, n, scaled})));
+        RT((launch_coop<GroupSum::BLOCK>((uint32_t)W, ctx->stream, GroupSum{GroupSumSrc{scaled, chains, wsum}})));
         return TC_OK;
     }
     if (nb == 128 || nb == 256) {
@@ -1315,7 +1335,7 @@ static int reduce_windows(tc_ctx* ctx, const g1_xyzz* bucket, int W, uint32_t nb
         WS(scaled, g1_xyzz, 16u * (uint32_t)W);
         RT((launch_coop<RowCol::BLOCK>(384u * (uint32_t)W, ctx->stream, RowCol{RowColSrc{bucket, rows, cols}})));
         RT((launch_coop<BitSum::BLOCK>(16u * (uint32_t)W, ctx->stream, BitSum{BitSumSrc{rows, cols, bits}})));
-        RT((launch_coop<BitSumScale::BLOCK>((16u * (uint32_t)W + 63u) / 64u, ctx->stream, BitSumScale{bits, 16u * (uint32_t)W, scaled})));
+        RT((launch_coop<BitSumScale<16>::BLOCK>((16u * (uint32_t)W + 63u) / 64u, ctx->stream, BitSumScale<16>{bits, 16u * (uint32_t)W, scaled})));
         RT((launch_coop<GroupSum::BLOCK>((uint32_t)W, ctx->stream, GroupSum{GroupSumSrc{scaled, 16u, wsum}})));
         return TC_OK;
     }
