@@ -529,8 +529,8 @@ __device__ __forceinline__ fr_t fr_mul(const fr_t& a, const fr_t& b) {
     return fr_mul_call(u32x4{a.l[0], a.l[1], a.l[2], a.l[3]}, u32x4{a.l[4], a.l[5], a.l[6], a.l[7]},
                        u32x4{b.l[0], b.l[1], b.l[2], b.l[3]}, u32x4{b.l[4], b.l[5], b.l[6], b.l[7]});
 }
-/* Products for kernels whose cost is depth, not volume (the doubling chains of batch verification ran 8 % faster
- * with this form than with the integer one); a chip full of waves gets through fewer of them a second. */
+/* The FP64 products as tc_ctx_alu_rate and tc_ctx_field_op call them (chains of doublings, where depth is the cost, ran
+ * 8 % faster with them than with the 32-bit integer form, and faster again in 28-bit limbs, which they use now). */
 __device__ __attribute__((noinline)) fp_t fp_mul_lat_call(u32x4 a0, u32x4 a1, u32x4 a2, u32x4 b0, u32x4 b1, u32x4 b2) {
     fp_t a, b;
     a.l[0] = a0.x; a.l[1] = a0.y; a.l[2] = a0.z; a.l[3] = a0.w; a.l[4] = a1.x; a.l[5] = a1.y; a.l[6] = a1.z; a.l[7] = a1.w;
