@@ -381,7 +381,9 @@ int tc_interpolate(tc_ctx* ctx, int m, const uint32_t* shape, const void* d_scal
  * faster), Gregory (forward differences Delta^k T[0] on the equispaced grid, weights binom(X - zeta_0, k)) or barycentric (weights beta_l, the interpolant assembled as
  * sum_l beta_l T_l prod_(r != l) (X - zeta_r) node by node).  All three return the identical array; they differ
  * in their steps and running time.  The barycentric form needs five Fr arrays of the tensor's size as
- * workspace, the others three (tc_interpolate two and its tables).  Unknown form: TC_ERR_ARG. */
+ * workspace, the others three; tc_interpolate takes three if any axis longer than 1 goes by its differences and at most
+ * two otherwise, and tables of at most 3.5 MB for each length among the axes that go over the tree.  Unknown form:
+ * TC_ERR_ARG. */
 #define TC_INTERP_NEWTON 0
 #define TC_INTERP_GREGORY 1
 #define TC_INTERP_BARYCENTRIC 2

@@ -3318,7 +3318,7 @@ struct InterpAxisTree {
     static constexpr uint32_t TILE = 4096;
     static constexpr size_t LDS_BYTES = TILE * 32;
     fr_t* data;                /* (outer, d, inner), in place */
-    fr_t* half;                /* lines_per_wg * n / 2 elements per workgroup: the even half of a level while the odd half is computed */
+    fr_t* half;                /* 2^(logn - 1) elements per line: the even half of a level while the odd half is computed */
     uint64_t outer, inner;
     uint32_t d, lines_per_wg;
     int logn;                  /* lines_per_wg << logn <= TILE */
@@ -3332,19 +3332,17 @@ struct InterpAxisTree {
         for (int t = 0; t < logn; ++t) ph += InterpTile::extend_stages(t) + 2;
         return ph;
     }
-    TC_DEV fr_t* element(uint32_t wg, uint32_t local, uint32_t k) const {
-        uint64_t line = (uint64_t)wg * lines_per_wg + local;
-        return line < outer * inner && k < d ? data + ((line / inner) * d + k) * inner + line % inner : nullptr;
-    }
+    TC_DEV fr_t* element(uint64_t line, uint32_t k) const { return data + ((line / inner) * d + k) * inner + line % inner; }
     TC_DEV void phase(int ph, uint32_t lane, uint32_t wg, uint8_t* lds) const {
         InterpTile x{(FrHalf*)lds, (FrHalf*)lds + TILE, roots, twist};
-        const uint32_t n = 1u << logn, elements = lines_per_wg << logn, pairs = elements >> 1;
+        const uint64_t first = (uint64_t)wg * lines_per_wg, left = outer * inner - first;
+        const uint32_t lines = left < lines_per_wg ? (uint32_t)left : lines_per_wg;       /* fewer in the last workgroup */
+        const uint32_t n = 1u << logn, elements = lines << logn, pairs = elements >> 1;
         if (ph == 0) {
             /* neighbouring lines first where they are neighbours in memory */
             for (uint32_t i = lane; i < elements; i += BLOCK) {
-                uint32_t local = inner > 1 ? i % lines_per_wg : i >> logn, k = inner > 1 ? i / lines_per_wg : i & (n - 1);
-                const fr_t* at = element(wg, local, k);
-                x.put((local << logn) + k, at ? fr_mul(*at, weights[k]) : fe_zero<FrParams>());
+                uint32_t local = inner > 1 ? i % lines : i >> logn, k = inner > 1 ? i / lines : i & (n - 1);
+                x.put((local << logn) + k, k < d ? fr_mul(*element(first + local, k), weights[k]) : fe_zero<FrParams>());
             }
             return;
         }
@@ -3358,7 +3356,7 @@ struct InterpAxisTree {
             const bool at_odd = (uint32_t)r == odd_phase;
             if (r == 0 || at_odd) {
                 const fr_t* m = (at_odd ? odd : even) + ((size_t)t << logn);
-                fr_t* keep = half + (size_t)wg * pairs;
+                fr_t* keep = half + (first << (logn - 1));
                 for (uint32_t p = lane; p < pairs; p += BLOCK) {
                     uint32_t i = (p >> t << (t + 1)) + (p & (h - 1)), at = i & (n - 1);
                     fr_t v = fr_add(fr_mul(x.get(i), m[at + h]), fr_mul(x.get(i + h), m[at]));
@@ -3376,9 +3374,8 @@ struct InterpAxisTree {
             for (uint32_t p = lane; p < pairs; p += BLOCK) x.inverse_stage((uint32_t)r, p);
         } else {
             for (uint32_t i = lane; i < elements; i += BLOCK) {
-                uint32_t local = inner > 1 ? i % lines_per_wg : i >> logn, k = inner > 1 ? i / lines_per_wg : i & (n - 1);
-                fr_t* at = element(wg, local, k);
-                if (at) *at = x.get((local << logn) + k);
+                uint32_t local = inner > 1 ? i % lines : i >> logn, k = inner > 1 ? i / lines : i & (n - 1);
+                if (k < d) *element(first + local, k) = x.get((local << logn) + k);
             }
         }
     }

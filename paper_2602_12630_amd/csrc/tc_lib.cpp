@@ -3253,20 +3253,19 @@ static int interp_plan(tc_ctx* ctx, InterpPlan& plan, uint32_t count, const uint
     }
     return TC_OK;
 }
-/* One axis of an (outer, d, inner) array, in place. */
-static int interpolate_axis_tree(tc_ctx* ctx, const InterpPlan& plan, fr_t* data, uint64_t outer, uint64_t inner, uint32_t d) {
+/* One axis of an (outer, d, inner) array, in place; `half` as large as interp_half says. */
+static uint64_t interp_half(uint64_t lines, int logn) { return lines << (logn - 1); }
+static int interpolate_axis_tree(tc_ctx* ctx, const InterpPlan& plan, fr_t* data, fr_t* half, fr_t* weights, uint64_t outer, uint64_t inner, uint32_t d) {
     const InterpTables& a = *plan.tables(d);
-    WS(d_weights, fr_t, d);
-    RT(rt::launch<64>(d, ctx->stream, InterpWeights{plan.inv_fact, d, plan.roots.half_pow[a.logn], d_weights}));
+    RT(rt::launch<64>(d, ctx->stream, InterpWeights{plan.inv_fact, d, plan.roots.half_pow[a.logn], weights}));
     InterpAxisTree k;
     const uint64_t lines = outer * inner;
     /* as many lines as fill the tile, fewer while compute units would stand idle */
     k.lines_per_wg = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(InterpAxisTree::TILE >> a.logn, (lines + 255) / 256));
     const uint64_t groups = (lines + k.lines_per_wg - 1) / k.lines_per_wg;
-    WS(d_half, fr_t, groups * ((uint64_t)k.lines_per_wg << a.logn) / 2);
-    k.data = data; k.half = d_half;
+    k.data = data; k.half = half;
     k.outer = outer; k.inner = inner; k.d = d; k.logn = a.logn;
-    k.weights = d_weights; k.roots = plan.roots.roots; k.twist = plan.roots.twist; k.even = a.even; k.odd = a.odd;
+    k.weights = weights; k.roots = plan.roots.roots; k.twist = plan.roots.twist; k.even = a.even; k.odd = a.odd;
     RT((launch_coop_n<InterpAxisTree::BLOCK>((uint32_t)groups, ctx->stream, k, k.phases())));
     return TC_OK;
 }
@@ -3290,11 +3289,12 @@ static int interpolate(tc_ctx* ctx, int m, const uint32_t* shape, const void* d_
         RT(rt::set_device(ctx->device));
         TRY(ws_reset(ctx));
         uint32_t dmax = 1, ntree = 0, by_tree[TC_MAX_INTERP_ORDER];
+        bool by_lines = form != INTERP_ANY_FORM;
         for (int j = 0; j < m; ++j) {
             dmax = std::max(dmax, shape[j]);
             if (interp_by_tree(form, n, shape[j])) by_tree[ntree++] = shape[j];
+            else if (shape[j] > 1) by_lines = true;
         }
-        const bool by_lines = ntree < (uint32_t)m;
         /* 1 / l, 1 / l! and zeta_k = k + 1 up to the longest axis; (dmax - 1)! from as many factors at a time as fit 32 bits */
         std::vector<fr_t> inv(dmax), zeta(dmax), inv_fact(dmax);
         const fr_t one = fe_one<FrParams>();
@@ -3333,6 +3333,20 @@ static int interpolate(tc_ctx* ctx, int m, const uint32_t* shape, const void* d_
             buf[i] = ws_array<fr_t>(ctx, n);
             if (!buf[i]) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
         }
+        /* what a tree axis puts aside is less than an array (2^(logn - 1) < d): it goes into one of the two that lie idle
+         * between axes by lines, or into one that all tree axes share */
+        fr_t* half = nullptr;
+        fr_t* weights = nullptr;
+        if (ntree) {
+            weights = ws_array<fr_t>(ctx, dmax);
+            if (!weights) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
+            if (!by_lines) {
+                uint64_t most = 0;
+                for (uint32_t i = 0; i < ntree; ++i) most = std::max(most, interp_half(n / by_tree[i], plan.tables(by_tree[i])->logn));
+                half = ws_array<fr_t>(ctx, most);
+                if (!half) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
+            }
+        }
         RT(rt::launch<256>(n, ctx->stream, ScalarsToFr{d_scalars, dtype, buf[0]}));
         std::vector<fr_t> beta;
         uint64_t outer = 1;
@@ -3343,9 +3357,7 @@ static int interpolate(tc_ctx* ctx, int m, const uint32_t* shape, const void* d_
             uint32_t lines_per_wg = d >= (uint32_t)InterpAxis<false>::BLOCK ? 1u : (uint32_t)InterpAxis<false>::BLOCK / d;
             uint64_t groups = (lines + lines_per_wg - 1) / lines_per_wg;
             if (interp_by_tree(form, n, d)) {
-                size_t mark = ctx->wsp->off;
-                TRY(interpolate_axis_tree(ctx, plan, buf[0], outer, inner, d));
-                ctx->wsp->off = mark;                 /* the next axis is behind this one on the stream */
+                TRY(interpolate_axis_tree(ctx, plan, buf[0], by_lines ? buf[1] : half, weights, outer, inner, d));
             } else if (d > 1 && form == TC_INTERP_BARYCENTRIC) {
                 /* beta_l = (-1)^(d-1-l) / (l! (d-1-l)!) on the nodes 1 .. d */
                 beta.resize(d);

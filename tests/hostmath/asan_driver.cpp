@@ -136,6 +136,32 @@ int main() {
         std::free(r);
         std::free(d);
     }
+    // --- interpolation as tc_interpolate chooses it: the tree over the nodes of an axis on axes at, below and past a power
+    //     of two, alone and beside axes that keep to the lines; the same array as Newton's form, and no more workspace
+    //     than that form takes but for the tables of the nodes
+    for (const std::vector<uint32_t>& shape : std::vector<std::vector<uint32_t>>{
+             {48}, {64, 33}, {2049}, {8, 48, 9}, {1, 65, 49}, {15, 16, 17, 17}, {33, 33, 65}}) {
+        size_t n = 1, tables = 8 * 256;
+        for (uint32_t d : shape) {
+            size_t logn = 1;
+            while ((1u << logn) < d) ++logn;
+            n *= d;
+            if (d > 1) tables += ((2 * logn + 4) << logn) * sizeof(fr_t);
+        }
+        std::vector<int16_t> x(n);
+        for (auto& v : x) v = (int16_t)(rng() % 65536 - 32768);
+        int16_t* d = exact(x);
+        std::vector<uint8_t> zero(32 * n, 0);
+        uint8_t *lines = exact(zero), *tree = exact(zero);
+        CHECK(tc_interpolate_form(ctx, (int)shape.size(), shape.data(), d, TC_I16, TC_INTERP_NEWTON, lines));
+        const size_t by_lines = ctx->ws.demand;
+        CHECK(tc_interpolate(ctx, (int)shape.size(), shape.data(), d, TC_I16, tree));
+        REQUIRE(std::memcmp(lines, tree, 32 * n) == 0);
+        REQUIRE(ctx->ws.demand <= by_lines + tables);
+        std::free(lines);
+        std::free(tree);
+        std::free(d);
+    }
     // --- trees: entries tree with ragged grid, batched openings, batch verification, an update
     {
         const uint32_t node[2] = {2, 2};
