@@ -3188,6 +3188,11 @@ static bool interp_shape_ok(int m, const uint32_t* shape, uint64_t* total) {
     return true;
 }
 
+static int interp_logn(uint32_t d) {
+    int logn = 1;
+    while ((1u << logn) < d) ++logn;
+    return logn;
+}
 /* What the tree over the nodes of an axis needs of the grid: roots of unity up to the longest axis, and per distinct
  * axis length the tables of its nodes. */
 struct InterpPlan {
@@ -3216,8 +3221,7 @@ static int interp_plan(tc_ctx* ctx, InterpPlan& plan, uint32_t count, const uint
         if (plan.tables(lengths[i])) continue;
         InterpTables& a = plan.axis[plan.count];
         a.d = lengths[i];
-        a.logn = 1;
-        while ((1u << a.logn) < a.d) ++a.logn;
+        a.logn = interp_logn(a.d);
         logmax = std::max(logmax, a.logn);
         WS(even, fr_t, (size_t)a.logn << a.logn);
         WS(odd, fr_t, (size_t)a.logn << a.logn);
@@ -3253,6 +3257,16 @@ static int interp_plan(tc_ctx* ctx, InterpPlan& plan, uint32_t count, const uint
     }
     return TC_OK;
 }
+/* A tile fills the LDS of a compute unit: launches of 256 workgroups one behind the other, as many as full tiles need, and
+ * the lines spread evenly over them (33^4: 562 full tiles in 2.2 launches 4425 us, 765 of 47 lines 3373). */
+static uint64_t interp_tree_rounds(uint64_t lines, int logn) {
+    const uint64_t full = 256ull * (InterpAxisTree::TILE >> logn);
+    return (lines + full - 1) / full;
+}
+static uint32_t interp_tree_lines(uint64_t lines, int logn) {
+    const uint64_t groups = 256 * interp_tree_rounds(lines, logn);
+    return (uint32_t)((lines + groups - 1) / groups);
+}
 /* One axis of an (outer, d, inner) array, in place; `half` as large as interp_half says. */
 static uint64_t interp_half(uint64_t lines, int logn) { return lines << (logn - 1); }
 static int interpolate_axis_tree(tc_ctx* ctx, const InterpPlan& plan, fr_t* data, fr_t* half, fr_t* weights, uint64_t outer, uint64_t inner, uint32_t d) {
@@ -3260,8 +3274,7 @@ static int interpolate_axis_tree(tc_ctx* ctx, const InterpPlan& plan, fr_t* data
     RT(rt::launch<64>(d, ctx->stream, InterpWeights{plan.inv_fact, d, plan.roots.half_pow[a.logn], weights}));
     InterpAxisTree k;
     const uint64_t lines = outer * inner;
-    /* as many lines as fill the tile, fewer while compute units would stand idle */
-    k.lines_per_wg = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(InterpAxisTree::TILE >> a.logn, (lines + 255) / 256));
+    k.lines_per_wg = interp_tree_lines(lines, a.logn);
     const uint64_t groups = (lines + k.lines_per_wg - 1) / k.lines_per_wg;
     k.data = data; k.half = half;
     k.outer = outer; k.inner = inner; k.d = d; k.logn = a.logn;
@@ -3269,13 +3282,37 @@ static int interpolate_axis_tree(tc_ctx* ctx, const InterpPlan& plan, fr_t* data
     RT((launch_coop_n<InterpAxisTree::BLOCK>((uint32_t)groups, ctx->stream, k, k.phases())));
     return TC_OK;
 }
-/* tc_interpolate takes the tree over the nodes where an axis fits a tile; tc_interpolate_form keeps to its form.  The tree's
- * tables are a chain of launches, so few lines have to be longer before it pays than many: a line of 16 alone 0.11 ms against
- * 0.08 by its differences, of 33 0.19 against 0.14, of 64 0.19 against 0.25; 16^5 entries 1.2 against 2.0 ms, 9^6 1.3
- * against 0.95, 8^7 the same 2.8. */
+/* tc_interpolate takes the tree over the nodes for the axes that fit a tile and gain by it; tc_interpolate_form keeps to its
+ * form.  What an axis costs either way is counted in products of the whole chip, lanes that idle included, in launches of
+ * 256 workgroups: a tree works on 2^logn places per line, whatever d, and Newton's differences keep d (d - 1) lanes per
+ * line busy twice, floor(1024 / d) lines to a workgroup.  The tables of the nodes are a chain of launches of their own,
+ * shared by the axes of a call.  Measured (us, tree against differences; share of the tree's count in the other's):
+ *   17^5 3461 / 2915 (1.22), 11^4 x 17 544 / 456 (1.30), 14^4 x 17 1438 / 1320 (1.14), 4096 x 13 x 18 2708 / 2649 (1.10),
+ *   8^5 x 17 1052 / 1008 (0.96, one axis to pay for the tables), 14^4 x 33 2673 / 2611 (0.91; 33 first 2649 / 2774),
+ *   33^4 3373 / 3928 (0.84), 20^4 432 / 612 (0.60), 8^4 x 16 347 / 354 (0.14); shorter axes are faster by differences.
+ * Few entries leave most of the chip idle either way, and a short tree is as deep as a short line: below 65536 entries
+ * from 48 nodes on (alone: 33 nodes 190 / 140, 48 187 / 189, 64 188 / 245). */
 static const int INTERP_ANY_FORM = -1;
-static bool interp_by_tree(int form, uint64_t n, uint32_t d) {
-    return form == INTERP_ANY_FORM && d >= (n >= 65536 ? 16u : 48u) && d <= InterpAxisTree::TILE;
+static const int64_t INTERP_TABLES = 6500000;
+static int64_t interp_tree_gain(uint64_t lines, uint32_t d) {
+    const uint64_t logn = (uint64_t)interp_logn(d), lanes = 1024, whole = lanes / d ? lanes / d : 1;
+    const uint64_t tree = (256ull * interp_tree_rounds(lines, (int)logn) * interp_tree_lines(lines, (int)logn) << logn) * (logn * logn + 4 * logn + 1) / 2;
+    const uint64_t slots = (whole * d + lanes - 1) / lanes * lanes, rounds = ((lines + whole - 1) / whole + 255) / 256;
+    return (int64_t)(256 * rounds * slots * 2 * (d - 1)) - (int64_t)tree;
+}
+/* bit j set: axis j goes over the tree */
+static uint32_t interp_tree_axes(int form, int m, const uint32_t* shape, uint64_t n) {
+    uint32_t axes = 0;
+    int64_t gain = 0;
+    for (int j = 0; j < m; ++j) {
+        const uint32_t d = shape[j];
+        if (form != INTERP_ANY_FORM || d < (n >= 65536 ? 16u : 48u) || d > InterpAxisTree::TILE) continue;
+        const int64_t g = interp_tree_gain(n / d, d);
+        if (g <= 0) continue;
+        gain += g;
+        axes |= 1u << j;
+    }
+    return gain > INTERP_TABLES ? axes : 0;
 }
 static int interpolate(tc_ctx* ctx, int m, const uint32_t* shape, const void* d_scalars, int dtype, int form, void* d_coeffs) {
     try {
@@ -3290,9 +3327,10 @@ static int interpolate(tc_ctx* ctx, int m, const uint32_t* shape, const void* d_
         TRY(ws_reset(ctx));
         uint32_t dmax = 1, ntree = 0, by_tree[TC_MAX_INTERP_ORDER];
         bool by_lines = form != INTERP_ANY_FORM;
+        const uint32_t tree_axes = interp_tree_axes(form, m, shape, n);
         for (int j = 0; j < m; ++j) {
             dmax = std::max(dmax, shape[j]);
-            if (interp_by_tree(form, n, shape[j])) by_tree[ntree++] = shape[j];
+            if (tree_axes >> j & 1u) by_tree[ntree++] = shape[j];
             else if (shape[j] > 1) by_lines = true;
         }
         /* 1 / l, 1 / l! and zeta_k = k + 1 up to the longest axis; (dmax - 1)! from as many factors at a time as fit 32 bits */
@@ -3356,7 +3394,7 @@ static int interpolate(tc_ctx* ctx, int m, const uint32_t* shape, const void* d_
             uint64_t lines = outer * inner;
             uint32_t lines_per_wg = d >= (uint32_t)InterpAxis<false>::BLOCK ? 1u : (uint32_t)InterpAxis<false>::BLOCK / d;
             uint64_t groups = (lines + lines_per_wg - 1) / lines_per_wg;
-            if (interp_by_tree(form, n, d)) {
+            if (tree_axes >> j & 1u) {
                 TRY(interpolate_axis_tree(ctx, plan, buf[0], by_lines ? buf[1] : half, weights, outer, inner, d));
             } else if (d > 1 && form == TC_INTERP_BARYCENTRIC) {
                 /* beta_l = (-1)^(d-1-l) / (l! (d-1-l)!) on the nodes 1 .. d */

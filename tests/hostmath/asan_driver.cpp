@@ -162,6 +162,31 @@ int main() {
         std::free(tree);
         std::free(d);
     }
+    // --- which axes take the tree: none that was measured slower that way, all that were measured faster; and a tile holds
+    //     the lines of a workgroup, whose launches cover all lines
+    {
+        auto axes = [](std::vector<uint32_t> shape) {
+            uint64_t n = 1;
+            for (uint32_t d : shape) n *= d;
+            return interp_tree_axes(INTERP_ANY_FORM, (int)shape.size(), shape.data(), n);
+        };
+        for (const auto& s : std::vector<std::vector<uint32_t>>{{17, 17, 17, 17, 17}, {18, 18, 18, 18, 18}, {14, 14, 14, 14, 17}, {11, 11, 11, 11, 17},
+                                                                {8, 8, 8, 8, 17}, {8, 8, 8, 8, 8, 18}, {14, 19, 14, 14, 14}, {11, 11, 11, 11, 33},
+                                                                {33}, {16}, {8, 33}, {16, 16, 16}, {15, 4097}})
+            REQUIRE(axes(s) == 0);
+        REQUIRE(axes({4096, 13, 18}) == 1 && axes({17, 4096, 13}) == 2);
+        for (const auto& s : std::vector<std::vector<uint32_t>>{{33, 33, 33, 33}, {20, 20, 20, 20}, {512, 4096}, {512, 1000}, {64}, {48, 48}, {16, 16, 16, 16}, {16, 8, 8, 8, 8}})
+            REQUIRE(axes(s) == (s[1 % s.size()] == 8 ? 1u : (1u << s.size()) - 1));
+        const uint32_t all[3] = {33, 33, 65};
+        for (int form : {TC_INTERP_NEWTON, TC_INTERP_GREGORY, TC_INTERP_BARYCENTRIC}) REQUIRE(interp_tree_axes(form, 3, all, 33 * 33 * 65) == 0);
+        for (uint32_t d : {2u, 16u, 17u, 100u, 512u, 513u, 2048u, 2049u, 4096u})
+            for (uint64_t lines = 1; lines < (1ull << 31) / d; lines = lines * 9 / 8 + 1) {
+                const int logn = interp_logn(d);
+                const uint64_t per = interp_tree_lines(lines, logn), groups = (lines + per - 1) / per;
+                REQUIRE(per >= 1 && (per << logn) <= InterpAxisTree::TILE && groups <= 256 * interp_tree_rounds(lines, logn));
+                REQUIRE(interp_half(lines, logn) < lines * d);
+            }
+    }
     // --- trees: entries tree with ragged grid, batched openings, batch verification, an update
     {
         const uint32_t node[2] = {2, 2};

@@ -1079,7 +1079,7 @@ def test_coefficient_route(T, ctx):
         lag.close()
 
 
-@pytest.mark.parametrize("shape", [(48,), (64, 33), (15, 16, 17, 17), (3, 512, 5), (511, 7), (7, 513), (2049, 2), (4095,), (4096, 3), (2, 4097)])
+@pytest.mark.parametrize("shape", [(48,), (64, 33), (15, 16, 17, 17), (3, 512, 5), (511, 7), (7, 513), (2049, 2), (4095,), (4096, 3), (2, 4097), (33, 33, 33, 33), (1024, 1025)])
 def test_interpolation_by_tree(T, ctx, shape):
     """The tree over the nodes of an axis against Newton's differences line by line, bit for bit."""
     import torch
