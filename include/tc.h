@@ -146,6 +146,8 @@ int tc_ctx_alu_rate(tc_ctx* ctx, int kind, int waves_per_simd, double* out_per_s
  *          13 ((a - b)(a + b) - b (a - b)) / R: the 28-bit-limb form of the bucket accumulation (operands re-cut, sums
  *          and differences left unreduced with signed limbs, one product -- for 13 the difference of two products
  *          under one reduction --, back to the canonical element).
+ *          14 2^776 / a by the inversion of a whole wave (n <= 2^24): a is given as 14 signed limbs of 28 bits, one to a
+ *          word, limbs 0 .. 12 in [0, 2^28), the sign in limb 13, |a| < 2 p, a no multiple of p but 0 (which gives 0).
  * b is ignored by the one-operand operations but must be valid. */
 int tc_ctx_field_op(tc_ctx* ctx, int op, const void* d_a, const void* d_b, size_t n, void* d_out);
 

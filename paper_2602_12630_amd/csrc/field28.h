@@ -384,8 +384,10 @@ TC_HD fp_t fp_inv28(const fp_t& x) {
  * that starts at delta = 1/2; D = delta - 1/2.  A step: if D >= 0 and g odd (f, g, D) <- (g, (g - f) / 2, -D), else
  * (f, g, D) <- (f, (g + (g mod 2) f) / 2, D + 1).  Only the low bits of f and g decide, so 28 steps need the lowest
  * limb alone and their matrix, entries of at most 2^28 in absolute row sum, is applied to the whole numbers
- * afterwards.  Several steps at a time: zeros of g are stripped by a count, and while D < 0 no swap can come, so up
- * to six low bits of g are cleared by one multiple of f (-1 / f = f (f f - 2) mod 2^6 for odd f).
+ * afterwards.  Several steps at a time, in the order in which the variable-time inversion of libsecp256k1 (Dettman,
+ * Wuille, 2021) takes them: zeros of g are stripped by a count, and while D < 0 no swap can come, so up
+ * to six low bits of g are cleared by one multiple of f (-1 / f = f (f f - 2) mod 2^6 for odd f); the start at
+ * delta = 1/2 is described there too.
  * About 9.5 passes of the loop per 28 steps, and 28 rounds for a 381-bit modulus (measured on random values). */
 TC_HD void fp28_divsteps(int32_t& D, uint32_t f, uint32_t g, int32_t (&m)[4]) {
     uint32_t u = 1, v = 0, q = 0, r = 1;
@@ -413,11 +415,15 @@ TC_HD void fp28_divsteps(int32_t& D, uint32_t f, uint32_t g, int32_t (&m)[4]) {
     }
     m[0] = (int32_t)u; m[1] = (int32_t)v; m[2] = (int32_t)q; m[3] = (int32_t)r;
 }
-/* Rounds after which f = +-1 and g = 0 for any input below 2 p (at most 32); the margin covers the rounds in which g
- * = 0 still stands in limbs that cancel.  The loop leaves as soon as the limbs of g are zero. */
+/* The loop leaves as soon as the limbs of g are zero, after at most 32 + 14 rounds.
+ * 32: from f = p, |g| <= 2 p no more than 881 steps leave a g != 0 (for every D the convex hull of the (f, g) that some
+ * sequence of parities reaches, cut at |g| >= 1, until all hulls are empty; the same count for 256 bits and |g| <= f
+ * gives 591, one more than published for these steps).
+ * 14: g = 0 may stand in limbs that cancel.  The lazily carried limbs are in [-2, 2^28 + 2], so such limbs are
+ * l_j = 2^28 k_(j+1) - k_j with k_j in {0, 1}, and each round settles one of them at least. */
 static constexpr int FP28_INV_MAX_ROUNDS = 48;
 /* The inverse of an element in the form of this header (R^2 / x on the limbs, R = 2^392), x with normal limbs and
- * |x| < 2 p; 0 for a multiple of p.  All lanes of a wave hold the same x and get the same result.
+ * |x| < 2 p; 0 for 0, and x no other multiple of p.  All lanes of a wave hold the same x and get the same result.
  * Row k = lane / 16 of the wave holds f, g, d, e (k = 0 .. 3), a lane one limb: f = d x, g = e x (mod p).  A round runs
  * the steps once for the wave, on scalar registers (what decides is the same for all lanes), and then spends some
  * thirty vector instructions on the four updates: the limbs of the partner row (permlane16 swap), two

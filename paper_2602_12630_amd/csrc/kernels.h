@@ -53,7 +53,8 @@ enum { FOP_FP_MUL = 0, FOP_FP_SQR = 1, FOP_FP_MUL_F64 = 2, FOP_FP_SQR_F64 = 3, F
        /* through the 28-bit-limb form and back: a b, a^2, (a - b)(a + b), (a - 2 b)(a - b) (limbs grown and signed) */
        FOP_FP28_MUL = 9, FOP_FP28_SQR = 10, FOP_FP28_DIFF_SUM = 11, FOP_FP28_GROWN = 12,
        FOP_FP28_MUL_SUB = 13,      /* (a - b)(a + b) - b (a - b) under one reduction */
-       FOP_COUNT = 14 };
+       FOP_FP28_INV = 14,          /* the inversion of a whole wave (FieldInvWave) */
+       FOP_COUNT = 15 };
 struct FieldOp {
     int op;
     const uint32_t* a;      /* 12 limbs per element (8 for the Fr operations) */
@@ -102,6 +103,27 @@ struct FieldOp {
         }
 #pragma unroll
         for (int i = 0; i < 12; ++i) out[12 * (uint64_t)t + i] = r.l[i];
+    }
+};
+
+/* The same for the inversion of a whole wave: a workgroup of one wave per element, 14 signed limbs in, 12 words out. */
+struct FieldInvWave {
+    static constexpr int BLOCK = 64;
+    static constexpr int PHASES = 1;
+    static constexpr size_t LDS_BYTES = 16;
+    const int32_t* a;
+    uint32_t* out;
+    TC_DEV void phase(int, uint32_t lane, uint32_t wg, uint8_t*) const {
+#if defined(TC_HOST_EMU)
+        if (lane) return;
+#endif
+        fp28 x;
+#pragma unroll
+        for (int j = 0; j < 14; ++j) x.l[j] = a[14 * (uint64_t)wg + j];
+        fp_t r = fp28_to_fp(fp28_inv_wave(x));
+        if (lane) return;
+#pragma unroll
+        for (int i = 0; i < 12; ++i) out[12 * (uint64_t)wg + i] = r.l[i];
     }
 };
 

@@ -637,7 +637,12 @@ extern "C" int tc_ctx_field_op(tc_ctx* ctx, int op, const void* d_a, const void*
     if (!ctx) return TC_ERR_ARG;
     if (op < 0 || op >= FOP_COUNT || ((!d_a || !d_b || !d_out) && n)) return fail(ctx, TC_ERR_ARG, "bad argument");
     if (n > 0xFFFFFFFFull) return fail(ctx, TC_ERR_SHAPE, "too many elements");
+    if (op == FOP_FP28_INV && n > 1u << 24) return fail(ctx, TC_ERR_SHAPE, "too many elements");
     RT(rt::set_device(ctx->device));
+    if (op == FOP_FP28_INV) {
+        RT((launch_coop<FieldInvWave::BLOCK>((uint32_t)n, ctx->stream, FieldInvWave{(const int32_t*)d_a, (uint32_t*)d_out})));
+        return TC_OK;
+    }
     RT(rt::launch<64>(n, ctx->stream, FieldOp{op, (const uint32_t*)d_a, (const uint32_t*)d_b, (uint32_t*)d_out}));
     return TC_OK;
 }

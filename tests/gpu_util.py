@@ -142,6 +142,27 @@ def check_field_arithmetic(run, n_fp, n_fr):
     assert all(g == RR * RR * pow(v, -1, Rr) % Rr for g, v in zip(got, nzr)), "Fr inverse"
 
 
+def check_wave_inversion(run, n):
+    """run(a_words, n) -> result words of field operation 14, the inversion of a whole wave: edges of the range |a| < 2 p
+    on both sides of zero, powers of two, values with runs of full and of empty limbs, random ones; 2^776 / a (mod p)."""
+    import random
+
+    P = ec.P
+    rng = random.Random(23)
+    vals = [1, 2, 3, P - 1, P - 2, P + 1, P + 2, (P - 1) // 2, (P + 1) // 2, 2 * P - 1, 2 * P - 2, (1 << 28) - 1, P >> 28,
+            (1 << 364) - 1, 1 << 364, ((1 << 364) - 1) ^ ((1 << 28) - 1)]
+    vals += [1 << k for k in range(0, 382, 7)] + [P - (1 << k) for k in range(0, 380, 7)] + [P + (1 << k) for k in range(0, 380, 13)]
+    vals += [int("0fffffff0000000" * 6, 16) & ((1 << 381) - 1), int("0000000fffffff" * 6, 16) & ((1 << 381) - 1)]
+    vals += [rng.randrange(1, 2 * P) for _ in range(n)] + [rng.randrange(1, 1 << rng.randrange(1, 382)) for _ in range(n)]
+    vals = [0] + [v * s for v in vals for s in (1, -1) if v % P]
+    assert all(abs(v) < 2 * P for v in vals)
+    limbs = np.array([[(v >> 28 * j) & ((1 << 28) - 1) if j < 13 else v >> 364 for j in range(14)] for v in vals], dtype=np.int32)
+    raw = np.ascontiguousarray(run(limbs.reshape(-1), len(vals))).tobytes()
+    for i, v in enumerate(vals):
+        got = int.from_bytes(raw[48 * i : 48 * (i + 1)], "little")
+        assert got == (pow(2, 776, P) * pow(v, -1, P) % P if v else 0), hex(v)
+
+
 def check_one_point_throughout(ctx, upload, shape):
     """Public parameters that are one and the same point at every position, at a size whose passes over the partial
     sums fill the chip: every addition in them is a doubling or a cancellation, so every lane of the fast passes

@@ -29,7 +29,7 @@ void hm_fp_inv(const uint8_t* a, uint8_t* o) { fp_store(o, fe_inv_fermat<FpParam
 void hm_fp_inv_binary(const uint8_t* a, uint8_t* o) { fp_store(o, fe_inv<FpParams>(fp_load(a))); }
 void hm_fr_inv_binary(const uint8_t* a, uint8_t* o) { fr_store(o, fe_inv<FrParams>(fr_load(a))); }
 void hm_fp_inv_gcd(const uint8_t* a, uint8_t* o) { fp_store(o, fe_inv_gcd<FpParams>(fp_load(a))); }
-void hm_fp_inv_wave(const uint8_t* a, uint8_t* o) { fp_store(o, fp28_to_fp(fp28_inv_wave(fp28_from_fp(fp_load(a))))); }
+void hm_fp_inv_wave(const uint8_t* a, uint8_t* o) { fp_store(o, fp28_to_fp(fp28_inv_wave(fp28_mul(fp28_from_fp(fp_load(a)), fp28_one())))); }
 void hm_fr_inv_gcd(const uint8_t* a, uint8_t* o) { fr_store(o, fe_inv_gcd<FrParams>(fr_load(a))); }
 void hm_fr_mul(const uint8_t* a, const uint8_t* b, uint8_t* o) { fr_store(o, fr_mul(fr_load(a), fr_load(b))); }
 void hm_fr_add(const uint8_t* a, const uint8_t* b, uint8_t* o) { fr_store(o, fr_add(fr_load(a), fr_load(b))); }

@@ -12,7 +12,7 @@ from oracle import bls12_381 as ec
 from oracle import cbind, quantize, tc, terkle
 from oracle.bls12_381 import R
 
-from gpu_util import HOST_THREADS, TAU_BYTES, Stopwatch, check_field_arithmetic, check_one_point_throughout, check_repeated_points, fr_bytes_array, oracle_pool, parse_proof, pps, progress, serialize_steps, to_device
+from gpu_util import HOST_THREADS, TAU_BYTES, Stopwatch, check_field_arithmetic, check_wave_inversion, check_one_point_throughout, check_repeated_points, fr_bytes_array, oracle_pool, parse_proof, pps, progress, serialize_steps, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -64,6 +64,19 @@ def test_device_field_arithmetic_against_integers(T, ctx):
         return out.cpu().numpy().view(np.uint32)
 
     check_field_arithmetic(run, 4096, 1024)
+
+
+def test_device_wave_inversion_against_integers(T, ctx):
+    """The inversion that normalisation uses, whole waves through permlane, DPP and readlane, one value each."""
+    import torch
+
+    def run(a, n):
+        da, out = to_device(a), torch.empty(12 * n, dtype=torch.int32, device="cuda")
+        ctx.field_op(14, da, da, n, out)
+        ctx.sync()
+        return out.cpu().numpy()
+
+    check_wave_inversion(run, 1500)
 
 
 def test_options_do_not_change_results(T, ctx):

@@ -25,7 +25,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 import __graft_entry__ as entry  # noqa: E402
 import paper_2602_12630_amd as T  # noqa: E402
-from gpu_util import TAU_BYTES, check_field_arithmetic, check_one_point_throughout, check_repeated_points, fr_bytes_array, pps, serialize_steps  # noqa: E402
+from gpu_util import TAU_BYTES, check_field_arithmetic, check_wave_inversion, check_one_point_throughout, check_repeated_points, fr_bytes_array, pps, serialize_steps  # noqa: E402
 
 EMU = os.path.join(ROOT, "tests", "hostmath", "libtc_hostemu.so")
 
@@ -714,6 +714,19 @@ def test_emulated_field_ops(emu):
         return out
 
     check_field_arithmetic(run, 200, 100)
+
+
+def test_emulated_wave_inversion(emu):
+    """The inversion of a whole wave, its rows and limbs written out as arrays, on the operands of the GPU test."""
+
+    def run(a, n):
+        out = np.zeros(12 * n, np.int32)
+        emu.field_op(14, a, a, n, out)
+        return out
+
+    check_wave_inversion(run, 200)
+    with pytest.raises(T.TcError):
+        emu.field_op(15, np.zeros(14, np.int32), np.zeros(14, np.int32), 1, np.zeros(12, np.int32))
 
 
 def test_emulated_options(emu, monkeypatch):

@@ -68,6 +68,35 @@ def test_inversion_by_division_steps(hm, group):
         assert int.from_bytes(bytes(out), "little") == (pow(a, -1, P) if a else 0), a
 
 
+def test_rounds_of_the_wave_inversion():
+    """What the 48 rounds of that inversion rest on: no operand takes more than 881 division steps (32 rounds of 28), and a
+    g = 0 that stands in limbs that cancel, in whichever of the 2^13 ways, is all zeros after at most 14 rounds more."""
+    rng = random.Random(9)
+    edges = [1, 2, P - 1, P + 1, 2 * P - 1, (P + 1) // 2, (1 << 381) - 1] + [1 << k for k in range(0, 381, 20)]
+    for x in edges + [rng.randrange(1, 2 * P) for _ in range(200)]:
+        for g in (x, -x):
+            f, D, steps = P, 0, 0
+            while g:
+                if D >= 0 and g & 1:
+                    f, g, D = g, (g - f) >> 1, -D
+                else:
+                    g, D = (g + (g & 1) * f) >> 1, D + 1
+                steps += 1
+            assert abs(f) == 1 and steps <= 881, x
+    assert 881 <= 32 * 28
+    mask = (1 << 28) - 1
+    for ways in range(1 << 13):
+        k = [0] + [ways >> j & 1 for j in range(13)] + [0]
+        limbs = [(k[j + 1] << 28) - k[j] for j in range(14)]
+        assert sum(l << 28 * j for j, l in enumerate(limbs)) == 0
+        rounds = 0
+        while any(limbs):
+            n = [(limbs[j] >> 28) + (limbs[j + 1] & mask if j < 13 else 0) for j in range(14)]
+            limbs = [(n[j] & mask if j < 13 else n[j]) + (n[j - 1] >> 28 if j else 0) for j in range(14)]
+            rounds += 1
+        assert rounds <= 14
+
+
 def test_fp_fr_arithmetic(hm):
     rng = random.Random(1)
     edge_p = [0, 1, 2, P - 1, P - 2, (P - 1) // 2, (1 << 380), 0xFFFFFFFF, (1 << 352) - 1, (1 << 380) - 1]
