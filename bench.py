@@ -620,11 +620,20 @@ def encode_stream(ctx, T, torch):
                       "note": "tc_quant_scale: 2 bytes read per element"}}
 
 
+def tree_products(d):
+    """Fr products per entry that tc_interpolate spends on an axis of d nodes over the tree of its nodes, padded to the
+    2^L that it works on: one for the weight, at level t two to form the values of a parent on either half of its domain
+    and t to extend a child's (one at t = 1's only stage, the twist), half of L - 1 for the transform at the end."""
+    L = max(1, (d - 1).bit_length())
+    return (1 << L) / d * (1 + sum(2 + t for t in range(L)) + (L - 1) / 2)
+
+
 def coefficient_route(ctx, T, torch, with_oracle, peak):
     """Interpolation to monomial coefficients (the first step of Com as Def. 4.1 prints it, bypassed by the hot
-    path): the sweep of Fig. 1, N = 2^12 samples reshaped to order-m grids, in Newton form (`gpu_ms`) and in the
-    Gregory and barycentric forms of App. C, and the C2 activation; one Fr product
-    = 2 * 8^2 + 8 = 136 multiply-adds, an axis of length d costs 2 (d - 1) products per entry."""
+    path): the sweep of Fig. 1, N = 2^12 samples reshaped to order-m grids, in Newton form (`gpu_ms`), in the
+    Gregory and barycentric forms of App. C and as tc_interpolate does it (`gpu_ms_tc_interpolate`: over a tree of the
+    nodes where that is faster), and the C2 activation by tc_interpolate, both axes over the tree; one Fr product
+    = 2 * 8^2 + 8 = 136 multiply-adds."""
     from oracle import tc as otc
 
     out = {"sweep_n_4096": []}
@@ -639,8 +648,8 @@ def coefficient_route(ctx, T, torch, with_oracle, peak):
         for _ in range(3):
             ctx.interpolate(shape, dx, T.TC_I16, coeffs)
         torch.cuda.synchronize()
-        line = {"m": len(shape), "shape": list(shape), "gpu_ms": (time.perf_counter() - t0) * 1e3 / 3}
-        for form, name in ((T.TC_INTERP_GREGORY, "gregory"), (T.TC_INTERP_BARYCENTRIC, "barycentric")):
+        line = {"m": len(shape), "shape": list(shape), "gpu_ms_tc_interpolate": (time.perf_counter() - t0) * 1e3 / 3}
+        for form, name in ((T.TC_INTERP_NEWTON, ""), (T.TC_INTERP_GREGORY, "_gregory"), (T.TC_INTERP_BARYCENTRIC, "_barycentric")):
             other = torch.empty_like(coeffs)
             ctx.interpolate_form(shape, dx, T.TC_I16, form, other)
             torch.cuda.synchronize()
@@ -648,7 +657,7 @@ def coefficient_route(ctx, T, torch, with_oracle, peak):
             for _ in range(3):
                 ctx.interpolate_form(shape, dx, T.TC_I16, form, other)
             torch.cuda.synchronize()
-            line["gpu_ms_" + name] = (time.perf_counter() - t1) * 1e3 / 3
+            line["gpu_ms" + name] = (time.perf_counter() - t1) * 1e3 / 3
             assert torch.equal(other, coeffs), (shape, name)
         if with_oracle and len(shape) >= 2:
             t1 = time.perf_counter()
@@ -668,7 +677,7 @@ def coefficient_route(ctx, T, torch, with_oracle, peak):
     ctx.interpolate(shape, dx, T.TC_I16, coeffs)
     torch.cuda.synchronize()
     ms = (time.perf_counter() - t0) * 1e3
-    mads = q.size * sum(2 * (d - 1) for d in shape) * 136
+    mads = q.size * sum(tree_products(d) for d in shape) * 136
     out["c2_activation"] = {"shape": list(shape), "ms": ms, "achieved": mads / (ms * 1e-3) / 1e12,
                             "frac": mads / (ms * 1e-3) / peak, "unit": "T 32x32->64 multiply-add/s"}
     return out

@@ -345,6 +345,25 @@ def test_emulated_interpolation_by_tree(emu, shape):
         emu.interpolate_form(shape, X, T.TC_FR, -1, tree)
 
 
+@pytest.mark.parametrize("d", [2, 16, 48, 512, 4096])
+def test_bench_counts_the_products_of_the_tree(d):
+    """The products per entry that bench.py charges to an axis over the tree, against a walk over the kernel's stages
+    (butterflies of neighbours multiply by nothing)."""
+    import bench
+
+    n = 1
+    while n < d:
+        n *= 2
+    per_pair, t = 0, 0
+    while 1 << t < n:
+        per_pair += 4                                                     # P_L M_R + P_R M_L on both halves of the domain
+        if t:
+            per_pair += sum(1 for k in range(t) if k) * 2 + 2             # back and forth, the twist of both elements
+        t += 1
+    per_pair += sum(1 for k in range(t) if k)
+    assert abs(bench.tree_products(d) * d - (per_pair * n / 2 + n)) < 1e-6 * n
+
+
 def test_emulated_coefficient_route(emu):
     """The literal route of Def. 4.1 through the library: interpolation to monomial coefficients, Algorithm 1 on
     the coefficient array, commitments against the monomial SRS -- each against the oracle's own literal route,
