@@ -18,6 +18,15 @@ static void fr_store(uint8_t* b, const fr_t& a) { fr_t p = fe_to_plain(a); memcp
 static g1_affine pt_load(const uint8_t* b) { uint32_t w[24]; memcpy(w, b, 96); return affine_from_canonical(w); }
 static void pt_store(uint8_t* b, const g1_affine& p) { uint32_t w[24]; affine_to_canonical(p, w); memcpy(b, w, 96); }
 
+// the phases of a cooperative kernel, lane by lane
+template <class K>
+static void coop_run(const K& k, uint32_t groups) {
+    std::vector<uint8_t> lds(K::LDS_BYTES);
+    for (uint32_t g = 0; g < groups; ++g)
+        for (int ph = 0; ph < K::PHASES; ++ph)
+            for (uint32_t lane = 0; lane < (uint32_t)K::BLOCK; ++lane) k.phase(ph, lane, g, lds.data());
+}
+
 extern "C" {
 void hm_fp_mul(const uint8_t* a, const uint8_t* b, uint8_t* o) { fp_store(o, fp_mul(fp_load(a), fp_load(b))); }
 void hm_fp_mul_limbs32(const uint8_t* a, const uint8_t* b, uint8_t* o) { fp_store(o, fe_mul<FpParams>(fp_load(a), fp_load(b))); }
@@ -75,10 +84,22 @@ void hm_coop_reduce(const uint8_t* pts, uint32_t n, int spread, uint8_t* o) {
     g1_xyzz r;
     typedef CoopReduce<ArraySrc> K;
     K k{ArraySrc{in.data(), n, &r}};
-    std::vector<uint8_t> lds(K::LDS_BYTES);
-    for (int ph = 0; ph < K::PHASES; ++ph)
-        for (uint32_t lane = 0; lane < (uint32_t)K::BLOCK; ++lane) k.phase(ph, lane, 0, lds.data());
+    coop_run(k, 1);
     pt_store(o, xyzz_to_affine(r));
+}
+// sum_k k B_k of windows of 2^lognb buckets bit by bit: the sums per bit, their place values, the total
+void hm_window_bits(const uint8_t* pts, uint32_t lognb, uint32_t windows, uint8_t* o) {
+    const uint32_t chains = lognb + 1, n = chains * windows;
+    std::vector<g1_xyzz> bucket((size_t)windows << lognb), bits(n), scaled(n), sum(windows);
+    for (size_t i = 0; i < bucket.size(); ++i) {
+        g1_affine a = pt_load(pts + 96 * i);
+        bucket[i] = i % 2 ? xyzz_madd(xyzz_dbl_affine(a), affine_neg(a)) : xyzz_from_affine(a);
+    }
+    coop_run(CoopReduce<SmallBitSumSrc>{SmallBitSumSrc{bucket.data(), lognb, bits.data()}}, n);
+    if (lognb == 7) coop_run(BitSumScale<8>{bits.data(), n, scaled.data()}, (n + 63) / 64);
+    else coop_run(BitSumScale<9>{bits.data(), n, scaled.data()}, (n + 63) / 64);
+    coop_run(CoopReduce<GroupSumSrc>{GroupSumSrc{scaled.data(), chains, sum.data()}}, windows);
+    for (uint32_t w = 0; w < windows; ++w) pt_store(o + 96 * (size_t)w, xyzz_to_affine(sum[w]));
 }
 // the verifier's short final exponentiation against the plain one: must be its cube; also x^p, x^(p^2) by powers
 int hm_final_exponentiation_forms(const uint8_t* p, uint32_t k) {

@@ -159,6 +159,17 @@ def test_emulated_open_by_rows(emu):
                 assert pi == [ec.g1_to_bytes(p) for p in po]
     finally:
         srs.close()
+    # two long rows: their few windows of 256 buckets are weighted bit by bit
+    shape = (2, 16384)
+    pp = pps(shape)
+    srs = emu.setup_from_trapdoor(TAU_BYTES, shape, T.TC_SRS_SUFFIX)
+    try:
+        X = tc_inputs.int16_uniform(shape, 8, -32768, 32767)
+        y, pi = emu.open(srs, X, T.TC_I16, (1, 16383))
+        yo, po = tc.open_(pp, X, (1, 16383))
+        assert y == ec.fr_to_bytes(yo) and pi == [ec.g1_to_bytes(p) for p in po]
+    finally:
+        srs.close()
     # many rows: the bucket reduction of the row problems switches to the 16 x 16 form
     shape = (260, 64)
     pp = pps(shape)

@@ -172,9 +172,10 @@ def test_group_law_including_exceptional_cases(hm):
         assert _pt(hm.hm_g1_mul, _b(k, 32), _pb(pts[0])) == ec.mul_affine(k, pts[0])
 
 def test_cooperative_reduction(hm):
-    """Sums of up to 256 points through the shared-addition kernel, with the operand patterns that leave the
-    regular chord rule: identities anywhere, equal neighbours (tangent rule), opposite neighbours, everything
-    cancelling."""
+    """Sums of up to 256 points through the shared-addition kernel, which adds points i and 64 + i, then 128 + i and
+    192 + i, the two sums, and halves of the 64 sums: every length at which another step begins or ends, and the operand
+    patterns that leave the regular chord rule, namely identities anywhere, equal points (tangent rule), opposite points
+    in the first, second and third step, everything cancelling."""
     rng = random.Random(5)
     base = [ec.mul(rng.randrange(1, R), ec.G1) for _ in range(6)]
 
@@ -195,23 +196,49 @@ def test_cooperative_reduction(hm):
         [],
         [base[0]],
         [base[0], base[1]],
-        [base[0], base[0]],                                  # tangent rule at the first level
+        [base[0], base[0]],                                  # tangent rule in the last step
         [base[0], ec.neg(base[0])],                          # opposite points
         [ec.INF, base[2]],
         [base[2], ec.INF],
         [ec.INF, ec.INF, ec.INF],
-        [base[0], base[1], base[0], base[1]],                # equal partial sums one level up
+        [base[0], base[1], base[0], base[1]],                # equal points, then a regular sum of theirs
         [base[0], base[1], ec.neg(base[0]), ec.neg(base[1])],
         [base[i % 6] for i in range(17)],
         [base[rng.randrange(6)] if rng.random() < 0.6 else ec.INF for _ in range(255)],
         [ec.mul(i + 1, base[3]) for i in range(64)] + [ec.neg(ec.mul(i + 1, base[3])) for i in range(64)],
         [base[rng.randrange(6)] for _ in range(256)],
     ]
+    many = [ec.mul(i + 2, base[4]) for i in range(64)]
+    minus = [ec.neg(p) for p in many]
+    cases += [many, many + minus[:1], many + many[:1], many + many, many + minus + many[:1], many + minus + many,
+              many + minus + many + minus[:1], many + many + many + many, many + minus + minus + minus,
+              many + many + minus + minus, many + [ec.INF] * 64 + many + minus, [ec.INF] * 192 + many,
+              many[:33] + [ec.INF] * 95 + minus[:33] + [ec.INF] * 63 + many[:1]]
+    for n in (32, 33, 63, 64, 65, 127, 128, 129, 191, 192, 193, 255):
+        cases.append([base[rng.randrange(6)] for _ in range(n)])
     for spread in (0, 1):
         for pts in cases:
             got = run(pts, spread)
             w = want(pts)
             assert (got is ec.INF and w is ec.INF) or got == w, (len(pts), spread)
+
+
+@pytest.mark.parametrize("lognb,windows", [(7, 1), (7, 9), (8, 1), (8, 2), (8, 8)])
+def test_window_bit_by_bit(hm, lognb, windows):
+    """sum_k k B_k of a few windows of 128 or 256 buckets through the sums per bit, from one workgroup of chains to more
+    than 64 chains; buckets empty, equal and opposite among them, and a window with nothing in it."""
+    rng = random.Random(lognb * 100 + windows)
+    nb = 1 << lognb
+    table = [ec.mul(i + 1, ec.G1) for i in range(40)]
+    mult = [[0 if w and w == windows - 1 else rng.choice([0, 0, 1, -1]) * rng.randrange(1, 41) for _ in range(nb)] for w in range(windows)]
+    mult[0][nb - 1] = 40
+    pts = [ec.INF if not m else table[m - 1] if m > 0 else ec.neg(table[-m - 1]) for row in mult for m in row]
+    buf = b"".join(ec.g1_to_bytes(p) for p in pts)
+    out = (ctypes.c_uint8 * (96 * windows))()
+    hm.hm_window_bits((ctypes.c_uint8 * len(buf)).from_buffer_copy(buf), lognb, windows, out)
+    for w, row in enumerate(mult):
+        total = sum((k + 1) * m for k, m in enumerate(row)) % R
+        assert ec.g1_from_bytes(bytes(out)[96 * w : 96 * (w + 1)]) == (ec.mul(total, ec.G1) if total else ec.INF), w
 
 
 def test_pairing_building_blocks(hm):
