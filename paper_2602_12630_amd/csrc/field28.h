@@ -260,8 +260,8 @@ TC_HD bool fp28_is_zero(const fp28& a, uint32_t K) {
  * a round adds at most p to their magnitude.  After 2 len(p) - 1 steps a = 0 and b = 1, so x^-1 = v; further
  * rounds change nothing.  The product with 2^1168 leaves the 28-bit form of R^2 / x.
  * Signed multiply-adds and no sign or carry bookkeeping in the updates: about 1500 vector instructions a round
- * (700 of them the 28 steps) where the 32-bit version (fe_inv_gcd, kept for Fr and the host) takes 2000; a lone
- * normalisation 114 -> 102 us. */
+ * (700 of them the 28 steps) where the 32-bit version (fe_inv_gcd, kept for Fr and the host) takes 2000.  For one lane
+ * that inverts by itself, the end of an update's path; normalisation inverts by whole waves (fp28_inv_wave). */
 TC_HD fp_t fp_inv28(const fp_t& x) {
     constexpr int N = 14, K = 28;
     int32_t a[N], b[N], u[N], v[N];
