@@ -39,6 +39,14 @@ struct Fp28Params {
     static constexpr int32_t INV_FIX[14] = {0x4d1dd0e, 0x41d94cc, 0x109f399, 0x8cb551c, 0x2b7ff56, 0x980df0c, 0x71cc8ea, 0x76862c6, 0xbf76e0c, 0xae37e1d, 0x527bf47, 0xb194cef, 0x04d56b3, 0x0008347};  /* 2^1168 mod p: 1 / a (mod p) -> the 28-bit form of R^2 / a, R = 2^384 */
     static constexpr int32_t INV_START[14] = {0x10370ed, 0x6d1c345, 0xe243d62, 0xec45c53, 0x3b1d65a, 0x093317d, 0xb4f36a0, 0x5d74088, 0xc10ea72, 0x865d118, 0x7320a75, 0xfd5cd50, 0xcc8a759, 0x000c8d4};  /* 2^784 mod p: a R -> R / a under the radix R = 2^392 */
 };
+#define TC_WAVE28_ROWS \
+    {0x002faabbu, 0x04c203d2u, 0x02c07e7au, 0x018f8f15u, 0x06c7b6b8u, 0x0961f5b3u, 0x0e3a59f5u, 0x0f43940du, 0x0de40cc3u, 0x0ef9c7a5u, 0x025598bbu, 0x0c2b4463u, 0x01b1fd61u, 0x00019fc3u, 0, 0}, /* (c p + 1) / 2^28, c = -1 / p mod 2^28 */ \
+    {0x0fffaaabu, 0x0fefffffu, 0x03ffffb9u, 0x0fffeb15u, 0x06241eabu, 0x0a0f6b0fu, 0x0f6730d2u, 0x0f38512bu, 0x04774b84u, 0x04bacd76u, 0x0ba7b643u, 0x0e69a4b1u, 0x01ea397fu, 0x0001a011u, 0, 0}, /* p */ \
+    {0x4fd55580u, 0x47fffffbu, 0x4fffdcfbu, 0x4ff58a9bu, 0x420f55fbu, 0x47b587adu, 0x4398694cu, 0x4c2895f7u, 0x4ba5c275u, 0x4d66bb1fu, 0x43db21a1u, 0x44d258d9u, 0x451cbfefu, 0x00d0088bu, 0, 0}, /* 128 p in raised limbs */ \
+    {0x4f555600u, 0x4ffffffbu, 0x4fff73f9u, 0x4fd62a7bu, 0x483d57fbu, 0x4ed61ec0u, 0x4e61a53du, 0x40a257e8u, 0x4e9709e3u, 0x459aec8au, 0x4f6c8693u, 0x43496370u, 0x4472ffc9u, 0x03402239u, 0, 0}, /* 512 p in raised limbs */ \
+    {0x0347fcb8u, 0x0d800000u, 0x0002b119u, 0x00cde6d2u, 0x0c7212e0u, 0x083a2090u, 0x0037669fu, 0x0da0f73eu, 0x09b09b42u, 0x01297bb0u, 0x0515d98fu, 0x0012ca7cu, 0x0659fcfau, 0x0000577au, 0, 0}, /* 2^392 mod p */ \
+    {0x0450f071u, 0x0cc341c3u, 0x00f2242du, 0x0a6ebfb4u, 0x0ea1bcaau, 0x085e0207u, 0x05294915u, 0x00c96153u, 0x06eaa0bbu, 0x0715fd90u, 0x0e2f899fu, 0x0d455b78u, 0x0a49ef74u, 0x00005d6cu, 0, 0}, /* 2^776 mod p: plain value moved up by 8 bits -> the form */ \
+    {0x02421b59u, 0x0bee4867u, 0x01d31002u, 0x04760184u, 0x04cc5086u, 0x0c76dc00u, 0x0aae891bu, 0x0ac70ad2u, 0x0fe377c4u, 0x0e4686b8u, 0x05ed1568u, 0x08f5a180u, 0x002b5c1fu, 0x0000d1a4u, 0, 0} /* beta 2^392 mod p */
 /* G1 generator, Montgomery form */
 static constexpr uint32_t G1_GEN_X[12] = {0xfd530c16u, 0x5cb38790u, 0x9976fff5u, 0x7817fc67u, 0x143ba1c1u, 0x154f95c7u, 0xf3d0e747u, 0xf0ae6acdu, 0x21dbf440u, 0xedce6eccu, 0x9e0bfb75u, 0x12017741u};
 static constexpr uint32_t G1_GEN_Y[12] = {0x0ce72271u, 0xbaac93d5u, 0x7918fd8eu, 0x8c22631au, 0x570725ceu, 0xdd595f13u, 0x50405194u, 0x51ac5829u, 0xad0059c0u, 0x0e1c8c3fu, 0x5008a26au, 0x0bbc3efcu};

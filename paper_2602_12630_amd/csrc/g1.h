@@ -381,28 +381,6 @@ TC_HD g1_xyzz xyzz_mul_affine(const uint32_t* k, int nbits, const g1_affine& p) 
     return acc_result(acc);
 }
 
-/* Jacobian coordinates (x = X / Z^2, y = Y / Z^3; identity: Z = 0): the doubling costs two products and five
- * squarings, against six and three in XYZZ form: the form of the verifier's long doubling chains. */
-struct g1_jac {
-    fp_t X, Y, Z;
-};
-TC_HD g1_jac jac_identity() {
-    g1_jac r;
-    r.X = fe_one<FpParams>();
-    r.Y = fe_one<FpParams>();
-    r.Z = fe_zero<FpParams>();
-    return r;
-}
-TC_HD g1_xyzz jac_to_xyzz(const g1_jac& p) {
-    if (fe_is_zero(p.Z)) return xyzz_identity();
-    g1_xyzz r;
-    r.X = p.X;
-    r.Y = p.Y;
-    r.ZZ = fp_sqr(p.Z);
-    r.ZZZ = fp_mul(p.Z, r.ZZ);
-    return r;
-}
-
 /* canonical 96-byte encoding <-> affine Montgomery point */
 TC_HD void affine_to_canonical(const g1_affine& p, uint32_t out[24]) {
     fp_t x = fe_to_plain(p.x), y = fe_to_plain(p.y);

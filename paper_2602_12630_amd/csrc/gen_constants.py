@@ -148,6 +148,33 @@ def block28():
     return "\n".join(out)
 
 
+def wave28():
+    """Lane tables of the form that spreads an element over a row of sixteen lanes: limb j in lane j, lanes 14 and 15 zero."""
+    c = (-pow(P_MOD, -1, 1 << 28)) % (1 << 28)
+
+    def spread(multiple):
+        """multiple * p with limbs 0 .. 12 raised by four units of the limb above: no smaller than a sum of three normal limbs"""
+        d = [(multiple * P_MOD >> (28 * i)) & 0xFFFFFFF for i in range(14)]
+        z = [d[j] + ((4 << 28) if j < 13 else 0) - (4 if j else 0) for j in range(14)]
+        assert sum(v << (28 * j) for j, v in enumerate(z)) == multiple * P_MOD
+        return z
+
+    rows = [
+        ("(c p + 1) / 2^28, c = -1 / p mod 2^28", [((c * P_MOD + 1 >> 28) >> (28 * i)) & 0xFFFFFFF for i in range(14)]),
+        ("p", [(P_MOD >> (28 * i)) & 0xFFFFFFF for i in range(14)]),
+        ("128 p in raised limbs", spread(128)),
+        ("512 p in raised limbs", spread(512)),
+        ("2^392 mod p", [((1 << 392) % P_MOD >> (28 * i)) & 0xFFFFFFF for i in range(14)]),
+        ("2^776 mod p: plain value moved up by 8 bits -> the form", [(pow(2, 776, P_MOD) >> (28 * i)) & 0xFFFFFFF for i in range(14)]),
+        ("beta 2^392 mod p", [(endomorphism()[1] * (1 << 392) % P_MOD >> (28 * i)) & 0xFFFFFFF for i in range(14)]),
+    ]
+    out = ["#define TC_WAVE28_ROWS \\"]
+    for i, (what, v) in enumerate(rows):
+        out.append("    {%s, 0, 0}%s /* %s */%s" % (", ".join("0x%08xu" % x for x in v), "," if i + 1 < len(rows) else "", what,
+                                                  " \\" if i + 1 < len(rows) else ""))
+    return "\n".join(out)
+
+
 def main():
     here = os.path.dirname(os.path.abspath(__file__))
     Rp = 1 << 384
@@ -162,6 +189,7 @@ def main():
         block("FpParams", P_MOD, 12),
         block("FrParams", R_MOD, 8),
         block28(),
+        wave28(),
         "/* G1 generator, Montgomery form */",
         "static constexpr uint32_t G1_GEN_X[12] = {%s};" % limbs(GX * Rp % P_MOD, 12),
         "static constexpr uint32_t G1_GEN_Y[12] = {%s};" % limbs(GY * Rp % P_MOD, 12),

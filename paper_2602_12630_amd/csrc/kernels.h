@@ -16,6 +16,7 @@
 #pragma once
 #include "g1.h"
 #include "rt.h"
+#include "wave28.h"
 
 namespace tc {
 
@@ -2806,8 +2807,8 @@ struct NodeOpenTerms {         /* lane (job, axis, term, window pair): two windo
 /* One verification step: is  C - [y]G == sum_i [tau_i - (kappa_i + 1)] pi_i ?
  * Points arrive as canonical bytes; a point that is not on the curve rejects the step.
  * Each scalar k_i = tau_i - zeta_i arrives split as k_i = k1 + k2 lambda (both below 2^128), lambda the
- * eigenvalue of the endomorphism (x, y) -> (beta x, y), so that [k]P = [k1]P + [k2](beta x, y) costs two
- * half-length double-and-add chains that run in separate lanes. */
+ * eigenvalue of the endomorphism (x, y) -> (beta x, y), so that [k]P = [k1]P + [k2](beta x, y) costs one
+ * half-length chain of doublings. */
 struct VerifyStep {
     uint32_t C[24];
     uint32_t y[8];
@@ -2816,8 +2817,7 @@ struct VerifyStep {
     uint32_t k2[4][4];
     int m;
 };
-constexpr uint32_t VERIFY_CHAINS = 8;     /* two half-scalar terms per proof element, at most four elements */
-constexpr uint32_t VERIFY_BITS = 128;
+constexpr uint32_t VERIFY_BITS = 128;     /* of a half scalar */
 TC_HD bool affine_on_curve(const g1_affine& p) {
     if (affine_is_identity(p)) return true;
     fp_t y2 = fp_sqr(p.y);
@@ -2831,198 +2831,142 @@ TC_HD bool xyzz_equal(const g1_xyzz& a, const g1_xyzz& b) {
     if (ia || ib) return ia && ib;
     return fe_eq(fp_mul(a.X, b.ZZ), fp_mul(b.X, a.ZZ)) && fe_eq(fp_mul(a.Y, b.ZZZ), fp_mul(b.Y, a.ZZZ));
 }
-/* The 128 doublings of a half-length scalar multiplication cannot be spread over lanes, everything else can:
- * chain (step, j) of VerifyChain walks P, 2P, 4P, .. 2^127 P (chain 2i: P = pi_i, chain 2i + 1: its image
- * (beta x, y)) and keeps every point; cooperative sums then add, for a step, the points whose bit is set in
- * the half scalars, the window terms of [y]G and -C, and the step is accepted iff
- *   sum_i [k_i] pi_i + [y] G - C = O. */
-/* Four waves per 64 chains.  The seven products of a Jacobian doubling (A = X^2, B = Y^2, Y Z; F = (3A)^2,
- * C = B^2, X B; E (D - X3)) fall into three levels of independent ones, and a wave alone on its SIMD issues them no
- * faster one after the other than three waves do side by side: wave 0 carries X and Y, wave 1 the powers of Y,
- * wave 2 Z and D = 4 X B; operands pass through LDS, a barrier after every level.  The chain computes in the
- * 28-bit-limb form of the field (a wave alone gets through those products 1.6 times as fast as through the 32-bit
- * ones: 0.81 -> 0.60 ms for the chains of eight paths): sums and small multiples are limb-wise and get one carry
- * pass before they meet a product, nothing is reduced along the way.  The points that the chain keeps are in the
- * 32-bit form; wave 3 converts them, one coordinate per level, from copies that the other waves leave for it (X
- * and Y of a point in the slot of its parity, so that the next doubling may write while the last is still being
- * read).  Z = 0 (the identity) reproduces itself under these formulas, so the loop has no special cases. */
-struct VerifyChain {
-    static constexpr int BLOCK = 256;
-    enum { FX, FY, FZ, FE, FB, FC8, FD, FF, PZ, PX0, PX1, PY0, PY1, NFIELD };
-    static constexpr size_t LDS_BYTES = (size_t)NFIELD * 4 * 64 * 16;
-    static constexpr int PHASES = 1 + 3 * ((int)VERIFY_BITS - 1) + 2;
-    struct Quad { int32_t v[4]; };
-    const VerifyStep* steps;
-    uint32_t n_chains;         /* VERIFY_CHAINS per step */
-    uint32_t* ok;
-    g1_jac* chain;
-
-    TC_DEV static fp28 ld(const uint8_t* lds, int f, uint32_t l) {
-        const Quad* q = (const Quad*)lds;
-        fp28 r;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            Quad t = q[(f * 4 + i) * 64 + l];
-            r.l[4 * i] = t.v[0]; r.l[4 * i + 1] = t.v[1];
-            if (i < 3) { r.l[4 * i + 2] = t.v[2]; r.l[4 * i + 3] = t.v[3]; }
-        }
-        return r;
+/* The non-adjacent form of a half scalar, digits 8 t .. 8 t + 7: bit i of plus / minus is set where digit 8 t + i is 1 / -1.
+ * Digit i is bit i + 1 of 3 k minus bit i + 1 of k; 129 digits, no two neighbours set. */
+constexpr uint32_t VERIFY_NAF_BLOCKS = 17;
+TC_HD void naf_block(const uint32_t k[4], uint32_t t, uint32_t& plus, uint32_t& minus) {
+    uint32_t k3[5], carry = 0;
+    for (int i = 0; i < 5; ++i) {
+        uint64_t v = 3ull * (i < 4 ? k[i] : 0u) + carry;
+        k3[i] = (uint32_t)v;
+        carry = (uint32_t)(v >> 32);
     }
-    TC_DEV static void st(uint8_t* lds, int f, uint32_t l, const fp28& x) {
-        Quad* q = (Quad*)lds;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            Quad t;
-            t.v[0] = x.l[4 * i]; t.v[1] = x.l[4 * i + 1];
-            t.v[2] = i < 3 ? x.l[4 * i + 2] : 0; t.v[3] = i < 3 ? x.l[4 * i + 3] : 0;
-            q[(f * 4 + i) * 64 + l] = t;
-        }
-    }
-    TC_DEV static fp28 times2(const fp28& a) { return fp28_add(a, a); }
-    TC_DEV void phase(int ph, uint32_t lane, uint32_t wg, uint8_t* lds) const {
-        uint32_t wave = lane >> 6, l = lane & 63u;
-        uint32_t c = wg * 64u + l;
-        bool live = false;
-        if (c < n_chains) live = (int)((c % VERIFY_CHAINS) >> 1) < steps[c / VERIFY_CHAINS].m;
-        g1_jac* out = chain + (uint64_t)c * VERIFY_BITS;
-        if (ph == 0) {
-            if (wave != 0) return;
-            g1_jac q = jac_identity();
-            if (live) {
-                uint32_t s = c / VERIFY_CHAINS, j = c % VERIFY_CHAINS;
-                const uint32_t* w = steps[s].pi[j >> 1];
-                g1_affine p = affine_from_canonical(w);
-                bool second = (j & 1u) != 0;
-                if (!second && (!canonical_fp(w) || !canonical_fp(w + 12) || !affine_on_curve(p))) atomic_and_u32(&ok[s], 0u);
-                if (!affine_is_identity(p)) {
-                    if (second) {
-                        fp_t beta;
-#pragma unroll
-                        for (int t = 0; t < 12; ++t) beta.l[t] = GLV_BETA[t];
-                        p.x = fp_mul(p.x, beta);
-                    }
-                    q.X = p.x;
-                    q.Y = p.y;
-                    q.Z = fe_one<FpParams>();
-                }
-                out[0] = q;
-            }
-            st(lds, FX, l, fp28_from_fp(q.X));
-            st(lds, FY, l, fp28_from_fp(q.Y));
-            st(lds, FZ, l, fp28_from_fp(q.Z));
-            return;
-        }
-        const int last = 1 + 3 * ((int)VERIFY_BITS - 1);
-        if (ph >= last) {                       /* X and Y of the last point */
-            if (wave != 3 || !live) return;
-            const uint32_t b = VERIFY_BITS - 1;
-            if (ph == last) out[b].X = fp28_to_fp(ld(lds, (b & 1u) ? PX1 : PX0, l));
-            else out[b].Y = fp28_to_fp(ld(lds, (b & 1u) ? PY1 : PY0, l));
-            return;
-        }
-        uint32_t b = (uint32_t)(ph - 1) / 3u + 1u;      /* the point 2^b P is in the making */
-        int level = (ph - 1) % 3;
-        if (wave == 3) {                        /* the converter: X of the point before, Z of this one, Y of the point before */
-            if (!live) return;
-            if (level == 0) {
-                if (b > 1) out[b - 1].X = fp28_to_fp(ld(lds, ((b - 1) & 1u) ? PX1 : PX0, l));
-            } else if (level == 1) {
-                out[b].Z = fp28_to_fp(ld(lds, PZ, l));
-            } else if (b > 1) {
-                out[b - 1].Y = fp28_to_fp(ld(lds, ((b - 1) & 1u) ? PY1 : PY0, l));
-            }
-            return;
-        }
-        if (level == 0) {
-            if (wave == 0) {
-                fp28 A = fp28_sqr(ld(lds, FX, l));
-                st(lds, FE, l, fp28_carry(fp28_add(times2(A), A)));
-            } else if (wave == 1) {
-                st(lds, FB, l, fp28_sqr(ld(lds, FY, l)));
-            } else {
-                fp28 Z3 = times2(fp28_mul(ld(lds, FY, l), ld(lds, FZ, l)));       /* limbs below 2^29: a factor of the next Y Z only */
-                st(lds, FZ, l, Z3);
-                st(lds, PZ, l, Z3);
-            }
-            return;
-        }
-        if (level == 1) {
-            if (wave == 0) {
-                st(lds, FF, l, fp28_sqr(ld(lds, FE, l)));
-            } else if (wave == 1) {
-                fp28 C = fp28_sqr(ld(lds, FB, l));
-                st(lds, FC8, l, fp28_carry(times2(times2(times2(C)))));
-            } else {
-                fp28 XB = fp28_mul(ld(lds, FX, l), ld(lds, FB, l));
-                st(lds, FD, l, fp28_carry(times2(times2(XB))));
-            }
-            return;
-        }
-        if (wave == 0) {
-            fp28 D = ld(lds, FD, l);
-            fp28 X3 = fp28_carry(fp28_sub(fp28_sub(ld(lds, FF, l), D), D));
-            fp28 Y3 = fp28_carry(fp28_sub(fp28_mul(ld(lds, FE, l), fp28_sub(D, X3)), ld(lds, FC8, l)));
-            st(lds, FX, l, X3);
-            st(lds, FY, l, Y3);
-            st(lds, (b & 1u) ? PX1 : PX0, l, X3);
-            st(lds, (b & 1u) ? PY1 : PY0, l, Y3);
-        }
-    }
-};
-/* What the cooperative sums of a step add: group g < groups - 1 the points of chains 2g and 2g + 1 whose bit is
- * set (an identity elsewhere), the last group the window terms of [y]G and -C; `groups` is one more than the
- * largest order among the steps of the launch. */
-struct VerifyGroupSrc {
+    const uint32_t at = 8u * t + 1u, w = at >> 5, sh = at & 31u;
+    const uint64_t a = ((uint64_t)(w + 1u < 5u ? k3[w + 1u] : 0u) << 32) | k3[w];
+    const uint64_t b = ((uint64_t)(w + 1u < 4u ? k[w + 1u] : 0u) << 32) | (w < 4u ? k[w] : 0u);
+    const uint32_t three = (uint32_t)(a >> sh) & 0xFFu, one = (uint32_t)(b >> sh) & 0xFFu;
+    plus = three & ~one;
+    minus = one & ~three;
+}
+/* One workgroup decides one step: sum_i [k_i] pi_i + [y] G - C = O.  What cannot be spread is the 128 doublings of a
+ * half-length scalar multiplication; a wave per proof element walks P, 2P, .. 2^128 P with its elements spread over lanes (three
+ * levels of products a doubling, wave28.h) and leaves the points in LDS, eight at a time in one of two halves of a ring.
+ * Two waves per element, one phase behind, add those where the non-adjacent form of k1 or k2 has a digit: at most four of
+ * eight, so they keep up; the endomorphism is applied to the finished sum of k2, so that both share the chain.  One more wave adds the
+ * window terms of [y]G and -C, one or two a phase.  Then the 2 M + 1 sums are added pairwise.
+ * Bound by the latency of 128 doublings, 1.2 us each; nothing of it leaves the workgroup.  256 steps of order 2: 174 us, 48 steps:
+ * 167 us, against 847 and 759 us in three launches (chains of lane-wide products, four waves to 64 chains, every 2^b P kept in
+ * 144 KiB of memory a step; cooperative sums of those whose bit is set).
+ * PHASES: 0 .. 16 blocks of the chain (the sums one behind, up to 17), 18 the endomorphism, 19 .. 22 sums, 23 verdict. */
+template <int M>
+struct VerifyWave {
+    static constexpr int WAVES = 3 * M + 1;
+    static constexpr int PHASES = 24;
+    static constexpr uint32_t SUMS = 2 * M + 1;
+    static constexpr uint32_t PT = 64;                                /* words of a point */
+    static constexpr uint32_t RING = 0, SUM = RING + M * 16 * PT, AT = SUM + SUMS * PT;
+    static constexpr size_t LDS_BYTES = (AT + M * PT) * 4;
     const VerifyStep* steps;
     const g1_affine* gtable;
-    const g1_jac* chain;
     uint32_t* ok;
-    uint32_t groups;
-    g1_xyzz* partial;          /* steps * groups */
-    TC_DEV uint32_t count(uint32_t wg) const {
-        uint32_t s = wg / groups, g = wg % groups;
-        if (g + 1 == groups) return (uint32_t)FB_W + 1u;
-        return (int)g < steps[s].m ? 2u * VERIFY_BITS : 0u;
+
+    TC_DEV void chain_block(const wv_consts& k, const VerifyStep& st, uint32_t i, uint32_t t, uint32_t* lds) const {
+        uint32_t* ring = lds + RING + (i * 16u + (t & 1u) * 8u) * PT;
+        wv_point p;
+        uint32_t j = 0;
+        if (t == 0) {
+            p = wv_load_canonical(k, st.pi[i]);
+            wv_store_raw(ring, p);
+            j = 1;
+        } else {
+            p = wv_load_raw(lds + AT + i * PT);
+        }
+        for (; j < 8u && 8u * t + j <= VERIFY_BITS; ++j) {
+            if (!p.inf) p.v = wv_dbl(k, p.v);
+            wv_store_raw(ring + j * PT, p);
+        }
+        wv_store_raw(lds + AT + i * PT, p);
     }
-    TC_DEV g1_xyzz load(uint32_t wg, uint32_t i) const {
-        uint32_t s = wg / groups, g = wg % groups;
+    /* canonical coordinates of a point on the curve */
+    TC_DEV static bool point_ok(const uint32_t* w) { return canonical_fp(w) && canonical_fp(w + 12) && affine_on_curve(affine_from_canonical(w)); }
+    TC_DEV void phase(int ph, uint32_t wave, uint32_t s, uint8_t* bytes) const {
+        uint32_t* lds = (uint32_t*)bytes;
         const VerifyStep& st = steps[s];
-        if (g + 1 < groups) {
-            uint32_t j = 2 * g + i / VERIFY_BITS, b = i % VERIFY_BITS;
-            const uint32_t* k = (j & 1u) ? st.k2[j >> 1] : st.k1[j >> 1];
-            if (!((k[b >> 5] >> (b & 31)) & 1u)) return xyzz_identity();
-            return jac_to_xyzz(chain[((uint64_t)s * VERIFY_CHAINS + j) * VERIFY_BITS + b]);
-        }
-        g1_affine p = affine_identity();
-        if (i < (uint32_t)FB_W) {                /* window i of [y] G */
-            uint32_t carry = 0;
-            int32_t d = 0;
-            for (uint32_t w = 0; w <= i; ++w) d = fr_window_digit(st.y, (int)w, FB_C, carry);
-            if (d) {
-                p = gtable[(uint64_t)i * FB_NB + (uint32_t)(d < 0 ? -d : d) - 1u];
-                if (d < 0) p.y = fp_neg(p.y);
+        const wv_consts k = wv_constants();
+        const uint32_t live = (uint32_t)st.m < (uint32_t)M ? (uint32_t)st.m : (uint32_t)M;
+        if (ph < 18) {
+            if (wave < (uint32_t)M) {                                 /* the chain of element `wave` */
+                if (wave < live && ph < (int)VERIFY_NAF_BLOCKS) chain_block(k, st, wave, (uint32_t)ph, lds);
+                return;
             }
-        } else {                                 /* -C, and the checks on C and y */
-            p = affine_from_canonical(st.C);
-            bool good = canonical_fp(st.C) && canonical_fp(st.C + 12) && affine_on_curve(p) && limbs_gt<8>(FrParams::MOD, st.y);
-            if (!good) atomic_and_u32(&ok[s], 0u);
-            p = affine_neg(p);
+            if (wave < 3u * M) {                                      /* the sum of one of its half scalars */
+                const uint32_t j = wave - M, i = j >> 1;
+                uint32_t* sum = lds + SUM + j * PT;
+                if (ph == 0) {
+                    wv_store_raw(sum, wv_identity());
+                    if ((j & 1u) == 0u && i < live && !point_ok(st.pi[i]) && wv_first_lane()) atomic_and_u32(&ok[s], 0u);
+                    return;
+                }
+                if (i >= live) return;
+                uint32_t plus, minus;
+                naf_block((j & 1u) ? st.k2[i] : st.k1[i], (uint32_t)ph - 1u, plus, minus);
+                if (!(plus | minus)) return;
+                const uint32_t* ring = lds + RING + (i * 16u + (((uint32_t)ph - 1u) & 1u) * 8u) * PT;
+                wv_point acc = wv_load_raw(sum);
+                for (uint32_t d = 0; d < 8u; ++d) {
+                    if (!(((plus | minus) >> d) & 1u)) continue;
+                    wv_point p = wv_load_raw(ring + d * PT);
+                    if ((minus >> d) & 1u) p.v = wv_negate(p.v);
+                    wv_accumulate(k, acc, p);
+                }
+                wv_store_raw(sum, acc);
+                return;
+            }
+            uint32_t* sum = lds + SUM + 2u * M * PT;                  /* [y]G - C */
+            wv_point acc = ph == 0 ? wv_identity() : wv_load_raw(sum);
+            if (ph < 16) {
+                constexpr uint32_t per = (uint32_t)FB_W / 16u;
+                static_assert(FB_W % 16 == 0, "a whole number of windows a phase");
+                uint32_t carry = 0;
+                for (uint32_t w = 0; w < (uint32_t)ph * per; ++w) (void)fr_window_digit(st.y, (int)w, FB_C, carry);
+                for (uint32_t w = (uint32_t)ph * per; w < ((uint32_t)ph + 1u) * per; ++w) {
+                    const int32_t d = fr_window_digit(st.y, (int)w, FB_C, carry);
+                    if (!d) continue;
+                    wv_point p = wv_load_affine(gtable + (uint64_t)w * FB_NB + (uint32_t)(d < 0 ? -d : d) - 1u);
+                    if (d < 0) p.v = wv_negate(p.v);
+                    wv_accumulate(k, acc, p);
+                }
+            } else if (ph == 16) {
+                if ((!point_ok(st.C) || !limbs_gt<8>(FrParams::MOD, st.y)) && wv_first_lane()) atomic_and_u32(&ok[s], 0u);
+                wv_point c = wv_load_canonical(k, st.C);
+                c.v = wv_negate(c.v);
+                wv_accumulate(k, acc, c);
+            }
+            wv_store_raw(sum, acc);
+            return;
         }
-        return xyzz_from_affine(p);
+        if (ph == 18) {                                               /* [k2] phi(P) = phi([k2] P), phi(x, y) = (beta x, y) */
+            if (wave >= (uint32_t)M) return;
+            uint32_t* sum = lds + SUM + (2u * wave + 1u) * PT;
+            wv_point p = wv_load_raw(sum);
+            const wv beta = wv_table(W28_BETA), one = wv_table(W28_ONE);
+            p.v = wv_mul(k, p.v, wv_pick(beta, one, one, one));
+            wv_store_raw(sum, p);
+            return;
+        }
+        if (ph < 23) {
+            uint32_t n = SUMS;
+            for (int i = 19; i < ph; ++i) n = (n + 1u) / 2u;
+            const uint32_t half = (n + 1u) / 2u;
+            if (half + wave >= n) return;
+            wv_point a = wv_load_raw(lds + SUM + wave * PT);
+            wv_accumulate(k, a, wv_load_raw(lds + SUM + (half + wave) * PT));
+            wv_store_raw(lds + SUM + wave * PT, a);
+            return;
+        }
+        if (wave == 0 && !wv_load_raw(lds + SUM).inf && wv_first_lane()) ok[s] = 0;
     }
-    TC_DEV void store(uint32_t wg, const g1_xyzz& r) const { partial[wg] = r; }
 };
-struct VerifyDecideSrc {       /* workgroup = step: the partial sums must cancel */
-    const g1_xyzz* partial;
-    uint32_t groups;
-    uint32_t* ok;
-    TC_DEV uint32_t count(uint32_t) const { return groups; }
-    TC_DEV g1_xyzz load(uint32_t s, uint32_t i) const { return partial[(uint64_t)s * groups + i]; }
-    TC_DEV void store(uint32_t s, const g1_xyzz& r) const {
-        if (!xyzz_is_identity(r)) ok[s] = 0;
-    }
-};
-constexpr uint32_t VERIFY_MAX_GROUPS = VERIFY_CHAINS / 2 + 1;
 /* canonical bytes -> affine point in Montgomery form; a point that is not canonical or not on the curve clears *ok */
 struct FromCanonicalChecked {
     const uint32_t* in;     /* 24 words per point */

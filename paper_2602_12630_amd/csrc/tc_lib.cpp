@@ -341,6 +341,35 @@ static int launch_coop(uint32_t groups, rt::stream_t st, const F& f) {
 }
 #endif
 
+/* ---- the same by whole waves: a phase is a call per wave, its lanes the limbs of what the wave works on (wave28.h) ---- */
+#if defined(TC_HOST_EMU)
+template <class F>
+static int launch_wave_groups(uint32_t groups, rt::stream_t, const F& f) {
+    std::vector<uint8_t> lds(F::LDS_BYTES);
+    for (uint32_t g = 0; g < groups; ++g)
+        for (int ph = 0; ph < F::PHASES; ++ph)
+            for (uint32_t wave = 0; wave < (uint32_t)F::WAVES; ++wave) f.phase(ph, wave, g, lds.data());
+    return 0;
+}
+#else
+template <class F>
+__global__ __launch_bounds__(F::WAVES * 64) void wave_kernel(const F f) {
+    extern __shared__ __align__(16) uint8_t lds[];
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    for (int ph = 0; ph < F::PHASES; ++ph) {
+        f.phase(ph, wave, blockIdx.x, lds);
+        __syncthreads();
+    }
+}
+template <class F>
+static int launch_wave_groups(uint32_t groups, rt::stream_t st, const F& f) {
+    static_assert(F::LDS_BYTES <= 64 * 1024, "what a launch may take without asking");
+    if (!groups) return 0;
+    hipLaunchKernelGGL((wave_kernel<F>), dim3(groups), dim3(F::WAVES * 64), F::LDS_BYTES, st, f);
+    return (int)hipGetLastError();
+}
+#endif
+
 /* cooperative launch whose number of phases is known only at run time */
 #if defined(TC_HOST_EMU)
 template <int BLOCK, class F>
@@ -2236,9 +2265,6 @@ static void fill_step_scalars(const tc_vk* vk, const uint32_t* kappa, VerifyStep
     }
 }
 
-/* at most this many steps share the chain buffer (144 KiB per step) */
-static const uint32_t VERIFY_CHUNK_STEPS = 4096;
-
 /* runs the steps on the device; ok[i] = 1 iff step i verifies */
 static int verify_steps(tc_ctx* ctx, const tc_vk* vk, const std::vector<VerifyStep>& steps, std::vector<uint32_t>& ok) {
     uint32_t n = (uint32_t)steps.size();
@@ -2248,26 +2274,19 @@ static int verify_steps(tc_ctx* ctx, const tc_vk* vk, const std::vector<VerifySt
     TRY(ensure_gtable(ctx));
     WS(d_steps, VerifyStep, n);
     WS(d_ok, uint32_t, n);
-    uint32_t chunk = n < VERIFY_CHUNK_STEPS ? n : VERIFY_CHUNK_STEPS;
-    WS(d_chain, g1_jac, (uint64_t)chunk * VERIFY_CHAINS * VERIFY_BITS);
-    WS(d_part, g1_xyzz, (uint64_t)chunk * VERIFY_MAX_GROUPS);
     TRY(h2d(ctx, d_steps, steps.data(), sizeof(VerifyStep) * n));
     RT(rt::launch<256>(n, ctx->stream, Fill32{d_ok, 1u}));
-    for (uint32_t c0 = 0; c0 < n; c0 += chunk) {       /* the chain buffer serves one chunk of steps after the other */
-        uint32_t cn = n - c0 < chunk ? n - c0 : chunk;
-        rt::event_t e0, e1;
-        prof_begin(ctx, TC_PROF_VERIFY_CHAIN, &e0, &e1);
-        int ce = launch_coop<VerifyChain::BLOCK>((VERIFY_CHAINS * cn + 63) / 64, ctx->stream, VerifyChain{d_steps + c0, VERIFY_CHAINS * cn, d_ok + c0, d_chain});
-        prof_end(ctx, TC_PROF_VERIFY_CHAIN, e0, e1);
-        RT(ce);
-        int mmax = 1;
-        for (uint32_t i = c0; i < c0 + cn; ++i) mmax = steps[i].m > mmax ? steps[i].m : mmax;
-        uint32_t groups = (uint32_t)mmax + 1u;
-        typedef CoopReduce<VerifyGroupSrc> Sum;
-        typedef CoopReduce<VerifyDecideSrc> Decide;
-        RT((launch_coop<Sum::BLOCK>(cn * groups, ctx->stream, Sum{VerifyGroupSrc{d_steps + c0, ctx->gtable, d_chain, d_ok + c0, groups, d_part}})));
-        RT((launch_coop<Decide::BLOCK>(cn, ctx->stream, Decide{VerifyDecideSrc{d_part, groups, d_ok + c0}})));
-    }
+    int mmax = 1;
+    for (uint32_t i = 0; i < n; ++i) mmax = steps[i].m > mmax ? steps[i].m : mmax;
+    rt::event_t e0, e1;
+    prof_begin(ctx, TC_PROF_VERIFY_CHAIN, &e0, &e1);
+    int e;
+    if (mmax == 1) e = launch_wave_groups(n, ctx->stream, VerifyWave<1>{d_steps, ctx->gtable, d_ok});
+    else if (mmax == 2) e = launch_wave_groups(n, ctx->stream, VerifyWave<2>{d_steps, ctx->gtable, d_ok});
+    else if (mmax == 3) e = launch_wave_groups(n, ctx->stream, VerifyWave<3>{d_steps, ctx->gtable, d_ok});
+    else e = launch_wave_groups(n, ctx->stream, VerifyWave<4>{d_steps, ctx->gtable, d_ok});
+    prof_end(ctx, TC_PROF_VERIFY_CHAIN, e0, e1);
+    RT(e);
     RT(rt::memcpy_d2h(ok.data(), d_ok, 4ull * n, ctx->stream));
     TRY(ctx_sync(ctx));
     return TC_OK;

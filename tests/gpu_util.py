@@ -251,3 +251,33 @@ def check_repeated_points(ctx, upload, many=512):
                 want, _ = cbind.msm_naive(X, blob, HOST_THREADS)
                 assert got[j] == ec.g1_to_bytes(want), (dtype, j)
         back.close()
+
+
+def check_verification(ctx, m):
+    """Ver at order m on equations built from the group law alone, C = [y]G + sum_i [tau_i - zeta_i] pi_i: the scalars at the
+    edges of the split k = k1 + k2 lambda and of the digits of its halves; proof elements random, the identity, and equal or
+    opposite with equal scalars, so that the sums of two elements meet the tangent rule and cancel; y at the ends of its range.
+    Each equation also with a wrong y, a wrong element, a point off the curve and y = r."""
+    import random
+
+    rng = random.Random(100 + m)
+    lam = (-0xD201000000010000) ** 2 - 1
+    edge = [0, 1, 2, 3, lam - 1, lam, lam + 1, ec.R - 1, (1 << 128) - 1, (1 << 127), 0xAAAAAAAAAAAAAAAA5555555555555555, lam * (1 << 127) % ec.R]
+    base = [ec.mul(rng.randrange(1, ec.R), ec.G1) for _ in range(4)]
+    shape, kappa = (5,) * m, tuple(rng.randrange(5) for _ in range(m))
+    cases = [([rng.choice(edge) for _ in range(m)], [rng.choice(base + [ec.INF]) for _ in range(m)], rng.choice([0, 1, ec.R - 1])) for _ in range(6)]
+    cases += [([e] * m, [base[0]] * m, rng.randrange(ec.R)) for e in (lam + 1, ec.R - 1)]                  # equal sums
+    cases += [([ec.R - 2] * m, [base[1] if i % 2 else ec.neg(base[1]) for i in range(m)], 0)]             # sums that cancel
+    cases += [([rng.randrange(ec.R) for _ in range(m)], [ec.mul(rng.randrange(1, ec.R), ec.G1) for _ in range(m)], rng.randrange(ec.R)) for _ in range(3)]
+    cases += [([0] * m, [ec.INF] * m, 0)]                                                                   # C = O
+    for k, pi, y in cases:
+        vk = ctx.vk_from_trapdoor(b"".join(ec.fr_to_bytes((k[i] + kappa[i] + 1) % ec.R) for i in range(m)).ljust(128, b"\0"))
+        C = ec.mul(y, ec.G1)
+        for i in range(m):
+            C = ec.add(C, ec.mul(k[i], pi[i]))
+        Cb, yb, pb = ec.g1_to_bytes(C), ec.fr_to_bytes(y), [ec.g1_to_bytes(p) for p in pi]
+        assert ctx.verify(vk, shape, Cb, kappa, yb, pb), (k, y)
+        assert not ctx.verify(vk, shape, Cb, kappa, ec.fr_to_bytes((y + 1) % ec.R), pb), (k, y)
+        assert not ctx.verify(vk, shape, ec.g1_to_bytes(ec.add(C, ec.G1)), kappa, yb, pb), (k, y)
+        assert not ctx.verify(vk, shape, Cb, kappa, yb, pb[:-1] + [(1).to_bytes(48, "little") * 2]), (k, y)
+        assert not ctx.verify(vk, shape, Cb, kappa, (y + ec.R).to_bytes(32, "little"), pb), (k, y)

@@ -101,6 +101,32 @@ void hm_window_bits(const uint8_t* pts, uint32_t lognb, uint32_t windows, uint8_
     coop_run(CoopReduce<GroupSumSrc>{GroupSumSrc{scaled.data(), chains, sum.data()}}, windows);
     for (uint32_t w = 0; w < windows; ++w) pt_store(o + 96 * (size_t)w, xyzz_to_affine(sum[w]));
 }
+// the form spread over lanes: a product of raw limbs (14 words each, four rows), and sums and doublings of points
+void hm_wave_mul(const uint32_t* a, const uint32_t* b, uint32_t* o) {
+    wv x, y;
+    for (int i = 0; i < 64; ++i) { x.l[i] = i % 16 < 14 ? a[14 * (i / 16) + i % 16] : 0; y.l[i] = i % 16 < 14 ? b[14 * (i / 16) + i % 16] : 0; }
+    wv r = wv_mul(wv_constants(), x, y);
+    for (int i = 0; i < 64; ++i) {
+        if (i % 16 < 14) o[14 * (i / 16) + i % 16] = r.l[i];
+        else if (r.l[i]) o[0] = 0xFFFFFFFFu;
+    }
+}
+void hm_wave_sum(const uint8_t* pts, uint32_t n, int doublings, int spread, uint8_t* o) {
+    const wv_consts k = wv_constants();
+    wv_point acc = wv_identity();
+    for (uint32_t i = 0; i < n; ++i) {
+        g1_affine a = pt_load(pts + 96 * (size_t)i);
+        g1_xyzz s = spread ? xyzz_madd(xyzz_dbl_affine(a), affine_neg(a)) : xyzz_from_affine(a);
+        wv_point p = wv_load(&s);
+        if (spread == 2) { p.v = wv_negate(p.v); p.v = wv_negate(wv_mul(k, p.v, wv_table(W28_ONE))); }
+        wv_accumulate(k, acc, p);
+    }
+    for (int i = 0; i < doublings; ++i)
+        if (!acc.inf) acc.v = wv_dbl(k, acc.v);
+    g1_xyzz r;
+    wv_store(&r, acc);
+    pt_store(o, xyzz_to_affine(r));
+}
 // the verifier's short final exponentiation against the plain one: must be its cube; also x^p, x^(p^2) by powers
 int hm_final_exponentiation_forms(const uint8_t* p, uint32_t k) {
     using namespace tc::pairing;

@@ -12,7 +12,7 @@ from oracle import bls12_381 as ec
 from oracle import cbind, quantize, tc, terkle
 from oracle.bls12_381 import R
 
-from gpu_util import HOST_THREADS, TAU_BYTES, Stopwatch, check_field_arithmetic, check_wave_inversion, check_one_point_throughout, check_repeated_points, fr_bytes_array, oracle_pool, parse_proof, pps, progress, serialize_steps, to_device
+from gpu_util import HOST_THREADS, TAU_BYTES, Stopwatch, check_field_arithmetic, check_wave_inversion, check_one_point_throughout, check_repeated_points, check_verification, fr_bytes_array, oracle_pool, parse_proof, pps, progress, serialize_steps, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -1176,8 +1176,13 @@ def test_arity_64_trees(T, ctx, node, grid):
         srs.close()
 
 
+@pytest.mark.parametrize("m", [1, 2, 3, 4])
+def test_verification_of_every_order(ctx, m):
+    check_verification(ctx, m)
+
+
 def test_verification_in_chunks(T, ctx, node_srs):
-    """More steps than one pass of the verifier holds (4096): 1400 paths of 3 steps through a (64, 64) entries tree,
+    """Thousands of steps in one batch: 1400 paths of 3 steps through a (64, 64) entries tree,
     a few of them with a wrong value or a damaged proof; the verdicts must come out per path, in order."""
     grid, node = (64, 64), tc_inputs.NODE_SHAPE
     X = tc_inputs.int16_uniform(grid, 21)
@@ -1193,7 +1198,7 @@ def test_verification_in_chunks(T, ctx, node_srs):
         paths = [tree.path(l) for l in leaves]
         values = [ec.fr_to_bytes(int(X[l]) % R) for l in leaves]
         want = [True] * len(leaves)
-        for i in (3, 1365, 1366, 1399):                     # the last ones fall into the second pass
+        for i in (3, 1365, 1366, 1399):                     
             values[i] = ec.fr_to_bytes((int(X[leaves[i]]) + 1) % R)
             want[i] = False
         damaged = bytearray(proofs[1370])

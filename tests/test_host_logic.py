@@ -25,7 +25,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 import __graft_entry__ as entry  # noqa: E402
 import paper_2602_12630_amd as T  # noqa: E402
-from gpu_util import TAU_BYTES, check_field_arithmetic, check_wave_inversion, check_one_point_throughout, check_repeated_points, fr_bytes_array, pps, serialize_steps  # noqa: E402
+from gpu_util import TAU_BYTES, check_field_arithmetic, check_wave_inversion, check_one_point_throughout, check_repeated_points, check_verification, fr_bytes_array, pps, serialize_steps  # noqa: E402
 
 EMU = os.path.join(ROOT, "tests", "hostmath", "libtc_hostemu.so")
 
@@ -182,6 +182,11 @@ def test_emulated_open_by_rows(emu):
             assert y == ec.fr_to_bytes(yo) and pi == [ec.g1_to_bytes(p) for p in po]
     finally:
         srs.close()
+
+
+@pytest.mark.parametrize("m", [1, 2, 3, 4])
+def test_emulated_verification_of_every_order(emu, m):
+    check_verification(emu, m)
 
 
 def test_emulated_entries_tree(emu, node_srs):

@@ -20,7 +20,7 @@ LIB = os.path.join(HERE, "hostmath", "libhostmath.so")
 
 @pytest.fixture(scope="module")
 def hm():
-    hdrs = [os.path.join(HERE, "..", "paper_2602_12630_amd", "csrc", h) for h in ("field.h", "field28.h", "g1.h", "constants.h", "kernels.h", "rt.h", "pairing.h")]
+    hdrs = [os.path.join(HERE, "..", "paper_2602_12630_amd", "csrc", h) for h in ("field.h", "field28.h", "g1.h", "constants.h", "kernels.h", "wave28.h", "rt.h", "pairing.h")]
     newest = max(os.path.getmtime(f) for f in [SRC] + hdrs)
     if not os.path.exists(LIB) or os.path.getmtime(LIB) < newest:
         subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", LIB, SRC])
@@ -221,6 +221,44 @@ def test_cooperative_reduction(hm):
             got = run(pts, spread)
             w = want(pts)
             assert (got is ec.INF and w is ec.INF) or got == w, (len(pts), spread)
+
+
+def test_product_spread_over_lanes(hm):
+    """a b 2^-392 (mod p) with the limbs at the bounds that the group law relies on: 2^29.6 on both sides, 2^30 - 4 against a normal
+    operand; the result's limbs are normal and its value is below a b / 2^392 + 2 p.  (The host form stops on a limb sum that leaves
+    its word.)"""
+    rng = random.Random(12)
+    radix, normal, grown = 1 << 392, (1 << 28) + 15, 3 * ((1 << 28) + 15)
+    limits = [(grown, grown), ((1 << 30) - 4, normal), (normal, (1 << 30) - 4), (normal, normal), (0, grown), (1, 1)]
+    for la, lb in limits * 8:
+        draw = lambda l: [rng.choice([l, rng.randrange(l + 1), 0]) for _ in range(13)] + [rng.randrange(1 << 26) if l else 0]
+        a, b = [draw(la) for _ in range(4)], [draw(lb) for _ in range(4)]
+        if (la, lb) in limits[:4] and rng.random() < 0.3:
+            a[0], b[0] = [la] * 13 + [1 << 26], [lb] * 13 + [1 << 26]
+        out = (ctypes.c_uint32 * 56)()
+        hm.hm_wave_mul((ctypes.c_uint32 * 56)(*sum(a, [])), (ctypes.c_uint32 * 56)(*sum(b, [])), out)
+        for row in range(4):
+            x, y, r = (sum(v << (28 * j) for j, v in enumerate(l)) for l in (a[row], b[row], out[14 * row : 14 * row + 14]))
+            assert r * radix % P == x * y % P
+            assert max(out[14 * row : 14 * row + 14]) <= normal and r < x * y // radix + 2 * P
+
+
+def test_group_law_spread_over_lanes(hm):
+    rng = random.Random(13)
+    base = [ec.mul(rng.randrange(1, R), ec.G1) for _ in range(5)]
+    cases = [[], [base[0]], [base[0], base[0]], [base[0], ec.neg(base[0])], [ec.INF, base[1]], [base[1], ec.INF], [ec.INF] * 3,
+             [base[0], base[1], ec.neg(ec.add_affine(base[0], base[1])), base[2]], [base[0], base[1], ec.add_affine(base[0], base[1])],
+             [base[i % 5] for i in range(40)], [rng.choice(base + [ec.INF]) for _ in range(40)]]
+    for spread in (0, 1, 2):
+        for pts in cases:
+            for doublings in (0, 1, 130):
+                buf = b"".join(ec.g1_to_bytes(p) for p in pts)
+                want = ec.INF
+                for p in pts:
+                    want = ec.add_affine(want, p)
+                got = _pt(hm.hm_wave_sum, (ctypes.c_uint8 * max(len(buf), 1)).from_buffer_copy(buf or b"\0"), len(pts), doublings, spread)
+                want = ec.mul(1 << doublings, want)
+                assert (got is ec.INF and want is ec.INF) or got == want, (len(pts), spread, doublings)
 
 
 @pytest.mark.parametrize("lognb,windows", [(7, 1), (7, 9), (8, 1), (8, 2), (8, 8)])
