@@ -803,7 +803,8 @@ struct ScanChunkOffsets {     /* one workgroup: every lane owns a slice of the c
     uint32_t nchunks;
     uint32_t* tot_a;
     uint32_t* tot_b;
-    uint32_t* tot_max;     /* in: per-chunk maxima; out: tot_max[nchunks] = overall maximum */
+    const uint32_t* tot_max;     /* per-chunk maxima */
+    uint32_t* total_max;
     TC_DEV void phase(int ph, uint32_t lane, uint32_t, uint8_t* lds) const {
         uint32_t* sa = (uint32_t*)lds;
         uint32_t* sb = sa + BLOCK;
@@ -830,7 +831,7 @@ struct ScanChunkOffsets {     /* one workgroup: every lane owns a slice of the c
                 }
                 tot_a[nchunks] = a;
                 tot_b[nchunks] = b;
-                tot_max[nchunks] = mx;
+                *total_max = mx;
             }
         } else {
             uint32_t a = sa[lane], b = sb[lane];
@@ -1620,204 +1621,299 @@ struct CoopReduce {
     }
 };
 
+/* ---- sums by whole waves (wave28.h) ---------------------------------------------------------------------------------
+ * What the launches below have in common: few additions for the size of the chip, so that their time is the length of the
+ * longest chain of additions.  A wave adds two points in 1.6 us, a lane (13 products one after the other) in 15 to 20; where a chip's worth of
+ * lanes would be busy the lanes win, at a fifth of the cost per addition. */
+/* acc += the points that `bits` names, each fetched while the one before is being added; at(i) is the index of bit i */
+template <class At>
+TC_DEV void wave_add_points(const wv_consts& k, wv_point& acc, const WavePoints& pts, uint64_t bits, const At& at) {
+    if (!bits) return;
+    wv_words next = pts.fetch(at((uint32_t)__builtin_ctzll(bits)));
+    while (bits) {
+        bits &= bits - 1u;
+        const wv_point p = pts.unpack(next);
+        if (bits) next = pts.fetch(at((uint32_t)__builtin_ctzll(bits)));
+        wv_accumulate(k, acc, p);
+    }
+}
+/* the same for the points begin, begin + step, .. below end */
+TC_DEV void wave_add_run(const wv_consts& k, wv_point& acc, const WavePoints& pts, uint32_t begin, uint32_t end, uint32_t step) {
+    if (begin >= end) return;
+    wv_words next = pts.fetch(begin);
+    for (uint32_t i = begin; i < end; i += step) {
+        const wv_point p = pts.unpack(next);
+        if (i + step < end) next = pts.fetch(i + step);
+        wv_accumulate(k, acc, p);
+    }
+}
+/* the sums of the waves of a workgroup, side by side in LDS, added pairwise: level `level` of log2(waves) */
+TC_DEV void wave_pair_level(const wv_consts& k, uint32_t* lds, uint32_t wave, uint32_t waves, int level) {
+    const uint32_t half = waves >> (level + 1);
+    if (wave >= half) return;
+    wv_point a = wv_load_raw(lds + wave * WV_POINT_WORDS);
+    wv_accumulate(k, a, wv_load_raw(lds + (wave + half) * WV_POINT_WORDS));
+    wv_store_raw(lds + wave * WV_POINT_WORDS, a);
+}
+/* The accumulation of a small problem: wave t owns sub-run t (as lane t of AccAffine), settles every case and leaves its sum raw. */
+struct AccWave {
+    static constexpr int WAVES = 4;
+    static constexpr int PHASES = 1;
+    static constexpr size_t LDS_BYTES = 0;
+    const g1_affine* const* tables;
+    uint32_t nbk_pp;
+    const uint32_t* sorted;
+    const uint32_t* start;
+    const uint32_t* lstart;
+    uint32_t nbk;
+    uint32_t* out;
+    TC_DEV static wv_point entry(const g1_affine* pts, uint32_t e) {
+        wv_point p;
+        if (table_is_padded(pts)) {
+            const uint32_t* q = (const uint32_t*)padded_point(pts, e & 0x7FFFFFFFu);
+            const wv one = wv_table(W28_ONE);
+            p.inf = q[27] == 0xFFFFFFFFu;
+            WV_LANES(const uint32_t j = lane & 15u; WV_AT(p.v) = lane < 32u ? (j < 14u ? q[14u * (lane >> 4) + j] : 0u) : WV_AT(one))
+        } else {
+            p = wv_load_affine(pts + (e & 0x7FFFFFFFu));
+        }
+        if (e >> 31) p.v = wv_negate(p.v);
+        return p;
+    }
+    TC_DEV void phase(int, uint32_t wave, uint32_t wg, uint8_t*) const {
+        const uint32_t t = wg * (uint32_t)WAVES + wave;
+        if (t >= lstart[nbk]) return;
+        const uint32_t b = find_segment(lstart, nbk, t);
+        uint32_t begin, end;
+        subrun_bounds(start, lstart, b, t, begin, end);
+        const g1_affine* pts = tables[b / nbk_pp];
+        const wv_consts k = wv_constants();
+        wv_point acc = entry(pts, sorted[begin]);
+        for (uint32_t i = begin + 1u; i < end; ++i) wv_accumulate(k, acc, entry(pts, sorted[i]));
+        wv_store_raw(out + (uint64_t)t * WV_POINT_WORDS, acc);
+    }
+};
+/* A pass over the partial sums: wave t owns sub-run t of at most L of them (subrun_bounds). */
+struct PassWave {
+    static constexpr int WAVES = 4;
+    static constexpr int PHASES = 1;
+    static constexpr size_t LDS_BYTES = 0;
+    WavePoints in;
+    const uint32_t* start;
+    const uint32_t* lstart;
+    uint32_t nbk;
+    uint32_t* out;
+    TC_DEV void phase(int, uint32_t wave, uint32_t wg, uint8_t*) const {
+        const uint32_t t = wg * (uint32_t)WAVES + wave;
+        if (t >= lstart[nbk]) return;
+        const uint32_t b = find_segment(lstart, nbk, t);
+        uint32_t begin, end;
+        subrun_bounds(start, lstart, b, t, begin, end);
+        const wv_consts k = wv_constants();
+        wv_point acc = wv_identity();
+        wave_add_run(k, acc, in, begin, end, 1u);
+        wv_store_raw(out + (uint64_t)t * WV_POINT_WORDS, acc);
+    }
+};
+/* Last pass over the partial sums: N waves (1 or 4) to a bucket, left raw or in the 32-bit form. */
+template <int N>
+struct BucketWave {
+    static constexpr int WAVES = 4;
+    static constexpr int PHASES = N == 1 ? 1 : 3;
+    static constexpr size_t LDS_BYTES = N == 1 ? 0 : 4 * WV_POINT_WORDS * 4;
+    WavePoints in;
+    const uint32_t* start;
+    uint32_t nbk;
+    uint32_t* raw;             /* one of the two */
+    g1_xyzz* bucket;
+    TC_DEV void phase(int ph, uint32_t wave, uint32_t wg, uint8_t* bytes) const {
+        uint32_t* lds = (uint32_t*)bytes;
+        const uint32_t b = N == 1 ? wg * 4u + wave : wg;
+        if (b >= nbk) return;
+        const uint32_t begin = start[b], end = start[b + 1];
+        const uint32_t first = N == 1 ? begin : begin + wave;
+        if (N == 4 && begin == end) {
+            if (ph == 0 && wave == 0) leave(b, wv_identity());
+            return;
+        }
+        const wv_consts k = wv_constants();
+        if (ph == 0) {
+            wv_point acc = wv_identity();
+            wave_add_run(k, acc, in, first, end, (uint32_t)N);
+            if (N == 1) leave(b, acc);
+            else wv_store_raw(lds + wave * WV_POINT_WORDS, acc);
+            return;
+        }
+        wave_pair_level(k, lds, wave, 4u, ph - 1);
+        if (ph == 2 && wave == 0) leave(b, wv_load_raw(lds));
+    }
+    TC_DEV void leave(uint32_t b, const wv_point& p) const {
+        if (raw) wv_store_raw(raw + (uint64_t)b * WV_POINT_WORDS, p);
+        else wv_store(bucket + b, p);
+    }
+};
+
 /* ---- bucket reduction: sum_k k B_k --------------------------------------------------- */
-/* Cooperative kernel (one workgroup = BLOCK consecutive entries of `in`), phases separated
- * by barriers.  For block g:  S_g = sum_j in[g BLOCK + j]  and
- * W_g = sum_j (j + 1) in[g BLOCK + j]  (suffix sums by doubling strides, then their sum). */
-template <int BLOCK>
-struct WeightedBlockSum {
-    static constexpr int LOG = (BLOCK == 256) ? 8 : (BLOCK == 128) ? 7 : (BLOCK == 64) ? 6 : -1;
-    static constexpr int PHASES = 1 + LOG + 1 + LOG + 1;
-    static constexpr size_t LDS_BYTES = 2 * BLOCK * sizeof(g1_xyzz);
-    const g1_xyzz* in;
-    uint32_t n;                 /* entries of `in`; positions >= n count as the identity */
-    g1_xyzz* out_w;             /* per block */
-    g1_xyzz* out_s;             /* per block */
-    const g1_xyzz* in2;         /* optional second array: blocks split .. read in2 from position 0 */
-    uint32_t split;             /* first block that reads in2 (ignored when in2 is null) */
-    TC_DEV void phase(int ph, uint32_t lane, uint32_t wg, uint8_t* lds) const {
-        g1_xyzz* buf0 = (g1_xyzz*)lds;
-        g1_xyzz* buf1 = buf0 + BLOCK;
-        if (ph == 0) {
-            bool second = in2 && wg >= split;
-            uint64_t i = (uint64_t)(second ? wg - split : wg) * BLOCK + lane;
-            buf0[lane] = i < n ? (second ? in2[i] : in[i]) : xyzz_identity();
-            return;
-        }
-        if (ph <= LOG) {                       /* suffix sums, ping-pong */
-            int s = ph - 1;
-            g1_xyzz* cur = (s & 1) ? buf1 : buf0;
-            g1_xyzz* nxt = (s & 1) ? buf0 : buf1;
-            uint32_t stride = 1u << s;
-            g1_xyzz v = cur[lane];
-            if (lane + stride < (uint32_t)BLOCK) v = xyzz_add(v, cur[lane + stride]);
-            nxt[lane] = v;
-            return;
-        }
-        g1_xyzz* cur = (LOG & 1) ? buf1 : buf0;     /* suffix sums live here now */
-        if (ph == LOG + 1) {
-            if (lane == 0) out_s[wg] = cur[0];
-            return;
-        }
-        if (ph <= 2 * LOG + 1) {                     /* tree sum in place */
-            int s = ph - (LOG + 2);
-            uint32_t stride = 1u << s;
-            if ((lane & (2 * stride - 1)) == 0) cur[lane] = xyzz_add(cur[lane], cur[lane + stride]);
-            return;
-        }
-        if (lane == 0) out_w[wg] = cur[0];
-    }
-};
-
-/* Bucket reduction of a window of 32768 buckets seen as a 128 x 256 matrix (bucket k = 256 h + l + 1).  With the
- * row sums R_h (the 256 buckets with that high part) and the column sums C_l (the 128 buckets with that low part),
+/* A window of 32768 buckets is a 128 x 256 matrix (bucket k = 256 h + l + 1).  With the row sums R_h (the 256 buckets with
+ * that high part) and the column sums C_l (the 128 buckets with that low part),
  *     sum_k k B_k = 256 sum_h h R_h + sum_l (l + 1) C_l,
- * one plain addition per bucket and direction instead of a weighted scan over all of them. */
-/* Launches with few windows (a lone commitment), where nothing but depth counts: every
- * sum is a cooperative sum whose additions are shared by the four waves of a workgroup (CoopReduce), and the
- * weights are taken bit by bit.  With R_h and C_l the row and column sums of the 128 x 256 bucket matrix,
+ * one plain addition per bucket and direction instead of a weighted scan over all of them, and the weights are taken bit by bit:
  *     sum_k k B_k = sum_(j=0..8) 2^j X_j + 256 sum_(j=0..6) 2^j Y_j,
- *     X_j = sum of the C_l with bit j of l + 1 set,   Y_j = sum of the R_h with bit j of h set:
- * one launch for the 384 row and column sums, one for the 16 bit sums, 16 independent chains of at most 14
- * doublings, one sum of 16 points. */
-struct RowColSrc {             /* workgroup (w, g): g < 128 row g, else column g - 128 */
-    const g1_xyzz* bucket;     /* windows * 32768 */
-    g1_xyzz* rows;             /* windows * 256 (128 used) */
-    g1_xyzz* cols;             /* windows * 256 */
-    TC_DEV uint32_t count(uint32_t wg) const { return wg % 384u < 128u ? 256u : 128u; }
-    TC_DEV g1_xyzz load(uint32_t wg, uint32_t i) const {
-        uint32_t w = wg / 384u, g = wg % 384u;
-        const g1_xyzz* base = bucket + (uint64_t)w * 32768u;
-        return g < 128u ? base[g * 256u + i] : base[i * 256u + (g - 128u)];
-    }
-    TC_DEV void store(uint32_t wg, const g1_xyzz& r) const {
-        uint32_t w = wg / 384u, g = wg % 384u;
-        if (g < 128u) rows[(uint64_t)w * 256u + g] = r; else cols[(uint64_t)w * 256u + (g - 128u)] = r;
-    }
-};
-struct BitSumSrc {             /* workgroup (w, j): j < 9 the columns with bit j of l + 1, else the rows with bit j - 9 of h */
-    const g1_xyzz* rows;
-    const g1_xyzz* cols;
-    g1_xyzz* out;              /* windows * 16 */
-    TC_DEV uint32_t count(uint32_t wg) const { return wg % 16u < 9u ? 256u : 128u; }
-    TC_DEV g1_xyzz load(uint32_t wg, uint32_t i) const {
-        uint32_t w = wg / 16u, j = wg % 16u;
-        if (j < 9u) return (((i + 1u) >> j) & 1u) ? cols[(uint64_t)w * 256u + i] : xyzz_identity();
-        return ((i >> (j - 9u)) & 1u) ? rows[(uint64_t)w * 256u + i] : xyzz_identity();
-    }
-    TC_DEV void store(uint32_t wg, const g1_xyzz& r) const { out[wg] = r; }
-};
-/* 2^e X for every bit sum X, e the place value of its bit: chain t of CHAINS per window.  CHAINS = 16: X_j with e = j, then
- * Y_j with e = 8 + j; otherwise e = t % CHAINS.  Up to 14 doublings in a row and few chains: the nine products of an
- * XYZZ doubling are shared by the four waves of a workgroup in three levels (V = (2Y)^2, A = X^2 | W = 2Y V, S = X V,
- * (3A)^2, V ZZ | 3A (S - X3), W Y, W ZZZ), operands in LDS in the 28-bit form, a barrier after every level and one more
- * for the subtraction that ends the doubling; a chain that has done its own number of doublings no longer takes the
- * results.  ZZ = 0 (the identity) reproduces itself; bounds as for acc_dbl.
- * Bound by the chain of products: 14 doublings 91 -> 69 us against the form on the FP64 pipe. */
-template <int CHAINS>
-struct BitSumScale {
-    static constexpr int BLOCK = 256;
-    static constexpr int MAX_DOUBLINGS = CHAINS == 16 ? 14 : CHAINS - 1;
-    enum { FX, FY, FZZ, FZZZ, FU, FV, FM, FW, FS, FMM, FT, FWY, FZZN, FZZZN, FX3, NFIELD };
-    static constexpr size_t LDS_BYTES = (size_t)NFIELD * sizeof(fp28) * 64;
-    static constexpr int PHASES = 1 + 4 * MAX_DOUBLINGS + 1;
-    const g1_xyzz* in;
-    uint32_t n;                /* chains */
-    g1_xyzz* out;
-    TC_DEV static uint32_t doublings(uint32_t t) {
-        uint32_t j = t % (uint32_t)CHAINS;
-        return CHAINS == 16 && j >= 9u ? j - 1u : j;
-    }
-    TC_DEV static fp28 ld(const uint8_t* lds, int f, uint32_t l) { return Fp28Planes::ld(lds, f, 64, l); }
-    TC_DEV static void st(uint8_t* lds, int f, uint32_t l, const fp28& x) { Fp28Planes::st(lds, f, 64, l, x); }
-    TC_DEV void phase(int ph, uint32_t lane, uint32_t wg, uint8_t* lds) const {
-        uint32_t wave = lane >> 6, l = lane & 63u;
-        uint32_t t = wg * 64u + l;
-        bool live = t < n;
+ *     X_j = sum of the C_l with bit j of l + 1 set,   Y_j = sum of the R_h with bit j of h set.
+ * A window of 128 or 256 buckets is taken bit by bit at once: X_j = sum of the B_k with bit j of k set. */
+/* The 384 row and column sums of a window in pieces of 64 buckets (ROWCOL_PIECES to a row, half as many to a column), a workgroup of four
+ * waves to a piece; an empty bucket costs a look at one word.  Launches with few windows (a lone commitment); many windows fill the
+ * chip and take BigRowColSums.  The pieces are there because the buckets of a quantised activation are dense near zero: whole rows, sixteen waves to
+ * a row, left the compute units that had them busy for 72 us and the others idle; in pieces 34 us
+ * (and CoopReduce, 256 points to a workgroup of lanes, 120). */
+constexpr uint32_t ROW_PIECES = 4, COL_PIECES = 2, ROWCOL_PIECES = 128 * ROW_PIECES + 256 * COL_PIECES;
+struct RowColWave {
+    static constexpr int WAVES = 4;
+    static constexpr int PHASES = 3;
+    static constexpr size_t LDS_BYTES = WAVES * WV_POINT_WORDS * 4;
+    WavePoints bucket;         /* windows * 32768 */
+    uint32_t* out;             /* raw, per window the pieces of the rows, then those of the columns */
+    TC_DEV void phase(int ph, uint32_t wave, uint32_t wg, uint8_t* bytes) const {
+        uint32_t* lds = (uint32_t*)bytes;
+        const uint32_t w = wg / ROWCOL_PIECES, g = wg % ROWCOL_PIECES;
+        const wv_consts k = wv_constants();
         if (ph == 0) {
-            if (wave != 0) return;
-            g1_xyzz28 p = xyzz28_from(live ? in[t] : xyzz_identity());
-            st(lds, FX, l, p.X); st(lds, FY, l, p.Y); st(lds, FZZ, l, p.ZZ); st(lds, FZZZ, l, p.ZZZ);
-            st(lds, FU, l, fp28_add(p.Y, p.Y));
+            const uint64_t base = (uint64_t)w * 32768u;
+            const bool row = g < 128u * ROW_PIECES;
+            const uint32_t u = row ? g : g - 128u * ROW_PIECES, h0 = u % COL_PIECES * 64u, l = u / COL_PIECES;
+            /* the waves take every fourth bucket: what is dense is shared */
+            const auto at = [=](uint32_t i) { const uint32_t x = 4u * i + wave; return base + (row ? u * 64u + x : (h0 + x) * 256u + l); };
+            const uint64_t bits = wv_ballot([&](uint32_t lane) { return lane < 16u && !bucket.empty(at(lane)); });
+            wv_point acc = wv_identity();
+            wave_add_points(k, acc, bucket, bits, at);
+            wv_store_raw(lds + wave * WV_POINT_WORDS, acc);
             return;
         }
-        if (ph == PHASES - 1) {
-            if (wave != 0 || !live) return;
-            g1_xyzz28 p;
-            p.X = ld(lds, FX, l); p.Y = ld(lds, FY, l); p.ZZ = ld(lds, FZZ, l); p.ZZZ = ld(lds, FZZZ, l);
-            out[t] = xyzz28_to(p);
-            return;
-        }
-        uint32_t d = (uint32_t)(ph - 1) / 4u + 1u;          /* the d-th doubling is in the making */
-        int level = (ph - 1) % 4;
-        if (level == 0) {
-            if (wave == 0) {
-                st(lds, FV, l, fp28_sqr(ld(lds, FU, l)));
-            } else if (wave == 1) {
-                fp28 A = fp28_sqr(ld(lds, FX, l));
-                st(lds, FM, l, fp28_carry(fp28_add(fp28_add(A, A), A)));
-            }
-        } else if (level == 1) {
-            if (wave == 0) st(lds, FW, l, fp28_mul(ld(lds, FU, l), ld(lds, FV, l)));
-            else if (wave == 1) st(lds, FS, l, fp28_mul(ld(lds, FX, l), ld(lds, FV, l)));
-            else if (wave == 2) st(lds, FMM, l, fp28_sqr(ld(lds, FM, l)));
-            else st(lds, FZZN, l, fp28_mul(ld(lds, FV, l), ld(lds, FZZ, l)));
-        } else if (level == 2) {
-            if (wave == 0) {
-                fp28 S = ld(lds, FS, l);
-                fp28 X3 = fp28_carry(fp28_sub(fp28_sub(ld(lds, FMM, l), S), S));
-                st(lds, FX3, l, X3);
-                st(lds, FT, l, fp28_mul(ld(lds, FM, l), fp28_sub(S, X3)));
-            } else if (wave == 1) {
-                st(lds, FWY, l, fp28_mul(ld(lds, FW, l), ld(lds, FY, l)));
-            } else if (wave == 2) {
-                st(lds, FZZZN, l, fp28_mul(ld(lds, FW, l), ld(lds, FZZZ, l)));
-            }
-        } else if (wave == 0 && live && d <= doublings(t)) {
-            fp28 Y3 = fp28_sub(ld(lds, FT, l), ld(lds, FWY, l));
-            st(lds, FX, l, ld(lds, FX3, l));
-            st(lds, FY, l, Y3);
-            st(lds, FU, l, fp28_add(Y3, Y3));
-            st(lds, FZZ, l, ld(lds, FZZN, l));
-            st(lds, FZZZ, l, ld(lds, FZZZN, l));
-        }
+        wave_pair_level(k, lds, wave, WAVES, ph - 1);
+        if (ph == 2 && wave == 0) wv_store_raw(out + (uint64_t)wg * WV_POINT_WORDS, wv_load_raw(lds));
     }
 };
-/* The same bit by bit for a few windows of 128 or 256 buckets: workgroup (w, j) adds the buckets k = 1 .. nb with bit j of k
- * set, nb / 2 of them for j < log2(nb) and bucket nb alone for the last j. */
-struct SmallBitSumSrc {
-    const g1_xyzz* bucket;     /* windows * nb, bucket k at k - 1 */
+/* (The weights of one window: this, ScaleWave and WindowWave 53 us where three launches that shared lane-wide products among four waves
+ * took 243; of 96 windows 0.26 ms, 0.62 in two launches of lanes.) */
+/* The sums per bit.  Window w has `chains` of them, each in BITSUM_PARTS pieces (eight waves, at most eight points a wave).  lognb = 15: from the
+ * column and row sums, which come in pieces (9 + 7 chains), otherwise from 2^lognb buckets (lognb + 1 chains, bucket k at k - 1). */
+constexpr uint32_t BITSUM_PARTS = 4;
+TC_HD uint32_t bitsum_chains(uint32_t lognb) { return lognb == 15u ? 16u : lognb + 1u; }
+/* number i with bit j set */
+TC_HD uint32_t with_bit(uint32_t i, uint32_t j) { return (i >> j << (j + 1u)) | (1u << j) | (i & ((1u << j) - 1u)); }
+struct BitSumWave {
+    static constexpr int WAVES = 8;
+    static constexpr int PHASES = 4;
+    static constexpr size_t LDS_BYTES = WAVES * WV_POINT_WORDS * 4;
+    WavePoints pts;            /* buckets, or column sums */
+    WavePoints rows;           /* row sums (lognb = 15) */
+    uint32_t pts_stride, rows_stride;      /* points per window */
+    uint32_t logp, rows_logp;  /* log2 of the pieces of a sum, which lie side by side */
     uint32_t lognb;
-    g1_xyzz* out;              /* windows * (lognb + 1) */
-    TC_DEV uint32_t count(uint32_t wg) const { return wg % (lognb + 1u) == lognb ? 1u : 1u << (lognb - 1u); }
-    TC_DEV g1_xyzz load(uint32_t wg, uint32_t i) const {
-        uint32_t w = wg / (lognb + 1u), j = wg % (lognb + 1u);
-        uint32_t k = (i >> j << (j + 1u)) | (1u << j) | (i & ((1u << j) - 1u));
-        return bucket[((uint64_t)w << lognb) + k - 1u];
+    uint32_t* out;             /* raw: windows * chains * BITSUM_PARTS */
+    TC_DEV void phase(int ph, uint32_t wave, uint32_t wg, uint8_t* bytes) const {
+        uint32_t* lds = (uint32_t*)bytes;
+        const uint32_t chains = bitsum_chains(lognb), part = wg % BITSUM_PARTS, j = wg / BITSUM_PARTS % chains, w = wg / (BITSUM_PARTS * chains);
+        const uint32_t bits = lognb == 15u ? (j < 9u ? 8u : 7u) : lognb;          /* of the index */
+        const bool high = lognb == 15u && j >= 9u;
+        const uint32_t jj = high ? j - 9u : j, lp = high ? rows_logp : logp;
+        const uint32_t n = (jj == bits ? 1u : 1u << (bits - 1u)) << lp;            /* points of the chain: at most 256 */
+        const uint32_t per = n <= 128u ? 4u : 8u, first = (part * WAVES + wave) * per;
+        uint32_t* to = out + (uint64_t)wg * WV_POINT_WORDS;
+        if (part * WAVES * per >= n) {
+            if (ph == 0 && wave == 0) wv_store_raw(to, wv_identity());
+            return;
+        }
+        const wv_consts k = wv_constants();
+        if (ph == 0) {
+            const uint32_t mine = first >= n ? 0u : n - first < per ? n - first : per;
+            /* columns and buckets carry the weight index + 1, rows their index */
+            const WavePoints& src = high ? rows : pts;
+            const uint64_t base = (uint64_t)w * (high ? rows_stride : pts_stride);
+            const uint32_t off = high ? 0u : 1u;
+            wv_point acc = wv_identity();
+            wave_add_points(k, acc, src, (1ull << mine) - 1ull, [=](uint32_t i) {
+                const uint32_t x = first + i;
+                return base + ((uint64_t)(with_bit(x >> lp, jj) - off) << lp) + (x & ((1u << lp) - 1u));
+            });
+            wv_store_raw(lds + wave * WV_POINT_WORDS, acc);
+            return;
+        }
+        wave_pair_level(k, lds, wave, WAVES, ph - 1);
+        if (ph == 3 && wave == 0) wv_store_raw(to, wv_load_raw(lds));
     }
-    TC_DEV void store(uint32_t wg, const g1_xyzz& r) const { out[wg] = r; }
 };
-struct GroupSumSrc {           /* out[g] = sum of in[g * group .. (g + 1) * group), group <= 256 */
-    const g1_xyzz* in;
-    uint32_t group;
-    g1_xyzz* out;
-    TC_DEV uint32_t count(uint32_t) const { return group; }
-    TC_DEV g1_xyzz load(uint32_t g, uint32_t i) const { return in[(uint64_t)g * group + i]; }
-    TC_DEV void store(uint32_t g, const g1_xyzz& r) const { out[g] = r; }
+/* 2^e X for every bit sum X, e the place value of its bit (14 at most): a workgroup per chain, four waves to add its pieces up and one to double.
+ * Bound by the chain of doublings, 1.2 us each. */
+struct ScaleWave {
+    static constexpr int WAVES = (int)BITSUM_PARTS;
+    static constexpr int PHASES = 4;
+    static constexpr size_t LDS_BYTES = WAVES * WV_POINT_WORDS * 4;
+    const uint32_t* sums;      /* what BitSumWave leaves */
+    uint32_t lognb;
+    uint32_t* out;             /* raw: windows * chains */
+    TC_DEV void phase(int ph, uint32_t wave, uint32_t wg, uint8_t* bytes) const {
+        uint32_t* lds = (uint32_t*)bytes;
+        if (ph == 0) {
+            wv_store_raw(lds + wave * WV_POINT_WORDS, wv_load_raw(sums + ((uint64_t)wg * BITSUM_PARTS + wave) * WV_POINT_WORDS));
+            return;
+        }
+        const wv_consts k = wv_constants();
+        if (ph <= 2) {
+            wave_pair_level(k, lds, wave, WAVES, ph - 1);
+            return;
+        }
+        if (wave) return;
+        const uint32_t j = wg % bitsum_chains(lognb), e = lognb == 15u && j >= 9u ? j - 1u : j;
+        wv_point acc = wv_load_raw(lds);
+        for (uint32_t i = 0; i < e && !acc.inf; ++i) acc.v = wv_dbl(k, acc.v);
+        wv_store_raw(out + (uint64_t)wg * WV_POINT_WORDS, acc);
+    }
 };
-
-/* one lane per window: 256 (W_R - S_R) + W_C */
-struct RowColFinish {
-    const g1_xyzz* w_rows;      /* sum_h (h + 1) R_h */
-    const g1_xyzz* s_rows;      /* sum_h R_h */
-    const g1_xyzz* w_cols;      /* sum_l (l + 1) C_l */
+/* The sum of the scaled chains of a window (at most 16 of them): to `result` in the 32-bit form (problems of one window) or raw to `wsum`. */
+struct WindowWave {
+    static constexpr int WAVES = 8;
+    static constexpr int PHASES = 4;
+    static constexpr size_t LDS_BYTES = WAVES * WV_POINT_WORDS * 4;
+    const uint32_t* scaled;
+    uint32_t chains;
+    uint32_t* wsum;
+    g1_xyzz* result;
+    TC_DEV void phase(int ph, uint32_t wave, uint32_t w, uint8_t* bytes) const {
+        uint32_t* lds = (uint32_t*)bytes;
+        const wv_consts k = wv_constants();
+        if (ph == 0) {
+            wv_point acc = wv_identity();
+            wave_add_run(k, acc, WavePoints{scaled + (uint64_t)w * chains * WV_POINT_WORDS, 1u}, wave, chains, WAVES);
+            wv_store_raw(lds + wave * WV_POINT_WORDS, acc);
+            return;
+        }
+        wave_pair_level(k, lds, wave, WAVES, ph - 1);
+        if (ph == 3 && wave == 0) {
+            const wv_point r = wv_load_raw(lds);
+            if (result) wv_store(result + w, r);
+            else wv_store_raw(wsum + (uint64_t)w * WV_POINT_WORDS, r);
+        }
+    }
+};
+/* One wave per problem: Horner over its windows, result = sum_w 2^(c w) Wsum_w */
+struct CombineWave {
+    static constexpr int WAVES = 1;
+    static constexpr int PHASES = 1;
+    static constexpr size_t LDS_BYTES = 0;
+    WavePoints wsum;
+    uint32_t W, c;
     g1_xyzz* out;
-    TC_DEV void operator()(uint32_t w) const {
-        xyzz_acc t = acc_from(w_rows[w]);
-        acc_add(t, acc_from(xyzz_neg(s_rows[w])));
-        for (int i = 0; i < 8; ++i) acc_dbl(t);
-        acc_add(t, acc_from(w_cols[w]));
-        out[w] = acc_result(t);
+    TC_DEV void phase(int, uint32_t, uint32_t p, uint8_t*) const {
+        const wv_consts k = wv_constants();
+        const uint64_t first = (uint64_t)p * W;
+        wv_point acc = wsum.load(first + W - 1u);
+        for (uint32_t w = W - 1u; w-- > 0;) {
+            const wv_words next = wsum.fetch(first + w);
+            for (uint32_t i = 0; i < c && !acc.inf; ++i) acc.v = wv_dbl(k, acc.v);
+            wv_accumulate(k, acc, wsum.unpack(next));
+        }
+        wv_store(out + p, acc);
     }
 };
 
@@ -1981,40 +2077,6 @@ struct SmallFinish {             /* cols * (row part) + (column part) */
         for (uint32_t c = cols; c > 1u; c >>= 1) acc_dbl(t);
         acc_add(t, acc_from(parts[n_windows + w]));
         out[w] = acc_result(t);
-    }
-};
-
-/* One lane per window: Wsum = sumW + BLOCK * (W2 - S2) where, over the G blocks of the window,
- * sumW = sum_g W_g, W2 = sum_g (g+1) S_g, S2 = sum_g S_g.  With G == 1: Wsum = W_0. */
-struct WindowFinish {
-    const g1_xyzz* w1;     /* W_g of stage 1, G per window (G == 1) or sum of them (stage 3 S) */
-    const g1_xyzz* w2;     /* W of stage 2 per window */
-    const g1_xyzz* s2;     /* S of stage 2 per window */
-    int G, log_block;
-    g1_xyzz* out;
-    TC_DEV void operator()(uint32_t w) const {
-        if (G == 1) { out[w] = w1[w]; return; }
-        xyzz_acc t = acc_from(w2[w]);
-        acc_add(t, acc_from(xyzz_neg(s2[w])));
-        for (int i = 0; i < log_block; ++i) acc_dbl(t);
-        acc_add(t, acc_from(w1[w]));
-        out[w] = acc_result(t);
-    }
-};
-/* One lane per problem: Horner over its windows, result = sum_w 2^(c w) Wsum_w */
-struct WindowCombine {
-    const g1_xyzz* wsum;
-    int W, c;
-    g1_xyzz* out;
-    TC_DEV void operator()(uint32_t p) const {
-        const g1_xyzz* ws = wsum + (uint64_t)p * W;
-        if (W == 1) { out[p] = ws[0]; return; }
-        xyzz_acc acc = acc_from(ws[W - 1]);
-        for (int w = W - 2; w >= 0; --w) {
-            for (int i = 0; i < c; ++i) acc_dbl(acc);
-            acc_add(acc, acc_from(ws[w]));
-        }
-        out[p] = acc_result(acc);
     }
 };
 

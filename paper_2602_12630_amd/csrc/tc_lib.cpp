@@ -1289,11 +1289,11 @@ static int scan_counts(tc_ctx* ctx, const uint32_t* cnt, uint32_t n, uint32_t L,
     uint32_t nchunks = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
     if (n <= ScanSmall::MAX_N) {          /* few buckets: one workgroup, one launch; the totals land where the chunked scan leaves them */
         RT((launch_coop<ScanSmall::BLOCK>(1, ctx->stream,
-                                          ScanSmall{cnt, n, L, start, lstart, zero_me, tot_a + nchunks, tot_b + nchunks, tot_max + nchunks})));
+                                          ScanSmall{cnt, n, L, start, lstart, zero_me, tot_a + nchunks, tot_b + nchunks, tot_b + nchunks + 1})));
         return TC_OK;
     }
     RT(rt::launch<64>(nchunks, ctx->stream, ScanChunkTotals{cnt, n, L, tot_a, tot_b, tot_max}));
-    RT((launch_coop<ScanChunkOffsets::BLOCK>(1, ctx->stream, ScanChunkOffsets{nchunks, tot_a, tot_b, tot_max})));
+    RT((launch_coop<ScanChunkOffsets::BLOCK>(1, ctx->stream, ScanChunkOffsets{nchunks, tot_a, tot_b, tot_max, tot_b + nchunks + 1})));
     RT(rt::launch<64>(nchunks, ctx->stream, ScanWrite{cnt, n, L, tot_a, tot_b, nchunks, start, lstart, zero_me}));
     return TC_OK;
 }
@@ -1306,94 +1306,80 @@ static const int SMALL_WINDOW_REDUCE_MIN = 8;          /* the CPU build of the t
 #else
 static const int SMALL_WINDOW_REDUCE_MIN = 512;
 #endif
-/* up to this many of them the weights are taken bit by bit: at most two workgroups per compute unit (nine chains of a
- * window of 256 buckets each), each a sum of half the window's buckets, against fourteen additions in a row (one window of
- * 128: 262 -> 175 us in three launches, four: 345 -> 168; whole batches of 1024-entry int8 tensors: 56 of them 522 us,
- * 57, which go the other way, 685) */
-#if defined(TC_HOST_EMU)
-static const int SMALL_WINDOW_BITS_MAX = 2;
-#else
-static const int SMALL_WINDOW_BITS_MAX = 56;
-#endif
 /* from this many 32768-bucket windows on, a launch fills the chip with the packed row / column sums */
 static const int ROWCOL_PACKED_WINDOWS = 8;
 
-/* sum_k k B_k for every window of `bucket` (W windows of nb buckets) -> wsum[W] */
-static int reduce_windows(tc_ctx* ctx, const g1_xyzz* bucket, int W, uint32_t nb, g1_xyzz* wsum) {
-    if ((nb == 256 || nb == 128) && W >= SMALL_WINDOW_REDUCE_MIN) {
+/* do these windows' sums read their buckets in the 32-bit form (kernels of lanes)? */
+static bool windows_by_lanes(uint64_t windows, uint32_t nb) {
+    return nb == 32768 ? windows >= (uint64_t)ROWCOL_PACKED_WINDOWS : windows >= (uint64_t)SMALL_WINDOW_REDUCE_MIN;
+}
+/* `count` problems of W windows of nb buckets: result = sum_w 2^(c w) sum_k k B_(w,k) */
+static int reduce_windows(tc_ctx* ctx, const WavePoints& bucket, int count, int W, int c, uint32_t nb, g1_xyzz* results) {
+    if ((uint64_t)W * (uint64_t)count > 0x7FFFFFFFull) return fail(ctx, TC_ERR_SHAPE, "too many windows in one launch");
+    const uint32_t windows = (uint32_t)W * (uint32_t)count;
+    const uint32_t lognb = nb == 32768 ? 15u : nb == 256 ? 8u : nb == 128 ? 7u : 0u;
+    if (!lognb) return fail(ctx, TC_ERR_STATE, "unsupported bucket count");
+    if (nb != 32768 && windows_by_lanes(windows, nb)) {
         /* many small windows (row problems of openings): throughput matters, not depth */
-        StridedSums S{bucket, nb, (uint32_t)W, nullptr, nullptr, nullptr};
+        StridedSums S{(const g1_xyzz*)bucket.base, nb, windows, nullptr, nullptr, nullptr};
         uint64_t lanes = S.lanes();
         if (lanes > 0xFFFFFFF0ull) return fail(ctx, TC_ERR_SHAPE, "too many windows in one launch");
         WS(sums, g1_xyzz, lanes);
-        WS(parts, g1_xyzz, 2ull * (uint32_t)W);
+        WS(parts, g1_xyzz, 2ull * windows);
         WS(redo, uint32_t, lanes + 1);
+        WS(wsum, g1_xyzz, W > 1 ? windows : 1u);
         S.out = sums; S.redo_count = redo; S.redo_list = redo + 1;
         RT(rt::launch<64>(1, ctx->stream, Fill32{redo, 0u}));
         RT((rt::launch_waves<64, 2>(lanes, ctx->stream, S)));
         uint32_t redo_lanes = (uint32_t)std::min<uint64_t>(lanes, ACC_RESIDENT_LANES);
         RT(rt::launch<64>(redo_lanes, ctx->stream, StridedRedo<StridedSums>{S, redo_lanes}));
-        RT(rt::launch<64>(2ull * (uint32_t)W, ctx->stream, SmallWeighted{sums, S.cols(), (uint32_t)W, parts}));
-        RT(rt::launch<64>((uint32_t)W, ctx->stream, SmallFinish{parts, S.cols(), (uint32_t)W, wsum}));
+        RT(rt::launch<64>(2ull * windows, ctx->stream, SmallWeighted{sums, S.cols(), windows, parts}));
+        RT(rt::launch<64>(windows, ctx->stream, SmallFinish{parts, S.cols(), windows, W > 1 ? wsum : results}));
+        if (W > 1) RT(launch_wave_groups((uint32_t)count, ctx->stream, CombineWave{WavePoints{wsum, 0u}, (uint32_t)W, (uint32_t)c, results}));
         return TC_OK;
     }
-    if ((nb == 128 || nb == 256) && W <= SMALL_WINDOW_BITS_MAX) {
-        typedef CoopReduce<SmallBitSumSrc> BitSum;
-        typedef CoopReduce<GroupSumSrc> GroupSum;
-        const uint32_t lognb = nb == 128 ? 7u : 8u, chains = lognb + 1u, n = chains * (uint32_t)W;
-        WS(bits, g1_xyzz, n);
-        WS(scaled, g1_xyzz, n);
-        RT((launch_coop<BitSum::BLOCK>(n, ctx->stream, BitSum{SmallBitSumSrc{bucket, lognb, bits}})));
-        if (nb == 128) RT((launch_coop<BitSumScale<8>::BLOCK>((n + 63u) / 64u, ctx->stream, BitSumScale<8>{bits, n, scaled})));
-        else RT((launch_coop<BitSumScale<9>::BLOCK>((n + 63u) / 64u, ctx->stream, BitSumScale<9>{bits, n, scaled})));
-        RT((launch_coop<GroupSum::BLOCK>((uint32_t)W, ctx->stream, GroupSum{GroupSumSrc{scaled, chains, wsum}})));
-        return TC_OK;
+    /* bit by bit */
+    const uint32_t chains = bitsum_chains(lognb);
+    if ((uint64_t)windows * chains * BITSUM_PARTS > 0x7FFFFFFFull) return fail(ctx, TC_ERR_SHAPE, "too many windows in one launch");
+    WS(sums, uint32_t, (uint64_t)windows * chains * BITSUM_PARTS * WV_POINT_WORDS);
+    WS(scaled, uint32_t, (uint64_t)windows * chains * WV_POINT_WORDS);
+    WS(wsum, uint32_t, W > 1 ? (uint64_t)windows * WV_POINT_WORDS : 1u);
+    BitSumWave bits{bucket, bucket, nb, nb, 0u, 0u, lognb, sums};
+    if (nb == 32768) {
+        /* 128 x 256 bucket matrix: column and row sums first */
+        if (!windows_by_lanes(windows, nb)) {
+            WS(pieces, uint32_t, (uint64_t)ROWCOL_PIECES * windows * WV_POINT_WORDS);
+            RT(launch_wave_groups(ROWCOL_PIECES * windows, ctx->stream, RowColWave{bucket, pieces}));
+            bits.rows = WavePoints{pieces, 1u};
+            bits.pts = WavePoints{pieces + 128ull * ROW_PIECES * WV_POINT_WORDS, 1u};
+            bits.rows_stride = bits.pts_stride = ROWCOL_PIECES;
+            bits.rows_logp = 2;
+            bits.logp = 1;
+            static_assert(ROW_PIECES == 4 && COL_PIECES == 2, "their logarithms");
+        } else {
+            if ((uint64_t)windows * 4096u > 0xFFFFFFF0ull) return fail(ctx, TC_ERR_SHAPE, "too many windows in one launch");
+            WS(rows, g1_xyzz, 512ull * windows);          /* the row sums of all windows, then the column sums of all windows */
+            WS(pieces, g1_xyzz, 4096ull * windows);
+            WS(redo, uint32_t, 4096ull * windows + 1);
+            RT(rt::launch<64>(1, ctx->stream, Fill32{redo, 0u}));
+            BigRowColSums L1{(const g1_xyzz*)bucket.base, 1, windows, pieces, redo, redo + 1};
+            BigRowColSums L2{pieces, 2, windows, rows, redo, redo + 1};
+            uint32_t redo_lanes = (uint32_t)std::min<uint64_t>(L1.lanes(), ACC_RESIDENT_LANES);
+            RT((rt::launch_waves<64, 2>(L1.lanes(), ctx->stream, L1)));
+            RT(rt::launch<64>(redo_lanes, ctx->stream, StridedRedo<BigRowColSums>{L1, redo_lanes}));
+            RT(rt::launch<64>(1, ctx->stream, Fill32{redo, 0u}));
+            RT((rt::launch_waves<64, 2>(L2.lanes(), ctx->stream, L2)));
+            redo_lanes = (uint32_t)std::min<uint64_t>(L2.lanes(), ACC_RESIDENT_LANES);
+            RT(rt::launch<64>(redo_lanes, ctx->stream, StridedRedo<BigRowColSums>{L2, redo_lanes}));
+            bits.pts = WavePoints{rows + 256ull * windows, 0u};
+            bits.rows = WavePoints{rows, 0u};
+            bits.pts_stride = bits.rows_stride = 256u;
+        }
     }
-    if (nb == 128 || nb == 256) {
-        WS(w1, g1_xyzz, (uint32_t)W);
-        WS(s1, g1_xyzz, (uint32_t)W);
-        if (nb == 128) RT((launch_coop<128>((uint32_t)W, ctx->stream, WeightedBlockSum<128>{bucket, (uint32_t)W * nb, w1, s1, nullptr, 0})));
-        else RT((launch_coop<256>((uint32_t)W, ctx->stream, WeightedBlockSum<256>{bucket, (uint32_t)W * nb, w1, s1, nullptr, 0})));
-        RT(rt::launch<64>((uint32_t)W, ctx->stream, WindowFinish{w1, nullptr, nullptr, 1, 0, wsum}));
-        return TC_OK;
-    }
-    if (nb != 32768) return fail(ctx, TC_ERR_STATE, "unsupported bucket count");
-    /* 128 x 256 bucket matrix: row / column sums, then two small weighted sums per window */
-    WS(rows, g1_xyzz, 512ull * W);          /* the row sums of all windows, then the column sums of all windows */
-    g1_xyzz* cols = rows + 256ull * W;
-    if (W < ROWCOL_PACKED_WINDOWS) {
-        /* few windows: depth is the cost; cooperative sums and bit-wise weights */
-        typedef CoopReduce<RowColSrc> RowCol;
-        typedef CoopReduce<BitSumSrc> BitSum;
-        typedef CoopReduce<GroupSumSrc> GroupSum;
-        WS(bits, g1_xyzz, 16u * (uint32_t)W);
-        WS(scaled, g1_xyzz, 16u * (uint32_t)W);
-        RT((launch_coop<RowCol::BLOCK>(384u * (uint32_t)W, ctx->stream, RowCol{RowColSrc{bucket, rows, cols}})));
-        RT((launch_coop<BitSum::BLOCK>(16u * (uint32_t)W, ctx->stream, BitSum{BitSumSrc{rows, cols, bits}})));
-        RT((launch_coop<BitSumScale<16>::BLOCK>((16u * (uint32_t)W + 63u) / 64u, ctx->stream, BitSumScale<16>{bits, 16u * (uint32_t)W, scaled})));
-        RT((launch_coop<GroupSum::BLOCK>((uint32_t)W, ctx->stream, GroupSum{GroupSumSrc{scaled, 16u, wsum}})));
-        return TC_OK;
-    }
-    WS(w_rc, g1_xyzz, 2u * (uint32_t)W);     /* [0, W): columns, [W, 2W): rows */
-    WS(s_rc, g1_xyzz, 2u * (uint32_t)W);
-    {
-        if ((uint64_t)W * 4096u > 0xFFFFFFF0ull) return fail(ctx, TC_ERR_SHAPE, "too many windows in one launch");
-        WS(pieces, g1_xyzz, 4096ull * W);
-        WS(redo, uint32_t, 4096ull * W + 1);
-        RT(rt::launch<64>(1, ctx->stream, Fill32{redo, 0u}));
-        BigRowColSums L1{bucket, 1, (uint32_t)W, pieces, redo, redo + 1};
-        BigRowColSums L2{pieces, 2, (uint32_t)W, rows, redo, redo + 1};
-        uint32_t redo_lanes = (uint32_t)std::min<uint64_t>(L1.lanes(), ACC_RESIDENT_LANES);
-        RT((rt::launch_waves<64, 2>(L1.lanes(), ctx->stream, L1)));
-        RT(rt::launch<64>(redo_lanes, ctx->stream, StridedRedo<BigRowColSums>{L1, redo_lanes}));
-        RT(rt::launch<64>(1, ctx->stream, Fill32{redo, 0u}));
-        RT((rt::launch_waves<64, 2>(L2.lanes(), ctx->stream, L2)));
-        redo_lanes = (uint32_t)std::min<uint64_t>(L2.lanes(), ACC_RESIDENT_LANES);
-        RT(rt::launch<64>(redo_lanes, ctx->stream, StridedRedo<BigRowColSums>{L2, redo_lanes}));
-    }
-    RT((launch_coop<256>(2u * (uint32_t)W, ctx->stream,
-                         WeightedBlockSum<256>{cols, 256u * (uint32_t)W, w_rc, s_rc, rows, (uint32_t)W})));
-    RT(rt::launch<64>((uint32_t)W, ctx->stream, RowColFinish{w_rc + W, s_rc + W, w_rc, wsum}));
+    RT(launch_wave_groups(windows * chains * BITSUM_PARTS, ctx->stream, bits));
+    RT(launch_wave_groups(windows * chains, ctx->stream, ScaleWave{sums, lognb, scaled}));
+    RT(launch_wave_groups(windows, ctx->stream, WindowWave{scaled, chains, wsum, W > 1 ? nullptr : results}));
+    if (W > 1) RT(launch_wave_groups((uint32_t)count, ctx->stream, CombineWave{WavePoints{wsum, 1u}, (uint32_t)W, (uint32_t)c, results}));
     return TC_OK;
 }
 
@@ -1494,6 +1480,9 @@ static const uint64_t ORDERED_LANES_MIN = 64;
 #else
 static const uint64_t ORDERED_LANES_MIN = 1ull << 20;
 #endif
+/* ... but not where a bucket holds sixteen sub-runs on average: the k sub-runs of a bucket are equally long, L (1 - 1 / k) at least, and
+ * a launch of few buckets places its sub-runs with few workgroups (512 buckets, 10^6 sub-runs: 510 of 11 300 us) */
+static const uint64_t ORDERED_LOAD_MAX = 16;
 
 /* from this many 16-bit terms on, a launch sorts them in two levels */
 #if defined(TC_HOST_EMU)
@@ -1507,6 +1496,25 @@ static const uint64_t SORT_SEVEN_BITS_MAX_TERMS = 1ull << 24;
  * workgroup and five barriers per handful of entries */
 static const uint64_t SORT_MIN_BIN_LOAD = SORT_TILE / 4;
 #endif
+
+/* Sums by whole waves.  A wave's addition costs the chip about 1 ns (1.6 us in the wave, a thousand SIMDs), a lane's 0.4 ns, but 15 us each
+ * in a row and 25 to 40 us for the prefix sums between two passes; the lines lie where the two meet.
+ * WAVE_ACC_MAX_ITEMS: entries of a launch that are accumulated by waves (AccWave; lanes took 45 us and up whatever there was, and
+ * AccFinal 50: commitment of 1024 int8 entries 121 -> 15 us for the two).
+ * WAVE_PASS_MAX: partial sums that go straight into the buckets (BucketWave).  Whole calls at 1.93e5 and 1e5 partial sums with
+ * the line at 200000 / 110000: 512 x 4096 int16 826 / 769 us, 487 x 11008 1320 / 1241 us; where the pass by lanes that it saves is one over
+ * 131072 buckets or more, with three launches of prefix sums, twice as many: four tensors of 64 x 4096 in one call 805 / 1015 us. */
+#if defined(TC_HOST_EMU)
+/* the CPU build of the tests walks both sides with small problems */
+static const uint64_t WAVE_ACC_MAX_ITEMS = 100, WAVE_PASS_MAX = 2048;
+static const uint64_t BUCKET_WAVE_MAX = 16, BUCKET_WAVE_MAX_UNSEEN = 32;
+#else
+static const uint64_t WAVE_ACC_MAX_ITEMS = 16384;
+static const uint64_t WAVE_PASS_MAX = 110000;          /* partial sums */
+static const uint64_t BUCKET_WAVE_MAX = 64;            /* partial sums in the fullest bucket when the last pass starts */
+static const uint64_t BUCKET_WAVE_MAX_UNSEEN = 256;    /* the same where it is not known but cannot be more */
+#endif
+static const uint32_t WAVE_PASS_FANIN = 16;
 
 /* One MSM problem: result = sum_i [e(s_i)] pts[i] over n terms */
 struct MsmProblem {
@@ -1569,7 +1577,7 @@ static int msm_engine_multi(tc_ctx* ctx, int count, const MsmProblem* prob, int 
     WS(lstart, uint32_t, nbk + 1);
     WS(lstart2, uint32_t, nbk + 1);
     WS(tot_a, uint32_t, nchunks + 1);
-    WS(tot_b, uint32_t, nchunks + 1);
+    WS(tot_b, uint32_t, nchunks + 2);
     WS(tot_max, uint32_t, nchunks + 1);
     WS(sorted, uint32_t, items ? items : 1);
     WS(tables, const g1_affine*, (uint32_t)count);
@@ -1583,28 +1591,35 @@ static int msm_engine_multi(tc_ctx* ctx, int count, const MsmProblem* prob, int 
         TRY(upload_small(ctx, tables, count > 1 ? many.data() : &one, sizeof(void*) * (size_t)count));
     }
 
-    /* Lanes of the first pass: sub-runs of at most L1 entries, about twice as many as the chip holds at once
-     * (the accumulation kernel keeps 3 waves per SIMD), so that the second round evens out what the first left
-     * uneven; at least 4 and at most 64 entries each.  Measured on the 2^21-entry int16 tensor: the kernel itself
-     * is fastest with the shortest sub-runs (the first entry of a sub-run is a copy, not an addition), the later
-     * passes with the longest, and steps in flight run equally fast from 4 to 13.  Not longer than half the
-     * average bucket load either: longer sub-runs leave the lanes of a wave with very different amounts of work
-     * (measured, with the 32-bit-limb accumulation of the time, on the 64 openings of the LLaMA2-7B-shaped forward, row buckets of 16 entries on average: sub-runs
-     * of 8 and 16 entries 136 and 138 ms, of 24 and 32 entries 145 and 163 ms; on that forward's build, 101 entries
-     * per bucket: sub-runs of 50 entries and one middle pass 69.2 ms, of 64 entries and no middle pass 70.3 ms). */
-    const uint64_t target_lanes = 2 * ACC_RESIDENT_LANES;
-    uint32_t L1 = (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(4, (items + target_lanes - 1) / target_lanes));
-    /* (launches large enough to hand their sub-runs out in the order of their lengths need no such bound: with it
-     * the LLaMA2-7B-shaped step takes 126.4 ms, with sub-runs of 64 entries 125.9 ms, and no less with 80 to 128) */
-    if (ctx->static_mode || items / L1 + nbk + 1 < ORDERED_LANES_MIN)
-        L1 = (uint32_t)std::min<uint64_t>(L1, std::max<uint64_t>(4, (items + 2 * (uint64_t)nbk - 1) / (2 * (uint64_t)nbk)));
+    /* Lanes of the first pass: sub-runs of at most L1 entries, at least 4 and at most 64 each.
+     * Launches large enough to hand their sub-runs out in the order of their lengths: twice as many as the chip holds at
+     * once (the accumulation kernel keeps 3 waves per SIMD), so that the second round evens out what the first left uneven (with 64 entries the
+     * LLaMA2-7B-shaped step takes 125.9 ms, and no less with 80 to 128).
+     * Others: just as many as the chip holds at once (a bucket's last sub-run is half full on average: an eighth of the buckets for them,
+     * most being empty), as long as that is seven entries or more, since every sub-run is a sum that the passes add up (whole
+     * calls at 6 / 9 / 11 / 14 / 22 entries, int16: 2^21 terms 848 / 781 / 748 / 880 / 768 us; at 14 / 20 / 28 / 30: 5.4e6 terms 1262 / 1398 / 1234 /
+     * 1276 us); from there down seven, or four below 2.6e5 terms, where the chain of a sub-run counts (at 4 / 7 / 11: 2^18 terms 426 / 402 / 408 us,
+     * 2^16 terms 323 / 342 / 375 us).  Not longer than half the average bucket load: longer sub-runs leave the lanes of a wave
+     * with very different amounts of work. */
+    uint32_t L1 = (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(4, (items + 2 * ACC_RESIDENT_LANES - 1) / (2 * ACC_RESIDENT_LANES)));
+    if (ctx->static_mode || items / L1 + nbk + 1 < ORDERED_LANES_MIN) {
+        const uint64_t lanes = std::max<uint64_t>(ACC_RESIDENT_LANES / 2, ACC_RESIDENT_LANES - std::min<uint64_t>(nbk / 8, ACC_RESIDENT_LANES / 2));
+        const uint64_t least = std::max<uint64_t>(4, std::min<uint64_t>(7, items / 36864));
+        L1 = (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(least, (items + lanes - 1) / lanes));
+        L1 = (uint32_t)std::min<uint64_t>(L1, std::max<uint64_t>(least, (items + 2 * (uint64_t)nbk - 1) / (2 * (uint64_t)nbk)));
+    }
     if (ctx->opt[TC_OPT_ACC_SUBRUN]) L1 = (uint32_t)ctx->opt[TC_OPT_ACC_SUBRUN];
     if (ctx->static_mode) L1 = STATIC_L1;      /* fewer, longer sub-runs: the partial sums must fit the static scratch */
     /* fan-in of the middle passes: with few buckets a pass costs the chain of additions of one lane, and shorter
      * chains in more passes win (flat commitment of 2^21 terms: 2.74 / 2.70 / 2.59 / 3.08 ms with 16 / 8 / 4 / 2) */
     const uint32_t L2 = ctx->opt[TC_OPT_ACC_FANIN] && !ctx->static_mode ? (uint32_t)ctx->opt[TC_OPT_ACC_FANIN] : nbk <= ScanSmall::MAX_N ? 4 : 16;
 
-    uint32_t max_count = 0;        /* largest bucket: fixes how many shrinking passes are needed */
+    const bool wave_acc = items <= WAVE_ACC_MAX_ITEMS;
+    if (wave_acc && !ctx->opt[TC_OPT_ACC_SUBRUN] && !ctx->static_mode) L1 = 4;
+    uint32_t totals[2] = {0, 0};   /* sub-runs of the first pass and the largest bucket: which passes are needed */
+    /* where even the worst case, every term in one bucket, is a short sum, the fullest bucket is not read back (a wait for the
+     * stream in the middle of the call) */
+    const bool planned = ctx->static_mode || (wave_acc && (max_items + L1 - 1) / L1 <= BUCKET_WAVE_MAX_UNSEEN);
     if ((dtype != TC_FR && dtype != DT_FR128) || ((nbk_pp == 4096 || nbk_pp == 2176) && !ctx->static_mode)) {
         /* small scalars (one or two digits per term), and full-width scalars in 8-bit windows (4096 keys per problem):
          * tile histograms in LDS, no global atomics */
@@ -1665,7 +1680,7 @@ static int msm_engine_multi(tc_ctx* ctx, int count, const MsmProblem* prob, int 
             RT((launch_coop<CountKeys::BLOCK>(max_tiles, ctx->stream, CountKeys{packed, bin_start, bin_tiles, tile_owner, bins, sort_low, tile_keys})));
             RT(rt::launch<256>(nbk, ctx->stream, KeyColumnScan{bin_tiles, sort_low, tile_keys, cnt}));
             TRY(scan_counts(ctx, cnt, nbk, L1, start, lstart, nullptr, tot_a, tot_b, tot_max));
-            RT(rt::memcpy_d2h(&max_count, tot_max + nchunks, 4, ctx->stream));
+            if (!planned) RT(rt::memcpy_d2h(totals, tot_b + nchunks, sizeof totals, ctx->stream));
             RT((launch_coop<SortKeys::BLOCK>(max_tiles, ctx->stream, SortKeys{packed, bin_start, bin_tiles, tile_owner, bins, sort_low, tile_keys, start, sorted})));
         } else {
             WS(M, uint32_t, (uint64_t)count * n_wg * nbk_pp);
@@ -1684,7 +1699,7 @@ static int msm_engine_multi(tc_ctx* ctx, int count, const MsmProblem* prob, int 
             else return fail(ctx, TC_ERR_STATE, "internal: unsupported key count");
             RT(rt::launch<256>(nbk, ctx->stream, TileColumnScan{nbk_pp, n_wg, M, cnt}));
             TRY(scan_counts(ctx, cnt, nbk, L1, start, lstart, nullptr, tot_a, tot_b, tot_max));
-            if (!ctx->static_mode) RT(rt::memcpy_d2h(&max_count, tot_max + nchunks, 4, ctx->stream));
+            if (!planned) RT(rt::memcpy_d2h(totals, tot_b + nchunks, sizeof totals, ctx->stream));
             /* (the scatter is faster with 1024 lanes even on short tiles: 1.04 against 1.28 ms on those rows) */
             if (nbk_pp == 128) RT((launch_coop<1024>(groups, ctx->stream, ScatterTile<128>{d_prob, dtype, D, c, n_wg, M, start, sorted})));
             else if (nbk_pp == 256) RT((launch_coop<1024>(groups, ctx->stream, ScatterTile<256>{d_prob, dtype, D, c, n_wg, M, start, sorted})));
@@ -1707,100 +1722,132 @@ static int msm_engine_multi(tc_ctx* ctx, int count, const MsmProblem* prob, int 
         if (count == 1) RT(rt::launch<256>(prob[0].n, ctx->stream, j_count[0]));
         else TRY((launch_jobs<256>(ctx, j_count, n_items)));
         TRY(scan_counts(ctx, cnt, nbk, L1, start, lstart, cursor, tot_a, tot_b, tot_max));
-        RT(rt::memcpy_d2h(&max_count, tot_max + nchunks, 4, ctx->stream));
+        if (!planned) RT(rt::memcpy_d2h(totals, tot_b + nchunks, sizeof totals, ctx->stream));
         if (count == 1) RT(rt::launch<256>(prob[0].n, ctx->stream, j_scatter[0]));
         else TRY((launch_jobs<256>(ctx, j_scatter, n_items)));
     }
 
-    uint64_t max_part = items / L1 + nbk + 1;          /* upper bound on first-pass lanes */
-    WS(bufA, g1_xyzz, max_part);
-    WS(bufB, g1_xyzz, max_part / L2 + nbk + 1);
-    WS(bucket, g1_xyzz, nbk);
-    WS(wsum, g1_xyzz, (uint64_t)W * count);
+    const uint64_t max_part = std::min<uint64_t>(items ? items : 1, items / L1 + nbk + 1);          /* upper bound on first-pass lanes */
+    const auto fewer = [nbk](uint64_t sums, uint64_t fanin) { return std::min<uint64_t>(sums, sums / fanin + nbk + 1); };
+    size_t cur_bytes = (size_t)max_part * (wave_acc ? WV_POINT_WORDS * 4 : sizeof(g1_xyzz)), spare_bytes = 0;
+    /* (a call that may not allocate has room for two arrays of partial sums: the first is taken again by the second pass) */
+    if (ctx->static_mode) cur_bytes = std::max<size_t>(cur_bytes, (size_t)fewer(fewer(max_part, WAVE_PASS_FANIN), WAVE_PASS_FANIN) * WV_POINT_WORDS * 4);
+    uint8_t *cur = (uint8_t*)ws_alloc(ctx, cur_bytes), *spare = nullptr;
+    if (!cur) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
     /* lists of the lanes that a fast kernel gave up: [0] the count of the accumulation, [1 ..] which; the passes after
      * it have their counts in redo_pass and reuse the list (a pass starts when the one before is done) */
-    WS(redo, uint32_t, max_part + 1);
+    WS(redo, uint32_t, wave_acc ? 1 : max_part + 1);
     WS(redo_pass, uint32_t, MAX_ACC_PASSES);
-    RT(rt::launch<64>(1, ctx->stream, Fill32{redo, 0u}));
-    RT(rt::launch<64>(MAX_ACC_PASSES, ctx->stream, Fill32{redo_pass, 0u}));
+    if (!wave_acc) {
+        RT(rt::launch<64>(1, ctx->stream, Fill32{redo, 0u}));
+        RT(rt::launch<64>(MAX_ACC_PASSES, ctx->stream, Fill32{redo_pass, 0u}));
+    }
     /* launches with many more lanes than the chip holds hand their sub-runs out in the order of their lengths */
     uint32_t* perm = nullptr;
-    if (max_part >= ORDERED_LANES_MIN && !ctx->static_mode) TRY(order_lanes(ctx, start, lstart, nbk, max_part, &perm));
+    if (max_part >= ORDERED_LANES_MIN && !ctx->static_mode && items / nbk < ORDERED_LOAD_MAX * (uint64_t)L1) TRY(order_lanes(ctx, start, lstart, nbk, max_part, &perm));
     {
         rt::event_t e0, e1;
         prof_begin(ctx, TC_PROF_BUCKET_ACC, &e0, &e1);
+        g1_xyzz* bufA = (g1_xyzz*)cur;
         int padded = 0;
         for (int p = 0; p < count; ++p) padded += table_is_padded(prob[p].pts) ? 1 : 0;
-        if (padded == count) RT((rt::launch_waves<64, 3>(max_part, ctx->stream, AccAffine<TABLES_PADDED>{tables, nbk_pp, sorted, start, lstart, nbk, L1, bufA, redo, redo + 1, perm})));
+        if (wave_acc) RT(launch_wave_groups((uint32_t)((max_part + 3) / 4), ctx->stream, AccWave{tables, nbk_pp, sorted, start, lstart, nbk, (uint32_t*)cur}));
+        else if (padded == count) RT((rt::launch_waves<64, 3>(max_part, ctx->stream, AccAffine<TABLES_PADDED>{tables, nbk_pp, sorted, start, lstart, nbk, L1, bufA, redo, redo + 1, perm})));
         else if (padded == 0) RT((rt::launch_waves<64, 3>(max_part, ctx->stream, AccAffine<TABLES_PLAIN>{tables, nbk_pp, sorted, start, lstart, nbk, L1, bufA, redo, redo + 1, perm})));
         else RT((rt::launch_waves<64, 3>(max_part, ctx->stream, AccAffine<TABLES_MIXED>{tables, nbk_pp, sorted, start, lstart, nbk, L1, bufA, redo, redo + 1, perm})));
         prof_end(ctx, TC_PROF_BUCKET_ACC, e0, e1);
     }
     /* sub-runs with equal or opposite points in them: none in honest inputs; a degenerate input sends every sub-run
      * here, so the launch is as wide as the chip and its lanes stride over the list */
-    {
+    if (!wave_acc) {
         uint32_t redo_lanes = (uint32_t)std::min<uint64_t>(max_part, ACC_RESIDENT_LANES);
-        RT(rt::launch<64>(redo_lanes, ctx->stream, AccAffineRedo{tables, nbk_pp, sorted, start, lstart, nbk, L1, bufA, redo, redo + 1, redo_lanes}));
+        RT(rt::launch<64>(redo_lanes, ctx->stream, AccAffineRedo{tables, nbk_pp, sorted, start, lstart, nbk, L1, (g1_xyzz*)cur, redo, redo + 1, redo_lanes}));
     }
 
-    /* Middle passes shrink the per-bucket partial count by L2 until at most L2 remain. */
     uint32_t acc_terms = 0, acc_lanes = 0;             /* non-zero digits and sub-runs of the first pass (profiling only) */
-    if (ctx->profiling && !ctx->static_mode) {
+    const bool counted = ctx->profiling && !ctx->static_mode;
+    if (counted) {
         RT(rt::memcpy_d2h(&acc_terms, tot_a + nchunks, 4, ctx->stream));
         RT(rt::memcpy_d2h(&acc_lanes, tot_b + nchunks, 4, ctx->stream));
     }
-    if (ctx->static_mode) {
-        /* no wait for the stream: the passes are planned for the fullest bucket there could be, one that holds every
-         * term of the largest problem (a pass over buckets that are already down to few partial sums copies them) */
-        max_count = (uint32_t)max_items;
-    } else {
-        TRY(ctx_sync(ctx));
-    }
-    if (ctx->profiling && acc_terms >= acc_lanes) ctx->prof_units[TC_PROF_BUCKET_ACC] += acc_terms - acc_lanes;
-    if (max_count > max_items) return fail(ctx, TC_ERR_STATE, "internal: bucket count exceeds the term count");
-    uint64_t worst = ((uint64_t)max_count + L1 - 1) / L1;
-    g1_xyzz *cur = bufA, *nxt = bufB;
-    uint32_t *cur_start = lstart, *nxt_start = lstart2;
-    uint64_t lanes_bound = max_part;
-    /* (Leaving the middle passes out when the buckets outnumber the lanes the chip holds -- the last pass then
+    if (counted || !planned) TRY(ctx_sync(ctx));
+    /* no wait for the stream: the passes are planned for the fullest bucket there could be, one that holds every term of
+     * the largest problem (a pass over buckets that are already down to few partial sums copies them) */
+    const uint32_t max_count = planned ? (uint32_t)max_items : totals[1];
+    if (counted && acc_terms >= acc_lanes) ctx->prof_units[TC_PROF_BUCKET_ACC] += acc_terms - acc_lanes;
+    if (max_count > max_items || totals[0] > max_part) return fail(ctx, TC_ERR_STATE, "internal: bucket count exceeds the term count");
+
+    /* The passes over the partial sums.  As long as there are many of them a pass is a launch of lanes, fan-in L2; what is left
+     * goes by waves, first sub-runs of WAVE_PASS_FANIN where a bucket still has more than a short sum, then the buckets
+     * themselves.  Launches of many buckets (tens of problems) end by lanes too: one lane per bucket.
+     * (Leaving the lanes' passes out when the buckets outnumber the lanes the chip holds -- the last pass then
      * sums up to 64 partial sums per bucket -- was measured and is worse: its lanes diverge with the bucket loads;
      * 64 openings of the LLaMA2-7B-shaped forward 136 -> 206 ms, the build 69 -> 74 ms.) */
+    const bool by_lanes = windows_by_lanes((uint64_t)W * (uint64_t)count, nb);       /* the windows read their buckets in the 32-bit form */
+    uint64_t worst = ((uint64_t)max_count + L1 - 1) / L1, lanes_bound = planned ? max_part : std::max<uint64_t>(1, totals[0]);
+    uint32_t *cur_start = lstart, *nxt_start = lstart2;
+    bool raw = wave_acc;
     uint32_t pass = 0;
-    while (worst > L2) {
+    const auto spare_room = [&](size_t bytes) {
+        if (spare_bytes >= bytes) return true;
+        spare = (uint8_t*)ws_alloc(ctx, bytes);
+        spare_bytes = bytes;
+        return spare != nullptr;
+    };
+    const auto next_pass = [&](uint64_t fanin) {
+        std::swap(cur, spare);
+        std::swap(cur_bytes, spare_bytes);
+        std::swap(cur_start, nxt_start);
+        worst = (worst + fanin - 1) / fanin;
+    };
+    const uint64_t by_waves = nbk >= FAST_PASS_LANES ? 2 * WAVE_PASS_MAX : WAVE_PASS_MAX;
+    const bool final_lanes = !raw && nbk >= FAST_PASS_LANES && (nbk >= ORDERED_LANES_MIN || lanes_bound > by_waves) && !ctx->static_mode;
+    while (final_lanes ? worst > L2 : !raw && lanes_bound > by_waves && worst > 1 && !ctx->static_mode) {
         /* counts of this pass = number of partials per bucket = differences of cur_start */
         RT(rt::launch<256>(nbk, ctx->stream, DiffCounts{cur_start, cnt}));
         TRY(scan_counts(ctx, cnt, nbk, L2, start, nxt_start, nullptr, tot_a, tot_b, tot_max));
         /* `start` now equals cur_start (prefix of the same counts) */
-        lanes_bound = lanes_bound / L2 + nbk + 1;
+        lanes_bound = fewer(lanes_bound, L2);
+        if (!spare_room((size_t)lanes_bound * sizeof(g1_xyzz))) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
         if (lanes_bound >= FAST_PASS_LANES && pass + 1 < MAX_ACC_PASSES) {
             uint32_t redo_lanes = (uint32_t)std::min<uint64_t>(lanes_bound, ACC_RESIDENT_LANES);
             uint32_t* pperm = nullptr;
-            if (lanes_bound >= ORDERED_LANES_MIN && !ctx->static_mode) TRY(order_lanes(ctx, cur_start, nxt_start, nbk, lanes_bound, &pperm));
-            RT((rt::launch_waves<64, 2>(lanes_bound, ctx->stream, AccXyzzFast{cur, cur_start, nxt_start, nbk, L2, nxt, redo_pass + pass, redo + 1, false, pperm})));
-            RT(rt::launch<64>(redo_lanes, ctx->stream, AccXyzzRedo{cur, cur_start, nxt_start, nbk, L2, nxt, redo_pass + pass, redo + 1, false, redo_lanes}));
-            ++pass;
+            if (lanes_bound >= ORDERED_LANES_MIN) TRY(order_lanes(ctx, cur_start, nxt_start, nbk, lanes_bound, &pperm));
+            RT((rt::launch_waves<64, 2>(lanes_bound, ctx->stream, AccXyzzFast{(g1_xyzz*)cur, cur_start, nxt_start, nbk, L2, (g1_xyzz*)spare, redo_pass + pass, redo + 1, false, pperm})));
+            RT(rt::launch<64>(redo_lanes, ctx->stream, AccXyzzRedo{(g1_xyzz*)cur, cur_start, nxt_start, nbk, L2, (g1_xyzz*)spare, redo_pass + pass, redo + 1, false, redo_lanes}));
         } else {
-            RT(rt::launch<64>(lanes_bound, ctx->stream, AccXyzz{cur, cur_start, nxt_start, nbk, L2, nxt}));
+            RT(rt::launch<64>(lanes_bound, ctx->stream, AccXyzz{(g1_xyzz*)cur, cur_start, nxt_start, nbk, L2, (g1_xyzz*)spare}));
         }
-        std::swap(cur, nxt);
-        std::swap(cur_start, nxt_start);
-        worst = (worst + L2 - 1) / L2;
+        ++pass;
+        next_pass(L2);
     }
-    if (nbk >= FAST_PASS_LANES && nbk <= max_part) {
+    if (final_lanes) {
+        WS(bucket, g1_xyzz, nbk);
         uint32_t redo_lanes = (uint32_t)std::min<uint64_t>(nbk, ACC_RESIDENT_LANES);
-        uint32_t* count = redo_pass + (MAX_ACC_PASSES - 1);
+        uint32_t* given_up = redo_pass + (MAX_ACC_PASSES - 1);
         uint32_t* pperm = nullptr;
         /* (after a middle pass nearly every bucket is down to one sum and the order is not worth its three launches) */
-        if (nbk >= ORDERED_LANES_MIN && !ctx->static_mode && pass == 0) TRY(order_lanes(ctx, cur_start, nullptr, nbk, nbk, &pperm));
-        RT((rt::launch_waves<64, 2>(nbk, ctx->stream, AccXyzzFast{cur, cur_start, nullptr, nbk, 0, bucket, count, redo + 1, true, pperm})));
-        RT(rt::launch<64>(redo_lanes, ctx->stream, AccXyzzRedo{cur, cur_start, nullptr, nbk, 0, bucket, count, redo + 1, true, redo_lanes}));
-    } else {
-        RT(rt::launch<64>(nbk, ctx->stream, AccFinal{cur, cur_start, bucket}));
+        if (nbk >= ORDERED_LANES_MIN && pass == 0) TRY(order_lanes(ctx, cur_start, nullptr, nbk, nbk, &pperm));
+        RT((rt::launch_waves<64, 2>(nbk, ctx->stream, AccXyzzFast{(g1_xyzz*)cur, cur_start, nullptr, nbk, 0, bucket, given_up, redo + 1, true, pperm})));
+        RT(rt::launch<64>(redo_lanes, ctx->stream, AccXyzzRedo{(g1_xyzz*)cur, cur_start, nullptr, nbk, 0, bucket, given_up, redo + 1, true, redo_lanes}));
+        return reduce_windows(ctx, WavePoints{bucket, 0u}, count, W, c, nb, results);
     }
-
-    TRY(reduce_windows(ctx, bucket, W * count, nb, wsum));
-    RT(rt::launch<64>((uint32_t)count, ctx->stream, WindowCombine{wsum, W, c, results}));
-    return TC_OK;
+    while (worst > (planned && !ctx->static_mode ? BUCKET_WAVE_MAX_UNSEEN : BUCKET_WAVE_MAX)) {
+        RT(rt::launch<256>(nbk, ctx->stream, DiffCounts{cur_start, cnt}));
+        TRY(scan_counts(ctx, cnt, nbk, WAVE_PASS_FANIN, start, nxt_start, nullptr, tot_a, tot_b, tot_max));
+        lanes_bound = fewer(lanes_bound, WAVE_PASS_FANIN);
+        if (!spare_room((size_t)lanes_bound * WV_POINT_WORDS * 4)) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
+        RT(launch_wave_groups((uint32_t)((lanes_bound + 3) / 4), ctx->stream, PassWave{WavePoints{cur, raw}, cur_start, nxt_start, nbk, (uint32_t*)spare}));
+        raw = true;
+        next_pass(WAVE_PASS_FANIN);
+    }
+    uint8_t* bucket = (uint8_t*)ws_alloc(ctx, (size_t)nbk * (by_lanes ? sizeof(g1_xyzz) : WV_POINT_WORDS * 4));
+    if (!bucket) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
+    uint32_t* to_raw = by_lanes ? nullptr : (uint32_t*)bucket;
+    const WavePoints parts{cur, raw ? 1u : 0u};
+    if (worst > 16) RT(launch_wave_groups(nbk, ctx->stream, BucketWave<4>{parts, cur_start, nbk, to_raw, (g1_xyzz*)bucket}));
+    else RT(launch_wave_groups((nbk + 3u) / 4u, ctx->stream, BucketWave<1>{parts, cur_start, nbk, to_raw, (g1_xyzz*)bucket}));
+    return reduce_windows(ctx, WavePoints{bucket, by_lanes ? 0u : 1u}, count, W, c, nb, results);
 }
 
 /* result[0] = sum_i [e(s_i)] pts[i] */

@@ -45,19 +45,19 @@ struct wv_consts {
 };
 
 #if defined(__HIPCC__)
-#define WV_LANES(expr)                                            \
+#define WV_LANES(...) \
     {                                                             \
         const uint32_t lane = threadIdx.x & 63u;                  \
         (void)lane;                                               \
-        expr;                                                     \
+        __VA_ARGS__;                                                \
     }
 #define WV_AT(x) (x).l
 /* true in the one lane that writes what the whole wave has worked out */
 TC_DEV bool wv_first_lane() { return (threadIdx.x & 63u) == 0u; }
 #else
-#define WV_LANES(expr)                                            \
+#define WV_LANES(...) \
     for (uint32_t lane = 0; lane < 64u; ++lane) {                 \
-        expr;                                                     \
+        __VA_ARGS__;                                                \
     }
 #define WV_AT(x) (x).l[lane]
 inline bool wv_first_lane() { return true; }
@@ -208,6 +208,17 @@ TC_DEV wv wv_sub(const wv_consts& k, const wv& a, const wv& b) {
     WV_LANES(WV_AT(r) = WV_AT(a) + (WV_AT(k.p128) - WV_AT(b)))
     return wv_carry(r);
 }
+/* one bit per lane of the wave */
+template <class Each>
+TC_DEV uint64_t wv_ballot(const Each& each) {
+#if defined(__HIPCC__)
+    return __ballot(each(threadIdx.x & 63u));
+#else
+    uint64_t bits = 0;
+    for (uint32_t lane = 0; lane < 64u; ++lane) bits |= (uint64_t)(each(lane) ? 1 : 0) << lane;
+    return bits;
+#endif
+}
 /* does row 0 of x (below 256 p, normal limbs) stand for zero?  A multiple of p is told from its lowest limb but for some
  * 2^-20 of the other values; then the limbs are looked at one by one. */
 TC_DEV bool wv_is_zero(const wv& x) {
@@ -310,16 +321,57 @@ TC_DEV wv_point wv_load_canonical(const wv_consts& k, const uint32_t* w) {
     r.v = wv_mul(k, r.v, wv_pick(plain, plain, one, one));
     return r;
 }
-/* the form itself, 64 words (points on their way from one wave to another); ZZ = 0 says identity */
+/* The form itself, 64 words, for points on their way from one wave to another: word 63 (the last lane of ZZZ's row, no limb) is 1 for a
+ * finite point and 0 for the identity. */
+constexpr uint32_t WV_POINT_WORDS = 64, WV_FINITE = 63;
 TC_DEV void wv_store_raw(uint32_t* to, const wv_point& p) {
-    WV_LANES(to[lane] = p.inf ? 0u : WV_AT(p.v))
+    WV_LANES(to[lane] = p.inf ? 0u : lane == WV_FINITE ? 1u : WV_AT(p.v))
 }
-TC_DEV wv_point wv_load_raw(const uint32_t* from) {
+TC_DEV wv_point wv_from_raw(const wv& words) {
     wv_point r;
-    WV_LANES(WV_AT(r.v) = from[lane])
-    r.inf = !wv_row_any(r.v, 2);
+    r.inf = wv_read(words, WV_FINITE) == 0u;
+    WV_LANES(WV_AT(r.v) = lane == WV_FINITE ? 0u : WV_AT(words))
     return r;
 }
+TC_DEV wv_point wv_load_raw(const uint32_t* from) {
+    wv w;
+    WV_LANES(WV_AT(w) = from[lane])
+    return wv_from_raw(w);
+}
+/* An array of points, raw or in the 32-bit form.  A point is fetched (one or two words a lane) while the one before is being
+ * added, and unpacked when its turn comes. */
+struct wv_words {
+    wv a, b;
+};
+struct WavePoints {
+    const void* base;
+    uint32_t raw;
+    TC_DEV wv_words fetch(uint64_t i) const {
+        wv_words w;
+        if (raw) {
+            const uint32_t* p = (const uint32_t*)base + i * WV_POINT_WORDS;
+            WV_LANES(WV_AT(w.a) = p[lane]; WV_AT(w.b) = 0u)
+        } else {
+            const uint32_t* p = (const uint32_t*)((const g1_xyzz*)base + i);
+            WV_LANES(const uint32_t o = 28u * (lane & 15u) + 24u; const uint32_t at = (o >> 5) < 12u ? o >> 5 : 12u; const uint32_t* c = p + 12u * (lane >> 4);
+                     WV_AT(w.a) = at ? c[at - 1u] : 0u; WV_AT(w.b) = at < 12u ? c[at] : 0u)
+        }
+        return w;
+    }
+    TC_DEV wv_point unpack(const wv_words& w) const {
+        if (raw) return wv_from_raw(w.a);
+        wv_point r;
+        WV_LANES(const uint32_t sh = (28u * (lane & 15u) + 24u) & 31u;
+                 WV_AT(r.v) = (lane & 15u) < 14u ? (uint32_t)((((uint64_t)WV_AT(w.b) << 32) | WV_AT(w.a)) >> sh) & (uint32_t)FP28_MASK : 0u)
+        r.inf = !wv_row_any(r.v, 2);
+        return r;
+    }
+    TC_DEV wv_point load(uint64_t i) const { return unpack(fetch(i)); }
+    /* by a lane of its own */
+    TC_DEV bool empty(uint64_t i) const {
+        return raw ? ((const uint32_t*)base)[i * WV_POINT_WORDS + WV_FINITE] == 0u : fe_is_zero(((const g1_xyzz*)base)[i].ZZ);
+    }
+};
 /* all limbs of a lane's row */
 TC_DEV fp28 wv_row_limbs(const wv& x, uint32_t lane) {
     fp28 v;

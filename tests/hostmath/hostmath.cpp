@@ -26,6 +26,13 @@ static void coop_run(const K& k, uint32_t groups) {
         for (int ph = 0; ph < K::PHASES; ++ph)
             for (uint32_t lane = 0; lane < (uint32_t)K::BLOCK; ++lane) k.phase(ph, lane, g, lds.data());
 }
+template <class K>
+static void wave_run(const K& k, uint32_t groups) {
+    std::vector<uint8_t> lds(K::LDS_BYTES);
+    for (uint32_t g = 0; g < groups; ++g)
+        for (int ph = 0; ph < K::PHASES; ++ph)
+            for (uint32_t wave = 0; wave < (uint32_t)K::WAVES; ++wave) k.phase(ph, wave, g, lds.data());
+}
 
 extern "C" {
 void hm_fp_mul(const uint8_t* a, const uint8_t* b, uint8_t* o) { fp_store(o, fp_mul(fp_load(a), fp_load(b))); }
@@ -90,15 +97,17 @@ void hm_coop_reduce(const uint8_t* pts, uint32_t n, int spread, uint8_t* o) {
 // sum_k k B_k of windows of 2^lognb buckets bit by bit: the sums per bit, their place values, the total
 void hm_window_bits(const uint8_t* pts, uint32_t lognb, uint32_t windows, uint8_t* o) {
     const uint32_t chains = lognb + 1, n = chains * windows;
-    std::vector<g1_xyzz> bucket((size_t)windows << lognb), bits(n), scaled(n), sum(windows);
+    std::vector<g1_xyzz> bucket((size_t)windows << lognb), sum(windows);
     for (size_t i = 0; i < bucket.size(); ++i) {
         g1_affine a = pt_load(pts + 96 * i);
         bucket[i] = i % 2 ? xyzz_madd(xyzz_dbl_affine(a), affine_neg(a)) : xyzz_from_affine(a);
     }
-    coop_run(CoopReduce<SmallBitSumSrc>{SmallBitSumSrc{bucket.data(), lognb, bits.data()}}, n);
-    if (lognb == 7) coop_run(BitSumScale<8>{bits.data(), n, scaled.data()}, (n + 63) / 64);
-    else coop_run(BitSumScale<9>{bits.data(), n, scaled.data()}, (n + 63) / 64);
-    coop_run(CoopReduce<GroupSumSrc>{GroupSumSrc{scaled.data(), chains, sum.data()}}, windows);
+    std::vector<uint32_t> pieces((size_t)n * BITSUM_PARTS * WV_POINT_WORDS);
+    const WavePoints in{bucket.data(), 0u};
+    std::vector<uint32_t> scaled((size_t)n * WV_POINT_WORDS);
+    wave_run(BitSumWave{in, in, 1u << lognb, 1u << lognb, 0u, 0u, lognb, pieces.data()}, n * BITSUM_PARTS);
+    wave_run(ScaleWave{pieces.data(), lognb, scaled.data()}, n);
+    wave_run(WindowWave{scaled.data(), chains, nullptr, sum.data()}, windows);
     for (uint32_t w = 0; w < windows; ++w) pt_store(o + 96 * (size_t)w, xyzz_to_affine(sum[w]));
 }
 // the form spread over lanes: a product of raw limbs (14 words each, four rows), and sums and doublings of points

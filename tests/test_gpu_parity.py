@@ -252,6 +252,26 @@ def test_degenerate_bucket_loads_at_size(T, ctx):
         srs.close()
 
 
+@pytest.mark.parametrize("n", [1, 3, 1023, 1025, 16384, 16385, 36863, 110592])
+@pytest.mark.parametrize("dtype", ["i8", "i16"])
+def test_commit_where_waves_take_over_from_lanes(T, ctx, n, dtype):
+    """Lengths on both sides of the lines between sums by waves and by lanes (16384 entries accumulated by waves; at four to
+    a sub-run 1024 entries are the most whose fullest bucket is not read back), with random entries, all of them in one
+    bucket (the passes over its partial sums), in two that cancel, and one entry alone; 1 and 2 problems a call."""
+    pp = pps((n,))
+    srs = ctx.setup_from_trapdoor(TAU_BYTES, (n,), 0)
+    try:
+        lim, np_t, code = (127, np.int8, T.TC_I8) if dtype == "i8" else (32767, np.int16, T.TC_I16)
+        rng = np.random.default_rng(n)
+        tensors = [rng.integers(-lim - 1, lim + 1, size=n), np.full(n, -lim - 1), np.where(np.arange(n) % 2, 5, -5), (np.arange(n) == n - 1) * lim]
+        tensors = [t.astype(np_t) for t in tensors]
+        want = [ec.g1_to_bytes(cbind.commit(pp, t, nthreads=8)) for t in tensors]
+        assert [ctx.commit(srs, to_device(t), code) for t in tensors] == want
+        assert ctx.commit_batch([srs, srs], [to_device(t) for t in tensors[:2]], [code] * 2) == want[:2]
+    finally:
+        srs.close()
+
+
 def test_degenerate_bucket_loads_in_ordered_launches(T, ctx):
     """The same at 2^26 entries, where the accumulation hands its sub-runs out in the order of their lengths: a
     constant tensor (one bucket with a million sub-runs, all placed by one workgroup), and a tensor whose upper half is
