@@ -398,9 +398,7 @@ TC_HD g1_affine affine_from_canonical(const uint32_t in[24]) {
  * (the paper leaves it open): phi(O) = 0, phi(C) = (2 x + s(y)) mod r on the
  * canonical affine coordinates, s(y) = 1 iff y > (p-1)/2.  Returns the plain
  * (non-Montgomery) value. */
-TC_HD fr_t phi_map(const g1_affine& c) {
-    if (affine_is_identity(c)) return fe_zero<FrParams>();
-    fp_t x = fe_to_plain(c.x), y = fe_to_plain(c.y);
+TC_HD fr_t phi_plain(const fp_t& x, const fp_t& y) {          /* of a finite point, plain coordinates */
     uint32_t s = limbs_gt<12>(y.l, FpParams::HALF) ? 1u : 0u;
     uint32_t v[13];
     uint32_t carry = s;
@@ -417,6 +415,10 @@ TC_HD fr_t phi_map(const g1_affine& c) {
     for (int i = 0; i < 8; ++i) { lo.l[i] = v[i]; hi.l[i] = (i < 4) ? v[8 + i] : 0u; r2.l[i] = FrParams::R2[i]; r3.l[i] = FrParams::R3[i]; }
     fr_t m = fr_add(fr_mul(lo, r2), fr_mul(hi, r3));
     return fe_to_plain(m);
+}
+TC_HD fr_t phi_map(const g1_affine& c) {
+    if (affine_is_identity(c)) return fe_zero<FrParams>();
+    return phi_plain(fe_to_plain(c.x), fe_to_plain(c.y));
 }
 
 }  // namespace tc

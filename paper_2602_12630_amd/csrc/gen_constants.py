@@ -166,6 +166,7 @@ def wave28():
         ("512 p in raised limbs", spread(512)),
         ("2^392 mod p", [((1 << 392) % P_MOD >> (28 * i)) & 0xFFFFFFF for i in range(14)]),
         ("2^776 mod p: plain value moved up by 8 bits -> the form", [(pow(2, 776, P_MOD) >> (28 * i)) & 0xFFFFFFF for i in range(14)]),
+        ("2^8: the form -> plain value moved up by 8 bits", [256] + [0] * 13),
         ("beta 2^392 mod p", [(endomorphism()[1] * (1 << 392) % P_MOD >> (28 * i)) & 0xFFFFFFF for i in range(14)]),
     ]
     out = ["#define TC_WAVE28_ROWS \\"]

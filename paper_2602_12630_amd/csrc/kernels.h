@@ -1884,7 +1884,7 @@ struct WindowWave {
         const wv_consts k = wv_constants();
         if (ph == 0) {
             wv_point acc = wv_identity();
-            wave_add_run(k, acc, WavePoints{scaled + (uint64_t)w * chains * WV_POINT_WORDS, 1u}, wave, chains, WAVES);
+            wave_add_run(k, acc, WavePoints{scaled + (uint64_t)w * chains * WV_POINT_WORDS, WAVE_RAW}, wave, chains, WAVES);
             wv_store_raw(lds + wave * WV_POINT_WORDS, acc);
             return;
         }
@@ -2164,6 +2164,68 @@ struct BatchNormalize {
         }
     }
 };
+/* Few points: a workgroup of WAVES waves per point, the sum of `group` consecutive ones of `in` (the pieces of a sum that other waves have
+ * left), each with an inversion of its own by its first wave.  Bound by the inversion: one to 512 points 36 to 42 us, 45 to 65
+ * where up to 64 of them shared one (BatchNormalize). */
+template <int WAVES_>
+struct NormalizeWave {
+    static constexpr int WAVES = WAVES_;
+    static constexpr int LEVELS = WAVES == 8 ? 3 : 0;
+    static constexpr int PHASES = 1 + LEVELS + 2;
+    static constexpr size_t LDS_BYTES = WAVES * WV_POINT_WORDS * 4;
+    static_assert(WAVES == 1 || WAVES == 8, "levels of the pairwise sum");
+    WavePoints in;
+    uint32_t group;
+    g1_affine* out;
+    fr_plain* phi;          /* or null */
+    uint32_t* canonical;    /* 24 words per point, or null */
+    TC_DEV void phase(int ph, uint32_t wave, uint32_t g, uint8_t* bytes) const {
+        uint32_t* lds = (uint32_t*)bytes;
+        const wv_consts k = wv_constants();
+        if (ph == 0) {
+            wv_point acc = wv_identity();
+            for (uint64_t i = wave; i < group; i += WAVES) wv_accumulate(k, acc, in.load((uint64_t)g * group + i));
+            wv_store_raw(lds + wave * WV_POINT_WORDS, acc);
+            return;
+        }
+        if (ph <= LEVELS) {
+            wave_pair_level(k, lds, wave, WAVES, ph - 1);
+            return;
+        }
+        if (wave) return;
+        if (ph == LEVELS + 1) {
+            const wv_point p = wv_load_raw(lds);
+            if (!wv_first_lane_rows(p.inf, out + g)) {
+                const wv xy = wv_to_affine(k, p.v);
+                const wv plain = wv_mul(k, xy, wv_table(W28_TO_PLAIN));
+                /* words 0 .. 23 of the LDS: the plain coordinates, for the lane that computes phi; word 63 stays: finite */
+                WV_LANES(const uint32_t row = lane >> 4; fp28 a = wv_row_limbs(xy, lane); fp28 b = wv_row_limbs(plain, lane);
+                         if ((lane & 15u) == 0u && row < 2u) {
+                             (&out[g].x)[row] = fp28_to_fp(a);
+                             ((fp_t*)lds)[row] = fp28_to_fp(b);
+                         })
+            }
+            return;
+        }
+        if (!wv_first_lane()) return;
+        const bool finite = lds[WV_FINITE] != 0u;
+        const fp_t x = finite ? ((const fp_t*)lds)[0] : fe_zero<FpParams>(), y = finite ? ((const fp_t*)lds)[1] : fe_zero<FpParams>();
+        if (canonical) {
+#pragma unroll
+            for (int i = 0; i < 12; ++i) { canonical[24ull * g + i] = x.l[i]; canonical[24ull * g + 12 + i] = y.l[i]; }
+        }
+        if (phi) {
+            const fr_t v = finite ? phi_plain(x, y) : fe_zero<FrParams>();
+#pragma unroll
+            for (int i = 0; i < 8; ++i) phi[g].l[i] = v.l[i];
+        }
+    }
+    /* the identity is written as such */
+    TC_DEV static bool wv_first_lane_rows(bool inf, g1_affine* to) {
+        if (inf && wv_first_lane()) *to = affine_identity();
+        return inf;
+    }
+};
 struct ToCanonical {
     const g1_affine* in;
     uint32_t* out;          /* 24 words per point */
@@ -2232,26 +2294,6 @@ TC_HD void fb_mul_accumulate(xyzz_acc& acc, const g1_affine* table, uint32_t k, 
         int32_t d = fr_window_digit(v, w, FB_C, carry);
         if (d) acc_madd(acc, table[((uint64_t)k * FB_W + w) * FB_NB + (uint32_t)(d < 0 ? -d : d) - 1u], d < 0);
     }
-}
-/* windows 2h and 2h + 1 only: digit_{2h}(v) table[(k, 2h)] + digit_{2h+1}(v) table[(k, 2h + 1)].  The digits are
- * found first (their carries come from the windows below), so that the two additions sit outside any loop
- * whose length differs between the lanes of a wave. */
-TC_HD g1_xyzz fb_window_pair(const g1_affine* table, uint32_t k, const uint32_t* v, uint32_t h) {
-    uint32_t carry = 0;
-    int32_t d0 = 0, d1 = 0;
-    for (int w = 0; w <= (int)(2 * h + 1); ++w) {
-        int32_t d = fr_window_digit(v, w, FB_C, carry);
-        if (w == (int)(2 * h)) d0 = d;
-        if (w == (int)(2 * h + 1)) d1 = d;
-    }
-    xyzz_acc acc = acc_identity();
-    for (int j = 0; j < 2; ++j) {
-        int32_t d = j ? d1 : d0;
-        g1_affine p = affine_identity();
-        if (d) p = table[((uint64_t)k * FB_W + 2 * h + j) * FB_NB + (uint32_t)(d < 0 ? -d : d) - 1u];
-        acc_madd(acc, p, d < 0);
-    }
-    return acc_result(acc);
 }
 /* same for a small signed integer |d| <= 2^15 (one lookup when the window is 16 bits wide) */
 TC_HD void fb_small_accumulate(xyzz_acc& acc, const g1_affine* table, uint32_t k, int32_t d) {
@@ -2366,23 +2408,76 @@ struct NodeCommitSmall {
         out[a] = acc_result(acc);
     }
 };
-/* the same for a bottom level of very few nodes: every child its own slot of a cooperative sum */
-struct NodeSmallSrc {
-    TreeGeom g;
-    const void* payload;
-    int dtype;
-    const g1_affine* table;
-    g1_xyzz* out;
-    TC_DEV uint32_t count(uint32_t) const { return g.B < 256u ? g.B : 256u; }
-    TC_DEV g1_xyzz load(uint32_t node, uint32_t i) const {
-        xyzz_acc acc = acc_identity();
-        for (uint32_t k = i; k < g.B; k += 256) {
-            int64_t f = child_index(g, node, k);
-            if (f >= 0) fb_small_accumulate(acc, table, k, small_scalar(payload, dtype, (uint64_t)f));
+/* Levels of few nodes: a node is the sum of the table points of its children's digits (an entry's one or two, or the FB_W of phi of
+ * the commitment below), NODE_WAVE_POINTS of them to a workgroup of eight waves, which leave `pieces` raw sums a node; NormalizeWave adds
+ * those up.  32 nodes of 256 points 20 us, one node 19, where cooperative sums of lane-wide products took 111 and 106. */
+constexpr uint32_t NODE_WAVE_POINTS = 32;
+constexpr uint32_t FB_SMALL_W = FB_C == 16 ? 1u : 24u / FB_C;            /* windows of an entry: 16 bits and a sign */
+TC_HD uint32_t node_wave_windows(bool bottom) { return bottom ? FB_SMALL_W : (uint32_t)FB_W; }
+/* acc += sum over `per` windows from w0 on of the digits (digit(w, carry), negated where `flip`) times base `base` */
+template <class Digit>
+TC_DEV void wave_add_windows(const wv_consts& k, wv_point& acc, const g1_affine* table, uint32_t base, const Digit& digit, uint32_t w0, uint32_t per, bool flip) {
+    const WavePoints pts{table, WAVE_AFFINE};
+    uint32_t carry = 0;
+    for (uint32_t w = 0; w < w0; ++w) (void)digit((int)w, carry);
+    wv_words held{};
+    bool have = false, held_neg = false;
+    for (uint32_t w = w0; w <= w0 + per; ++w) {
+        const int32_t d = w < w0 + per ? digit((int)w, carry) : 0;
+        wv_words next{};
+        if (d) next = pts.fetch(((uint64_t)base * FB_W + w) * FB_NB + (uint32_t)(d < 0 ? -d : d) - 1u);
+        if (have && (d || w == w0 + per)) {
+            wv_point p = pts.unpack(held);
+            if (held_neg) p.v = wv_negate(p.v);
+            wv_accumulate(k, acc, p);
+            have = false;
         }
-        return acc_result(acc);
+        if (d) {
+            held = next;
+            held_neg = (d < 0) != flip;
+            have = true;
+        }
     }
-    TC_DEV void store(uint32_t node, const g1_xyzz& r) const { out[node] = r; }
+}
+struct NodeTermsWave {
+    static constexpr int WAVES = 8;
+    static constexpr int PHASES = 4;
+    static constexpr size_t LDS_BYTES = WAVES * WV_POINT_WORDS * 4;
+    TreeGeom g;
+    const void* payload;        /* bottom level, or null */
+    int dtype;
+    const fr_plain* below;
+    const g1_affine* table;
+    uint32_t pieces;
+    uint32_t* out;              /* raw: nodes * pieces */
+    TC_DEV void phase(int ph, uint32_t wave, uint32_t wg, uint8_t* bytes) const {
+        uint32_t* lds = (uint32_t*)bytes;
+        const wv_consts k = wv_constants();
+        if (ph == 0) {
+            const uint32_t node = wg / pieces, windows = node_wave_windows(payload != nullptr), points = g.B * windows;
+            const uint32_t first = wg % pieces * NODE_WAVE_POINTS + wave * 4u, end = first + 4u < points ? first + 4u : points;
+            wv_point acc = wv_identity();
+            for (uint32_t i = first; i < end;) {                     /* child by child */
+                const uint32_t c = i / windows, w0 = i % windows, here = end - i < windows - w0 ? end - i : windows - w0;
+                const int64_t f = child_index(g, node, c);
+                if (f >= 0) {
+                    if (payload) {
+                        const int32_t x = small_scalar(payload, dtype, (uint64_t)f);
+                        const uint32_t mag = (uint32_t)(x < 0 ? -x : x);
+                        wave_add_windows(k, acc, table, c, [=](int w, uint32_t& carry) { return small_window_digit(mag, w, FB_C, carry); }, w0, here, x < 0);
+                    } else {
+                        const uint32_t* v = below[f].l;
+                        wave_add_windows(k, acc, table, c, [=](int w, uint32_t& carry) { return fr_window_digit(v, w, FB_C, carry); }, w0, here, false);
+                    }
+                }
+                i += here;
+            }
+            wv_store_raw(lds + wave * WV_POINT_WORDS, acc);
+            return;
+        }
+        wave_pair_level(k, lds, wave, WAVES, ph - 1);
+        if (ph == 3 && wave == 0) wv_store_raw(out + (uint64_t)wg * WV_POINT_WORDS, wv_load_raw(lds));
+    }
 };
 /* upper levels: lane = (node, child); the child's value is phi of the commitment below */
 struct NodeCommitFr {
@@ -2493,25 +2588,6 @@ struct SumGroups {
         out[t] = acc_result(acc);
     }
 };
-/* out[t] = sum of segment t of `in`: the elements in[off[t] * scale .. off[t + 1] * scale) */
-struct SegmentSrc {
-    const g1_xyzz* in;
-    const uint32_t* off;
-    uint32_t scale;
-    g1_xyzz* out;
-    TC_DEV uint32_t count(uint32_t t) const {
-        uint64_t len = (uint64_t)(off[t + 1] - off[t]) * scale;
-        return len < 256 ? (uint32_t)len : 256u;
-    }
-    TC_DEV g1_xyzz load(uint32_t t, uint32_t i) const {
-        uint64_t lo = (uint64_t)off[t] * scale, hi = (uint64_t)off[t + 1] * scale;
-        g1_xyzz acc = in[lo + i];
-        for (uint64_t x = lo + i + 256; x < hi; x += 256) acc = xyzz_add32(acc, in[x]);
-        return acc;
-    }
-    TC_DEV void store(uint32_t t, const g1_xyzz& r) const { out[t] = r; }
-};
-
 /* ---- Open: quotient values on the grid (Algorithm 1 in evaluation form) ----------------- */
 /* Along one axis of length d with the opening at position kap, for every line t of the slice:
  *   q[k] = (g[k] - g[kap]) / (zeta_k - zeta_kap)            k != kap
@@ -2792,7 +2868,6 @@ struct NodeOpenJob {           /* one (path, level) */
     uint64_t node;             /* flat node index in the level grid */
     uint32_t kappa[4];         /* child multi-index */
     int level;                 /* 0 = bottom (children are payload entries) */
-    uint32_t term0;            /* first output slot of this job */
 };
 struct LevelView {             /* what a node's children are */
     TreeGeom g;
@@ -2801,16 +2876,14 @@ struct LevelView {             /* what a node's children are */
     const fr_plain* below;     /* upper levels: phi values of the level below */
 };
 constexpr int MAX_LEVELS = 16;
-struct NodeOpenTerms {         /* lane (job, axis, term, window pair): two windows of one quotient value times its suffix-SRS point */
+struct NodeOpenTerms {         /* lane (job, axis, term): the quotient value of one term */
     const NodeOpenJob* jobs;
     LevelView lv[MAX_LEVELS];
     ShapeInfo node;            /* node shape */
     uint32_t terms_per_job;    /* sum_a prod_{j>=a} d_j */
     uint32_t axis_first[5];    /* first term of axis a within a job */
     AxisTables ax[4];
-    const g1_affine* table[4]; /* fixed-base tables of S^(a) */
-    int logH;                  /* log2(FB_W / 2) window pairs per term */
-    g1_xyzz* out;              /* jobs * terms_per_job << logH */
+    fr_plain* out;             /* jobs * terms_per_job */
     fr_plain* y_out;           /* per job: the opened value */
 
     TC_DEV fr_t child_value(const LevelView& v, uint64_t a, const uint32_t* k) const {
@@ -2822,8 +2895,7 @@ struct NodeOpenTerms {         /* lane (job, axis, term, window pair): two windo
         return fe_from_limbs<FrParams>(v.below[f].l);
     }
     TC_DEV void operator()(uint32_t lane) const {
-        uint32_t h = lane & ((1u << logH) - 1u);
-        uint32_t job = (lane >> logH) / terms_per_job, term = (lane >> logH) % terms_per_job;
+        uint32_t job = lane / terms_per_job, term = lane % terms_per_job;
         const NodeOpenJob& J = jobs[job];
         const LevelView& v = lv[J.level];
         int a = 0;
@@ -2856,12 +2928,52 @@ struct NodeOpenTerms {         /* lane (job, axis, term, window pair): two windo
             qv = fr_neg(fr_mul(acc, ax[a].beta_inv[kap]));
         }
         fr_t plain = fe_to_plain(qv);
-        out[(((uint64_t)J.term0 + term) << logH) + h] = fb_window_pair(table[a], local, plain.l, h);
-        if (term == 0 && h == 0) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) out[lane].l[i] = plain.l[i];
+        if (term == 0) {
             fr_t y = fe_to_plain(child_value(v, J.node, J.kappa));
 #pragma unroll
             for (int i = 0; i < 8; ++i) y_out[job].l[i] = y.l[i];
         }
+    }
+};
+
+/* The proof elements of node tensors: workgroup (job, axis, piece), eight waves of `per` windows (4 or 8) of quotient values times their
+ * suffix-SRS points each; `pieces` raw sums to a proof element, which NormalizeWave adds up.  Four windows as long as that leaves two workgroups
+ * to a compute unit at most eight, for the shorter chain: 48 jobs 33 us, 41 with eight
+ * windows; lanes that added two windows each and cooperative sums of those took 138. */
+constexpr uint32_t OPEN_WAVES_SHORT = 2048;             /* workgroups */
+struct NodeOpenWave {
+    static constexpr int WAVES = 8;
+    static constexpr int PHASES = 4;
+    static constexpr size_t LDS_BYTES = WAVES * WV_POINT_WORDS * 4;
+    const fr_plain* q;         /* jobs * terms_per_job */
+    uint32_t terms_per_job, m, per, pieces;
+    uint32_t axis_first[5];
+    const g1_affine* table[4]; /* fixed-base tables of S^(a) */
+    uint32_t* out;             /* raw: jobs * m * pieces */
+    TC_DEV void phase(int ph, uint32_t wave, uint32_t wg, uint8_t* bytes) const {
+        uint32_t* lds = (uint32_t*)bytes;
+        const uint32_t piece = wg % pieces, a = wg / pieces % m, job = wg / (pieces * m);
+        const uint32_t points = (axis_first[a + 1] - axis_first[a]) * (uint32_t)FB_W;
+        static_assert(FB_W % 8 == 0, "a wave's windows belong to one term");
+        if (piece * per * WAVES >= points) {
+            if (ph == 0 && wave == 0) wv_store_raw(out + (uint64_t)wg * WV_POINT_WORDS, wv_identity());
+            return;
+        }
+        const wv_consts k = wv_constants();
+        if (ph == 0) {
+            const uint32_t first = (piece * WAVES + wave) * per, term = first / (uint32_t)FB_W;
+            wv_point acc = wv_identity();
+            if (first < points) {
+                const uint32_t* v = q[(uint64_t)job * terms_per_job + axis_first[a] + term].l;
+                wave_add_windows(k, acc, table[a], term, [=](int w, uint32_t& carry) { return fr_window_digit(v, w, FB_C, carry); }, first % (uint32_t)FB_W, per, false);
+            }
+            wv_store_raw(lds + wave * WV_POINT_WORDS, acc);
+            return;
+        }
+        wave_pair_level(k, lds, wave, WAVES, ph - 1);
+        if (ph == 3 && wave == 0) wv_store_raw(out + (uint64_t)wg * WV_POINT_WORDS, wv_load_raw(lds));
     }
 };
 

@@ -692,8 +692,18 @@ extern "C" int tc_ctx_sync(tc_ctx* ctx) {
 /* ======================================================================================= */
 /* normalisation and fixed-base tables                                                     */
 /* ======================================================================================= */
+/* up to this many points (two waves per SIMD) an inversion each; more share one per wave */
+#if defined(TC_HOST_EMU)
+static const uint64_t NORMALIZE_WAVES_MAX = 8;
+#else
+static const uint64_t NORMALIZE_WAVES_MAX = 2048;
+#endif
 static int normalize(tc_ctx* ctx, const g1_xyzz* d_in, uint64_t n, g1_affine* d_out, fr_plain* d_phi = nullptr, uint32_t* d_canonical = nullptr) {
     if (n == 0) return TC_OK;
+    if (n <= NORMALIZE_WAVES_MAX) {
+        RT(launch_wave_groups((uint32_t)n, ctx->stream, NormalizeWave<1>{WavePoints{d_in, WAVE_XYZZ}, 1u, d_out, d_phi, d_canonical}));
+        return TC_OK;
+    }
     /* one point per lane up to four waves per compute unit, then longer runs (of up to 16: past that the tree and the
      * inversion are a small share); fewer than 64 points take a tree of their own height */
     uint32_t G = (uint32_t)std::min<uint64_t>(16, (n + 65535) / 65536);
@@ -702,6 +712,18 @@ static int normalize(tc_ctx* ctx, const g1_xyzz* d_in, uint64_t n, g1_affine* d_
     while (leaves < 64 && leaves < runs) leaves *= 2;
     BatchNormalize k{d_in, n, G, leaves, d_out, d_phi, d_canonical};
     RT((launch_coop<BatchNormalize::BLOCK>((uint32_t)((runs + leaves - 1) / leaves), ctx->stream, k)));
+    return TC_OK;
+}
+/* the same for n sums in `pieces` raw points each */
+static int normalize_sums(tc_ctx* ctx, const uint32_t* d_raw, uint64_t n, uint32_t pieces, g1_affine* d_out, fr_plain* d_phi, uint32_t* d_canonical) {
+    if (n > NORMALIZE_WAVES_MAX) {
+        WS(sums, g1_xyzz, n);
+        RT(launch_wave_groups((uint32_t)n, ctx->stream, WindowWave{d_raw, pieces, nullptr, sums}));
+        return normalize(ctx, sums, n, d_out, d_phi, d_canonical);
+    }
+    const WavePoints in{d_raw, WAVE_RAW};
+    if (pieces == 1) RT(launch_wave_groups((uint32_t)n, ctx->stream, NormalizeWave<1>{in, 1u, d_out, d_phi, d_canonical}));
+    else RT(launch_wave_groups((uint32_t)n, ctx->stream, NormalizeWave<8>{in, pieces, d_out, d_phi, d_canonical}));
     return TC_OK;
 }
 /* XYZZ points on the device -> canonical bytes on the host */
@@ -1280,6 +1302,13 @@ extern "C" int tc_quant_scale(tc_ctx* ctx, const void* d_src, size_t n, float* d
 /* ======================================================================================= */
 /* a tree level of at most this many nodes (two workgroups per compute unit) takes the cooperative sums */
 static const uint64_t COOP_LEVEL_NODES = 512;
+/* a level with at most this many table points to add takes whole waves (a point costs the chip 1 ns, the cooperative sums 110 us and
+ * more whatever the number of nodes) */
+#if defined(TC_HOST_EMU)
+static const uint64_t WAVE_LEVEL_POINTS = 600;
+#else
+static const uint64_t WAVE_LEVEL_POINTS = 65536;
+#endif
 /* a tree level spreads the windows of a child over lanes as long as it stays within this many lanes (two waves per SIMD) */
 static const uint64_t SPLIT_LEVEL_LANES = 131072;
 
@@ -1335,7 +1364,7 @@ static int reduce_windows(tc_ctx* ctx, const WavePoints& bucket, int count, int 
         RT(rt::launch<64>(redo_lanes, ctx->stream, StridedRedo<StridedSums>{S, redo_lanes}));
         RT(rt::launch<64>(2ull * windows, ctx->stream, SmallWeighted{sums, S.cols(), windows, parts}));
         RT(rt::launch<64>(windows, ctx->stream, SmallFinish{parts, S.cols(), windows, W > 1 ? wsum : results}));
-        if (W > 1) RT(launch_wave_groups((uint32_t)count, ctx->stream, CombineWave{WavePoints{wsum, 0u}, (uint32_t)W, (uint32_t)c, results}));
+        if (W > 1) RT(launch_wave_groups((uint32_t)count, ctx->stream, CombineWave{WavePoints{wsum, WAVE_XYZZ}, (uint32_t)W, (uint32_t)c, results}));
         return TC_OK;
     }
     /* bit by bit */
@@ -1350,8 +1379,8 @@ static int reduce_windows(tc_ctx* ctx, const WavePoints& bucket, int count, int 
         if (!windows_by_lanes(windows, nb)) {
             WS(pieces, uint32_t, (uint64_t)ROWCOL_PIECES * windows * WV_POINT_WORDS);
             RT(launch_wave_groups(ROWCOL_PIECES * windows, ctx->stream, RowColWave{bucket, pieces}));
-            bits.rows = WavePoints{pieces, 1u};
-            bits.pts = WavePoints{pieces + 128ull * ROW_PIECES * WV_POINT_WORDS, 1u};
+            bits.rows = WavePoints{pieces, WAVE_RAW};
+            bits.pts = WavePoints{pieces + 128ull * ROW_PIECES * WV_POINT_WORDS, WAVE_RAW};
             bits.rows_stride = bits.pts_stride = ROWCOL_PIECES;
             bits.rows_logp = 2;
             bits.logp = 1;
@@ -1371,15 +1400,15 @@ static int reduce_windows(tc_ctx* ctx, const WavePoints& bucket, int count, int 
             RT((rt::launch_waves<64, 2>(L2.lanes(), ctx->stream, L2)));
             redo_lanes = (uint32_t)std::min<uint64_t>(L2.lanes(), ACC_RESIDENT_LANES);
             RT(rt::launch<64>(redo_lanes, ctx->stream, StridedRedo<BigRowColSums>{L2, redo_lanes}));
-            bits.pts = WavePoints{rows + 256ull * windows, 0u};
-            bits.rows = WavePoints{rows, 0u};
+            bits.pts = WavePoints{rows + 256ull * windows, WAVE_XYZZ};
+            bits.rows = WavePoints{rows, WAVE_XYZZ};
             bits.pts_stride = bits.rows_stride = 256u;
         }
     }
     RT(launch_wave_groups(windows * chains * BITSUM_PARTS, ctx->stream, bits));
     RT(launch_wave_groups(windows * chains, ctx->stream, ScaleWave{sums, lognb, scaled}));
     RT(launch_wave_groups(windows, ctx->stream, WindowWave{scaled, chains, wsum, W > 1 ? nullptr : results}));
-    if (W > 1) RT(launch_wave_groups((uint32_t)count, ctx->stream, CombineWave{WavePoints{wsum, 1u}, (uint32_t)W, (uint32_t)c, results}));
+    if (W > 1) RT(launch_wave_groups((uint32_t)count, ctx->stream, CombineWave{WavePoints{wsum, WAVE_RAW}, (uint32_t)W, (uint32_t)c, results}));
     return TC_OK;
 }
 
@@ -1830,24 +1859,24 @@ static int msm_engine_multi(tc_ctx* ctx, int count, const MsmProblem* prob, int 
         if (nbk >= ORDERED_LANES_MIN && pass == 0) TRY(order_lanes(ctx, cur_start, nullptr, nbk, nbk, &pperm));
         RT((rt::launch_waves<64, 2>(nbk, ctx->stream, AccXyzzFast{(g1_xyzz*)cur, cur_start, nullptr, nbk, 0, bucket, given_up, redo + 1, true, pperm})));
         RT(rt::launch<64>(redo_lanes, ctx->stream, AccXyzzRedo{(g1_xyzz*)cur, cur_start, nullptr, nbk, 0, bucket, given_up, redo + 1, true, redo_lanes}));
-        return reduce_windows(ctx, WavePoints{bucket, 0u}, count, W, c, nb, results);
+        return reduce_windows(ctx, WavePoints{bucket, WAVE_XYZZ}, count, W, c, nb, results);
     }
     while (worst > (planned && !ctx->static_mode ? BUCKET_WAVE_MAX_UNSEEN : BUCKET_WAVE_MAX)) {
         RT(rt::launch<256>(nbk, ctx->stream, DiffCounts{cur_start, cnt}));
         TRY(scan_counts(ctx, cnt, nbk, WAVE_PASS_FANIN, start, nxt_start, nullptr, tot_a, tot_b, tot_max));
         lanes_bound = fewer(lanes_bound, WAVE_PASS_FANIN);
         if (!spare_room((size_t)lanes_bound * WV_POINT_WORDS * 4)) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
-        RT(launch_wave_groups((uint32_t)((lanes_bound + 3) / 4), ctx->stream, PassWave{WavePoints{cur, raw}, cur_start, nxt_start, nbk, (uint32_t*)spare}));
+        RT(launch_wave_groups((uint32_t)((lanes_bound + 3) / 4), ctx->stream, PassWave{WavePoints{cur, raw ? WAVE_RAW : WAVE_XYZZ}, cur_start, nxt_start, nbk, (uint32_t*)spare}));
         raw = true;
         next_pass(WAVE_PASS_FANIN);
     }
     uint8_t* bucket = (uint8_t*)ws_alloc(ctx, (size_t)nbk * (by_lanes ? sizeof(g1_xyzz) : WV_POINT_WORDS * 4));
     if (!bucket) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
     uint32_t* to_raw = by_lanes ? nullptr : (uint32_t*)bucket;
-    const WavePoints parts{cur, raw ? 1u : 0u};
+    const WavePoints parts{cur, raw ? WAVE_RAW : WAVE_XYZZ};
     if (worst > 16) RT(launch_wave_groups(nbk, ctx->stream, BucketWave<4>{parts, cur_start, nbk, to_raw, (g1_xyzz*)bucket}));
     else RT(launch_wave_groups((nbk + 3u) / 4u, ctx->stream, BucketWave<1>{parts, cur_start, nbk, to_raw, (g1_xyzz*)bucket}));
-    return reduce_windows(ctx, WavePoints{bucket, by_lanes ? 0u : 1u}, count, W, c, nb, results);
+    return reduce_windows(ctx, WavePoints{bucket, by_lanes ? WAVE_XYZZ : WAVE_RAW}, count, W, c, nb, results);
 }
 
 /* result[0] = sum_i [e(s_i)] pts[i] */
@@ -2598,9 +2627,20 @@ extern "C" int tc_terkle_build(tc_ctx* ctx, const tc_tree_desc* desc, tc_tree** 
                     bool bottom = (L == 0);
                     if (use_fb) {
                         int e;
-                        if (bottom && lv.n <= COOP_LEVEL_NODES) {
-                            typedef CoopReduce<NodeSmallSrc> Sum;
-                            e = launch_coop<Sum::BLOCK>((uint32_t)lv.n, ctx->stream, Sum{NodeSmallSrc{g, t->d_payload, t->dtype, ns->fb[0], acc}});
+                        const uint64_t points = (uint64_t)t->B * node_wave_windows(bottom);
+                        if (lv.n * points <= WAVE_LEVEL_POINTS) {
+                            const uint32_t pieces = (uint32_t)((points + NODE_WAVE_POINTS - 1) / NODE_WAVE_POINTS);
+                            uint32_t* sums = ws_array<uint32_t>(ctx, lv.n * pieces * WV_POINT_WORDS);
+                            if (!sums) { rc = fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed"); break; }
+                            const int kind = bottom ? TC_PROF_NODE_COMMIT : TC_PROF_NODE_COMMIT_UPPER;
+                            rt::event_t e0, e1;
+                            prof_begin(ctx, kind, &e0, &e1);
+                            e = launch_wave_groups((uint32_t)lv.n * pieces, ctx->stream,
+                                                   NodeTermsWave{g, bottom ? t->d_payload : nullptr, t->dtype, bottom ? nullptr : t->levels[L - 1].phi, ns->fb[0], pieces, sums});
+                            prof_end(ctx, kind, e0, e1);
+                            if (e) { rc = fail_hip(ctx, e, "node commit"); break; }
+                            rc = normalize_sums(ctx, sums, lv.n, pieces, lv.C, lv.phi, nullptr);
+                            break;
                         } else if (bottom) {
                             rt::event_t e0, e1;
                             prof_begin(ctx, TC_PROF_NODE_COMMIT, &e0, &e1);
@@ -2609,7 +2649,7 @@ extern "C" int tc_terkle_build(tc_ctx* ctx, const tc_tree_desc* desc, tc_tree** 
                         } else if (lv.n <= COOP_LEVEL_NODES) {
                             rt::event_t e0, e1;
                             prof_begin(ctx, TC_PROF_NODE_COMMIT_UPPER, &e0, &e1);
-                            /* very few nodes: every (child, window) term its own lane, sums shared by four waves */
+                            /* some hundred nodes: every (child, window) term its own lane, sums shared by four waves */
                             typedef CoopReduce<NodeWindowSrc> Sum;
                             e = launch_coop<Sum::BLOCK>((uint32_t)lv.n, ctx->stream, Sum{NodeWindowSrc{g, t->levels[L - 1].phi, ns->fb[0], acc}});
                             prof_end(ctx, TC_PROF_NODE_COMMIT_UPPER, e0, e1);
@@ -2905,7 +2945,7 @@ extern "C" int tc_terkle_open_batch(tc_ctx* ctx, const tc_tree* t, int count, co
         uint32_t jobs = (uint32_t)count * (uint32_t)n_blocked;
         std::vector<uint8_t> h_pi((size_t)jobs * m * 96), h_y((size_t)jobs * 32);
         if (jobs) {
-            WS(d_pi, g1_xyzz, (uint64_t)jobs * m);
+            WS(d_can, uint32_t, 24ull * jobs * m);
             WS(d_y, fr_plain, jobs);
             if (use_fb) {
                 NodeOpenTerms k;
@@ -2917,7 +2957,6 @@ extern "C" int tc_terkle_open_batch(tc_ctx* ctx, const tc_tree* t, int count, co
                     k.axis_first[a] = terms;
                     terms += (uint32_t)ns->n[a];
                     k.ax[a] = ns->ax[a];
-                    k.table[a] = ns->fb[a];
                 }
                 for (int a = m; a <= 4; ++a) k.axis_first[a] = terms;
                 k.terms_per_job = terms;
@@ -2930,34 +2969,42 @@ extern "C" int tc_terkle_open_batch(tc_ctx* ctx, const tc_tree* t, int count, co
                     k.lv[b].below = L == 0 ? nullptr : t->levels[L - 1].phi;
                 }
                 std::vector<NodeOpenJob> hj(jobs);
-                std::vector<uint32_t> seg((size_t)jobs * m + 1);
                 for (int i = 0; i < count; ++i)
                     for (int b = 0; b < n_blocked; ++b) {
                         uint32_t j = (uint32_t)i * n_blocked + b;
                         hj[j].node = P[i].node[b];
                         for (int a = 0; a < 4; ++a) hj[j].kappa[a] = P[i].kap[b][a];
                         hj[j].level = b;
-                        hj[j].term0 = j * terms;
-                        for (int a = 0; a < m; ++a) seg[(size_t)j * m + a] = j * terms + k.axis_first[a];
                     }
-                seg[(size_t)jobs * m] = jobs * terms;
                 WS(d_jobs, NodeOpenJob, jobs);
-                WS(d_seg, uint32_t, (uint64_t)jobs * m + 1);
-                int logH = 0;
-                while ((2u << logH) < (uint32_t)FB_W) ++logH;
-                if ((((uint64_t)jobs * terms) << logH) > 0xFFFFFFFFull) return fail(ctx, TC_ERR_ARG, "too many openings in one batch");
-                WS(d_terms, g1_xyzz, ((uint64_t)jobs * terms) << logH);
+                if ((uint64_t)jobs * terms > 0xFFFFFFFFull) return fail(ctx, TC_ERR_ARG, "too many openings in one batch");
+                const uint64_t points = (uint64_t)ns->n[0] * FB_W;
+                const uint32_t per = (uint64_t)jobs * m * ((points + 31) / 32) <= OPEN_WAVES_SHORT ? 4 : 8;
+                const uint32_t pieces = (uint32_t)((points + 8 * per - 1) / (8 * per));
+                if ((uint64_t)jobs * m * pieces > 0x7FFFFFFFull) return fail(ctx, TC_ERR_ARG, "too many openings in one batch");
+                WS(d_q, fr_plain, (uint64_t)jobs * terms);
+                WS(d_sums, uint32_t, (uint64_t)jobs * m * pieces * WV_POINT_WORDS);
                 TRY(h2d(ctx, d_jobs, hj.data(), sizeof(NodeOpenJob) * jobs));
-                TRY(h2d(ctx, d_seg, seg.data(), 4 * seg.size()));
                 k.jobs = d_jobs;
-                k.out = d_terms;
+                k.out = d_q;
                 k.y_out = d_y;
-                k.logH = logH;
-                RT(rt::launch<64>(((uint64_t)jobs * terms) << logH, ctx->stream, k));
-                typedef CoopReduce<SegmentSrc> Sum;
-                RT((launch_coop<Sum::BLOCK>(jobs * (uint32_t)m, ctx->stream, Sum{SegmentSrc{d_terms, d_seg, 1u << logH, d_pi}})));
+                RT(rt::launch<64>((uint64_t)jobs * terms, ctx->stream, k));
+                NodeOpenWave o;
+                memset((void*)&o, 0, sizeof o);
+                o.q = d_q;
+                o.terms_per_job = terms;
+                o.m = (uint32_t)m;
+                o.per = per;
+                o.pieces = pieces;
+                for (int a = 0; a <= 4; ++a) o.axis_first[a] = k.axis_first[a];
+                for (int a = 0; a < m; ++a) o.table[a] = ns->fb[a];
+                o.out = d_sums;
+                RT(launch_wave_groups(jobs * (uint32_t)m * pieces, ctx->stream, o));
+                WS(aff, g1_affine, (uint64_t)jobs * m);
+                TRY(normalize_sums(ctx, d_sums, (uint64_t)jobs * m, pieces, aff, nullptr, d_can));
             } else {
                 /* large node shapes: gather the node tensor and open it like any tensor */
+                WS(d_pi, g1_xyzz, (uint64_t)jobs * m);
                 for (int i = 0; i < count; ++i)
                     for (int b = 0; b < n_blocked; ++b) {
                         int L = first_blocked + b;
@@ -2975,9 +3022,12 @@ extern "C" int tc_terkle_open_batch(tc_ctx* ctx, const tc_tree* t, int count, co
                         TRY(open_device(ctx, ns, z, bottom ? t->dtype : TC_FR, kap, d_pi + (uint64_t)j * m, d_y + j));
                         ctx->wsp->off = mk;
                     }
+                WS(aff, g1_affine, (uint64_t)jobs * m);
+                TRY(normalize(ctx, d_pi, (uint64_t)jobs * m, aff, nullptr, d_can));
             }
             RT(rt::memcpy_d2h(h_y.data(), d_y, 32ull * jobs, ctx->stream));
-            TRY(points_to_host(ctx, d_pi, jobs * (uint32_t)m, h_pi.data()));
+            RT(rt::memcpy_d2h(h_pi.data(), d_can, 96ull * jobs * m, ctx->stream));
+            TRY(ctx_sync(ctx));
         }
         /* leaf tensors: all openings in one batch */
         std::vector<std::vector<uint8_t>> leaf_part(count);

@@ -24,7 +24,7 @@
 
 namespace tc {
 
-enum { W28_MP = 0, W28_P = 1, W28_128P = 2, W28_512P = 3, W28_ONE = 4, W28_FROM_PLAIN = 5, W28_BETA = 6, W28_ROWS = 7 };
+enum { W28_MP = 0, W28_P = 1, W28_128P = 2, W28_512P = 3, W28_ONE = 4, W28_FROM_PLAIN = 5, W28_TO_PLAIN = 6, W28_BETA = 7, W28_ROWS = 8 };
 #if defined(__HIPCC__)
 static __device__ const uint32_t WAVE28_TABLE[W28_ROWS][16] = {TC_WAVE28_ROWS};
 #else
@@ -289,38 +289,6 @@ TC_DEV wv wv_negate(const wv& b) {
 }
 
 /* ---- in and out ------------------------------------------------------------------------------------------------- */
-/* limb j of the re-cut of a 12-word element (fp28_from_fp): bits 28 j - 8 .. 28 j + 19 */
-TC_HD uint32_t wv_limb(const uint32_t* w, uint32_t j) {
-    if (j >= 14u) return 0u;
-    const uint32_t o = 28u * j + 24u, i = o >> 5;                       /* counted from a word of zeros below the lowest */
-    const uint64_t two = ((uint64_t)(i < 12u ? w[i] : 0u) << 32) | (i ? w[i - 1] : 0u);
-    return (uint32_t)(two >> (o & 31u)) & (uint32_t)FP28_MASK;
-}
-/* rows 0 .. rows - 1 from consecutive elements of 12 words, the others one */
-TC_DEV wv wv_load_elements(const uint32_t* w, uint32_t rows) {
-    wv r, one = wv_table(W28_ONE);
-    WV_LANES(WV_AT(r) = (lane >> 4) < rows ? wv_limb(w + 12u * (lane >> 4), lane & 15u) : WV_AT(one))
-    return r;
-}
-TC_DEV wv_point wv_load(const g1_xyzz* p) {
-    wv_point r;
-    r.v = wv_load_elements((const uint32_t*)p, 4);
-    r.inf = !wv_row_any(r.v, 2);
-    return r;
-}
-TC_DEV wv_point wv_load_affine(const g1_affine* p) {
-    wv_point r;
-    r.v = wv_load_elements((const uint32_t*)p, 2);
-    r.inf = !wv_row_any(r.v, 0) && !wv_row_any(r.v, 1);
-    return r;
-}
-/* canonical bytes (x, y as plain numbers of 12 words; anything below 2^384 is taken) */
-TC_DEV wv_point wv_load_canonical(const wv_consts& k, const uint32_t* w) {
-    wv_point r = wv_load_affine((const g1_affine*)w);
-    const wv plain = wv_table(W28_FROM_PLAIN), one = wv_table(W28_ONE);
-    r.v = wv_mul(k, r.v, wv_pick(plain, plain, one, one));
-    return r;
-}
 /* The form itself, 64 words, for points on their way from one wave to another: word 63 (the last lane of ZZZ's row, no limb) is 1 for a
  * finite point and 0 for the identity. */
 constexpr uint32_t WV_POINT_WORDS = 64, WV_FINITE = 63;
@@ -338,40 +306,58 @@ TC_DEV wv_point wv_load_raw(const uint32_t* from) {
     WV_LANES(WV_AT(w) = from[lane])
     return wv_from_raw(w);
 }
-/* An array of points, raw or in the 32-bit form.  A point is fetched (one or two words a lane) while the one before is being
- * added, and unpacked when its turn comes. */
+/* An array of points: raw, in the 32-bit form, or affine.  A point is fetched (one or two words a lane) while the one before is
+ * being added, and unpacked when its turn comes. */
 struct wv_words {
     wv a, b;
 };
+enum { WAVE_XYZZ = 0, WAVE_RAW = 1, WAVE_AFFINE = 2 };
 struct WavePoints {
     const void* base;
-    uint32_t raw;
+    uint32_t kind;
     TC_DEV wv_words fetch(uint64_t i) const {
         wv_words w;
-        if (raw) {
+        if (kind == WAVE_RAW) {
             const uint32_t* p = (const uint32_t*)base + i * WV_POINT_WORDS;
             WV_LANES(WV_AT(w.a) = p[lane]; WV_AT(w.b) = 0u)
         } else {
-            const uint32_t* p = (const uint32_t*)((const g1_xyzz*)base + i);
-            WV_LANES(const uint32_t o = 28u * (lane & 15u) + 24u; const uint32_t at = (o >> 5) < 12u ? o >> 5 : 12u; const uint32_t* c = p + 12u * (lane >> 4);
-                     WV_AT(w.a) = at ? c[at - 1u] : 0u; WV_AT(w.b) = at < 12u ? c[at] : 0u)
+            /* words at and at - 1 of the lane's coordinate (nothing below the lowest and above the highest); an affine point has two */
+            const uint32_t words = kind == WAVE_AFFINE ? 24u : 48u;
+            const uint32_t* p = (const uint32_t*)base + i * words;
+            WV_LANES(const uint32_t o = 28u * (lane & 15u) + 24u; const uint32_t at = (o >> 5) < 12u ? o >> 5 : 12u; const uint32_t c = 12u * (lane >> 4);
+                     WV_AT(w.a) = at && c < words ? p[c + at - 1u] : 0u; WV_AT(w.b) = at < 12u && c < words ? p[c + at] : 0u)
         }
         return w;
     }
     TC_DEV wv_point unpack(const wv_words& w) const {
-        if (raw) return wv_from_raw(w.a);
+        if (kind == WAVE_RAW) return wv_from_raw(w.a);
         wv_point r;
         WV_LANES(const uint32_t sh = (28u * (lane & 15u) + 24u) & 31u;
                  WV_AT(r.v) = (lane & 15u) < 14u ? (uint32_t)((((uint64_t)WV_AT(w.b) << 32) | WV_AT(w.a)) >> sh) & (uint32_t)FP28_MASK : 0u)
-        r.inf = !wv_row_any(r.v, 2);
+        if (kind == WAVE_AFFINE) {
+            r.inf = !wv_row_any(r.v, 0) && !wv_row_any(r.v, 1);
+            const wv one = wv_table(W28_ONE);
+            WV_LANES(WV_AT(r.v) = lane < 32u ? WV_AT(r.v) : WV_AT(one))
+        } else {
+            r.inf = !wv_row_any(r.v, 2);
+        }
         return r;
     }
     TC_DEV wv_point load(uint64_t i) const { return unpack(fetch(i)); }
     /* by a lane of its own */
     TC_DEV bool empty(uint64_t i) const {
-        return raw ? ((const uint32_t*)base)[i * WV_POINT_WORDS + WV_FINITE] == 0u : fe_is_zero(((const g1_xyzz*)base)[i].ZZ);
+        return kind == WAVE_RAW ? ((const uint32_t*)base)[i * WV_POINT_WORDS + WV_FINITE] == 0u : fe_is_zero(((const g1_xyzz*)base)[i].ZZ);
     }
 };
+TC_DEV wv_point wv_load(const g1_xyzz* p) { return WavePoints{p, WAVE_XYZZ}.load(0); }
+TC_DEV wv_point wv_load_affine(const g1_affine* p) { return WavePoints{p, WAVE_AFFINE}.load(0); }
+/* canonical bytes (x, y as plain numbers of 12 words; anything below 2^384 is taken) */
+TC_DEV wv_point wv_load_canonical(const wv_consts& k, const uint32_t* w) {
+    wv_point r = WavePoints{w, WAVE_AFFINE}.load(0);
+    const wv plain = wv_table(W28_FROM_PLAIN), one = wv_table(W28_ONE);
+    r.v = wv_mul(k, r.v, wv_pick(plain, plain, one, one));
+    return r;
+}
 /* all limbs of a lane's row */
 TC_DEV fp28 wv_row_limbs(const wv& x, uint32_t lane) {
     fp28 v;
@@ -394,6 +380,29 @@ TC_DEV void wv_store(g1_xyzz* to, const wv_point& p) {
         return;
     }
     WV_LANES(fp28 v = wv_row_limbs(p.v, lane); if ((lane & 15u) == 0u) (&to->X)[lane >> 4] = fp28_to_fp(v))
+}
+
+/* an element that every lane holds (normal limbs, within 128 p either way), plus 128 p, in all rows */
+TC_DEV wv wv_from_lanes(const wv_consts& k, const fp28& a) {
+    wv r;
+    WV_LANES(const uint32_t j = lane & 15u; int32_t l = 0;
+             for (int i = 0; i < 14; ++i) l |= (j == (uint32_t)i ? -1 : 0) & a.l[i];
+             WV_AT(r) = (uint32_t)(l + (int32_t)WV_AT(k.p128)))
+    return wv_carry(r);
+}
+/* x and y of a finite point in the rows 0 and 1 (below 4 p): one inversion, four levels of products */
+TC_DEV wv wv_to_affine(const wv_consts& k, const wv& p) {
+    wv c[4];
+    wv_spread(p, c);
+    const wv den = wv_mul(k, wv_mul(k, c[2], c[3]), wv_table(W28_ONE));           /* ZZ ZZZ, below 2.02 p */
+    fp28 d = wv_row_limbs(den, 0), mod;
+#if defined(__HIPCC__)
+#pragma unroll
+#endif
+    for (int j = 0; j < 14; ++j) mod.l[j] = Fp28Params::MOD[j];
+    const wv inv = wv_from_lanes(k, fp28_inv_wave(fp28_carry(fp28_sub(d, mod))));  /* |d - p| < 2 p, as the inversion wants it */
+    const wv t = wv_mul(k, inv, wv_pick(c[3], c[2], c[2], c[2]));                  /* 1 / ZZ, 1 / ZZZ */
+    return wv_mul(k, t, wv_pick(c[0], c[1], c[1], c[1]));
 }
 
 }  // namespace tc

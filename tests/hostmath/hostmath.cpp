@@ -103,7 +103,7 @@ void hm_window_bits(const uint8_t* pts, uint32_t lognb, uint32_t windows, uint8_
         bucket[i] = i % 2 ? xyzz_madd(xyzz_dbl_affine(a), affine_neg(a)) : xyzz_from_affine(a);
     }
     std::vector<uint32_t> pieces((size_t)n * BITSUM_PARTS * WV_POINT_WORDS);
-    const WavePoints in{bucket.data(), 0u};
+    const WavePoints in{bucket.data(), WAVE_XYZZ};
     std::vector<uint32_t> scaled((size_t)n * WV_POINT_WORDS);
     wave_run(BitSumWave{in, in, 1u << lognb, 1u << lognb, 0u, 0u, lognb, pieces.data()}, n * BITSUM_PARTS);
     wave_run(ScaleWave{pieces.data(), lognb, scaled.data()}, n);
