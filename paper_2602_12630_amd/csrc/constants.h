@@ -26,6 +26,7 @@ struct FrParams {
     static constexpr int GCD_ROUNDS = 18;              /* ceil((2 len(q) - 1) / 30) + 1 */
     static constexpr uint32_t GCD_FIX[8] = {0xcb9d63b7u, 0x6e19d729u, 0x5f8be0ccu, 0xf8f3f232u, 0xa5edc8e5u, 0xbab78932u, 0xc66409cfu, 0x4a73978cu}; /* 4^GCD_ROUNDS * R^3 mod q */
     static constexpr uint32_t HALF[8] = {0x80000000u, 0x7fffffffu, 0x7fff2dffu, 0xa9ded201u, 0x04d0ec02u, 0x199cec04u, 0x94cebea4u, 0x39f6d3a9u};  /* (q - 1) / 2 */
+    static constexpr int32_t NEG29[9] = {-1, -536870904, -529989567, -457704959, -494949691, -201589968, -354471143, -174404527, -7597479};      /* the 29-bit limbs of q, negated (the lowest is 1) */
     static constexpr int TWO_ADICITY = 32;
     static constexpr uint32_t ROOT[8] = {0x0c17f47cu, 0x9cab6d5cu, 0xfd4b71e5u, 0x1ce1e93du, 0x471dd505u, 0x0d6db230u, 0x743a3b6au, 0x3f0ee990u};  /* a root of unity of order 2^TWO_ADICITY, Montgomery form */
 };

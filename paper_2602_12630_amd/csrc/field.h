@@ -251,7 +251,7 @@ TC_HD Fe<P> fe_mul(const Fe<P>& a, const Fe<P>& b) {
 }
 
 #if defined(__HIP_DEVICE_COMPILE__)
-/* Device form of the same product: product scanning (column by column) with one
+/* Device form of the same product (Fp; Fr's is fr_mul_limbs29): product scanning (column by column) with one
  * 96-bit accumulator.  Each limb product is one v_mad_u64_u32 into the low 64 bits
  * plus one v_addc_co_u32 of its carry into the third word; the modulus limbs sit
  * in scalar registers.  Column k collects a_i b_{k-i} and m_i q_{k-i}; m_k is
@@ -273,36 +273,19 @@ __device__ __forceinline__ void carry_into(uint32_t& hi, uint64_t carry) {
 }
 /* (volatile keeps the multiply-adds and the carry additions in the order written here; sending the unused
  * carry-out of the addition to VCC instead of an SGPR pair made the accumulation kernels 3 % slower) */
-/* LATE = false adds every carry at once, in an order the compiler is free to choose: the 8-limb products of the
- * line-by-line interpolation kernel, eight waves to a SIMD, never wait for a carry and ran 6 % faster that way (242 against
- * 256 ms for the 512 x 4096 tensor); the 12-limb products of kernels with three waves to a SIMD take it late. */
-template <bool LATE>
 __device__ __forceinline__ void macp_vv(Acc96P& A, uint32_t a, uint32_t b) {
     uint64_t carry;
-    if (LATE) {
-        asm volatile("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(A.lo), "=s"(carry) : "v"(a), "v"(b));
-        if (A.has) carry_into(A.hi, A.pending);
-        A.pending = carry;
-        A.has = true;
-    } else {
-        uint64_t unused;
-        asm("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(A.lo), "=s"(carry) : "v"(a), "v"(b));
-        asm("v_addc_co_u32_e64 %0, %1, 0, %0, %2" : "+v"(A.hi), "=s"(unused) : "s"(carry));
-    }
+    asm volatile("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(A.lo), "=s"(carry) : "v"(a), "v"(b));
+    if (A.has) carry_into(A.hi, A.pending);
+    A.pending = carry;
+    A.has = true;
 }
-template <bool LATE>
 __device__ __forceinline__ void macp_vs(Acc96P& A, uint32_t a, uint32_t b) {
     uint64_t carry;
-    if (LATE) {
-        asm volatile("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(A.lo), "=s"(carry) : "v"(a), "s"(b));
-        if (A.has) carry_into(A.hi, A.pending);
-        A.pending = carry;
-        A.has = true;
-    } else {
-        uint64_t unused;
-        asm("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(A.lo), "=s"(carry) : "v"(a), "s"(b));
-        asm("v_addc_co_u32_e64 %0, %1, 0, %0, %2" : "+v"(A.hi), "=s"(unused) : "s"(carry));
-    }
+    asm volatile("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(A.lo), "=s"(carry) : "v"(a), "s"(b));
+    if (A.has) carry_into(A.hi, A.pending);
+    A.pending = carry;
+    A.has = true;
 }
 __device__ __forceinline__ void flush(Acc96P& A) {
     if (A.has) carry_into(A.hi, A.pending);
@@ -322,19 +305,19 @@ __device__ __forceinline__ Fe<P> fe_mul_dev(const Fe<P>& a, const Fe<P>& b) {
 #pragma unroll
     for (int k = 0; k < N; ++k) {
 #pragma unroll
-        for (int i = 0; i <= k; ++i) macp_vv<(P::N > 8)>(A, a.l[i], b.l[k - i]);
+        for (int i = 0; i <= k; ++i) macp_vv(A, a.l[i], b.l[k - i]);
 #pragma unroll
-        for (int i = 0; i < k; ++i) macp_vs<(P::N > 8)>(A, m[i], P::MOD[k - i]);
+        for (int i = 0; i < k; ++i) macp_vs(A, m[i], P::MOD[k - i]);
         m[k] = (uint32_t)A.lo * P::INV;
-        macp_vs<(P::N > 8)>(A, m[k], P::MOD[0]);
+        macp_vs(A, m[k], P::MOD[0]);
         acc_shift(A);
     }
 #pragma unroll
     for (int k = N; k < 2 * N - 1; ++k) {
 #pragma unroll
-        for (int i = k - N + 1; i < N; ++i) macp_vv<(P::N > 8)>(A, a.l[i], b.l[k - i]);
+        for (int i = k - N + 1; i < N; ++i) macp_vv(A, a.l[i], b.l[k - i]);
 #pragma unroll
-        for (int i = k - N + 1; i < N; ++i) macp_vs<(P::N > 8)>(A, m[i], P::MOD[k - i]);
+        for (int i = k - N + 1; i < N; ++i) macp_vs(A, m[i], P::MOD[k - i]);
         r.l[k - N] = (uint32_t)A.lo;
         acc_shift(A);
     }
@@ -359,19 +342,19 @@ __device__ __forceinline__ Fe<P> fe_sqr_dev(const Fe<P>& a) {
 #pragma unroll
     for (int k = 0; k < 2 * N - 1; ++k) {
 #pragma unroll
-        for (int i = (k < N ? 0 : k - N + 1); i < k - i; ++i) macp_vv<(P::N > 8)>(A, d[i], a.l[k - i]);
+        for (int i = (k < N ? 0 : k - N + 1); i < k - i; ++i) macp_vv(A, d[i], a.l[k - i]);
         if ((k & 1) == 0) {
-            macp_vv<(P::N > 8)>(A, a.l[k / 2], a.l[k / 2]);
-            if (k) macp_vv<(P::N > 8)>(A, a.l[k / 2], a.l[k / 2 - 1] >> 31);       /* c_(k/2), formed here: registers are scarce */
+            macp_vv(A, a.l[k / 2], a.l[k / 2]);
+            if (k) macp_vv(A, a.l[k / 2], a.l[k / 2 - 1] >> 31);       /* c_(k/2), formed here: registers are scarce */
         }
         if (k < N) {
 #pragma unroll
-            for (int i = 0; i < k; ++i) macp_vs<(P::N > 8)>(A, m[i], P::MOD[k - i]);
+            for (int i = 0; i < k; ++i) macp_vs(A, m[i], P::MOD[k - i]);
             m[k] = (uint32_t)A.lo * P::INV;
-            macp_vs<(P::N > 8)>(A, m[k], P::MOD[0]);
+            macp_vs(A, m[k], P::MOD[0]);
         } else {
 #pragma unroll
-            for (int i = k - N + 1; i < N; ++i) macp_vs<(P::N > 8)>(A, m[i], P::MOD[k - i]);
+            for (int i = k - N + 1; i < N; ++i) macp_vs(A, m[i], P::MOD[k - i]);
             r.l[k - N] = (uint32_t)A.lo;
         }
         acc_shift(A);
@@ -380,6 +363,147 @@ __device__ __forceinline__ Fe<P> fe_sqr_dev(const Fe<P>& a) {
     return fe_reduce_once<P>(r, (uint32_t)(A.lo >> 32));
 }
 #endif
+
+/* ---- Fr in 29-bit limbs -----------------------------------------------------------------------------
+ * Nine signed limbs of 29 bits, Montgomery radix 2^261: whole columns of the product scan fit a signed 64-bit sum, so there are no
+ * carry instructions, sums and differences are nine independent limb operations, and values need not lie in [0, r).
+ * r = 1 (mod 2^29): the multiple of r that clears a column is its own low limb, taken off, and the carry is what is above it.
+ * "Normal": limbs 0 .. 7 in [0, 2^29), limb 8 a small signed number; what products and carries return.  A product needs
+ *   9 max|a_j| max|b_j| (both products counted in a sum of two) + 8 2^58 + 2^35 < 2^63, e.g. 2^30 against a normal operand,
+ * and is in (v / 2^261 - r, v / 2^261] for the integer v that is reduced; 2^261 = 70 r.
+ * A product is 153 multiply-adds and some 55 other instructions; 136 multiply-adds, as many carry additions and 80 more in the
+ * 32-bit form. */
+struct fr29 {
+    int32_t l[9];
+};
+static constexpr uint32_t FR29_MASK = (1u << 29) - 1u;
+/* the bits of a, moved up by SHIFT places (SHIFT = 5: an element of the 32-bit form becomes the same element of this one) */
+template <int SHIFT>
+TC_HD fr29 fr29_cut(const fr_t& a) {
+    fr29 r;
+#pragma unroll
+    for (int j = 0; j < 9; ++j) {
+        const int o = 29 * j - SHIFT, w = o >> 5, sh = o & 31;
+        const uint64_t two = ((uint64_t)(w + 1 < 8 ? a.l[w + 1] : 0u) << 32) | (w >= 0 ? a.l[w] : 0u);
+        r.l[j] = (int32_t)((uint32_t)(two >> sh) & FR29_MASK);
+    }
+    return r;
+}
+/* a b 2^-261, or (a b + c e) 2^-261 under one reduction */
+template <bool TWO>
+TC_HD fr29 fr29_mont(const fr29& a, const fr29& b, const fr29& c, const fr29& e) {
+    int32_t q[9];
+    fr29 r;
+    int64_t acc = 0;
+#pragma unroll
+    for (int k = 0; k < 17; ++k) {
+#pragma unroll
+        for (int i = (k < 9 ? 0 : k - 8); i <= (k < 9 ? k : 8); ++i) acc += (int64_t)a.l[i] * (int64_t)b.l[k - i];
+        if (TWO) {
+#pragma unroll
+            for (int i = (k < 9 ? 0 : k - 8); i <= (k < 9 ? k : 8); ++i) acc += (int64_t)c.l[i] * (int64_t)e.l[k - i];
+        }
+#pragma unroll
+        for (int i = (k < 9 ? 0 : k - 8); i < (k < 9 ? k : 9); ++i) acc += (int64_t)q[i] * (int64_t)FrParams::NEG29[k - i];
+        const int32_t low = (int32_t)((uint32_t)acc & FR29_MASK);
+        if (k < 9) q[k] = low; else r.l[k - 9] = low;
+        acc >>= 29;                        /* arithmetic: the sum is signed */
+    }
+    r.l[8] = (int32_t)acc;
+    return r;
+}
+TC_HD fr29 fr29_mul(const fr29& a, const fr29& b) { return fr29_mont<false>(a, b, a, b); }
+TC_HD fr29 fr29_mul_add(const fr29& a, const fr29& b, const fr29& c, const fr29& e) { return fr29_mont<true>(a, b, c, e); }
+TC_HD fr29 fr29_add(const fr29& a, const fr29& b) {
+    fr29 r;
+#pragma unroll
+    for (int j = 0; j < 9; ++j) r.l[j] = a.l[j] + b.l[j];
+    return r;
+}
+TC_HD fr29 fr29_sub(const fr29& a, const fr29& b) {
+    fr29 r;
+#pragma unroll
+    for (int j = 0; j < 9; ++j) r.l[j] = a.l[j] - b.l[j];
+    return r;
+}
+/* same value, normal limbs (limbs of up to 31 bits either sign in) */
+TC_HD fr29 fr29_carry(const fr29& a) {
+    fr29 r;
+    int32_t c = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int32_t s = a.l[j] + c;
+        r.l[j] = (int32_t)((uint32_t)s & FR29_MASK);
+        c = s >> 29;
+    }
+    r.l[8] = a.l[8] + c;
+    return r;
+}
+/* the same less the multiple of r that leaves it within 0.6 r either way, for a value within 60 r (limbs of up to 31 bits): the multiple is the
+ * value's upper bits over r 2^-232 = 7597479.3, by 565 / 2^32 */
+TC_HD fr29 fr29_reduce(const fr29& a) {
+    const int32_t top = a.l[8] + (a.l[7] >> 29);
+    const int32_t q = (int32_t)(((int64_t)top * 565 + (1ll << 31)) >> 32);
+    fr29 r;
+    int64_t acc = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        acc += (int64_t)q * (int64_t)FrParams::NEG29[j] + (int64_t)a.l[j];
+        r.l[j] = (int32_t)((uint32_t)acc & FR29_MASK);
+        acc >>= 29;
+    }
+    r.l[8] = (int32_t)(acc + (int64_t)q * (int64_t)FrParams::NEG29[8] + (int64_t)a.l[8]);
+    return r;
+}
+/* an element of the 32-bit form, within 0.6 r (its cut, five places up, is below 32 r) */
+TC_HD fr29 fr29_from_fr(const fr_t& a) { return fr29_reduce(fr29_cut<5>(a)); }
+/* the value of normal limbs, within 1.1 r, as a number of 256 bits in two's complement, and back */
+TC_HD fr_t fr29_pack(const fr29& a) {
+    fr_t v;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int o = 32 * i, j = o / 29, sh = o % 29;
+        uint32_t w = (uint32_t)a.l[j] >> sh;
+        if (j + 1 < 9) w |= (uint32_t)a.l[j + 1] << (29 - sh);
+        if (58 - sh < 32 && j + 2 < 9) w |= (uint32_t)a.l[j + 2] << (58 - sh);
+        v.l[i] = w;
+    }
+    return v;
+}
+TC_HD fr29 fr29_unpack(const fr_t& a) {
+    fr29 r = fr29_cut<0>(a);
+    r.l[8] = (int32_t)a.l[7] >> 8;
+    return r;
+}
+/* v + r if v is negative (two's complement) */
+TC_HD fr_t fr_add_if_negative(fr_t v) {
+    const uint32_t neg = (uint32_t)((int32_t)v.l[7] >> 31);
+#if defined(__HIP_DEVICE_COMPILE__)
+    lanemask_t cy;
+    v.l[0] = add_co(v.l[0], FrParams::MOD[0] & neg, cy);
+#pragma unroll
+    for (int i = 1; i < 8; ++i) v.l[i] = addc_co(v.l[i], FrParams::MOD[i] & neg, cy);
+#else
+    uint32_t c = 0;
+    for (int i = 0; i < 8; ++i) {
+        uint64_t t = (uint64_t)v.l[i] + (FrParams::MOD[i] & neg) + c;
+        v.l[i] = (uint32_t)t;
+        c = (uint32_t)(t >> 32);
+    }
+#endif
+    return v;
+}
+/* the canonical element of the 32-bit form (radix 2^256) for a value within 60 r, normal limbs: 2^256 < 2^261 is a limb, and the product is above
+ * -1.9 r and below 0.9 r */
+TC_HD fr_t fr29_to_fr(const fr29& a) {
+    fr29 down{};
+    const fr29 x = fr29_reduce(a);
+    down.l[8] = 1 << 24;
+    return fr_add_if_negative(fr_add_if_negative(fr29_pack(fr29_mul(x, down))));
+}
+/* a b 2^-256 mod r in the 32-bit form, for a, b below 2^256 with a b < 2^256 r: a cut five places higher makes the radix of nine
+ * limbs that of eight words; the product is in (-r, r) */
+TC_HD fr_t fr_mul_limbs29(const fr_t& a, const fr_t& b) { return fr_add_if_negative(fr29_pack(fr29_mul(fr29_cut<5>(a), fr29_cut<0>(b)))); }
 
 /* ---- Fp products on the FP64 pipe --------------------------------------------------------------
  * gfx950 issues double-precision fused multiply-adds at twice the rate of 32 x 32 + 64 integer multiply-adds,
@@ -508,7 +632,7 @@ __device__ __attribute__((noinline)) fr_t fr_mul_call(u32x4 a0, u32x4 a1, u32x4 
     fr_t a, b;
     a.l[0] = a0.x; a.l[1] = a0.y; a.l[2] = a0.z; a.l[3] = a0.w; a.l[4] = a1.x; a.l[5] = a1.y; a.l[6] = a1.z; a.l[7] = a1.w;
     b.l[0] = b0.x; b.l[1] = b0.y; b.l[2] = b0.z; b.l[3] = b0.w; b.l[4] = b1.x; b.l[5] = b1.y; b.l[6] = b1.z; b.l[7] = b1.w;
-    return fe_mul_dev<FrParams>(a, b);
+    return fr_mul_limbs29(a, b);
 }
 __device__ __attribute__((noinline)) fp_t fp_sqr_call(u32x4 a0, u32x4 a1, u32x4 a2) {
     fp_t a;

@@ -117,6 +117,9 @@ def block(name, mod, n):
         two_adicity = (mod - 1 & -(mod - 1)).bit_length() - 1
         g = next(g for g in range(2, 100) if pow(g, (mod - 1) // 2, mod) == mod - 1)       # no square: full 2-power order
         root = pow(g, (mod - 1) >> two_adicity, mod)
+        assert mod % (1 << 29) == 1
+        out.append("    static constexpr int32_t NEG29[9] = {%s};      /* the 29-bit limbs of q, negated (the lowest is 1) */"
+                   % ", ".join("%d" % -(mod >> (29 * i) & 0x1FFFFFFF) for i in range(9)))
         out.append("    static constexpr int TWO_ADICITY = %d;" % two_adicity)
         out.append("    static constexpr uint32_t ROOT[%d] = {%s};  /* a root of unity of order 2^TWO_ADICITY, Montgomery form */"
                    % (n, limbs(root * Rm % mod, n)))

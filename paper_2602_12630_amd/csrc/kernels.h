@@ -3288,11 +3288,15 @@ struct InterpAxisBarycentric {
  * Bound by the multiply-adds of those products (84 to 95 a nanosecond); 2 097 152 entries: axis of 4096 183 -> 2.43 ms,
  * axis of 512 56 -> 1.45 ms against the differences line by line, and 0.30 ms for the tables of both axes. */
 struct alignas(16) FrHalf { uint32_t v[4]; };
+struct alignas(16) Fr29Entry {          /* an element of a table in 29-bit limbs */
+    fr29 v;
+    uint32_t unused[3];
+};
 struct InterpRoots {           /* lane t: roots[t] = omega_(2 s)^j and twist[t] = roots[t] / s for t = s + j, s = 2^k, j < s */
     fr_t order[17];            /* order[k]: root of unity of order 2^k */
     fr_t half_pow[17];         /* 2^-k */
-    fr_t* roots;
-    fr_t* twist;
+    Fr29Entry* roots;
+    Fr29Entry* twist;
     TC_DEV void operator()(uint32_t t) const {
         if (t == 0) return;
         int k = 31 - __builtin_clz(t);
@@ -3300,8 +3304,8 @@ struct InterpRoots {           /* lane t: roots[t] = omega_(2 s)^j and twist[t] 
         fr_t v = fe_one<FrParams>();
         for (int b = 0; b < k; ++b)
             if (j >> b & 1u) v = fr_mul(v, order[k + 1 - b]);
-        roots[t] = v;
-        twist[t] = fr_mul(v, half_pow[k]);
+        roots[t].v = fr29_from_fr(v);
+        twist[t].v = fr29_from_fr(fr_mul(v, half_pow[k]));
     }
 };
 struct InterpWeights {         /* lane l: beta_l / n = (-1)^(d-1-l) / (n l! (d-1-l)!), nodes 1 .. d */
@@ -3314,41 +3318,62 @@ struct InterpWeights {         /* lane l: beta_l / n = (-1)^(d-1-l) / (n l! (d-1
         weights[l] = ((d - 1 - l) & 1u) ? fr_neg(v) : v;
     }
 };
-struct InterpTile {            /* elements of a tile in LDS, and the transforms on blocks of them */
+/* Elements of a tile in LDS, in 29-bit limbs, and the transforms on blocks of them.  Bound by the instructions of the products: a butterfly is
+ * one product and some 45 limb operations, few values being reduced along the way.  Bounds, in multiples of r (the factors from
+ * the tables are within 0.6): what enters is within 1.4, a stage of the inverse adds 1.2 to it (11 stages at most), the twist leaves 1.2, a stage
+ * of the forward transform doubles the sums, which every fourth stage reduces (20 at most).  Limbs: the inverse's stages of odd number carry what their predecessor left at 2^30, the forward stages
+ * carry their sums; a difference of normal operands is one limb of 29 bits either sign.
+ * 512 x 4096 entries: the two axes 1.09 and 1.84 ms (111 G products/s), 1.46 and 2.44 ms in the 32-bit form with everything reduced. */
+struct InterpTile {
     FrHalf* lo;
     FrHalf* hi;
-    const fr_t* roots;
-    const fr_t* twist;
-    TC_DEV fr_t get(uint32_t i) const {
+    int32_t* top;
+    const Fr29Entry* roots;
+    const Fr29Entry* twist;
+    TC_DEV InterpTile(uint8_t* lds, uint32_t tile, const Fr29Entry* r, const Fr29Entry* t)
+        : lo((FrHalf*)lds), hi((FrHalf*)lds + tile), top((int32_t*)((FrHalf*)lds + 2 * tile)), roots(r), twist(t) {}
+    TC_DEV fr29 get(uint32_t i) const {
         FrHalf a = lo[i], b = hi[i];
-        fr_t r;
+        fr29 r;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) { r.l[k] = a.v[k]; r.l[4 + k] = b.v[k]; }
+        for (int k = 0; k < 4; ++k) { r.l[k] = (int32_t)a.v[k]; r.l[4 + k] = (int32_t)b.v[k]; }
+        r.l[8] = top[i];
         return r;
     }
-    TC_DEV void put(uint32_t i, const fr_t& r) const {
+    TC_DEV void put(uint32_t i, const fr29& r) const {
         FrHalf a, b;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) { a.v[k] = r.l[k]; b.v[k] = r.l[4 + k]; }
+        for (int k = 0; k < 4; ++k) { a.v[k] = (uint32_t)r.l[k]; b.v[k] = (uint32_t)r.l[4 + k]; }
         lo[i] = a;
         hi[i] = b;
+        top[i] = r.l[8];
     }
-    /* x / omega_(2 s)^j up to the sign: omega_(2 s)^(-j) = -omega_(2 s)^(s - j) */
-    TC_DEV void inverse_butterfly(uint32_t s, uint32_t j, fr_t& u, fr_t& v) const {
-        if (s > 1) v = fr_mul(v, roots[j ? 2 * s - j : s]);
-        fr_t a = fr_add(u, v), b = fr_sub(u, v);
-        u = j ? b : a;
-        v = j ? a : b;
+    /* x / omega_(2 s)^j up to the sign: omega_(2 s)^(-j) = -omega_(2 s)^(s - j).  Stage k, s = 2^k. */
+    TC_DEV void inverse_butterfly(uint32_t k, uint32_t j, fr29& u, fr29& v) const {
+        const uint32_t s = 1u << k;
+        if (s > 1) v = fr29_mul(v, roots[j ? 2 * s - j : s].v);
+        fr29 a = fr29_add(u, v), b = fr29_sub(u, v);
+        if (k & 1u) {
+            a = fr29_carry(a);
+            b = fr29_carry(b);
+        }
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            u.l[i] = j ? b.l[i] : a.l[i];
+            v.l[i] = j ? a.l[i] : b.l[i];
+        }
     }
-    TC_DEV void forward_butterfly(uint32_t s, uint32_t j, fr_t& u, fr_t& v) const {
-        fr_t a = fr_add(u, v), b = fr_sub(u, v);
-        u = a;
-        v = s > 1 ? fr_mul(b, roots[s + j]) : b;
+    /* stage k of t - 1 .. 0 */
+    TC_DEV void forward_butterfly(int t, uint32_t k, uint32_t j, fr29& u, fr29& v) const {
+        const uint32_t s = 1u << k;
+        const fr29 a = fr29_add(u, v), b = fr29_sub(u, v);
+        u = ((t - (int)k) & 3) == 0 ? fr29_reduce(a) : fr29_carry(a);
+        v = s > 1 ? fr29_mul(b, roots[s + j].v) : b;
     }
     TC_DEV void inverse_stage(uint32_t k, uint32_t p) const {
         uint32_t s = 1u << k, j = p & (s - 1), i = (p >> k << (k + 1)) + j;
-        fr_t u = get(i), v = get(i + s);
-        inverse_butterfly(s, j, u, v);
+        fr29 u = get(i), v = get(i + s);
+        inverse_butterfly(k, j, u, v);
         put(i, u);
         put(i + s, v);
     }
@@ -3359,19 +3384,20 @@ struct InterpTile {            /* elements of a tile in LDS, and the transforms 
         if (e < t - 1) return inverse_stage((uint32_t)e, p);
         uint32_t k = (uint32_t)(e == t - 1 ? t - 1 : 2 * t - 2 - e);
         uint32_t s = 1u << k, j = p & (s - 1), i = (p >> k << (k + 1)) + j;
-        fr_t u = get(i), v = get(i + s);
+        fr29 u = get(i), v = get(i + s);
         if (e == t - 1) {
-            inverse_butterfly(s, j, u, v);
-            u = fr_mul(u, twist[2 * s + j]);
-            v = fr_mul(v, twist[3 * s + j]);
+            inverse_butterfly(k, j, u, v);
+            u = fr29_mul(u, twist[2 * s + j].v);
+            v = fr29_mul(v, twist[3 * s + j].v);
         }
-        forward_butterfly(s, j, u, v);
+        forward_butterfly(t, k, j, u, v);
         put(i, u);
         put(i + s, v);
     }
 };
+constexpr size_t INTERP_ELEMENT_BYTES = 36;
 /* M of all nodes with 2^t leaves of an axis, at t << logn: even[i], odd[i] = values of the node of leaf i on its own
- * domain and on the odd powers of its parent's root.  All distinct axes of a call in the same launches: a table is a
+ * domain and on the odd powers of its parent's root, packed (fr29_pack).  All distinct axes of a call in the same launches: a table is a
  * chain of some hundred dependent products however short the axis. */
 struct InterpTables {
     fr_t* even;
@@ -3386,7 +3412,7 @@ struct InterpNodesDirect {
     static constexpr int LEVELS = 6;
     InterpTables axis[INTERP_MAX_AXES];
     uint32_t first[INTERP_MAX_AXES + 1];      /* lanes: axis, then level, then even / odd, then leaf */
-    const fr_t* roots;
+    const Fr29Entry* roots;
     static uint32_t lanes(const InterpTables& a) { return (uint32_t)(a.logn < LEVELS ? a.logn : LEVELS) << (a.logn + 1); }
     TC_DEV void operator()(uint32_t lane) const {
         uint32_t x = 0;
@@ -3397,7 +3423,7 @@ struct InterpNodesDirect {
         /* the point: power m of the root of order 2 h */
         uint32_t j = g & (h - 1), m = odd;
         for (uint32_t b = 0; b < t; ++b) m |= (j >> b & 1u) << (t - b);
-        fr_t point = roots[h + (m & (h - 1))], v = fe_one<FrParams>();
+        fr_t point = fr29_to_fr(roots[h + (m & (h - 1))].v), v = fe_one<FrParams>();
         if (m >= h) point = fr_neg(point);
         const uint32_t lo = g - j, hi = lo + h < a.d ? lo + h : a.d;
         fr_t zeta = fe_from_u32<FrParams>(lo + 1);
@@ -3405,7 +3431,7 @@ struct InterpNodesDirect {
             v = fr_mul(v, fr_sub(point, zeta));
             zeta = fr_add(zeta, fe_one<FrParams>());
         }
-        (odd ? a.odd : a.even)[((size_t)t << a.logn) + g] = v;
+        (odd ? a.odd : a.even)[((size_t)t << a.logn) + g] = fr29_pack(fr29_from_fr(v));
     }
 };
 /* The larger ones level by level, each from the tables of t - 1; a workgroup takes max(2^t, 256) elements.  M of a full
@@ -3413,11 +3439,11 @@ struct InterpNodesDirect {
 struct InterpNodeTables {
     static constexpr int BLOCK = 1024;
     static constexpr uint32_t TILE = 2048, CHUNK = 256;
-    static constexpr size_t LDS_BYTES = TILE * 32;
+    static constexpr size_t LDS_BYTES = TILE * INTERP_ELEMENT_BYTES;
     InterpTables axis[INTERP_MAX_AXES];
     uint32_t first[INTERP_MAX_AXES + 1];      /* workgroups */
-    const fr_t* roots;
-    const fr_t* twist;
+    const Fr29Entry* roots;
+    const Fr29Entry* twist;
     int t;
     static uint32_t chunk(const InterpTables& a, int t) {
         uint32_t n = 1u << a.logn, least = n < CHUNK ? n : CHUNK;
@@ -3428,7 +3454,7 @@ struct InterpNodeTables {
         uint32_t ax = 0;
         while (wg >= first[ax + 1]) ++ax;
         const InterpTables& a = axis[ax];
-        InterpTile x{(FrHalf*)lds, (FrHalf*)lds + TILE, roots, twist};
+        const InterpTile x(lds, TILE, roots, twist);
         const uint32_t n = 1u << a.logn, h = 1u << t, least = n < CHUNK ? n : CHUNK, elements = h > least ? h : least;
         const uint32_t base = (wg - first[ax]) * elements;
         fr_t* even = a.even + ((size_t)t << a.logn);
@@ -3437,18 +3463,19 @@ struct InterpNodeTables {
             for (uint32_t i = lane; i < elements; i += BLOCK) {
                 uint32_t g = base + i, j = g & (h - 1), half = h >> 1, left = g - j + (j & (half - 1));
                 const fr_t* below = (j < half ? even : odd) - n;
-                fr_t v = fr_mul(below[left], below[left + half]);
-                even[g] = v;
+                const fr29 v = fr29_mul(fr29_unpack(below[left]), fr29_unpack(below[left + half]));
+                even[g] = fr29_pack(v);
                 x.put(i, v);
             }
         } else if (ph <= InterpTile::extend_stages(t)) {
             for (uint32_t p = lane; p < elements / 2; p += BLOCK) x.extend_stage(t, ph - 1, p);
         } else {
-            const fr_t two = fe_from_u32<FrParams>(2);
+            const fr29 two = fr29_from_fr(fe_from_u32<FrParams>(2));
             for (uint32_t i = lane; i < elements; i += BLOCK) {
                 uint32_t g = base + i;
-                fr_t v = x.get(i);
-                odd[g] = ((g >> t) + 1) << t <= a.d ? fr_sub(v, two) : v;
+                fr29 v = fr29_reduce(x.get(i));
+                if (((g >> t) + 1) << t <= a.d) v = fr29_reduce(fr29_sub(v, two));
+                odd[g] = fr29_pack(v);
             }
         }
     }
@@ -3456,15 +3483,15 @@ struct InterpNodeTables {
 struct InterpAxisTree {
     static constexpr int BLOCK = 1024;
     static constexpr uint32_t TILE = 4096;
-    static constexpr size_t LDS_BYTES = TILE * 32;
+    static constexpr size_t LDS_BYTES = TILE * INTERP_ELEMENT_BYTES;
     fr_t* data;                /* (outer, d, inner), in place */
-    fr_t* half;                /* 2^(logn - 1) elements per line: the even half of a level while the odd half is computed */
+    fr_t* half;                /* 2^(logn - 1) elements per line: the even half of a level while the odd half is computed (packed limbs) */
     uint64_t outer, inner;
     uint32_t d, lines_per_wg;
     int logn;                  /* lines_per_wg << logn <= TILE */
     const fr_t* weights;
-    const fr_t* roots;
-    const fr_t* twist;
+    const Fr29Entry* roots;
+    const Fr29Entry* twist;
     const fr_t* even;          /* tables of level t at t << logn */
     const fr_t* odd;
     int phases() const {
@@ -3474,7 +3501,7 @@ struct InterpAxisTree {
     }
     TC_DEV fr_t* element(uint64_t line, uint32_t k) const { return data + ((line / inner) * d + k) * inner + line % inner; }
     TC_DEV void phase(int ph, uint32_t lane, uint32_t wg, uint8_t* lds) const {
-        InterpTile x{(FrHalf*)lds, (FrHalf*)lds + TILE, roots, twist};
+        const InterpTile x(lds, TILE, roots, twist);
         const uint64_t first = (uint64_t)wg * lines_per_wg, left = outer * inner - first;
         const uint32_t lines = left < lines_per_wg ? (uint32_t)left : lines_per_wg;       /* fewer in the last workgroup */
         const uint32_t n = 1u << logn, elements = lines << logn, pairs = elements >> 1;
@@ -3482,7 +3509,7 @@ struct InterpAxisTree {
             /* neighbouring lines first where they are neighbours in memory */
             for (uint32_t i = lane; i < elements; i += BLOCK) {
                 uint32_t local = inner > 1 ? i % lines : i >> logn, k = inner > 1 ? i / lines : i & (n - 1);
-                x.put((local << logn) + k, k < d ? fr_mul(*element(first + local, k), weights[k]) : fe_zero<FrParams>());
+                x.put((local << logn) + k, k < d ? fr29_mul(fr29_cut<5>(*element(first + local, k)), fr29_from_fr(weights[k])) : fr29{});
             }
             return;
         }
@@ -3499,12 +3526,12 @@ struct InterpAxisTree {
                 fr_t* keep = half + (first << (logn - 1));
                 for (uint32_t p = lane; p < pairs; p += BLOCK) {
                     uint32_t i = (p >> t << (t + 1)) + (p & (h - 1)), at = i & (n - 1);
-                    fr_t v = fr_add(fr_mul(x.get(i), m[at + h]), fr_mul(x.get(i + h), m[at]));
+                    const fr29 v = fr29_mul_add(x.get(i), fr29_unpack(m[at + h]), x.get(i + h), fr29_unpack(m[at]));
                     if (at_odd) {
-                        x.put(i, keep[p]);
+                        x.put(i, fr29_unpack(keep[p]));
                         x.put(i + h, v);
                     } else {
-                        keep[p] = v;
+                        keep[p] = fr29_pack(v);        /* within 1.1 r either way: a number of 256 bits and a sign in it */
                     }
                 }
             } else {
@@ -3515,7 +3542,7 @@ struct InterpAxisTree {
         } else {
             for (uint32_t i = lane; i < elements; i += BLOCK) {
                 uint32_t local = inner > 1 ? i % lines : i >> logn, k = inner > 1 ? i / lines : i & (n - 1);
-                if (k < d) *element(first + local, k) = x.get((local << logn) + k);
+                if (k < d) *element(first + local, k) = fr29_to_fr(fr29_carry(x.get((local << logn) + k)));
             }
         }
     }

@@ -3351,8 +3351,8 @@ static int interp_plan(tc_ctx* ctx, InterpPlan& plan, uint32_t count, const uint
         a.odd = odd;
         ++plan.count;
     }
-    WS(d_roots, fr_t, 1u << logmax);
-    WS(d_twist, fr_t, 1u << logmax);
+    WS(d_roots, Fr29Entry, 1u << logmax);
+    WS(d_twist, Fr29Entry, 1u << logmax);
     roots.roots = d_roots;
     roots.twist = d_twist;
     RT(rt::launch<64>(1u << logmax, ctx->stream, roots));

@@ -223,6 +223,16 @@ def test_cooperative_reduction(hm):
             assert (got is ec.INF and w is ec.INF) or got == w, (len(pts), spread)
 
 
+def test_fr_product_in_29_bit_limbs(hm):
+    """a b 2^-256 mod r, canonical, for operands up to 2^256 - 1 against operands below r (what the 32-bit form takes)."""
+    rng = random.Random(14)
+    edge = [0, 1, 2, R - 1, R - 2, (R - 1) // 2, (1 << 255) - 1, (1 << 29) - 1, (1 << 232) - 1, 0xFFFFFFFF << 200] + [1 << k for k in range(0, 255, 29)]
+    inv = pow(1 << 256, -1, R)
+    for a in edge + [(1 << 256) - 1, R, R + 1, 2 * R] + [rng.randrange(1 << 256) for _ in range(200)]:
+        for b in [e % R for e in edge] + [rng.randrange(R) for _ in range(4)]:
+            assert _call2(hm.hm_fr_mul_limbs29, a, b, 32) == a * b * inv % R
+
+
 def test_product_spread_over_lanes(hm):
     """a b 2^-392 (mod p) with the limbs at the bounds that the group law relies on: 2^29.6 on both sides, 2^30 - 4 against a normal
     operand; the result's limbs are normal and its value is below a b / 2^392 + 2 p.  (The host form stops on a limb sum that leaves
