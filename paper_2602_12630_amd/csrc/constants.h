@@ -40,6 +40,12 @@ struct Fp28Params {
     static constexpr int32_t INV_FIX[14] = {0x4d1dd0e, 0x41d94cc, 0x109f399, 0x8cb551c, 0x2b7ff56, 0x980df0c, 0x71cc8ea, 0x76862c6, 0xbf76e0c, 0xae37e1d, 0x527bf47, 0xb194cef, 0x04d56b3, 0x0008347};  /* 2^1168 mod p: 1 / a (mod p) -> the 28-bit form of R^2 / a, R = 2^384 */
     static constexpr int32_t INV_START[14] = {0x10370ed, 0x6d1c345, 0xe243d62, 0xec45c53, 0x3b1d65a, 0x093317d, 0xb4f36a0, 0x5d74088, 0xc10ea72, 0x865d118, 0x7320a75, 0xfd5cd50, 0xcc8a759, 0x000c8d4};  /* 2^784 mod p: a R -> R / a under the radix R = 2^392 */
 };
+struct Fp30Params {
+    static constexpr int32_t NINV = 1073545213;              /* -p^-1 mod 2^30 */
+    static constexpr int32_t PINV = 196611;              /* p^-1 mod 2^30 */
+    static constexpr int32_t MOD[13] = {-21845, -402915328, 356515836, -352321620, -252304353, 55215067, 288093811, 316751073, -321428361, 517541167, -375082566, -91332614, 1704210};
+    static constexpr int32_t ONE[13] = {13762350, 433586176, -192935228, -301937177, 37952645, -425753694, -36732706, 162803105, -437337492, 366579475, 78814996, -442511456, 89578};   /* 2^390 mod p */
+};
 #define TC_WAVE28_ROWS \
     {0x002faabbu, 0x04c203d2u, 0x02c07e7au, 0x018f8f15u, 0x06c7b6b8u, 0x0961f5b3u, 0x0e3a59f5u, 0x0f43940du, 0x0de40cc3u, 0x0ef9c7a5u, 0x025598bbu, 0x0c2b4463u, 0x01b1fd61u, 0x00019fc3u, 0, 0}, /* (c p + 1) / 2^28, c = -1 / p mod 2^28 */ \
     {0x0fffaaabu, 0x0fefffffu, 0x03ffffb9u, 0x0fffeb15u, 0x06241eabu, 0x0a0f6b0fu, 0x0f6730d2u, 0x0f38512bu, 0x04774b84u, 0x04bacd76u, 0x0ba7b643u, 0x0e69a4b1u, 0x01ea397fu, 0x0001a011u, 0, 0}, /* p */ \

@@ -389,6 +389,15 @@ TC_HD fr29 fr29_cut(const fr_t& a) {
     }
     return r;
 }
+/* acc += x y, one chain of multiply-adds to a column: left to itself the compiler starts a column from zero and joins it to the
+ * carry of the one before with an addition; a second use of every partial sum (of no instruction) keeps the sums as they are
+ * written.  (As an operand that is written the sum would cost a wait state before each multiply-add that follows.) */
+TC_HD void mac_chain(int64_t& acc, int32_t x, int32_t y) {
+    acc += (int64_t)x * (int64_t)y;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" :: "v"(acc));
+#endif
+}
 /* a b 2^-261, or (a b + c e) 2^-261 under one reduction */
 template <bool TWO>
 TC_HD fr29 fr29_mont(const fr29& a, const fr29& b, const fr29& c, const fr29& e) {
@@ -398,13 +407,13 @@ TC_HD fr29 fr29_mont(const fr29& a, const fr29& b, const fr29& c, const fr29& e)
 #pragma unroll
     for (int k = 0; k < 17; ++k) {
 #pragma unroll
-        for (int i = (k < 9 ? 0 : k - 8); i <= (k < 9 ? k : 8); ++i) acc += (int64_t)a.l[i] * (int64_t)b.l[k - i];
+        for (int i = (k < 9 ? 0 : k - 8); i <= (k < 9 ? k : 8); ++i) mac_chain(acc, a.l[i], b.l[k - i]);
         if (TWO) {
 #pragma unroll
-            for (int i = (k < 9 ? 0 : k - 8); i <= (k < 9 ? k : 8); ++i) acc += (int64_t)c.l[i] * (int64_t)e.l[k - i];
+            for (int i = (k < 9 ? 0 : k - 8); i <= (k < 9 ? k : 8); ++i) mac_chain(acc, c.l[i], e.l[k - i]);
         }
 #pragma unroll
-        for (int i = (k < 9 ? 0 : k - 8); i < (k < 9 ? k : 9); ++i) acc += (int64_t)q[i] * (int64_t)FrParams::NEG29[k - i];
+        for (int i = (k < 9 ? 0 : k - 8); i < (k < 9 ? k : 9); ++i) mac_chain(acc, q[i], FrParams::NEG29[k - i]);
         const int32_t low = (int32_t)((uint32_t)acc & FR29_MASK);
         if (k < 9) q[k] = low; else r.l[k - 9] = low;
         acc >>= 29;                        /* arithmetic: the sum is signed */

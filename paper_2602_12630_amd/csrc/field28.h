@@ -82,11 +82,15 @@ TC_HD fp28 fp28_carry(const fp28& a) {
  * so that the low 28 bits of the column vanish.  The difference of two products costs one reduction, not two; its
  * column sums must obey the bound above with both products counted. */
 enum { FP28_MUL = 0, FP28_SQR = 1, FP28_MUL_SUB = 2 };
-/* acc += x y.  (The compiler starts every column of the scan from zero and joins it to the carry of the column
- * before with a 64-bit addition; multiply-adds written out as one chain per column save those 26 additions and cost
- * a wait state between dependent multiply-adds: no faster with three waves per SIMD, slower with fewer.) */
-TC_HD void fp28_mac(int64_t& acc, int32_t x, int32_t y) { acc += (int64_t)x * (int64_t)y; }
-template <int MODE>
+/* acc += x y: as one chain per column (mac_chain) in products expanded in place, for kernels of two or three waves per SIMD; as the
+ * compiler likes it, a column from zero joined to the carry of the column before with an addition, in those that are calls, whose
+ * kernels run a wave alone on its SIMD and would wait for each multiply-add (a lone commitment of 2^21 terms 728 against 740 us). */
+template <bool CHAIN>
+TC_HD void fp28_mac(int64_t& acc, int32_t x, int32_t y) {
+    if (CHAIN) mac_chain(acc, x, y);
+    else acc += (int64_t)x * (int64_t)y;
+}
+template <int MODE, bool CHAIN>
 TC_HD fp28 fp28_mont(const fp28& a, const fp28& b, const fp28& c, const fp28& e) {
     int64_t acc = 0;
     int32_t q[14], d[14];
@@ -104,24 +108,24 @@ TC_HD fp28 fp28_mont(const fp28& a, const fp28& b, const fp28& c, const fp28& e)
         const int lo = k < 14 ? 0 : k - 13, hi = k < 14 ? k : 13;
         if (MODE == FP28_SQR) {
 #pragma unroll
-            for (int i = lo; i < k - i; ++i) fp28_mac(acc, d[i], a.l[k - i]);
-            if ((k & 1) == 0) fp28_mac(acc, a.l[k / 2], a.l[k / 2]);
+            for (int i = lo; i < k - i; ++i) fp28_mac<CHAIN>(acc, d[i], a.l[k - i]);
+            if ((k & 1) == 0) fp28_mac<CHAIN>(acc, a.l[k / 2], a.l[k / 2]);
         } else {
 #pragma unroll
-            for (int i = lo; i <= hi; ++i) fp28_mac(acc, a.l[i], b.l[k - i]);
+            for (int i = lo; i <= hi; ++i) fp28_mac<CHAIN>(acc, a.l[i], b.l[k - i]);
         }
         if (MODE == FP28_MUL_SUB) {
 #pragma unroll
-            for (int i = lo; i <= hi; ++i) fp28_mac(acc, d[i], e.l[k - i]);
+            for (int i = lo; i <= hi; ++i) fp28_mac<CHAIN>(acc, d[i], e.l[k - i]);
         }
         if (k < 14) {
 #pragma unroll
-            for (int i = 0; i < k; ++i) fp28_mac(acc, q[i], Fp28Params::MOD[k - i]);
+            for (int i = 0; i < k; ++i) fp28_mac<CHAIN>(acc, q[i], Fp28Params::MOD[k - i]);
             q[k] = (int32_t)(((uint32_t)acc * (uint32_t)Fp28Params::NINV) & (uint32_t)FP28_MASK);
-            fp28_mac(acc, q[k], Fp28Params::MOD[0]);
+            fp28_mac<CHAIN>(acc, q[k], Fp28Params::MOD[0]);
         } else {
 #pragma unroll
-            for (int i = lo; i <= 13; ++i) fp28_mac(acc, q[i], Fp28Params::MOD[k - i]);
+            for (int i = lo; i <= 13; ++i) fp28_mac<CHAIN>(acc, q[i], Fp28Params::MOD[k - i]);
             r.l[k - 14] = (int32_t)((uint32_t)acc & (uint32_t)FP28_MASK);
         }
         acc >>= 28;                        /* arithmetic: the accumulator is signed */
@@ -132,9 +136,9 @@ TC_HD fp28 fp28_mont(const fp28& a, const fp28& b, const fp28& c, const fp28& e)
 /* expanded in place: for a kernel whose loop is a handful of products and nothing else (no operand shuffling around
  * calls, and the scheduler sees across products).  The fused difference exists in this form only: the four operands
  * of a call would not fit the 32 registers in which arguments travel. */
-TC_HD fp28 fp28_mul_inline(const fp28& a, const fp28& b) { return fp28_mont<FP28_MUL>(a, b, a, a); }
-TC_HD fp28 fp28_sqr_inline(const fp28& a) { return fp28_mont<FP28_SQR>(a, a, a, a); }
-TC_HD fp28 fp28_mul_sub_inline(const fp28& a, const fp28& b, const fp28& c, const fp28& e) { return fp28_mont<FP28_MUL_SUB>(a, b, c, e); }
+TC_HD fp28 fp28_mul_inline(const fp28& a, const fp28& b) { return fp28_mont<FP28_MUL, true>(a, b, a, a); }
+TC_HD fp28 fp28_sqr_inline(const fp28& a) { return fp28_mont<FP28_SQR, true>(a, a, a, a); }
+TC_HD fp28 fp28_mul_sub_inline(const fp28& a, const fp28& b, const fp28& c, const fp28& e) { return fp28_mont<FP28_MUL_SUB, true>(a, b, c, e); }
 
 #if defined(__HIP_DEVICE_COMPILE__)
 /* real functions on the device, as for the 32-bit form: operands and result travel in VGPRs */
@@ -147,10 +151,12 @@ __device__ __forceinline__ fp28 fp28_unpack(i32x4 a0, i32x4 a1, i32x4 a2, i32x2 
     return a;
 }
 __device__ __attribute__((noinline)) fp28 fp28_mul_call(i32x4 a0, i32x4 a1, i32x4 a2, i32x2 a3, i32x4 b0, i32x4 b1, i32x4 b2, i32x2 b3) {
-    return fp28_mul_inline(fp28_unpack(a0, a1, a2, a3), fp28_unpack(b0, b1, b2, b3));
+    const fp28 a = fp28_unpack(a0, a1, a2, a3), b = fp28_unpack(b0, b1, b2, b3);
+    return fp28_mont<FP28_MUL, false>(a, b, a, a);
 }
 __device__ __attribute__((noinline)) fp28 fp28_sqr_call(i32x4 a0, i32x4 a1, i32x4 a2, i32x2 a3) {
-    return fp28_sqr_inline(fp28_unpack(a0, a1, a2, a3));
+    const fp28 a = fp28_unpack(a0, a1, a2, a3);
+    return fp28_mont<FP28_SQR, false>(a, a, a, a);
 }
 #define TC_FP28_ARGS(a) i32x4{a.l[0], a.l[1], a.l[2], a.l[3]}, i32x4{a.l[4], a.l[5], a.l[6], a.l[7]}, i32x4{a.l[8], a.l[9], a.l[10], a.l[11]}, i32x2{a.l[12], a.l[13]}
 __device__ __forceinline__ fp28 fp28_mul(const fp28& a, const fp28& b) {

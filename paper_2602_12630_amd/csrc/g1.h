@@ -23,6 +23,7 @@
 #pragma once
 #include "field.h"
 #include "field28.h"
+#include "field30.h"
 
 namespace tc {
 

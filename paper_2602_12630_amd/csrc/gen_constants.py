@@ -151,6 +151,35 @@ def block28():
     return "\n".join(out)
 
 
+def balanced30(x):
+    """13 limbs of 30 bits, all but the top one in [-2^29, 2^29)"""
+    out = []
+    for _ in range(12):
+        d = (x + (1 << 29)) % (1 << 30) - (1 << 29)
+        out.append(d)
+        x = (x - d) >> 30
+    return out + [x]
+
+
+def block30():
+    """Fp in 13 balanced limbs of 30 bits, Montgomery radix 2^390 (the loop of the accumulation)."""
+    mod = balanced30(P_MOD)
+    # a column of twelve full terms of 2^59, or of twice as many of 2^58, the terms with a top limb below 2^27, q p and the carry
+    for k in range(25):
+        lo, hi = max(0, k - 12), min(12, k)
+        full = sum(1 for i in range(lo, hi + 1) if i != 12 and k - i != 12)
+        qp = sum(abs(mod[j]) for j in range(lo, hi + 1)) << 29
+        assert (full << 59) + ((hi - lo + 1 - full) << 57) + qp + (1 << 35) < 1 << 63
+    out = []
+    out.append("struct Fp30Params {")
+    out.append("    static constexpr int32_t NINV = %d;              /* -p^-1 mod 2^30 */" % ((-pow(P_MOD, -1, 1 << 30)) % (1 << 30)))
+    out.append("    static constexpr int32_t PINV = %d;              /* p^-1 mod 2^30 */" % pow(P_MOD, -1, 1 << 30))
+    out.append("    static constexpr int32_t MOD[13] = {%s};" % ", ".join(str(v) for v in mod))
+    out.append("    static constexpr int32_t ONE[13] = {%s};   /* 2^390 mod p */" % ", ".join(str(v) for v in balanced30((1 << 390) % P_MOD)))
+    out.append("};")
+    return "\n".join(out)
+
+
 def wave28():
     """Lane tables of the form that spreads an element over a row of sixteen lanes: limb j in lane j, lanes 14 and 15 zero."""
     c = (-pow(P_MOD, -1, 1 << 28)) % (1 << 28)
@@ -193,6 +222,7 @@ def main():
         block("FpParams", P_MOD, 12),
         block("FrParams", R_MOD, 8),
         block28(),
+        block30(),
         wave28(),
         "/* G1 generator, Montgomery form */",
         "static constexpr uint32_t G1_GEN_X[12] = {%s};" % limbs(GX * Rp % P_MOD, 12),

@@ -1008,41 +1008,25 @@ TC_HD uint32_t find_segment(const uint32_t* prefix, uint32_t n, uint32_t t) {
 }
 
 /* ---- MSM: balanced segmented sums per bucket -------------------------------------- */
-/* The accumulator lives in the 28-bit-limb form of the field (carry-free products and additions, expanded in place:
- * the loop is 3542 multiply-adds and little else); points enter by a re-cut of their limbs, the sum leaves through
+/* The accumulator lives in the 30-bit-limb form of the field (carry-free products and additions, expanded in place:
+ * the loop is 3104 multiply-adds and 850 other vector instructions an addition, 3542 and 1235 in 28-bit limbs; the launch of the
+ * LLaMA2-7B-shaped build 44 -> 37.7 ms, 144 registers); points enter by a re-cut of their limbs, the sum leaves through
  * one full reduction per coordinate.  The chord rule runs without its case distinctions.  When its denominator may
  * be zero in the field (equal or opposite points; told from its two lowest limbs, which practically no other value
  * passes) the lane gives its sub-run up and enters it in a list, and a second launch (AccAffineRedo) sums the
  * listed sub-runs with the routine that settles every case. */
-/* acc += (x2, y2), both finite; false (acc unusable) when the sum may be a doubling or the identity.
- * |P| <= 317 p in the first addition after acc was a re-cut affine point (coordinates 2^8 times larger than a
- * reduced value), <= 43 p in the second, <= 5 p from then on. */
-TC_HD bool xyzz28_madd_regular(g1_xyzz28& a, const fp28& x2, const fp28& y2) {
-    fp28 P = fp28_sub(fp28_mul_inline(x2, a.ZZ), a.X);
-    if (fp28_maybe_zero(P, 512u)) return false;
-    fp28 R = fp28_sub(fp28_mul_inline(y2, a.ZZZ), a.Y);
-    fp28 PP = fp28_sqr_inline(P);
-    fp28 PPP = fp28_mul_inline(P, PP);
-    fp28 Q = fp28_mul_inline(a.X, PP);
-    fp28 X3 = fp28_carry(fp28_sub(fp28_sub(fp28_sub(fp28_sqr_inline(R), PPP), Q), Q));
-    a.Y = fp28_mul_sub_inline(R, fp28_sub(Q, X3), a.Y, PPP);          /* limbs below 2^29 against 2^28, twice */
-    a.ZZ = fp28_mul_inline(a.ZZ, PP);
-    a.ZZZ = fp28_mul_inline(a.ZZZ, PPP);
-    a.X = X3;
-    return true;
-}
 /* Tables of the accumulation.  A table of 96-byte points at a stride of 96 bytes puts every second point across two
  * of the 128-byte lines in which the second-level cache fetches: 192 bytes per point gathered at a random index.
  * The SRS therefore keeps a copy of its first table at a stride of 128 bytes for the launches that gather from it;
  * other tables (suffix tables, row commitments used as bases) stay at 96.  A table pointer carries its kind in
  * bit 0 (tables start on 16-byte boundaries).
- * The 128 bytes have room for the point as the accumulation wants it: words 0..13 the 28-bit limbs of x, 14..27 those
- * of y (fp28_from_fp), so that a lane neither re-cuts the 32-bit limbs of every point it adds (56 instructions) nor
+ * The 128 bytes have room for the point as the accumulation wants it: words 0..12 the 30-bit limbs of x, 13..25 those
+ * of y (fp30_from_fp), so that a lane neither re-cuts the 32-bit limbs of every point it adds (56 instructions) nor
  * tests 24 words for the identity, which has -1 as the top limb of y (that limb of a point is below 2^28). */
 constexpr uint32_t PADDED_STRIDE = 128;
 struct PaddedPoint {
-    fp28 x, y;
-    uint32_t unused[4];
+    fp30 x, y;
+    uint32_t unused[6];
 };
 static_assert(sizeof(PaddedPoint) == PADDED_STRIDE, "one point per 128-byte line");
 TC_HD const g1_affine* tag_padded(const void* table) { return (const g1_affine*)((uintptr_t)table | 1u); }
@@ -1051,40 +1035,40 @@ TC_HD const PaddedPoint* padded_point(const g1_affine* tagged, uint32_t i) {
     return (const PaddedPoint*)(((uintptr_t)tagged & ~(uintptr_t)15u) + (uint64_t)i * PADDED_STRIDE);
 }
 /* limbs of x and y from seven 16-byte loads */
-TC_HD void padded_load(const PaddedPoint* q, fp28& x, fp28& y) {
+TC_HD void padded_load(const PaddedPoint* q, fp30& x, fp30& y) {
     Words16 c[7];
 #pragma unroll
     for (int k = 0; k < 7; ++k) c[k] = ((const Words16*)q)[k];
 #pragma unroll
-    for (int j = 0; j < 14; ++j) {
+    for (int j = 0; j < 13; ++j) {
         x.l[j] = (int32_t)c[j >> 2].w[j & 3];
-        y.l[j] = (int32_t)c[(14 + j) >> 2].w[(14 + j) & 3];
+        y.l[j] = (int32_t)c[(13 + j) >> 2].w[(13 + j) & 3];
     }
 }
 /* point i of either kind of table in the 32-bit form (the kernels off the fast path) */
 TC_HD g1_affine table_point(const g1_affine* tagged, uint32_t i) {
     if (table_is_padded(tagged)) {
-        fp28 x, y;
+        fp30 x, y;
         padded_load(padded_point(tagged, i), x, y);
-        if (y.l[13] < 0) return affine_identity();
+        if (y.l[12] < 0) return affine_identity();
         g1_affine p;
-        p.x = fp28_recut_to_fp(x);
-        p.y = fp28_recut_to_fp(y);
+        p.x = fp30_recut_to_fp(x);
+        p.y = fp30_recut_to_fp(y);
         return p;
     }
     return tagged[i];
 }
-struct PadPoints {            /* out: the points of `in`, one per 128 bytes, in 28-bit limbs */
+struct PadPoints {            /* out: the points of `in`, one per 128 bytes, in 30-bit limbs */
     const g1_affine* in;
     uint8_t* out;
     TC_DEV void operator()(uint32_t t) const {
         g1_affine p = in[t];
         PaddedPoint v;
-        v.x = fp28_from_fp(p.x);
-        v.y = fp28_from_fp(p.y);
-        if (affine_is_identity(p)) v.y.l[13] = -1;
+        v.x = fp30_from_fp(p.x);
+        v.y = fp30_from_fp(p.y);
+        if (affine_is_identity(p)) v.y.l[12] = -1;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v.unused[k] = 0;
+        for (int k = 0; k < 6; ++k) v.unused[k] = 0;
         *(PaddedPoint*)(out + (uint64_t)t * PADDED_STRIDE) = v;
     }
 };
@@ -1102,9 +1086,8 @@ TC_HD void subrun_bounds(const uint32_t* start, const uint32_t* lstart, uint32_t
     end = begin + low + (j < more ? 1u : 0u);
 }
 enum { TABLES_PLAIN = 0, TABLES_PADDED = 1, TABLES_MIXED = 2 };
-/* What the launch gathers from.  Only the kernel for padded tables alone stays within the 168 registers of three waves
- * per SIMD (162); the other two spill some forty registers, which costs the full-width problems at the end of a batch
- * of openings about 3 % (4.0 -> 4.1 ms of 58). */
+/* What the launch gathers from.  All three stay within the 168 registers of three waves per SIMD (144 for padded tables alone; a budget of
+ * four waves spills 120: 37.7 -> 47 ms). */
 template <int TABLES>
 struct AccAffine {
     const g1_affine* const* tables;   /* SRS table of problem p; bucket b belongs to problem b / nbk_pp */
@@ -1131,7 +1114,7 @@ struct AccAffine {
             out[t] = xyzz_from_affine(p);
             return;
         }
-        g1_xyzz28 acc;
+        g1_xyzz30 acc;
         bool have = false;                                        /* acc holds a point (the sum so far is not the identity) */
         /* the indices come four at a time (the list starts on a 16-byte boundary and its allocation ends on one): an
          * addition lasts long enough for the other waves to push a line out of the caches, and a lane that fetches
@@ -1145,26 +1128,26 @@ struct AccAffine {
             }
             uint32_t j = i & 3u;
             uint32_t e = j == 0u ? four.w[0] : j == 1u ? four.w[1] : j == 2u ? four.w[2] : four.w[3];
-            fp28 x2, y2;
+            fp30 x2, y2;
             if (TABLES == TABLES_PADDED || (TABLES == TABLES_MIXED && table_is_padded(pts))) {
                 padded_load(padded_point(pts, e & 0x7FFFFFFFu), x2, y2);
-                if (y2.l[13] < 0) continue;
+                if (y2.l[12] < 0) continue;
             } else {
                 g1_affine p = pts[e & 0x7FFFFFFFu];
                 if (affine_is_identity(p)) continue;
-                x2 = fp28_from_fp(p.x);
-                y2 = fp28_from_fp(p.y);
+                x2 = fp30_from_fp(p.x);
+                y2 = fp30_from_fp(p.y);
             }
-            if (e >> 31) y2 = fp28_sub(fp28{}, y2);
+            if (e >> 31) y2 = fp30_neg(y2);
             if (!have) {
-                acc.X = x2;
-                acc.Y = y2;
-                acc.ZZ = fp28_one();
-                acc.ZZZ = fp28_one();
+                acc.X = fp30_balance(x2);
+                acc.Y = fp30_balance(y2);
+                acc.ZZ = fp30_one();
+                acc.ZZZ = fp30_one();
                 have = true;
                 continue;
             }
-            if (!xyzz28_madd_regular(acc, x2, y2)) {
+            if (!xyzz30_madd_regular(acc, x2, y2)) {
                 redo_list[atomic_add_u32(redo_count, 1u)] = t;
                 return;
             }
@@ -1173,8 +1156,8 @@ struct AccAffine {
         if (!have) {
             r = xyzz_identity();
         } else {
-            r.X = fp28_to_fp_outlined(acc.X); r.Y = fp28_to_fp_outlined(acc.Y);
-            r.ZZ = fp28_to_fp_outlined(acc.ZZ); r.ZZZ = fp28_to_fp_outlined(acc.ZZZ);
+            r.X = fp30_to_fp_outlined(acc.X); r.Y = fp30_to_fp_outlined(acc.Y);
+            r.ZZ = fp30_to_fp_outlined(acc.ZZ); r.ZZZ = fp30_to_fp_outlined(acc.ZZZ);
         }
         out[t] = r;
     }
@@ -1672,8 +1655,11 @@ struct AccWave {
         if (table_is_padded(pts)) {
             const uint32_t* q = (const uint32_t*)padded_point(pts, e & 0x7FFFFFFFu);
             const wv one = wv_table(W28_ONE);
-            p.inf = q[27] == 0xFFFFFFFFu;
-            WV_LANES(const uint32_t j = lane & 15u; WV_AT(p.v) = lane < 32u ? (j < 14u ? q[14u * (lane >> 4) + j] : 0u) : WV_AT(one))
+            p.inf = q[25] == 0xFFFFFFFFu;
+            /* limb j: the bits 28 j - 2 .. 28 j + 25 of what stands there in 30-bit limbs, six places up */
+            WV_LANES(const uint32_t j = lane & 15u, o = 28u * j + 28u, i = o / 30u, sh = o % 30u; const uint32_t* c = q + 13u * ((lane >> 4) & 1u);
+                     const uint32_t limb = (i ? c[(i < 13u ? i : 13u) - 1u] >> sh : 0u) | (i < 13u ? c[i] << (30u - sh) : 0u);
+                     WV_AT(p.v) = lane < 32u ? (j < 14u ? limb & (uint32_t)FP28_MASK : 0u) : WV_AT(one))
         } else {
             p = wv_load_affine(pts + (e & 0x7FFFFFFFu));
         }
@@ -3348,10 +3334,12 @@ struct InterpTile {
         hi[i] = b;
         top[i] = r.l[8];
     }
+    /* a copy in registers: the products must not read the table limb by limb */
+    TC_DEV static fr29 entry(const Fr29Entry* table, uint32_t i) { return table[i].v; }
     /* x / omega_(2 s)^j up to the sign: omega_(2 s)^(-j) = -omega_(2 s)^(s - j).  Stage k, s = 2^k. */
     TC_DEV void inverse_butterfly(uint32_t k, uint32_t j, fr29& u, fr29& v) const {
         const uint32_t s = 1u << k;
-        if (s > 1) v = fr29_mul(v, roots[j ? 2 * s - j : s].v);
+        if (s > 1) v = fr29_mul(v, entry(roots, j ? 2 * s - j : s));
         fr29 a = fr29_add(u, v), b = fr29_sub(u, v);
         if (k & 1u) {
             a = fr29_carry(a);
@@ -3368,7 +3356,7 @@ struct InterpTile {
         const uint32_t s = 1u << k;
         const fr29 a = fr29_add(u, v), b = fr29_sub(u, v);
         u = ((t - (int)k) & 3) == 0 ? fr29_reduce(a) : fr29_carry(a);
-        v = s > 1 ? fr29_mul(b, roots[s + j].v) : b;
+        v = s > 1 ? fr29_mul(b, entry(roots, s + j)) : b;
     }
     TC_DEV void inverse_stage(uint32_t k, uint32_t p) const {
         uint32_t s = 1u << k, j = p & (s - 1), i = (p >> k << (k + 1)) + j;
@@ -3387,8 +3375,8 @@ struct InterpTile {
         fr29 u = get(i), v = get(i + s);
         if (e == t - 1) {
             inverse_butterfly(k, j, u, v);
-            u = fr29_mul(u, twist[2 * s + j].v);
-            v = fr29_mul(v, twist[3 * s + j].v);
+            u = fr29_mul(u, entry(twist, 2 * s + j));
+            v = fr29_mul(v, entry(twist, 3 * s + j));
         }
         forward_butterfly(t, k, j, u, v);
         put(i, u);

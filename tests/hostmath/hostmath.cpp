@@ -111,6 +111,23 @@ void hm_window_bits(const uint8_t* pts, uint32_t lognb, uint32_t windows, uint8_
     wave_run(WindowWave{scaled.data(), chains, nullptr, sum.data()}, windows);
     for (uint32_t w = 0; w < windows; ++w) pt_store(o + 96 * (size_t)w, xyzz_to_affine(sum[w]));
 }
+// 13 limbs of 30 bits, raw: mode 0 a b, 1 a^2, 2 a b - c e, 3 a b - f, 4 a^2 - f - 2 g, 5 balanced a, 6 the cut of an element
+void hm_fp30(int mode, const int32_t* in, int32_t* o) {
+    fp30 x[4], r{};
+    for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < 13; ++j) x[i].l[j] = in[13 * i + j];
+    if (mode == 0) r = fp30_mul(x[0], x[1]);
+    else if (mode == 1) r = fp30_sqr(x[0]);
+    else if (mode == 2) r = fp30_mul_sub(x[0], x[1], x[2], x[3]);
+    else if (mode == 3) r = fp30_mul_less(x[0], x[1], x[2]);
+    else if (mode == 4) r = fp30_mont<FP30_SQR, 2>(x[0], x[0], x[0], x[0], x[2], -1, x[3], -2);
+    else if (mode == 5) r = fp30_balance(x[0]);
+    for (int j = 0; j < 13; ++j) o[j] = r.l[j];
+}
+// value (raw limbs) -> canonical coordinate and back, and the zero test
+void hm_fp30_to_fp(const int32_t* in, uint8_t* o) { fp30 a; for (int j = 0; j < 13; ++j) a.l[j] = in[j]; fp_store(o, fp30_to_fp(a)); }
+int hm_fp30_recut(const uint8_t* a) { fp_t x = fp_load(a); return fe_eq(fp30_recut_to_fp(fp30_from_fp(x)), x) && fe_eq(fp30_to_fp(fp30_from_fp(x)), x); }
+int hm_fp30_maybe_zero(const int32_t* in, uint32_t K) { fp30 a; for (int j = 0; j < 13; ++j) a.l[j] = in[j]; return fp30_maybe_zero(a, K) ? 1 : 0; }
 // the form spread over lanes: a product of raw limbs (14 words each, four rows), and sums and doublings of points
 void hm_wave_mul(const uint32_t* a, const uint32_t* b, uint32_t* o) {
     wv x, y;

@@ -20,7 +20,7 @@ LIB = os.path.join(HERE, "hostmath", "libhostmath.so")
 
 @pytest.fixture(scope="module")
 def hm():
-    hdrs = [os.path.join(HERE, "..", "paper_2602_12630_amd", "csrc", h) for h in ("field.h", "field28.h", "g1.h", "constants.h", "kernels.h", "wave28.h", "rt.h", "pairing.h")]
+    hdrs = [os.path.join(HERE, "..", "paper_2602_12630_amd", "csrc", h) for h in ("field.h", "field28.h", "field30.h", "g1.h", "constants.h", "kernels.h", "wave28.h", "rt.h", "pairing.h")]
     newest = max(os.path.getmtime(f) for f in [SRC] + hdrs)
     if not os.path.exists(LIB) or os.path.getmtime(LIB) < newest:
         subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", LIB, SRC])
@@ -231,6 +231,50 @@ def test_fr_product_in_29_bit_limbs(hm):
     for a in edge + [(1 << 256) - 1, R, R + 1, 2 * R] + [rng.randrange(1 << 256) for _ in range(200)]:
         for b in [e % R for e in edge] + [rng.randrange(R) for _ in range(4)]:
             assert _call2(hm.hm_fr_mul_limbs29, a, b, 32) == a * b * inv % R
+
+
+def test_products_in_30_bit_limbs(hm):
+    """Products, squares, differences of products and products less known elements at the bounds of their limbs: balanced
+    ones at either end of their range, 30 bits either sign against balanced; results balanced and within the stated value."""
+    rng = random.Random(15)
+    radix, half = 1 << 390, 1 << 29
+    val = lambda l: sum(v << (30 * j) for j, v in enumerate(l))
+    bal = lambda: [rng.choice([-half, half - 1, rng.randrange(-half, half)]) for _ in range(12)] + [rng.randrange(-(1 << 26), 1 << 26)]
+    wide = lambda: [rng.choice([-2 * half + 1, 2 * half - 1, rng.randrange(-2 * half, 2 * half)]) for _ in range(12)] + [rng.randrange(-(1 << 26), 1 << 26)]
+    ends = lambda v: [v] * 12 + [1 << 26]
+
+    def run(mode, *x):
+        out = (ctypes.c_int32 * 13)()
+        x = list(x) + [[0] * 13] * (4 - len(x))
+        hm.hm_fp30(mode, (ctypes.c_int32 * 52)(*sum(x, [])), out)
+        return list(out)
+
+    for i in range(300):
+        a, b, c, e = (bal() for _ in range(4)) if i > 8 else (ends(rng.choice([-half, half - 1])) for _ in range(4))
+        w = wide() if i % 3 else ends(rng.choice([-2 * half + 1, 2 * half - 1]))
+        A, B, C, E, W = (val(v) for v in (a, b, c, e, w))
+        for mode, args, want, folded in ((0, (w, b), W * B, 0), (0, (a, w), A * W, 0), (1, (a,), A * A, 0), (2, (a, b, c, e), A * B - C * E, 0),
+                                         (3, (w, b, c), W * B, -C), (4, (a, b, c, e), A * A, -C - 2 * E)):
+            r = run(mode, *args)
+            assert (val(r) - folded) * radix % P == want % P, mode
+            assert all(-half <= v < half for v in r[:12])
+            assert abs(val(r) - folded) <= abs(want) / radix + 0.52 * P, mode
+        s = [x - y for x, y in zip(a, b)]
+        r = run(5, s)
+        assert val(r) == A - B and all(-half <= v < half for v in r[:12])
+    for v in [0, 1, -1, P, -P, 63 * P, -63 * P, 64 * P - 1, 1 - 64 * P] + [rng.randrange(-64 * P, 64 * P) for _ in range(200)]:
+        l, x = [], v
+        for _ in range(12):
+            d = (x + half) % (2 * half) - half
+            l.append(d)
+            x = (x - d) >> 30
+        l.append(x)
+        out = (ctypes.c_uint8 * 48)()
+        hm.hm_fp30_to_fp((ctypes.c_int32 * 13)(*l), out)
+        assert int.from_bytes(bytes(out), "little") * radix % P == v % P
+        assert hm.hm_fp30_maybe_zero((ctypes.c_int32 * 13)(*l), 128) == (v % P == 0)
+    for x in [0, 1, P - 1, (1 << 380) + 5] + [rng.randrange(P) for _ in range(100)]:
+        assert hm.hm_fp30_recut(_b(x, 48))
 
 
 def test_product_spread_over_lanes(hm):
