@@ -39,6 +39,7 @@ struct Fp28Params {
     static constexpr int GCD_ROUNDS = 29;                /* ceil((2 len(p) - 1) / 28) + 1 rounds of 28 steps */
     static constexpr int32_t INV_FIX[14] = {0x4d1dd0e, 0x41d94cc, 0x109f399, 0x8cb551c, 0x2b7ff56, 0x980df0c, 0x71cc8ea, 0x76862c6, 0xbf76e0c, 0xae37e1d, 0x527bf47, 0xb194cef, 0x04d56b3, 0x0008347};  /* 2^1168 mod p: 1 / a (mod p) -> the 28-bit form of R^2 / a, R = 2^384 */
     static constexpr int32_t INV_START[14] = {0x10370ed, 0x6d1c345, 0xe243d62, 0xec45c53, 0x3b1d65a, 0x093317d, 0xb4f36a0, 0x5d74088, 0xc10ea72, 0x865d118, 0x7320a75, 0xfd5cd50, 0xcc8a759, 0x000c8d4};  /* 2^784 mod p: a R -> R / a under the radix R = 2^392 */
+    static constexpr int32_t INV_SCALE[14] = {0x1f7b890, 0x294cc4d, 0x9f3af22, 0xb5ba56c, 0xcb5c0cc, 0xc0d975c, 0xc89a8c5, 0x6c968b4, 0x22672ea, 0x91de8c9, 0x35652a6, 0x84977c8, 0x424bbb9, 0x00141ab};  /* 2^1176 mod p: a plain 1 / a -> R^2 / a, R = 2^392 */
 };
 struct Fp30Params {
     static constexpr int32_t NINV = 1073545213;              /* -p^-1 mod 2^30 */

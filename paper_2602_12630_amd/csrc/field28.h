@@ -385,7 +385,8 @@ TC_HD fp_t fp_inv28(const fp_t& x) {
     return fp28_to_fp(fp28_mul(r, fix));
 }
 
-/* ---- inversion of one value by a whole wave ----------------------------------------------------
+/* ---- inversion of one value by a whole wave: the division steps ---------------------------------
+ * (what fp28_inv_wave falls back to)
  * Division steps (Bernstein, Yang, "Fast constant-time gcd computation and modular inversion", 2019) in the variant
  * that starts at delta = 1/2; D = delta - 1/2.  A step: if D >= 0 and g odd (f, g, D) <- (g, (g - f) / 2, -D), else
  * (f, g, D) <- (f, (g + (g mod 2) f) / 2, D + 1).  Only the low bits of f and g decide, so 28 steps need the lowest
@@ -436,9 +437,9 @@ static constexpr int FP28_INV_MAX_ROUNDS = 48;
  * multiply-adds, q p for the rows of d and e (a division by 2^28 modulo p), the shift by one limb and one lazy pass of
  * carries (dpp row shifts), limbs staying within [-2, 2^28 + 2] and the sign in limb 13.  d and e grow by at most p a
  * round, 48 p at the end.
- * Bound by the latency of the scalar steps: one wave, nothing to overlap. */
+ * Bound by the latency of the scalar steps, 30 us. */
 #if defined(__HIP_DEVICE_COMPILE__)
-__device__ __forceinline__ fp28 fp28_inv_wave(const fp28& x) {
+__device__ __forceinline__ fp28 fp28_inv_divsteps(const fp28& x) {
     const uint32_t lane = threadIdx.x & 63u, row = lane >> 4, limb = lane & 15u;
     /* selections by mask: written with ?: they become forty branches */
     const int32_t row_f = row == 0 ? -1 : 0, row_g = row == 1 ? -1 : 0, row_d = row == 2 ? -1 : 0, row_e = row == 3 ? -1 : 0;
@@ -481,10 +482,10 @@ __device__ __forceinline__ fp28 fp28_inv_wave(const fp28& x) {
     return fp28_carry(r);
 }
 #elif defined(__HIPCC__)
-__device__ fp28 fp28_inv_wave(const fp28& x);
+__device__ fp28 fp28_inv_divsteps(const fp28& x);
 #else
 /* the same rounds with the lanes of the wave written out as an array (host build of the kernels) */
-inline fp28 fp28_inv_wave(const fp28& x) {
+inline fp28 fp28_inv_divsteps(const fp28& x) {
     int32_t s[4][16] = {}, p[16] = {};
     for (int j = 0; j < 14; ++j) {
         s[0][j] = p[j] = Fp28Params::MOD[j];
@@ -516,6 +517,163 @@ inline fp28 fp28_inv_wave(const fp28& x) {
     fp28 r;
     for (int j = 0; j < 14; ++j) r.l[j] = neg ? -s[2][j] : s[2][j];
     return fp28_carry(r);
+}
+#endif
+
+/* ---- inversion of one value by a whole wave: Euclid's algorithm in batches ----------------------
+ * Lehmer's idea (1938): quotients are found on approximations, here doubles of the upper 112 bits of both numbers, and up to a dozen or two of
+ * them are collected in a 2 x 2 matrix of 28-bit entries before it is applied to the numbers and their cofactors.  Whatever the quotients are, a
+ * matrix of determinant 1 keeps the greatest common divisor and a = s x, b = t x (mod p), so an inexact quotient costs
+ * progress at most, no correctness: quotients are rounded products with an approximate reciprocal.  Row k of the wave holds a, b, s, t
+ * (k = 0 .. 3; a = p, b = x, s = 0, t = 1 at first), a lane one limb, lazily carried to [-2, 2^28 + 2], the sign in limb 13.  An upper bound of
+ * the lengths of a and b says which four limbs to look at; limbs above them only continue the sign.  It ends with one of the
+ * two numbers 0 and the other 1 or -1, whose cofactor is the inverse.  Numbers that a batch cannot bring closer (a quotient of more than 27 bits), more
+ * than INV_BATCHES of them, or an end other than that: the division steps take over (x = 0 among them).
+ * About 16 batches of 10 quotients.  Bound by latency, a chain of four double-precision operations a quotient; a normalisation with one
+ * point to a wave 36 -> 22.6 us (one quotient to a comparison and a branch: 27). */
+static constexpr int FP28_INV_BATCHES = 30;
+TC_HD double fp28_quotient(double A, double B) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_rint(A * __builtin_amdgcn_rcp(B));
+#else
+    return __builtin_rint(A * (1.0 / B));
+#endif
+}
+/* Quotients on (A, B) until a cofactor would pass 2^27, two at a time (a comparison and a branch cost as much as a quotient), then one more if it
+ * fits; m = (u0 v0 u1 v1): the numbers become u0 a + v0 b, u1 a + v1 b.  Returns whether they came closer. */
+TC_HD bool fp28_euclid_batch(double& A, double& B, int32_t (&m)[4]) {
+    constexpr double LIMIT = 134217728.0;
+    double u0 = 1.0, v0 = 0.0, u1 = 0.0, v1 = 1.0;
+    for (int i = 0; i < 64; ++i) {
+        const double q = fp28_quotient(A, B), r = __builtin_fma(-q, B, A), nu = __builtin_fma(-q, u1, u0), nv = __builtin_fma(-q, v1, v0);
+        const double p = fp28_quotient(B, r), t = __builtin_fma(-p, r, B), mu = __builtin_fma(-p, nu, u1), mv = __builtin_fma(-p, nv, v1);
+        /* (also false for the infinities and the not-a-number that a zero leads to) */
+        if (!((__builtin_fabs(nu) + __builtin_fabs(nv)) + (__builtin_fabs(mu) + __builtin_fabs(mv)) <= LIMIT)) break;
+        A = r; B = t;
+        u0 = nu; v0 = nv; u1 = mu; v1 = mv;
+    }
+    const double q = fp28_quotient(A, B), nu = __builtin_fma(-q, u1, u0), nv = __builtin_fma(-q, v1, v0);
+    if (__builtin_fabs(nu) + __builtin_fabs(nv) <= LIMIT) {
+        const double r = __builtin_fma(-q, B, A);
+        A = B; B = r;
+        u0 = u1; v0 = v1; u1 = nu; v1 = nv;
+    }
+    m[0] = (int32_t)u0; m[1] = (int32_t)v0; m[2] = (int32_t)u1; m[3] = (int32_t)v1;
+    return __builtin_fabs(u0) + __builtin_fabs(v0) + __builtin_fabs(u1) + __builtin_fabs(v1) > 2.0;
+}
+/* four limbs as a double: h 2^56 + l, h of 56 bits and a sign; with l of the sign of h, so that a small negative number is exact */
+TC_HD double fp28_window(int32_t l3, int32_t l2, int32_t l1, int32_t l0) {
+    const int64_t h = (int64_t)((uint64_t)((int64_t)l3 * (1 << 28) + l2) << 8) >> 8, l = (int64_t)l1 * (1 << 28) + l0;
+    const int64_t up = h < 0 ? 1 : 0;
+    return __builtin_fma((double)(h + up), 72057594037927936.0, (double)(l - up * ((int64_t)1 << 56)));
+}
+/* which limb is the upper one of the four for numbers below 2^bits, and the bound after a batch: what the approximations say, and for their errors
+ * 2^27 times a double's rounding of the larger of the numbers before (`was`) and the limbs left out */
+TC_HD int fp28_window_top(int bits) {
+    const int top = (bits + 29) / 28 - 1;
+    return top < 3 ? 3 : top > 13 ? 13 : top;
+}
+TC_HD int fp28_bits_after(double A, double B, double was, int top) {
+    const double bound = __builtin_fmax(__builtin_fabs(A), __builtin_fabs(B)) + was * 5.9604644775390625e-08 + (top > 3 ? 1073741824.0 : 0.0);
+    union { double d; uint64_t u; } e;
+    e.d = bound;
+    return 28 * (top - 3) + (int)(e.u >> 52) - 1022;
+}
+#if defined(__HIP_DEVICE_COMPILE__)
+__device__ __forceinline__ fp28 fp28_inv_wave(const fp28& x) {
+    const uint32_t lane = threadIdx.x & 63u, row = lane >> 4, limb = lane & 15u;
+    const int32_t row_a = row == 0 ? -1 : 0, row_b = row == 1 ? -1 : 0;
+    int32_t s = (row == 3 && limb == 0) ? 1 : 0;
+#pragma unroll
+    for (int j = 0; j < 14; ++j) {
+        const int32_t here = limb == (uint32_t)j ? -1 : 0;
+        s |= here & ((row_a & Fp28Params::MOD[j]) | (row_b & x.l[j]));
+    }
+    const bool odd_row = (row & 1u) != 0, low = limb < 13u;
+    int bits = 382;
+    double A = 0.0, B = 0.0;
+    bool done = false;
+    for (int batch = 0; batch < FP28_INV_BATCHES; ++batch) {
+        const int top = fp28_window_top(bits);
+        A = fp28_window(__builtin_amdgcn_readlane(s, top), __builtin_amdgcn_readlane(s, top - 1), __builtin_amdgcn_readlane(s, top - 2), __builtin_amdgcn_readlane(s, top - 3));
+        B = fp28_window(__builtin_amdgcn_readlane(s, 16 + top), __builtin_amdgcn_readlane(s, 15 + top), __builtin_amdgcn_readlane(s, 14 + top), __builtin_amdgcn_readlane(s, 13 + top));
+        if (top == 3 && (A == 0.0 || B == 0.0)) { done = true; break; }
+        const double was = __builtin_fmax(__builtin_fabs(A), __builtin_fabs(B));
+        int32_t m[4];
+        if (!fp28_euclid_batch(A, B, m)) break;
+        bits = fp28_bits_after(A, B, was, top);
+        auto pair = __builtin_amdgcn_permlane16_swap((uint32_t)s, (uint32_t)s, false, false);
+        const int32_t even = (int32_t)pair[0], odd = (int32_t)pair[1];
+        const int32_t ma = __builtin_amdgcn_readfirstlane(m[0]), mb = __builtin_amdgcn_readfirstlane(m[1]);
+        const int32_t mc = __builtin_amdgcn_readfirstlane(m[2]), md = __builtin_amdgcn_readfirstlane(m[3]);
+        const int64_t t = (int64_t)(odd_row ? mc : ma) * (int64_t)even + (int64_t)(odd_row ? md : mb) * (int64_t)odd;
+        const int32_t hi = low ? (int32_t)(t >> 28) : 0;
+        const int32_t n = (low ? (int32_t)((uint32_t)t & (uint32_t)FP28_MASK) : (int32_t)t) + __builtin_amdgcn_update_dpp(0, hi, 0x111, 0xF, 0xF, true);
+        const int32_t c = low ? n >> 28 : 0;
+        s = (low ? n & FP28_MASK : n) + __builtin_amdgcn_update_dpp(0, c, 0x111, 0xF, 0xF, true);
+    }
+    if (!done || __builtin_fabs(A + B) != 1.0) return fp28_inv_divsteps(x);
+    const bool second = A == 0.0, neg = A + B < 0.0;
+    fp28 r, scale;
+#pragma unroll
+    for (int j = 0; j < 14; ++j) {
+        const int32_t l = __builtin_amdgcn_readlane(s, (second ? 48 : 32) + j);
+        r.l[j] = neg ? -l : l;
+        scale.l[j] = Fp28Params::INV_SCALE[j];
+    }
+    return fp28_mul(fp28_carry(r), scale);
+}
+#elif defined(__HIPCC__)
+__device__ fp28 fp28_inv_wave(const fp28& x);
+#else
+/* the same with the lanes of the wave written out as an array (host build of the kernels); `batches` for the tests */
+inline fp28 fp28_inv_wave(const fp28& x, int* batches = nullptr) {
+    int32_t s[4][14] = {};
+    for (int j = 0; j < 14; ++j) {
+        s[0][j] = Fp28Params::MOD[j];
+        s[1][j] = x.l[j];
+    }
+    s[3][0] = 1;
+    int bits = 382;
+    double A = 0.0, B = 0.0;
+    bool done = false;
+    if (batches) *batches = -1;
+    for (int batch = 0; batch < FP28_INV_BATCHES; ++batch) {
+        const int top = fp28_window_top(bits);
+        A = fp28_window(s[0][top], s[0][top - 1], s[0][top - 2], s[0][top - 3]);
+        B = fp28_window(s[1][top], s[1][top - 1], s[1][top - 2], s[1][top - 3]);
+        if (top == 3 && (A == 0.0 || B == 0.0)) {
+            done = true;
+            if (batches) *batches = batch;
+            break;
+        }
+        const double was = __builtin_fmax(__builtin_fabs(A), __builtin_fabs(B));
+        int32_t m[4], n[4][14], c[4][14];
+        if (!fp28_euclid_batch(A, B, m)) break;
+        bits = fp28_bits_after(A, B, was, top);
+        for (int k = 0; k < 4; ++k)
+            for (int j = 0, hi = 0; j < 14; ++j) {
+                const int64_t t = (int64_t)m[2 * (k & 1)] * s[k & 2][j] + (int64_t)m[2 * (k & 1) + 1] * s[(k & 2) + 1][j];
+                n[k][j] = (int32_t)((j < 13 ? (uint32_t)t & (uint32_t)FP28_MASK : (uint32_t)t) + (uint32_t)hi);
+                hi = (int32_t)(t >> 28);
+            }
+        for (int k = 0; k < 4; ++k)
+            for (int j = 0; j < 14; ++j) {
+                c[k][j] = j < 13 ? n[k][j] >> 28 : 0;
+                s[k][j] = (j < 13 ? n[k][j] & FP28_MASK : n[k][j]) + (j ? c[k][j - 1] : 0);
+            }
+    }
+    if (!done || __builtin_fabs(A + B) != 1.0) {
+        if (batches) *batches = -1;
+        return fp28_inv_divsteps(x);
+    }
+    const int k = A == 0.0 ? 3 : 2;
+    fp28 r, scale;
+    for (int j = 0; j < 14; ++j) {
+        r.l[j] = A + B < 0.0 ? -s[k][j] : s[k][j];
+        scale.l[j] = Fp28Params::INV_SCALE[j];
+    }
+    return fp28_mul(fp28_carry(r), scale);
 }
 #endif
 

@@ -147,6 +147,8 @@ def block28():
                % limbs28(pow(2, 1168, P_MOD)))
     out.append("    static constexpr int32_t INV_START[14] = {%s};  /* 2^784 mod p: a R -> R / a under the radix R = 2^392 */"
                % limbs28(pow(2, 784, P_MOD)))
+    out.append("    static constexpr int32_t INV_SCALE[14] = {%s};  /* 2^1176 mod p: a plain 1 / a -> R^2 / a, R = 2^392 */"
+               % limbs28(pow(2, 1176, P_MOD)))
     out.append("};")
     return "\n".join(out)
 

@@ -46,6 +46,9 @@ void hm_fp_inv_binary(const uint8_t* a, uint8_t* o) { fp_store(o, fe_inv<FpParam
 void hm_fr_inv_binary(const uint8_t* a, uint8_t* o) { fr_store(o, fe_inv<FrParams>(fr_load(a))); }
 void hm_fp_inv_gcd(const uint8_t* a, uint8_t* o) { fp_store(o, fe_inv_gcd<FpParams>(fp_load(a))); }
 void hm_fp_inv_wave(const uint8_t* a, uint8_t* o) { fp_store(o, fp28_to_fp(fp28_inv_wave(fp28_mul(fp28_from_fp(fp_load(a)), fp28_one())))); }
+// batches of the wave's inversion (-1: the division steps took over), and those steps by themselves
+int hm_fp_inv_batches(const uint8_t* a) { int n; fp28_inv_wave(fp28_mul(fp28_from_fp(fp_load(a)), fp28_one()), &n); return n; }
+void hm_fp_inv_divsteps(const uint8_t* a, uint8_t* o) { fp_store(o, fp28_to_fp(fp28_inv_divsteps(fp28_mul(fp28_from_fp(fp_load(a)), fp28_one())))); }
 void hm_fr_inv_gcd(const uint8_t* a, uint8_t* o) { fr_store(o, fe_inv_gcd<FrParams>(fr_load(a))); }
 void hm_fr_mul(const uint8_t* a, const uint8_t* b, uint8_t* o) { fr_store(o, fr_mul(fr_load(a), fr_load(b))); }
 void hm_fr_mul_limbs29(const uint32_t* a, const uint32_t* b, uint32_t* o) { fr_t x, y; memcpy(x.l, a, 32); memcpy(y.l, b, 32); fr_t r = fr_mul_limbs29(x, y); memcpy(o, r.l, 32); }

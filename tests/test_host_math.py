@@ -57,7 +57,7 @@ def test_fp64_product_columns_stay_exact():
 
 @pytest.mark.parametrize("group", ["edges", "powers", "random"])
 def test_inversion_by_division_steps(hm, group):
-    """The wave's inversion (rows of limbs, division steps on the lowest limbs, lazily carried updates)."""
+    """The wave's inversion (rows of limbs, lazily carried updates)."""
     rng = random.Random(3)
     vals = {"edges": [0, 1, 2, 3, P - 1, P - 2, (P - 1) // 2, (P + 1) // 2, (1 << 28) - 1, P >> 28],
             "powers": [1 << k for k in range(0, 381, 7)] + [P - (1 << k) for k in range(0, 380, 7)],
@@ -66,6 +66,22 @@ def test_inversion_by_division_steps(hm, group):
     for a in vals:
         hm.hm_fp_inv_wave(_b(a, 48), out)
         assert int.from_bytes(bytes(out), "little") == (pow(a, -1, P) if a else 0), a
+
+
+def test_inversion_in_batches_of_quotients(hm):
+    """What the wave's inversion does before it falls back on division steps: random values take 15 to 17 batches and never fall
+    back, plain values so small that the first quotient has more than 27 bits always do; the division steps by themselves."""
+    rng = random.Random(16)
+    small = [k * pow(2, -392, P) % P for k in (1, 2, 3, -1, -2, 1 << 100, (1 << 353) - 1)]           # their form's limbs are k's
+    out = (ctypes.c_uint8 * 48)()
+    for a in small + [0]:
+        assert hm.hm_fp_inv_batches(_b(a, 48)) == -1
+    for a in [rng.randrange(1, P) for _ in range(2000)]:
+        assert 1 <= hm.hm_fp_inv_batches(_b(a, 48)) <= 20
+    for a in small + [0, 1, P - 1] + [rng.randrange(P) for _ in range(200)]:
+        for f in (hm.hm_fp_inv_wave, hm.hm_fp_inv_divsteps):
+            f(_b(a, 48), out)
+            assert int.from_bytes(bytes(out), "little") == (pow(a, -1, P) if a else 0), a
 
 
 def test_rounds_of_the_wave_inversion():
