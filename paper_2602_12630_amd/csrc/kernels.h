@@ -2085,8 +2085,8 @@ struct ShiftPoints {
  * inverted by the whole wave (fp28_inv_wave) and the inverses come back down the tree, every child taking its parent's
  * inverse times its sibling's product.  phi and the canonical bytes of a point are written along with it where the
  * caller wants them: the point is in registers, and a launch of their own costs as much as their arithmetic.
- * Bound by depth: two products per level of the tree in a lone wave, and the inversion.  Measured against one binary
- * GCD per lane: 131072 points 157 -> 104 us (phi included), 8192 points 114 -> 68 us, one point 110 -> 45 us.
+ * Bound by depth: two products per level of the tree in a lone wave, and the inversion.  131072 points 84 us (phi included), 8192 points
+ * 51 us.
  * Phases: 0 run products, 1 .. 6 up (one level each), 7 inversion, 8 .. 13 down, 14 backward sweep; levels above the
  * root of a smaller tree are empty. */
 struct BatchNormalize {
@@ -2151,8 +2151,8 @@ struct BatchNormalize {
     }
 };
 /* Few points: a workgroup of WAVES waves per point, the sum of `group` consecutive ones of `in` (the pieces of a sum that other waves have
- * left), each with an inversion of its own by its first wave.  Bound by the inversion: one to 512 points 36 to 42 us, 45 to 65
- * where up to 64 of them shared one (BatchNormalize). */
+ * left), each with an inversion of its own by its first wave.  Bound by the inversion: one to 512 points 23 to 32 us.  (With the division steps
+ * 36 to 42, and 45 to 65 where up to 64 points shared one inversion.) */
 template <int WAVES_>
 struct NormalizeWave {
     static constexpr int WAVES = WAVES_;
@@ -2281,25 +2281,6 @@ TC_HD void fb_mul_accumulate(xyzz_acc& acc, const g1_affine* table, uint32_t k, 
         if (d) acc_madd(acc, table[((uint64_t)k * FB_W + w) * FB_NB + (uint32_t)(d < 0 ? -d : d) - 1u], d < 0);
     }
 }
-/* same for a small signed integer |d| <= 2^15 (one lookup when the window is 16 bits wide) */
-TC_HD void fb_small_accumulate(xyzz_acc& acc, const g1_affine* table, uint32_t k, int32_t d) {
-    if (!d) return;
-    uint32_t mag = (uint32_t)(d < 0 ? -d : d);
-    if (FB_C == 16) {
-        acc_madd(acc, table[((uint64_t)k * FB_W) * FB_NB + mag - 1u], d < 0);
-        return;
-    }
-    uint32_t v[8] = {mag, 0, 0, 0, 0, 0, 0, 0};
-    uint32_t carry = 0;
-    for (int w = 0; w * FB_C < 24; ++w) {
-        int32_t dw = fr_window_digit(v, w, FB_C, carry);
-        if (dw) {
-            bool negative = (dw < 0) != (d < 0);
-            acc_madd(acc, table[((uint64_t)k * FB_W + w) * FB_NB + (uint32_t)(dw < 0 ? -dw : dw) - 1u], negative);
-        }
-    }
-}
-
 /* ---- SRS generation (Def. 4.1 Setup, Lagrange image) ---------------------------------- */
 struct ShapeInfo {
     int m;
@@ -2360,45 +2341,150 @@ struct TreeGeom {
     uint32_t grid[4];          /* grid of this level */
     uint32_t B;                /* arity */
 };
-/* flat index in the level below of child k (flat in node shape) of node a (flat in grid); -1 if outside */
-TC_HD int64_t child_index(const TreeGeom& g, uint64_t a, uint32_t k) {
-    uint32_t ai[4], ki[4];
+/* flat index in the level below of child k (flat in node shape) of node a (flat in grid; a level has fewer than 2^32 children); -1 if
+ * outside */
+TC_HD int64_t child_index(const TreeGeom& g, uint64_t node, uint32_t k) {
+    uint32_t a = (uint32_t)node;
+    uint64_t f = 0, stride = 1;
     for (int j = g.m - 1; j >= 0; --j) {
-        ai[j] = (uint32_t)(a % g.grid[j]);
-        a /= g.grid[j];
-        ki[j] = k % g.node[j];
-        k /= g.node[j];
-    }
-    uint64_t f = 0;
-    for (int j = 0; j < g.m; ++j) {
-        uint64_t p = (uint64_t)ai[j] * g.node[j] + ki[j];
+        const uint32_t a1 = a / g.grid[j], k1 = k / g.node[j];
+        const uint64_t p = (uint64_t)(a - a1 * g.grid[j]) * g.node[j] + (k - k1 * g.node[j]);
         if (p >= g.below[j]) return -1;
-        f = f * g.below[j] + p;
+        f += p * stride;
+        stride *= g.below[j];
+        a = a1;
+        k = k1;
     }
     return (int64_t)f;
 }
-/* bottom level of an entries tree: lane = node, children are small integers */
-struct NodeCommitSmall {
+constexpr uint32_t FB_SMALL_W = FB_C == 16 ? 1u : 24u / FB_C;            /* windows of an entry: 16 bits and a sign */
+/* Levels that fill the chip.  Bottom level of an entries tree: lane = node, children are small integers; upper levels: lane = (node,
+ * child), the child's value is phi of the commitment below.  Sixteen mixed additions in a row either way, expanded in place in the
+ * 30-bit form as in AccAffine; a lane that meets equal or opposite points enters itself in a list that NodeCommitRedo works off.
+ * 131072 lanes of sixteen: 277 us at either level, 363 and (with the sums of
+ * the children, 95 us now) 590 with products as calls. */
+template <bool BOTTOM>
+struct NodeCommit {
     TreeGeom g;
-    const void* payload;
+    const void* payload;        /* bottom level */
     int dtype;
+    const fr_plain* below;      /* upper levels */
     const g1_affine* table;
+    uint64_t first;             /* of the lanes of the level */
     g1_xyzz* out;
-    TC_DEV void operator()(uint32_t a) const {
-        xyzz_acc acc = acc_identity();
-        for (uint32_t k = 0; k < g.B; ++k) {
-            int64_t f = child_index(g, a, k);
-            if (f < 0) continue;
-            fb_small_accumulate(acc, table, k, small_scalar(payload, dtype, (uint64_t)f));
-        }
-        out[a] = acc_result(acc);
+    uint32_t* redo_count;
+    uint32_t* redo_list;
+    /* The table points that a lane adds, one call each: the i-th, if it is there.  A cursor holds where the child's value stands, or its magnitude and sign, and the
+     * carry between the windows. */
+    struct Cursor {
+        int64_t f;
+        uint32_t mag, carry;
+        bool negative;
+    };
+    TC_DEV uint32_t terms() const { return BOTTOM ? g.B * FB_SMALL_W : (uint32_t)FB_W; }
+    TC_DEV void begin(uint64_t at, Cursor& c) const {
+        c.carry = 0;
+        if (!BOTTOM) c.f = child_index(g, at / g.B, (uint32_t)(at % g.B));
     }
+    TC_DEV bool term(uint64_t at, uint32_t i, Cursor& c, uint64_t& index, bool& negative) const {
+        int32_t d;
+        uint32_t k, w;
+        if (BOTTOM) {
+            k = i / FB_SMALL_W;
+            w = i % FB_SMALL_W;
+            if (w == 0) {
+                const int64_t f = child_index(g, at, k);
+                const int32_t x = f < 0 ? 0 : small_scalar(payload, dtype, (uint64_t)f);
+                c.mag = (uint32_t)(x < 0 ? -x : x);
+                c.negative = x < 0;
+                c.carry = 0;
+            }
+            d = small_window_digit(c.mag, (int)w, FB_C, c.carry);
+            negative = (d < 0) != c.negative;
+        } else {
+            if (c.f < 0) return false;
+            k = (uint32_t)(at % g.B);
+            w = i;
+            d = fr_window_digit(below[c.f].l, (int)w, FB_C, c.carry);
+            negative = d < 0;
+        }
+        index = ((uint64_t)k * FB_W + w) * FB_NB + (uint32_t)(d < 0 ? -d : d) - 1u;
+        return d != 0;
+    }
+    TC_DEV void operator()(uint32_t t) const {
+        const uint64_t at = first + t;
+        const uint32_t n = terms();
+        g1_xyzz30 acc;
+        bool have = false;
+        Cursor c;
+        begin(at, c);
+        for (uint32_t i = 0; i < n; ++i) {
+            uint64_t index;
+            bool negative;
+            if (!term(at, i, c, index, negative)) continue;
+            const g1_affine p = table[index];
+            const fp30 x = fp30_from_fp(p.x);
+            fp30 y = fp30_from_fp(p.y);
+            if (negative) y = fp30_neg(y);
+            if (!have) {
+                acc.X = fp30_balance(x);
+                acc.Y = fp30_balance(y);
+                acc.ZZ = fp30_one();
+                acc.ZZZ = fp30_one();
+                have = true;
+                continue;
+            }
+            if (!xyzz30_madd_regular(acc, x, y)) {
+                redo_list[atomic_add_u32(redo_count, 1u)] = t;
+                return;
+            }
+        }
+        g1_xyzz r;
+        if (!have) {
+            r = xyzz_identity();
+        } else {
+            r.X = fp30_to_fp_outlined(acc.X); r.Y = fp30_to_fp_outlined(acc.Y);
+            r.ZZ = fp30_to_fp_outlined(acc.ZZ); r.ZZZ = fp30_to_fp_outlined(acc.ZZZ);
+        }
+        out[t] = r;
+    }
+};
+template <bool BOTTOM>
+struct NodeCommitRedo {
+    NodeCommit<BOTTOM> n;
+    uint32_t lanes;
+    TC_DEV void operator()(uint32_t lane) const {
+        for (uint32_t j = lane; j < *n.redo_count; j += lanes) {
+            const uint32_t t = n.redo_list[j];
+            const uint64_t at = n.first + t;
+            xyzz_acc acc = acc_identity();
+            typename NodeCommit<BOTTOM>::Cursor c;
+            n.begin(at, c);
+            for (uint32_t i = 0; i < n.terms(); ++i) {
+                uint64_t index;
+                bool negative;
+                if (n.term(at, i, c, index, negative)) acc_madd(acc, n.table[index], negative);
+            }
+            n.out[t] = acc_result(acc);
+        }
+    }
+};
+/* out[t] = sum of in[t * group .. (t + 1) * group), a few of them (StridedRedo takes what it gives up) */
+struct GroupSums {
+    const g1_xyzz* in;
+    uint32_t group;
+    g1_xyzz* out;
+    uint32_t* redo_count;
+    uint32_t* redo_list;
+    TC_HD void job(uint32_t t, uint64_t& first, uint32_t& step, uint32_t& cnt, uint64_t& slot) const {
+        first = (uint64_t)t * group; step = 1u; cnt = group; slot = t;
+    }
+    TC_DEV void operator()(uint32_t t) const { strided_sum_fast(*this, t); }
 };
 /* Levels of few nodes: a node is the sum of the table points of its children's digits (an entry's one or two, or the FB_W of phi of
  * the commitment below), NODE_WAVE_POINTS of them to a workgroup of eight waves, which leave `pieces` raw sums a node; NormalizeWave adds
  * those up.  32 nodes of 256 points 20 us, one node 19, where cooperative sums of lane-wide products took 111 and 106. */
 constexpr uint32_t NODE_WAVE_POINTS = 32;
-constexpr uint32_t FB_SMALL_W = FB_C == 16 ? 1u : 24u / FB_C;            /* windows of an entry: 16 bits and a sign */
 TC_HD uint32_t node_wave_windows(bool bottom) { return bottom ? FB_SMALL_W : (uint32_t)FB_W; }
 /* acc += sum over `per` windows from w0 on of the digits (digit(w, carry), negated where `flip`) times base `base` */
 template <class Digit>
@@ -2465,25 +2551,9 @@ struct NodeTermsWave {
         if (ph == 3 && wave == 0) wv_store_raw(out + (uint64_t)wg * WV_POINT_WORDS, wv_load_raw(lds));
     }
 };
-/* upper levels: lane = (node, child); the child's value is phi of the commitment below */
-struct NodeCommitFr {
-    TreeGeom g;
-    const fr_plain* below;
-    const g1_affine* table;
-    g1_xyzz* out;               /* n_nodes * B partial sums */
-    TC_DEV void operator()(uint32_t t) const {
-        uint32_t a = t / g.B, k = t % g.B;
-        int64_t f = child_index(g, a, k);
-        xyzz_acc acc = acc_identity();
-        if (f >= 0) fb_mul_accumulate(acc, table, k, below[f].l);
-        out[t] = acc_result(acc);
-    }
-};
-/* upper levels, arity a power of two <= 64: a lane commits FB_W >> logH consecutive windows of one child
- * (B << logH <= 64 lanes per node, BLOCK / (B << logH) nodes per workgroup), then the partial sums of a node are
- * added pairwise through LDS.  Large levels take four waves per workgroup, so that most waves skip the later
- * halving steps; small ones a single wave.  logH = 0 (one lane per child) does the least work in
- * total; a level of few nodes is bound by the depth of one lane's work instead and takes logH > 0. */
+/* upper levels too small for a lane per child, arity a power of two <= 32: a lane commits FB_W >> logH consecutive windows
+ * of one child (B << logH <= 64 lanes per node, BLOCK / (B << logH) nodes per workgroup), then the partial sums of a
+ * node are added pairwise through LDS.  Bound by the depth of one lane's work. */
 template <int BLOCK>
 struct NodeCommitFrCoop {
     static constexpr size_t LDS_BYTES = BLOCK * sizeof(g1_xyzz);
@@ -2561,18 +2631,6 @@ struct NodeWindowSrc {
         return acc;
     }
     TC_DEV void store(uint32_t node, const g1_xyzz& r) const { out[node] = r; }
-};
-/* out[i] = sum of in[i * group .. (i + 1) * group) */
-struct SumGroups {
-    const g1_xyzz* in;
-    uint32_t group;
-    g1_xyzz* out;
-    TC_DEV void operator()(uint32_t t) const {
-        const g1_xyzz* p = in + (uint64_t)t * group;
-        xyzz_acc acc = acc_from(p[0]);
-        for (uint32_t i = 1; i < group; ++i) acc_add(acc, acc_from(p[i]));
-        out[t] = acc_result(acc);
-    }
 };
 /* ---- Open: quotient values on the grid (Algorithm 1 in evaluation form) ----------------- */
 /* Along one axis of length d with the opening at position kap, for every line t of the slice:

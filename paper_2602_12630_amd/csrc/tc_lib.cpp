@@ -1301,16 +1301,24 @@ extern "C" int tc_quant_scale(tc_ctx* ctx, const void* d_src, size_t n, float* d
 /* MSM engine                                                                              */
 /* ======================================================================================= */
 /* a tree level of at most this many nodes (two workgroups per compute unit) takes the cooperative sums */
+#if defined(TC_HOST_EMU)
+static const uint64_t COOP_LEVEL_NODES = 12;
+#else
 static const uint64_t COOP_LEVEL_NODES = 512;
+#endif
 /* a level with at most this many table points to add takes whole waves (a point costs the chip 1 ns, the cooperative sums 110 us and
  * more whatever the number of nodes) */
 #if defined(TC_HOST_EMU)
-static const uint64_t WAVE_LEVEL_POINTS = 600;
+static const uint64_t WAVE_LEVEL_POINTS = 300;
 #else
 static const uint64_t WAVE_LEVEL_POINTS = 65536;
 #endif
 /* a tree level spreads the windows of a child over lanes as long as it stays within this many lanes (two waves per SIMD) */
+#if defined(TC_HOST_EMU)
+static const uint64_t SPLIT_LEVEL_LANES = 256;          /* the CPU build of the tests walks the levels that fill the chip as well */
+#else
 static const uint64_t SPLIT_LEVEL_LANES = 131072;
+#endif
 
 /* prefix sums of cnt (n entries): start, lstart (of ceil(cnt / L)); optional zeroing of a cursor array */
 static int scan_counts(tc_ctx* ctx, const uint32_t* cnt, uint32_t n, uint32_t L, uint32_t* start, uint32_t* lstart,
@@ -2601,6 +2609,47 @@ static int tree_prepare(tc_ctx* ctx, const tc_tree_desc* desc, tc_tree** out) {
     return TC_OK;
 }
 
+/* a level of n nodes by lanes, a lane per node (bottom level) or per child, in chunks that bound the partial sums */
+static const uint64_t NODE_CHUNK_LANES = 1ull << 20;
+template <bool BOTTOM>
+static int node_commit_lanes(tc_ctx* ctx, NodeCommit<BOTTOM> k, uint64_t n, g1_xyzz* out) {
+    const uint32_t per = BOTTOM ? 1u : k.g.B;
+    const uint64_t chunk = std::max<uint64_t>(1, std::min<uint64_t>(n, NODE_CHUNK_LANES / per)), lanes_max = chunk * per;
+    g1_xyzz* part[2] = {nullptr, nullptr};
+    if (per > 1) {
+        part[0] = ws_array<g1_xyzz>(ctx, lanes_max);
+        part[1] = ws_array<g1_xyzz>(ctx, lanes_max / 2);
+        if (!part[0] || !part[1]) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
+    }
+    /* a list of given-up lanes that the launches of a chunk take in turn, and a counter for each of them */
+    constexpr uint32_t COUNTERS = 32;
+    WS(redo, uint32_t, COUNTERS + lanes_max);
+    k.redo_count = redo;
+    k.redo_list = redo + COUNTERS;
+    for (uint64_t n0 = 0; n0 < n; n0 += chunk) {
+        const uint64_t nodes = std::min<uint64_t>(chunk, n - n0), lanes = nodes * per;
+        const uint32_t redo_lanes = (uint32_t)std::min<uint64_t>(lanes, ACC_RESIDENT_LANES);
+        k.first = n0 * per;
+        k.out = per > 1 ? part[0] : out + n0;
+        RT(rt::launch<64>(COUNTERS, ctx->stream, Fill32{redo, 0u}));
+        RT((rt::launch_waves<64, 3>(lanes, ctx->stream, k)));
+        RT(rt::launch<64>(redo_lanes, ctx->stream, NodeCommitRedo<BOTTOM>{k, redo_lanes}));
+        /* sums of up to four, as many lanes as there are left; a prime arity above that in one go */
+        int from = 0;
+        uint32_t step = 0;
+        for (uint32_t left = per; left > 1; from ^= 1) {
+            ++step;          /* an arity is below 2^32: fewer than 32 steps */
+            const uint32_t group = left % 4 == 0 ? 4 : left % 3 == 0 ? 3 : left % 2 == 0 ? 2 : left;
+            left /= group;
+            GroupSums S{part[from], group, left > 1 ? part[from ^ 1] : out + n0, redo + step, redo + COUNTERS};
+            const uint64_t sums = nodes * left;
+            const uint32_t sum_redo = (uint32_t)std::min<uint64_t>(sums, ACC_RESIDENT_LANES);
+            RT((rt::launch_waves<64, 2>(sums, ctx->stream, S)));
+            RT(rt::launch<64>(sum_redo, ctx->stream, StridedRedo<GroupSums>{S, sum_redo}));
+        }
+    }
+    return TC_OK;
+}
 extern "C" int tc_terkle_build(tc_ctx* ctx, const tc_tree_desc* desc, tc_tree** out) {
     try {
         if (!ctx) return TC_ERR_ARG;
@@ -2644,8 +2693,10 @@ extern "C" int tc_terkle_build(tc_ctx* ctx, const tc_tree_desc* desc, tc_tree** 
                         } else if (bottom) {
                             rt::event_t e0, e1;
                             prof_begin(ctx, TC_PROF_NODE_COMMIT, &e0, &e1);
-                            e = rt::launch<64>(lv.n, ctx->stream, NodeCommitSmall{g, t->d_payload, t->dtype, ns->fb[0], acc});
+                            rc = node_commit_lanes(ctx, NodeCommit<true>{g, t->d_payload, t->dtype, nullptr, ns->fb[0], 0, nullptr, nullptr, nullptr}, lv.n, acc);
                             prof_end(ctx, TC_PROF_NODE_COMMIT, e0, e1);
+                            if (rc) break;
+                            e = 0;
                         } else if (lv.n <= COOP_LEVEL_NODES) {
                             rt::event_t e0, e1;
                             prof_begin(ctx, TC_PROF_NODE_COMMIT_UPPER, &e0, &e1);
@@ -2653,27 +2704,24 @@ extern "C" int tc_terkle_build(tc_ctx* ctx, const tc_tree_desc* desc, tc_tree** 
                             typedef CoopReduce<NodeWindowSrc> Sum;
                             e = launch_coop<Sum::BLOCK>((uint32_t)lv.n, ctx->stream, Sum{NodeWindowSrc{g, t->levels[L - 1].phi, ns->fb[0], acc}});
                             prof_end(ctx, TC_PROF_NODE_COMMIT_UPPER, e0, e1);
-                        } else if ((t->B & (t->B - 1)) == 0 && t->B <= 64) {
+                        } else {
                             int logB = 0;
                             while ((1u << logB) < t->B) ++logB;
                             /* few nodes: one lane's depth is the cost, spread the windows of a child over lanes too */
                             int logH = 0;
-                            while (logB + logH < 6 && (2 << logH) <= FB_W && (lv.n << (logB + logH + 1)) <= SPLIT_LEVEL_LANES) ++logH;
+                            if ((t->B & (t->B - 1)) == 0)
+                                while (logB + logH < 6 && (2 << logH) <= FB_W && (lv.n << (logB + logH + 1)) <= SPLIT_LEVEL_LANES) ++logH;
                             uint64_t lanes = lv.n << (logB + logH);
                             rt::event_t e0, e1;
                             prof_begin(ctx, TC_PROF_NODE_COMMIT_UPPER, &e0, &e1);
-                            if (logH == 0)      /* a level large enough to fill the chip: throughput counts */
-                                e = launch_coop<256>((uint32_t)((lanes + 255) / 256), ctx->stream,
-                                                     NodeCommitFrCoop<256>{g, t->levels[L - 1].phi, ns->fb[0], lv.n, logB, logH, acc});
+                            e = 0;
+                            if (logH == 0)
+                                rc = node_commit_lanes(ctx, NodeCommit<false>{g, nullptr, 0, t->levels[L - 1].phi, ns->fb[0], 0, nullptr, nullptr, nullptr}, lv.n, acc);
                             else
                                 e = launch_coop<64>((uint32_t)((lanes + 63) / 64), ctx->stream,
                                                     NodeCommitFrCoop<64>{g, t->levels[L - 1].phi, ns->fb[0], lv.n, logB, logH, acc});
                             prof_end(ctx, TC_PROF_NODE_COMMIT_UPPER, e0, e1);
-                        } else {
-                            g1_xyzz* part = ws_array<g1_xyzz>(ctx, lv.n * t->B);
-                            if (!part) { rc = fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed"); break; }
-                            e = rt::launch<64>(lv.n * t->B, ctx->stream, NodeCommitFr{g, t->levels[L - 1].phi, ns->fb[0], part});
-                            if (!e) e = rt::launch<64>(lv.n, ctx->stream, SumGroups{part, t->B, acc});
+                            if (rc) break;
                         }
                         if (e) { rc = fail_hip(ctx, e, "node commit"); break; }
                     } else {

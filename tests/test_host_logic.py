@@ -513,7 +513,7 @@ def test_emulated_incremental_update(emu, node_srs):
 
 
 def test_emulated_tree_with_a_large_upper_level(emu, node_srs):
-    """A level of more than 512 nodes above the bottom takes the four-wave node kernel with packed halving steps."""
+    """Levels large enough for a lane per node and a lane per child, with the sums of a node's children in steps of four."""
     node, grid = (2, 2), (96, 100)
     X = tc_inputs.int8_uniform(grid, 5)
     tree = emu.terkle_build_entries(node_srs, X, T.TC_I8, grid, node)
@@ -528,6 +528,37 @@ def test_emulated_tree_with_a_large_upper_level(emu, node_srs):
         assert tree.root == ec.g1_to_bytes(ot.root)
     finally:
         tree.close()
+
+
+def test_emulated_tree_over_repeated_bases(emu, node_srs):
+    """Node public parameters whose four bases are one point and its negative: levels that a lane per node and a lane per child commit
+    (36 nodes over 144) run into doublings and sums that cancel, which their list of given-up lanes settles, and so do the sums
+    of a node's children."""
+    node, grid = (2, 2), (24, 24)
+    data = bytes(node_srs.export())
+    P0 = ec.g1_from_bytes(data[56 : 56 + 96])
+    signs = [1, 1, -1, 1]
+    blob = b"".join(ec.g1_to_bytes(P0 if s > 0 else ec.neg(P0)) for s in signs)
+    srs = emu.srs_import(data[:56] + blob + data[56 + 96 * 4 :])
+    X = np.random.default_rng(31).integers(-2, 3, size=grid).astype(np.int8)
+    X[:8, :8] = 1
+    tree = emu.terkle_build_entries(srs, X, T.TC_I8, grid, node)
+    try:
+        below = {(i, j): int(X[i, j]) for i in range(24) for j in range(24)}
+        size = 24
+        for L in range(2):
+            size //= 2
+            level = {}
+            for i in range(size):
+                for j in range(size):
+                    total = sum(s * below[2 * i + k // 2, 2 * j + k % 2] for k, s in enumerate(signs)) % R
+                    C = ec.mul(total, P0) if total else ec.INF
+                    assert tree.node(L, i * size + j) == ec.g1_to_bytes(C), (L, i, j)
+                    level[i, j] = terkle.phi(C)
+            below = level
+    finally:
+        tree.close()
+        srs.close()
 
 
 def test_emulated_commit_static(emu):
