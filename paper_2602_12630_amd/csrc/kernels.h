@@ -771,29 +771,93 @@ struct SortKeys {              /* the tiles of CountKeys: entries in bucket orde
     }
 };
 
-/* ---- prefix sums over bucket counts (three lane-independent steps) ---------------- */
-/* chunk = 256 consecutive buckets.  A: per-chunk totals of cnt and of ceil(cnt / L);
- * B: one lane turns the chunk totals into exclusive offsets; C: per-chunk serial prefix. */
-constexpr uint32_t SCAN_CHUNK = 256;
+/* ---- prefix sums over bucket counts ------------------------------------------------ */
+/* A chunk is SCAN_CHUNK consecutive counts, four to a lane of one workgroup.  ScanChunkTotals leaves the sums of cnt and of
+ * ceil(cnt / L) and the largest count of every chunk; ScanWrite adds up the totals of the chunks before its own and writes
+ * the prefixes.  (Above SCAN_DIRECT_CHUNKS chunks that sum, which grows with the square of their number, is left to one
+ * workgroup in between: ScanChunkOffsets.)  What bounds them is the counts, read twice, and the two prefixes written once;
+ * a lane that walks 256 counts by itself reads a line per lane and step: 137 us for 3.1 M counts that way, 40 us
+ * with these; for 32768 counts one workgroup took 25.5 us, these 11 us.
+ * With `diff` the counts are the differences of a prefix, cnt[i] = prefix[i + 1] - prefix[i] (the sums that a bucket still
+ * has), and the prefix of cnt, which is at hand, is not written again. */
+constexpr uint32_t SCAN_CHUNK = 1024;
+#if defined(TC_HOST_EMU)
+constexpr uint32_t SCAN_DIRECT_CHUNKS = 3;         /* the CPU build of the tests goes both ways */
+#else
+constexpr uint32_t SCAN_DIRECT_CHUNKS = 4096;
+#endif
 
-struct ScanChunkTotals {
+struct ScanInput {
     const uint32_t* cnt;
     uint32_t n, L;
+    bool diff;
+    /* ceil(v / L) without a division per bucket: floor(x / L) = (x * ceil(2^32 / L)) >> 32 as long as x * L < 2^32 */
+    TC_DEV uint32_t lanes_for(uint32_t v) const {
+        if (L <= 1) return v;
+        uint32_t x = v + L - 1;
+        uint32_t magic = (uint32_t)(((1ull << 32) + L - 1) / L);
+        return (uint64_t)x * L < (1ull << 32) ? (uint32_t)(((uint64_t)x * magic) >> 32) : x / L;
+    }
+    struct Quad { uint32_t v[4]; };
+    /* counts i .. i + 3, zero from n on */
+    TC_DEV Quad quad(uint32_t i) const {
+        Quad q;
+        if (i + 4 <= n && ((uintptr_t)cnt & 15u) == 0) {
+            q = *(const Quad*)(cnt + i);
+            if (diff) {
+                uint32_t next = cnt[i + 4];
+                q.v[0] = q.v[1] - q.v[0];
+                q.v[1] = q.v[2] - q.v[1];
+                q.v[2] = q.v[3] - q.v[2];
+                q.v[3] = next - q.v[3];
+            }
+            return q;
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) q.v[k] = i + k >= n ? 0u : diff ? cnt[i + k + 1] - cnt[i + k] : cnt[i + k];
+        return q;
+    }
+};
+struct ScanChunkTotals {
+    static constexpr int BLOCK = SCAN_CHUNK / 4;
+    static constexpr int PHASES = 3;
+    static constexpr size_t LDS_BYTES = 3 * BLOCK * sizeof(uint32_t);
+    ScanInput in;
     uint32_t* tot_a;
     uint32_t* tot_b;
     uint32_t* tot_max;     /* per chunk: largest count */
-    TC_DEV void operator()(uint32_t ch) const {
-        uint32_t lo = ch * SCAN_CHUNK, hi = lo + SCAN_CHUNK < n ? lo + SCAN_CHUNK : n;
+    TC_DEV void phase(int ph, uint32_t lane, uint32_t wg, uint8_t* lds) const {
+        uint32_t* sa = (uint32_t*)lds;
+        uint32_t* sb = sa + BLOCK;
+        uint32_t* sm = sb + BLOCK;
         uint32_t a = 0, b = 0, mx = 0;
-        for (uint32_t i = lo; i < hi; ++i) {
-            uint32_t v = cnt[i];
-            a += v;
-            b += (v + L - 1) / L;
-            mx = v > mx ? v : mx;
+        if (ph == 0) {
+            ScanInput::Quad q = in.quad(wg * SCAN_CHUNK + lane * 4);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                a += q.v[k];
+                b += in.lanes_for(q.v[k]);
+                mx = q.v[k] > mx ? q.v[k] : mx;
+            }
+            sa[lane] = a; sb[lane] = b; sm[lane] = mx;
+        } else if (ph == 1) {
+            if (lane >= 16) return;
+            for (uint32_t i = lane; i < (uint32_t)BLOCK; i += 16) {
+                a += sa[i];
+                b += sb[i];
+                mx = sm[i] > mx ? sm[i] : mx;
+            }
+            sa[lane] = a; sb[lane] = b; sm[lane] = mx;
+        } else if (lane == 0) {
+            for (uint32_t i = 0; i < 16; ++i) {
+                a += sa[i];
+                b += sb[i];
+                mx = sm[i] > mx ? sm[i] : mx;
+            }
+            tot_a[wg] = a;
+            tot_b[wg] = b;
+            tot_max[wg] = mx;
         }
-        tot_a[ch] = a;
-        tot_b[ch] = b;
-        tot_max[ch] = mx;
     }
 };
 struct ScanChunkOffsets {     /* one workgroup: every lane owns a slice of the chunk totals */
@@ -846,155 +910,122 @@ struct ScanChunkOffsets {     /* one workgroup: every lane owns a slice of the c
     }
 };
 struct ScanWrite {
-    const uint32_t* cnt;
-    uint32_t n, L;
-    const uint32_t* tot_a;
-    const uint32_t* tot_b;
+    static constexpr int BLOCK = SCAN_CHUNK / 4;
+    static constexpr int PHASES = 4;
+    static constexpr int GROUPS = BLOCK / 16;          /* lanes are scanned in groups of 16 (a word of padding behind each) */
+    static constexpr size_t LDS_BYTES = (2 * (BLOCK + GROUPS) + 3 * BLOCK + 2 * GROUPS) * sizeof(uint32_t);
+    ScanInput in;
     uint32_t nchunks;
-    uint32_t* start;     /* n + 1 */
-    uint32_t* lstart;    /* n + 1 */
-    uint32_t* zero_me;   /* optional array of n counters to clear (scatter cursors) */
-    TC_DEV void operator()(uint32_t ch) const {
-        uint32_t lo = ch * SCAN_CHUNK, hi = lo + SCAN_CHUNK < n ? lo + SCAN_CHUNK : n;
-        uint32_t a = tot_a[ch], b = tot_b[ch];
-        for (uint32_t i = lo; i < hi; ++i) {
-            uint32_t v = cnt[i];
-            start[i] = a;
-            lstart[i] = b;
-            a += v;
-            b += (v + L - 1) / L;
-            if (zero_me) zero_me[i] = 0;
-        }
-        if (ch == nchunks - 1) {
-            start[n] = tot_a[nchunks];
-            lstart[n] = tot_b[nchunks];
-        }
-    }
-};
-/* The same prefix sums in one launch when there are few buckets (n <= MAX_N): one workgroup, every lane owns
- * ceil(n / BLOCK) consecutive buckets.  The three launches above take about 100 us for 32768 buckets, most of it the
- * serial loops of their few lanes; a flat commitment of 2^21 terms runs the scan once per pass. */
-struct ScanSmall {
-    static constexpr int BLOCK = 1024;
-    static constexpr int GROUP = 32;           /* lanes per group of the two-level scan over the lanes' sums */
-    static constexpr int PHASES = 5;
-    static constexpr size_t LDS_BYTES = (3 * BLOCK + 2 * (BLOCK / GROUP)) * sizeof(uint32_t);
-    static constexpr uint32_t MAX_N = 65536;
-    const uint32_t* cnt;
-    uint32_t n, L;
-    uint32_t* start;       /* n + 1 */
-    uint32_t* lstart;      /* n + 1 */
-    uint32_t* zero_me;     /* optional */
-    uint32_t* total_a;     /* one value each: sum of cnt, sum of ceil(cnt / L), largest cnt */
-    uint32_t* total_b;
-    uint32_t* total_max;
-    /* ceil(v / L) without a division per bucket: L <= 64, and floor(x / L) = (x * ceil(2^32 / L)) >> 32 for x < 2^26 */
-    TC_DEV uint32_t lanes_for(uint32_t v, uint32_t magic) const {
-        uint32_t x = v + L - 1;
-        return x < (1u << 26) ? (uint32_t)(((uint64_t)x * magic) >> 32) : x / L;
-    }
-    struct Quad { uint32_t v[4]; };
-    TC_DEV void phase(int ph, uint32_t lane, uint32_t, uint8_t* lds) const {
+    bool offsets;                /* the totals are prefixes already, and the grand totals are there */
+    uint32_t* tot_a;             /* [nchunks]: the sum over all */
+    uint32_t* tot_b;             /* [nchunks], and behind it the largest count */
+    const uint32_t* tot_max;
+    uint32_t* start;             /* n + 1; not written for differences of a prefix */
+    uint32_t* lstart;            /* n + 1 */
+    uint32_t* zero_me;           /* optional array of n counters to clear (scatter cursors) */
+    TC_DEV void phase(int ph, uint32_t lane, uint32_t wg, uint8_t* lds) const {
         uint32_t* sa = (uint32_t*)lds;
-        uint32_t* sb = sa + BLOCK;
-        uint32_t* sm = sb + BLOCK;
-        uint32_t* ga = sm + BLOCK;             /* per group of lanes */
-        uint32_t* gb = ga + BLOCK / GROUP;
-        uint32_t per = (n + BLOCK - 1) / BLOCK;
-        uint32_t lo = lane * per < n ? lane * per : n;
-        uint32_t hi = lo + per < n ? lo + per : n;
-        uint32_t magic = L > 1 ? (uint32_t)(((1ull << 32) + L - 1) / L) : 0u;         /* L = 1: the quotient is the count itself */
-        /* a lane's buckets as 16-byte pieces when they are whole pieces (32768 buckets: 32 per lane) */
-        bool quads = (per & 3u) == 0 && hi - lo == per && (((uintptr_t)cnt | (uintptr_t)start | (uintptr_t)lstart) & 15u) == 0;
-        if (ph == 0) {                         /* every lane: sums over its own buckets */
-            uint32_t a = 0, b = 0, mx = 0;
-            if (quads) {
-                const Quad* c4 = (const Quad*)(cnt + lo);
-                for (uint32_t i = 0; i < per / 4; ++i) {
-                    Quad q = c4[i];
+        uint32_t* sb = sa + BLOCK + GROUPS;
+        uint32_t* pa = sb + BLOCK + GROUPS;            /* totals of the chunks before this one */
+        uint32_t* pb = pa + BLOCK;
+        uint32_t* pm = pb + BLOCK;                     /* (the last workgroup: the largest count of all chunks) */
+        uint32_t* ga = pm + BLOCK;
+        uint32_t* gb = ga + GROUPS;
+        const bool last = wg == nchunks - 1;
+        const uint32_t slot = lane + lane / 16, i0 = wg * SCAN_CHUNK + lane * 4;
+        if (ph == 0) {
+            ScanInput::Quad q = in.quad(i0);
+            uint32_t a = 0, b = 0;
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        uint32_t v = q.v[k];
-                        a += v;
-                        b += L > 1 ? lanes_for(v, magic) : v;
-                        mx = v > mx ? v : mx;
-                    }
-                }
-            } else {
-                for (uint32_t i = lo; i < hi; ++i) {
-                    uint32_t v = cnt[i];
-                    a += v;
-                    b += L > 1 ? lanes_for(v, magic) : v;
-                    mx = v > mx ? v : mx;
-                }
+            for (int k = 0; k < 4; ++k) {
+                a += q.v[k];
+                b += in.lanes_for(q.v[k]);
             }
-            sa[lane] = a; sb[lane] = b; sm[lane] = mx;
-        } else if (ph == 1) {                  /* one lane per group: exclusive prefix inside the group, the group's totals */
-            if (lane < (uint32_t)(BLOCK / GROUP)) {
-                uint32_t a = 0, b = 0, mx = 0;
-                for (uint32_t i = lane * GROUP; i < (lane + 1) * GROUP; ++i) {
+            sa[slot] = a; sb[slot] = b;
+            a = 0; b = 0;
+            uint32_t mx = 0;
+            if (!offsets) {
+                for (uint32_t t = lane; t < wg; t += (uint32_t)BLOCK) {
+                    a += tot_a[t];
+                    b += tot_b[t];
+                    if (last && tot_max[t] > mx) mx = tot_max[t];
+                }
+                if (last && lane == 0 && tot_max[wg] > mx) mx = tot_max[wg];
+            }
+            pa[lane] = a; pb[lane] = b; pm[lane] = mx;
+        } else if (ph == 1) {
+            if (lane < (uint32_t)GROUPS) {             /* exclusive prefix inside a group, the group's sums */
+                uint32_t a = 0, b = 0;
+                for (uint32_t i = lane * 17; i < lane * 17 + 16; ++i) {
                     uint32_t va = sa[i], vb = sb[i];
                     sa[i] = a; sb[i] = b;
                     a += va; b += vb;
-                    mx = sm[i] > mx ? sm[i] : mx;
                 }
-                ga[lane] = a; gb[lane] = b; sm[lane * GROUP] = mx;
+                ga[lane] = a; gb[lane] = b;
+            } else if (lane >= 64 && lane < 80 && !offsets) {
+                uint32_t a = 0, b = 0, mx = 0;
+                for (uint32_t i = lane - 64; i < (uint32_t)BLOCK; i += 16) {
+                    a += pa[i];
+                    b += pb[i];
+                    mx = pm[i] > mx ? pm[i] : mx;
+                }
+                pa[lane - 64] = a; pb[lane - 64] = b; pm[lane - 64] = mx;
             }
-        } else if (ph == 2) {                  /* one lane: exclusive prefix over the groups, the grand totals */
+        } else if (ph == 2) {
             if (lane == 0) {
                 uint32_t a = 0, b = 0, mx = 0;
-                for (uint32_t g = 0; g < (uint32_t)(BLOCK / GROUP); ++g) {
+                if (offsets) {
+                    a = tot_a[wg];
+                    b = tot_b[wg];
+                } else {
+                    for (uint32_t i = 0; i < 16; ++i) {
+                        a += pa[i];
+                        b += pb[i];
+                        mx = pm[i] > mx ? pm[i] : mx;
+                    }
+                }
+                for (uint32_t g = 0; g < (uint32_t)GROUPS; ++g) {
                     uint32_t va = ga[g], vb = gb[g];
                     ga[g] = a; gb[g] = b;
                     a += va; b += vb;
-                    mx = sm[g * GROUP] > mx ? sm[g * GROUP] : mx;
                 }
-                *total_a = a;
-                *total_b = b;
-                *total_max = mx;
-                start[n] = a;
-                lstart[n] = b;
-            }
-        } else if (ph == 3) {
-            sa[lane] += ga[lane / GROUP];
-            sb[lane] += gb[lane / GROUP];
-        } else {
-            uint32_t a = sa[lane], b = sb[lane];
-            if (quads && !zero_me) {
-                const Quad* c4 = (const Quad*)(cnt + lo);
-                Quad* s4 = (Quad*)(start + lo);
-                Quad* l4 = (Quad*)(lstart + lo);
-                for (uint32_t i = 0; i < per / 4; ++i) {
-                    Quad q = c4[i], qs, ql;
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        uint32_t v = q.v[k];
-                        qs.v[k] = a;
-                        ql.v[k] = b;
-                        a += v;
-                        b += L > 1 ? lanes_for(v, magic) : v;
+                if (last) {
+                    if (!in.diff) start[in.n] = a;
+                    lstart[in.n] = b;
+                    if (!offsets) {
+                        tot_a[nchunks] = a;
+                        tot_b[nchunks] = b;
+                        tot_b[nchunks + 1] = mx;
                     }
-                    s4[i] = qs;
-                    l4[i] = ql;
                 }
+            }
+        } else {
+            if (i0 >= in.n) return;
+            ScanInput::Quad q = in.quad(i0), qs, ql;
+            uint32_t a = sa[slot] + ga[lane / 16], b = sb[slot] + gb[lane / 16];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                qs.v[k] = a;
+                ql.v[k] = b;
+                a += q.v[k];
+                b += in.lanes_for(q.v[k]);
+            }
+            if (i0 + 4 <= in.n && (((uintptr_t)start | (uintptr_t)lstart) & 15u) == 0) {
+                if (!in.diff) *(ScanInput::Quad*)(start + i0) = qs;
+                *(ScanInput::Quad*)(lstart + i0) = ql;
             } else {
-                for (uint32_t i = lo; i < hi; ++i) {
-                    uint32_t v = cnt[i];
-                    start[i] = a;
-                    lstart[i] = b;
-                    a += v;
-                    b += L > 1 ? lanes_for(v, magic) : v;
-                    if (zero_me) zero_me[i] = 0;
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) {
+                    if (i0 + k >= in.n) break;
+                    if (!in.diff) start[i0 + k] = qs.v[k];
+                    lstart[i0 + k] = ql.v[k];
                 }
+            }
+            if (zero_me) {
+                for (uint32_t k = 0; k < 4 && i0 + k < in.n; ++k) zero_me[i0 + k] = 0;
             }
         }
     }
-};
-/* cnt[i] = prefix[i + 1] - prefix[i] */
-struct DiffCounts {
-    const uint32_t* prefix;
-    uint32_t* cnt;
-    TC_DEV void operator()(uint32_t t) const { cnt[t] = prefix[t + 1] - prefix[t]; }
 };
 
 /* largest b in [0, n) with prefix[b] <= t, for a non-decreasing prefix with prefix[n] > t */
@@ -1167,12 +1198,16 @@ struct AccAffine {
  * (the rows of an opening: 30 to 170 entries per bucket side by side) lanes in bucket order leave a fifth of a wave's
  * lane-time idle; handed out in the order of their lengths, longest first, the sub-runs of a wave are equally long.
  * perm[lane] = sub-run; its output slot stays the sub-run's own, so nothing after the accumulation changes.
- * SubrunHist: one lane per bucket (k sub-runs of a bucket with c entries: c mod k of length c / k + 1, the others of
- * length c / k).  SubrunBinStarts: one lane.  SubrunOrder: one lane per bucket again (no search for the bucket of a
+ * SubrunHist: a lane takes a bucket at a time (k sub-runs of a bucket with c entries: c mod k of length c / k + 1, the others of
+ * length c / k).  SubrunBinStarts: one lane.  SubrunOrder: the same lanes again (no search for the bucket of a
  * sub-run; the sub-runs of a bucket that has more than 64 of them -- one that holds most of a tensor has a million --
  * are placed by its whole workgroup); positions inside a bin are handed out by atomics, so the order inside a bin varies from run to
  * run -- the sums do not.  The passes over the partial sums
  * are ordered the same way; lstart = null stands for their last one, a lane per bucket over all that it holds. */
+/* A workgroup takes `per` times 256 buckets.  What bounded the two kernels was neither the buckets nor the counters in LDS
+ * but the counters in memory: every workgroup adds to the same few, and 12288 of them took 110 us for the additions to a
+ * line; a few hundred workgroups are enough for the reads: both kernels together 220 -> 47 us for 3.1 M buckets. */
+constexpr uint32_t SUBRUN_PER_LANE_MAX = 16;
 constexpr uint32_t SUBRUN_BINS = 65;          /* lengths 0 .. 63, and 64 or more */
 TC_HD uint32_t subrun_bin(uint32_t len) { return len < SUBRUN_BINS - 1u ? len : SUBRUN_BINS - 1u; }
 struct SubrunHist {
@@ -1181,25 +1216,26 @@ struct SubrunHist {
     static constexpr size_t LDS_BYTES = SUBRUN_BINS * sizeof(uint32_t);
     const uint32_t* start;
     const uint32_t* lstart;
-    uint32_t nbk;
+    uint32_t nbk, per;           /* buckets; of them per lane */
     uint32_t* hist;              /* SUBRUN_BINS counters, zero before the launch */
     TC_DEV void phase(int ph, uint32_t lane, uint32_t wg, uint8_t* lds) const {
         uint32_t* h = (uint32_t*)lds;
         if (ph == 0) {
             if (lane < SUBRUN_BINS) h[lane] = 0;
         } else if (ph == 1) {
-            uint32_t b = wg * (uint32_t)BLOCK + lane;
-            if (b >= nbk) return;
-            uint32_t c = start[b + 1] - start[b];
-            if (!lstart) {                   /* one lane per bucket, whatever it holds */
-                atomic_add_u32(&h[subrun_bin(c)], 1u);
-                return;
+            uint32_t b = wg * per * (uint32_t)BLOCK + lane;
+            for (uint32_t i = 0; i < per && b < nbk; ++i, b += (uint32_t)BLOCK) {
+                uint32_t c = start[b + 1] - start[b];
+                if (!lstart) {                   /* one lane per bucket, whatever it holds */
+                    atomic_add_u32(&h[subrun_bin(c)], 1u);
+                    continue;
+                }
+                uint32_t k = lstart[b + 1] - lstart[b];
+                if (!k) continue;
+                uint32_t base = c / k, more = c % k;
+                if (more) atomic_add_u32(&h[subrun_bin(base + 1u)], more);
+                atomic_add_u32(&h[subrun_bin(base)], k - more);
             }
-            uint32_t k = lstart[b + 1] - lstart[b];
-            if (!k) return;
-            uint32_t base = c / k, more = c % k;
-            if (more) atomic_add_u32(&h[subrun_bin(base + 1u)], more);
-            atomic_add_u32(&h[subrun_bin(base)], k - more);
         } else if (lane < SUBRUN_BINS && h[lane]) {
             atomic_add_u32(&hist[lane], h[lane]);
         }
@@ -1221,11 +1257,11 @@ struct SubrunBinStarts {         /* longest first */
 struct SubrunOrder {             /* one lane per bucket, which places its sub-runs one after the other */
     static constexpr int BLOCK = 256;
     static constexpr int PHASES = 4;
-    static constexpr size_t LDS_BYTES = (2 * SUBRUN_BINS + 1 + BLOCK) * sizeof(uint32_t);
+    static constexpr size_t LDS_BYTES = (2 * SUBRUN_BINS + 1 + BLOCK * SUBRUN_PER_LANE_MAX) * sizeof(uint32_t);
     static constexpr uint32_t OWN_MAX = 64;      /* a bucket with more sub-runs than this is placed by the whole workgroup */
     const uint32_t* start;
     const uint32_t* lstart;
-    uint32_t nbk;
+    uint32_t nbk, per;           /* buckets; of them per lane */
     const uint32_t* binstart;
     uint32_t* cursor;            /* zero before the launch */
     uint32_t* perm;
@@ -1241,19 +1277,20 @@ struct SubrunOrder {             /* one lane per bucket, which places its sub-ru
         uint32_t* base = cnt + SUBRUN_BINS;
         uint32_t* n_big = base + SUBRUN_BINS;     /* buckets of this workgroup with more than OWN_MAX sub-runs ... */
         uint32_t* big = n_big + 1;                /* ... and which (a bucket that holds most of a tensor has a million) */
-        uint32_t b = wg * (uint32_t)BLOCK + lane;
+        uint32_t b = wg * per * (uint32_t)BLOCK + lane;
         if (ph == 0) {
             if (lane < SUBRUN_BINS) cnt[lane] = 0;
             if (lane == 0) *n_big = 0;
         } else if (ph == 1) {
-            if (b >= nbk) return;
-            uint32_t slot0, k, c;
-            bucket(b, slot0, k, c);
-            if (!k) return;
-            uint32_t low = c / k, more = c % k;
-            if (more) atomic_add_u32(&cnt[subrun_bin(low + 1u)], more);
-            atomic_add_u32(&cnt[subrun_bin(low)], k - more);
-            if (k > OWN_MAX) big[atomic_add_u32(n_big, 1u)] = b;
+            for (uint32_t i = 0; i < per && b < nbk; ++i, b += (uint32_t)BLOCK) {
+                uint32_t slot0, k, c;
+                bucket(b, slot0, k, c);
+                if (!k) continue;
+                uint32_t low = c / k, more = c % k;
+                if (more) atomic_add_u32(&cnt[subrun_bin(low + 1u)], more);
+                atomic_add_u32(&cnt[subrun_bin(low)], k - more);
+                if (k > OWN_MAX) big[atomic_add_u32(n_big, 1u)] = b;
+            }
         } else if (ph == 2) {
             if (lane < SUBRUN_BINS) {
                 base[lane] = cnt[lane] ? binstart[lane] + atomic_add_u32(&cursor[lane], cnt[lane]) : 0u;
@@ -1261,7 +1298,7 @@ struct SubrunOrder {             /* one lane per bucket, which places its sub-ru
             }
         } else {
             uint32_t slot0, k, c;
-            if (b < nbk) {
+            for (uint32_t i = 0; i < per && b < nbk; ++i, b += (uint32_t)BLOCK) {
                 bucket(b, slot0, k, c);
                 if (k && k <= OWN_MAX) {
                     uint32_t low = lstart ? c / k : c, more = lstart ? c - low * k : 0u;

@@ -1320,18 +1320,16 @@ static const uint64_t SPLIT_LEVEL_LANES = 256;          /* the CPU build of the 
 static const uint64_t SPLIT_LEVEL_LANES = 131072;
 #endif
 
-/* prefix sums of cnt (n entries): start, lstart (of ceil(cnt / L)); optional zeroing of a cursor array */
+/* prefix sums of cnt (n entries): start, lstart (of ceil(cnt / L)); optional zeroing of a cursor array.  start = null: cnt is
+ * itself a prefix (n + 1 entries) and the counts are its differences. */
 static int scan_counts(tc_ctx* ctx, const uint32_t* cnt, uint32_t n, uint32_t L, uint32_t* start, uint32_t* lstart,
                        uint32_t* zero_me, uint32_t* tot_a, uint32_t* tot_b, uint32_t* tot_max) {
-    uint32_t nchunks = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
-    if (n <= ScanSmall::MAX_N) {          /* few buckets: one workgroup, one launch; the totals land where the chunked scan leaves them */
-        RT((launch_coop<ScanSmall::BLOCK>(1, ctx->stream,
-                                          ScanSmall{cnt, n, L, start, lstart, zero_me, tot_a + nchunks, tot_b + nchunks, tot_b + nchunks + 1})));
-        return TC_OK;
-    }
-    RT(rt::launch<64>(nchunks, ctx->stream, ScanChunkTotals{cnt, n, L, tot_a, tot_b, tot_max}));
-    RT((launch_coop<ScanChunkOffsets::BLOCK>(1, ctx->stream, ScanChunkOffsets{nchunks, tot_a, tot_b, tot_max, tot_b + nchunks + 1})));
-    RT(rt::launch<64>(nchunks, ctx->stream, ScanWrite{cnt, n, L, tot_a, tot_b, nchunks, start, lstart, zero_me}));
+    const uint32_t nchunks = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
+    const ScanInput in{cnt, n, L, start == nullptr};
+    const bool offsets = nchunks > SCAN_DIRECT_CHUNKS;
+    RT((launch_coop<ScanChunkTotals::BLOCK>(nchunks, ctx->stream, ScanChunkTotals{in, tot_a, tot_b, tot_max})));
+    if (offsets) RT((launch_coop<ScanChunkOffsets::BLOCK>(1, ctx->stream, ScanChunkOffsets{nchunks, tot_a, tot_b, tot_max, tot_b + nchunks + 1})));
+    RT((launch_coop<ScanWrite::BLOCK>(nchunks, ctx->stream, ScanWrite{in, nchunks, offsets, tot_a, tot_b, tot_max, start, lstart, zero_me})));
     return TC_OK;
 }
 
@@ -1575,6 +1573,12 @@ static void msm_config(const tc_ctx* ctx, int dtype, uint64_t n, int* W, int* c)
         *W = 256 / *c;
     }
 }
+/* workgroups that order the buckets (as long as a lane has few buckets: SUBRUN_PER_LANE_MAX) */
+#if defined(TC_HOST_EMU)
+static const uint32_t SUBRUN_WORKGROUPS = 1;
+#else
+static const uint32_t SUBRUN_WORKGROUPS = 512;
+#endif
 /* perm[lane] = sub-run (slot of the pass), longest first: the sub-runs of bucket b are the slots lstart[b] ..
  * lstart[b + 1] over its entries start[b] .. start[b + 1]; lstart = null: one slot per bucket.  `lanes` bounds the
  * number of slots from above. */
@@ -1583,10 +1587,12 @@ static int order_lanes(tc_ctx* ctx, const uint32_t* start, const uint32_t* lstar
     uint32_t* bins = ws_array<uint32_t>(ctx, 3 * SUBRUN_BINS);          /* histogram, bin starts, cursors */
     if (!perm || !bins) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
     RT(rt::launch<64>(SUBRUN_BINS, ctx->stream, Fill32{bins, 0u}));
-    RT((launch_coop<SubrunHist::BLOCK>((nbk + SubrunHist::BLOCK - 1) / SubrunHist::BLOCK, ctx->stream, SubrunHist{start, lstart, nbk, bins})));
+    const uint32_t per = std::max<uint32_t>(1, std::min<uint32_t>(SUBRUN_PER_LANE_MAX, nbk / (SUBRUN_WORKGROUPS * SubrunHist::BLOCK)));
+    const uint32_t groups = (nbk + SubrunHist::BLOCK * per - 1) / (SubrunHist::BLOCK * per);
+    RT((launch_coop<SubrunHist::BLOCK>(groups, ctx->stream, SubrunHist{start, lstart, nbk, per, bins})));
     RT(rt::launch<64>(1, ctx->stream, SubrunBinStarts{bins, bins + SUBRUN_BINS, bins + 2 * SUBRUN_BINS}));
-    RT((launch_coop<SubrunOrder::BLOCK>((nbk + SubrunOrder::BLOCK - 1) / SubrunOrder::BLOCK, ctx->stream,
-                                        SubrunOrder{start, lstart, nbk, bins + SUBRUN_BINS, bins + 2 * SUBRUN_BINS, perm})));
+    RT((launch_coop<SubrunOrder::BLOCK>(groups, ctx->stream,
+                                        SubrunOrder{start, lstart, nbk, per, bins + SUBRUN_BINS, bins + 2 * SUBRUN_BINS, perm})));
     *out_perm = perm;
     return TC_OK;
 }
@@ -1649,7 +1655,7 @@ static int msm_engine_multi(tc_ctx* ctx, int count, const MsmProblem* prob, int 
     if (ctx->static_mode) L1 = STATIC_L1;      /* fewer, longer sub-runs: the partial sums must fit the static scratch */
     /* fan-in of the middle passes: with few buckets a pass costs the chain of additions of one lane, and shorter
      * chains in more passes win (flat commitment of 2^21 terms: 2.74 / 2.70 / 2.59 / 3.08 ms with 16 / 8 / 4 / 2) */
-    const uint32_t L2 = ctx->opt[TC_OPT_ACC_FANIN] && !ctx->static_mode ? (uint32_t)ctx->opt[TC_OPT_ACC_FANIN] : nbk <= ScanSmall::MAX_N ? 4 : 16;
+    const uint32_t L2 = ctx->opt[TC_OPT_ACC_FANIN] && !ctx->static_mode ? (uint32_t)ctx->opt[TC_OPT_ACC_FANIN] : nbk <= 65536 ? 4 : 16;
 
     const bool wave_acc = items <= WAVE_ACC_MAX_ITEMS;
     if (wave_acc && !ctx->opt[TC_OPT_ACC_SUBRUN] && !ctx->static_mode) L1 = 4;
@@ -1840,10 +1846,8 @@ static int msm_engine_multi(tc_ctx* ctx, int count, const MsmProblem* prob, int 
     const uint64_t by_waves = nbk >= FAST_PASS_LANES ? 2 * WAVE_PASS_MAX : WAVE_PASS_MAX;
     const bool final_lanes = !raw && nbk >= FAST_PASS_LANES && (nbk >= ORDERED_LANES_MIN || lanes_bound > by_waves) && !ctx->static_mode;
     while (final_lanes ? worst > L2 : !raw && lanes_bound > by_waves && worst > 1 && !ctx->static_mode) {
-        /* counts of this pass = number of partials per bucket = differences of cur_start */
-        RT(rt::launch<256>(nbk, ctx->stream, DiffCounts{cur_start, cnt}));
-        TRY(scan_counts(ctx, cnt, nbk, L2, start, nxt_start, nullptr, tot_a, tot_b, tot_max));
-        /* `start` now equals cur_start (prefix of the same counts) */
+        /* counts of this pass = number of partial sums per bucket = differences of cur_start */
+        TRY(scan_counts(ctx, cur_start, nbk, L2, nullptr, nxt_start, nullptr, tot_a, tot_b, tot_max));
         lanes_bound = fewer(lanes_bound, L2);
         if (!spare_room((size_t)lanes_bound * sizeof(g1_xyzz))) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
         if (lanes_bound >= FAST_PASS_LANES && pass + 1 < MAX_ACC_PASSES) {
@@ -1870,8 +1874,7 @@ static int msm_engine_multi(tc_ctx* ctx, int count, const MsmProblem* prob, int 
         return reduce_windows(ctx, WavePoints{bucket, WAVE_XYZZ}, count, W, c, nb, results);
     }
     while (worst > (planned && !ctx->static_mode ? BUCKET_WAVE_MAX_UNSEEN : BUCKET_WAVE_MAX)) {
-        RT(rt::launch<256>(nbk, ctx->stream, DiffCounts{cur_start, cnt}));
-        TRY(scan_counts(ctx, cnt, nbk, WAVE_PASS_FANIN, start, nxt_start, nullptr, tot_a, tot_b, tot_max));
+        TRY(scan_counts(ctx, cur_start, nbk, WAVE_PASS_FANIN, nullptr, nxt_start, nullptr, tot_a, tot_b, tot_max));
         lanes_bound = fewer(lanes_bound, WAVE_PASS_FANIN);
         if (!spare_room((size_t)lanes_bound * WV_POINT_WORDS * 4)) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
         RT(launch_wave_groups((uint32_t)((lanes_bound + 3) / 4), ctx->stream, PassWave{WavePoints{cur, raw ? WAVE_RAW : WAVE_XYZZ}, cur_start, nxt_start, nbk, (uint32_t*)spare}));
