@@ -334,31 +334,6 @@ TC_HD g1_xyzz xyzz_madd32(const g1_xyzz& a, const g1_affine& q) {
     return r;
 }
 
-/* a + b, both XYZZ */
-TC_HD g1_xyzz xyzz_add32(const g1_xyzz& a, const g1_xyzz& b) {
-    if (xyzz_is_identity(b)) return a;
-    if (xyzz_is_identity(a)) return b;
-    fp_t U1 = fp_mul(a.X, b.ZZ);
-    fp_t U2 = fp_mul(b.X, a.ZZ);
-    fp_t S1 = fp_mul(a.Y, b.ZZZ);
-    fp_t S2 = fp_mul(b.Y, a.ZZZ);
-    fp_t Pd = fp_sub(U2, U1);
-    fp_t Rd = fp_sub(S2, S1);
-    if (fe_is_zero(Pd)) {
-        if (fe_is_zero(Rd)) return xyzz_dbl32(a);
-        return xyzz_identity();
-    }
-    fp_t PP = fp_sqr(Pd);
-    fp_t PPP = fp_mul(Pd, PP);
-    fp_t Q = fp_mul(U1, PP);
-    g1_xyzz r;
-    r.X = fp_sub(fp_sub(fp_sub(fp_sqr(Rd), PPP), Q), Q);
-    r.Y = fp_sub(fp_mul(Rd, fp_sub(Q, r.X)), fp_mul(S1, PPP));
-    r.ZZ = fp_mul(fp_mul(a.ZZ, b.ZZ), PP);
-    r.ZZZ = fp_mul(fp_mul(a.ZZZ, b.ZZZ), PPP);
-    return r;
-}
-
 /* affine from XYZZ given inv = 1 / (ZZ * ZZZ):  1/ZZ = inv ZZZ, 1/ZZZ = inv ZZ */
 TC_HD g1_affine xyzz_to_affine_with_inv(const g1_xyzz& p, const fp_t& inv) {
     if (xyzz_is_identity(p)) return affine_identity();

@@ -469,6 +469,25 @@ def test_quant_scale_on_device(T, ctx):
         assert dsts[i][0 if i % 3 == 1 else -1].item() == 77           # nothing written outside the tensor
 
 
+@pytest.mark.parametrize("pieces", [1, 63, 511, 512, 513, 960, 1023, 1025])
+def test_batch_quantisation_by_waves(T, ctx, pieces):
+    """The waves of a shared quantisation at the edges of their 512 pieces of eight values, two aligned tensors of that
+    size with a ragged end, one of them in place: equal to the oracle's tensors."""
+    import torch
+
+    rng = np.random.default_rng(pieces)
+    flats = [rng.standard_normal(8 * pieces + r).astype(np.float16) for r in (0, 5)]
+    bufs = [to_device(np.concatenate([f.view(np.int16), np.full(16, 77, np.int16)])) for f in flats]
+    other = torch.full((flats[0].size + 16,), 77, dtype=torch.int16, device="cuda")
+    scales = torch.zeros(2, dtype=torch.float32, device="cuda")
+    ctx.encode_batch_scaled(bufs, [f.size for f in flats], scales, [other, bufs[1]])
+    ctx.sync()
+    for f, out in zip(flats, (other, bufs[1])):
+        got = out.cpu().numpy()
+        assert np.array_equal(got[: f.size], quantize.quantize_f16(f, quantize.inv_scale_for(f)))
+        assert (got[f.size :] == 77).all()
+
+
 def _check_tree_against_oracle(ctx, tree, otree):
     assert tree.levels == len(otree.levels)
     for L in range(tree.levels):
