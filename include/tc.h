@@ -143,7 +143,7 @@ int tc_ctx_alu_rate(tc_ctx* ctx, int kind, int waves_per_simd, double* out_per_s
  *          4 R^2 / a (inverse of a Montgomery representative, a != 0)   5 a b / R in Fr   6 a + b   7 a - b
  *          8 R^2 / a in Fr
  *          9 a b / R   10 a^2 / R   11 (a - b)(a + b) / R   12 (a - 2 b)(a - b) / R
- *          13 ((a - b)(a + b) - b (a - b)) / R: the 28-bit-limb form of the bucket accumulation (operands re-cut, sums
+ *          13 ((a - b)(a + b) - b (a - b)) / R: the 28-bit-limb form of the group law (operands re-cut, sums
  *          and differences left unreduced with signed limbs, one product -- for 13 the difference of two products
  *          under one reduction --, back to the canonical element).
  *          14 2^776 / a by the inversion of a whole wave (n <= 2^24): a is given as 14 signed limbs of 28 bits, one to a
