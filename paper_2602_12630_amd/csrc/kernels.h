@@ -175,7 +175,7 @@ struct EncodeF16x8 {
     Words16* dst;
     float inv_scale;
     const float* inv_scale_dev;
-    TC_DEV Words16 piece(const Words16& in, float s) const {
+    TC_DEV static Words16 piece(Words16 in, float s) {
         Words16 out;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -186,7 +186,10 @@ struct EncodeF16x8 {
         return out;
     }
     TC_DEV float scale() const { return inv_scale_dev ? *inv_scale_dev : inv_scale; }
-    TC_DEV void operator()(uint32_t t) const { dst[t] = piece(src[t], scale()); }
+    TC_DEV void operator()(uint32_t t) const {
+        Words16 in = src[t];
+        dst[t] = piece(in, scale());
+    }
 };
 /* Per-tensor scale of the quantisation: the largest magnitude among the finite fp16 values, then
  * inv_scale = float32(32767) / float32(amax) (0 for a tensor without a non-zero finite value).  Magnitudes of finite
@@ -307,11 +310,11 @@ struct EncodeF16x8Wave {
             for (uint32_t i = 0; i < PIECES; ++i) in[i] = one.src[first + 64 * i];
 #pragma unroll
             for (uint32_t i = 0; i < PIECES; ++i) {
-                Words16 o = one.piece(in[i], s);
+                Words16 o = EncodeF16x8::piece(in[i], s);
                 store(one.dst + first + 64 * i, o);
             }
         } else {
-            for (uint32_t i = 0; i < PIECES && first + 64 * i < pieces; ++i) one.dst[first + 64 * i] = one.piece(one.src[first + 64 * i], s);
+            for (uint32_t i = 0; i < PIECES && first + 64 * i < pieces; ++i) one.dst[first + 64 * i] = EncodeF16x8::piece(one.src[first + 64 * i], s);
         }
     }
 };
