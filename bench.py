@@ -41,10 +41,10 @@ import tc_inputs  # noqa: E402
 # Montgomery product of 12 x 32-bit limbs = 2 * 12^2 + 12 = 300 32x32->64 multiply-adds.
 FP_MULS_PER_MIXED_ADD = 10
 MADS_PER_FP_MUL = 300
-# What the accumulation kernel issues per mixed addition: it computes in 14 limbs of 28 bits (no carry
-# instructions), 392 multiply-adds a product, 301 a squaring, 588 for the difference of two products under one
-# reduction: 6 products + 2 squarings + 1 such difference.
-MADS_ISSUED_PER_MIXED_ADD = 6 * 392 + 2 * 301 + 588
+# What the accumulation kernel issues per mixed addition: it computes in 13 limbs of 30 bits (no carry
+# instructions), 338 multiply-adds a product, 260 a squaring, 507 for the difference of two products under one
+# reduction: 6 products + 2 squarings + 1 such difference, and 49 more in the loop's listing.
+MADS_ISSUED_PER_MIXED_ADD = 6 * 338 + 2 * 260 + 507 + 49
 # Integer-ALU peak by the formula: v_mad_u64_u32 at half the full vector rate, 256 CU x 4 SIMD x 16 lanes x
 # 2.4 GHz / 2.  Printed beside the rate that `alu_peak` measures in the same run, which is the denominator used.
 FORMULA_PEAK_MADS_PER_S = 256 * 4 * 16 * 2.4e9 / 2
@@ -52,12 +52,12 @@ R_MODULUS = 0x73EDA753299D7D483339D80809A1D80553BDA402FFFE5BFEFFFFFFFF00000001  
 # HBM bytes moved by the bucket-accumulation launch of one LLaMA2-7B-shaped build (rocprofv3 --pmc FETCH_SIZE /
 # WRITE_SIZE of `bench.py --only-c3-build`, scaled by a 256 MiB copy kernel; runs and scale factors in
 # profiles/c3_build_hbm_traffic_pmc.txt).
-ACC_TRAFFIC_BYTES_C3 = 5.179e10
+ACC_TRAFFIC_BYTES_C3 = 5.176e10
 # Vector instructions that the same launch issues per SIMD and clock, and per mixed addition (rocprofv3 --pmc
 # SQ_INSTS_VALU / GRBM_GUI_ACTIVE of the same command: profiles/c3_build_sq_counters_pmc.txt).  A 64-lane wave takes
 # four clocks of a 16-lane SIMD, so 0.25 is the most a SIMD can issue.
-ACC_VALU_PER_SIMD_CLK_C3 = 0.245
-ACC_VALU_PER_ADDITION_C3 = 4777
+ACC_VALU_PER_SIMD_CLK_C3 = 0.247
+ACC_VALU_PER_ADDITION_C3 = 4045
 
 
 # ----------------------------------------------------------------------------------------------------------
@@ -239,7 +239,7 @@ def bench_c3(ctx, T, torch, node_srs, tau, steps, warmup, peak):
                      "peak_source": "alu_peak.used, measured in this run",
                      "frac_of_formula_peak": achieved / FORMULA_PEAK_MADS_PER_S,
                      # the unit of `achieved` is the algorithm's count (10 Fp products x 300 multiply-adds at 32-bit
-                     # limbs); the kernel's own 28-bit-limb products issue more multiply-adds for the same addition
+                     # limbs); the kernel's own 30-bit-limb products issue a few more multiply-adds for the same addition
                      "multiply_adds_issued_per_addition": MADS_ISSUED_PER_MIXED_ADD,
                      "issue_frac": acc_executed * MADS_ISSUED_PER_MIXED_ADD / (kern_ms * 1e-3) / peak,
                      "issue_frac_note": "multiply-adds the launch really issues over the measured multiply-add peak",
@@ -564,7 +564,7 @@ def bench_c2_step(ctx, T, torch, lib, node_srs, tau, steps, warmup, in_flight, o
         "kernels": [
             kernel_line("AccAffine (bucket accumulation of tc_commit)", kern_ms, acc_executed * per_mixed,
                         "%d of %d mixed additions run in this launch, the rest in the passes after it" % (acc_executed, nonzero)),
-            kernel_line("NodeCommitSmall (level 0 of the tree)", node_ms / prof_steps, nonzero * per_mixed,
+            kernel_line("NodeCommit (level 0 of the tree)", node_ms / prof_steps, nonzero * per_mixed,
                         "one mixed addition per non-zero entry, fixed-base tables"),
             kernel_line("node commitments of levels 1..%d" % (len(levels) - 1), upper_ms / prof_steps,
                         upper_children * 16 * per_mixed, "16 window terms per child; %d launches a step, the small levels bound by depth" % (upper_launches // prof_steps)),
@@ -633,7 +633,7 @@ def coefficient_route(ctx, T, torch, with_oracle, peak):
     path): the sweep of Fig. 1, N = 2^12 samples reshaped to order-m grids, in Newton form (`gpu_ms`), in the
     Gregory and barycentric forms of App. C and as tc_interpolate does it (`gpu_ms_tc_interpolate`: over a tree of the
     nodes where that is faster), and the C2 activation by tc_interpolate, both axes over the tree; one Fr product
-    = 2 * 8^2 + 8 = 136 multiply-adds."""
+    = 2 * 8^2 + 8 = 136 multiply-adds in the algorithm's count (nine limbs of 29 bits issue 153)."""
     from oracle import tc as otc
 
     out = {"sweep_n_4096": []}
