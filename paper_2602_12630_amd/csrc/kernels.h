@@ -806,7 +806,7 @@ struct SortKeys {              /* the tiles of CountKeys: entries in bucket orde
 /* A chunk is SCAN_CHUNK consecutive counts, four to a lane of one workgroup.  ScanChunkTotals leaves the sums of cnt and of
  * ceil(cnt / L) and the largest count of every chunk; ScanWrite adds up the totals of the chunks before its own and writes
  * the prefixes.  (Above SCAN_DIRECT_CHUNKS chunks that sum, which grows with the square of their number, is left to one
- * workgroup in between: ScanChunkOffsets.)  What bounds them is the counts, read twice, and the two prefixes written once;
+ * workgroup in between: ScanChunkOffsets.  A lone chunk needs no totals.)  What bounds them is the counts, read twice, and the two prefixes written once;
  * a lane that walks 256 counts by itself reads a line per lane and step: 137 us for 3.1 M counts that way, 40 us
  * with these; for 32768 counts one workgroup took 25.5 us, these 11 us.
  * With `diff` the counts are the differences of a prefix, cnt[i] = prefix[i + 1] - prefix[i] (the sums that a bucket still
@@ -966,22 +966,21 @@ struct ScanWrite {
         const uint32_t slot = lane + lane / 16, i0 = wg * SCAN_CHUNK + lane * 4;
         if (ph == 0) {
             ScanInput::Quad q = in.quad(i0);
-            uint32_t a = 0, b = 0;
+            uint32_t a = 0, b = 0, mx = 0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 a += q.v[k];
                 b += in.lanes_for(q.v[k]);
+                mx = q.v[k] > mx ? q.v[k] : mx;
             }
             sa[slot] = a; sb[slot] = b;
             a = 0; b = 0;
-            uint32_t mx = 0;
             if (!offsets) {
                 for (uint32_t t = lane; t < wg; t += (uint32_t)BLOCK) {
                     a += tot_a[t];
                     b += tot_b[t];
                     if (last && tot_max[t] > mx) mx = tot_max[t];
                 }
-                if (last && lane == 0 && tot_max[wg] > mx) mx = tot_max[wg];
             }
             pa[lane] = a; pb[lane] = b; pm[lane] = mx;
         } else if (ph == 1) {

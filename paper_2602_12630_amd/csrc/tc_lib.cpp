@@ -1327,7 +1327,7 @@ static int scan_counts(tc_ctx* ctx, const uint32_t* cnt, uint32_t n, uint32_t L,
     const uint32_t nchunks = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
     const ScanInput in{cnt, n, L, start == nullptr};
     const bool offsets = nchunks > SCAN_DIRECT_CHUNKS;
-    RT((launch_coop<ScanChunkTotals::BLOCK>(nchunks, ctx->stream, ScanChunkTotals{in, tot_a, tot_b, tot_max})));
+    if (nchunks > 1) RT((launch_coop<ScanChunkTotals::BLOCK>(nchunks, ctx->stream, ScanChunkTotals{in, tot_a, tot_b, tot_max})));
     if (offsets) RT((launch_coop<ScanChunkOffsets::BLOCK>(1, ctx->stream, ScanChunkOffsets{nchunks, tot_a, tot_b, tot_max, tot_b + nchunks + 1})));
     RT((launch_coop<ScanWrite::BLOCK>(nchunks, ctx->stream, ScanWrite{in, nchunks, offsets, tot_a, tot_b, tot_max, start, lstart, zero_me})));
     return TC_OK;
