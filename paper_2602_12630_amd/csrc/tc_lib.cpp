@@ -105,6 +105,7 @@ struct tc_srs {
     uint64_t n[4] = {0, 0, 0, 0};
     g1_affine* pts[4] = {nullptr, nullptr, nullptr, nullptr};
     g1_affine* fb[4] = {nullptr, nullptr, nullptr, nullptr};
+    bool fb_identity = false;           /* fb[0] holds the identity: a base that is, or one outside the prime-order subgroup (imported points only) */
     g1_affine* open_tab = nullptr;      /* U[kappa, t] of the leading axis (TC_SRS_OPEN_TABLE), n[0] points */
     bool shifted = false;               /* pts[0] has 2 n[0] points, the second half holding 2^8 times the first (TC_SRS_OPEN_TABLE) */
     uint8_t* pad0 = nullptr;            /* pts[0] (both halves) once more at a stride of 128 bytes: what the accumulation gathers from */
@@ -1138,6 +1139,17 @@ extern "C" int tc_srs_export(tc_ctx* ctx, const tc_srs* srs, void* host_buf, siz
     }
 }
 
+static int holds_identity(tc_ctx* ctx, const g1_affine* d_pts, uint64_t n, bool* out) {
+    WS(d_found, uint32_t, 1);
+    uint32_t found = 0;
+    RT(rt::launch<64>(1, ctx->stream, Fill32{d_found, 0u}));
+    RT(rt::launch<256>(n, ctx->stream, AnyIdentity{d_pts, d_found}));
+    RT(rt::memcpy_d2h(&found, d_found, 4, ctx->stream));
+    TRY(ctx_sync(ctx));
+    *out = found != 0;
+    return TC_OK;
+}
+
 extern "C" int tc_srs_import(tc_ctx* ctx, const void* host_buf, size_t len, tc_srs** out) {
     try {
         if (!ctx) return TC_ERR_ARG;
@@ -1188,6 +1200,7 @@ extern "C" int tc_srs_import(tc_ctx* ctx, const void* host_buf, size_t len, tc_s
             rc = import_points(ctx, src, n[a], srs->pts[a]);
             src += 96 * (size_t)n[a];
             if (rc == TC_OK && (flags & TC_SRS_FIXED_BASE)) rc = build_fixed_base_table(ctx, srs->pts[a], (uint32_t)n[a], &srs->fb[a]);
+            if (rc == TC_OK && a == 0 && srs->fb[0]) rc = holds_identity(ctx, srs->fb[0], n[0] * FB_W * FB_NB, &srs->fb_identity);
             if (rc == TC_OK && twice) {
                 const uint64_t slab = std::min<uint64_t>(1ull << 20, n[a]);
                 void* tmp = nullptr;
@@ -2617,7 +2630,7 @@ static int tree_prepare(tc_ctx* ctx, const tc_tree_desc* desc, tc_tree** out) {
 /* a level of n nodes by lanes, a lane per node (bottom level) or per child, in chunks that bound the partial sums */
 static const uint64_t NODE_CHUNK_LANES = 1ull << 20;
 template <bool BOTTOM>
-static int node_commit_lanes(tc_ctx* ctx, NodeCommit<BOTTOM> k, uint64_t n, g1_xyzz* out) {
+static int node_commit_lanes(tc_ctx* ctx, NodeCommit<BOTTOM> k, bool identities, uint64_t n, g1_xyzz* out) {
     const uint32_t per = BOTTOM ? 1u : k.g.B;
     const uint64_t chunk = std::max<uint64_t>(1, std::min<uint64_t>(n, NODE_CHUNK_LANES / per)), lanes_max = chunk * per;
     g1_xyzz* part[2] = {nullptr, nullptr};
@@ -2637,7 +2650,8 @@ static int node_commit_lanes(tc_ctx* ctx, NodeCommit<BOTTOM> k, uint64_t n, g1_x
         k.first = n0 * per;
         k.out = per > 1 ? part[0] : out + n0;
         RT(rt::launch<64>(COUNTERS, ctx->stream, Fill32{redo, 0u}));
-        RT((rt::launch_waves<64, 3>(lanes, ctx->stream, k)));
+        if (identities) RT(rt::launch<64>(lanes, ctx->stream, ListAll{(uint32_t)lanes, k.redo_count, k.redo_list}));
+        else RT((rt::launch_waves<64, 3>(lanes, ctx->stream, k)));
         RT(rt::launch<64>(redo_lanes, ctx->stream, NodeCommitRedo<BOTTOM>{k, redo_lanes}));
         /* sums of up to four, as many lanes as there are left; a prime arity above that in one go */
         int from = 0;
@@ -2698,7 +2712,7 @@ extern "C" int tc_terkle_build(tc_ctx* ctx, const tc_tree_desc* desc, tc_tree** 
                         } else if (bottom) {
                             rt::event_t e0, e1;
                             prof_begin(ctx, TC_PROF_NODE_COMMIT, &e0, &e1);
-                            rc = node_commit_lanes(ctx, NodeCommit<true>{g, t->d_payload, t->dtype, nullptr, ns->fb[0], 0, nullptr, nullptr, nullptr}, lv.n, acc);
+                            rc = node_commit_lanes(ctx, NodeCommit<true>{g, t->d_payload, t->dtype, nullptr, ns->fb[0], 0, nullptr, nullptr, nullptr}, ns->fb_identity, lv.n, acc);
                             prof_end(ctx, TC_PROF_NODE_COMMIT, e0, e1);
                             if (rc) break;
                             e = 0;
@@ -2721,7 +2735,7 @@ extern "C" int tc_terkle_build(tc_ctx* ctx, const tc_tree_desc* desc, tc_tree** 
                             prof_begin(ctx, TC_PROF_NODE_COMMIT_UPPER, &e0, &e1);
                             e = 0;
                             if (logH == 0)
-                                rc = node_commit_lanes(ctx, NodeCommit<false>{g, nullptr, 0, t->levels[L - 1].phi, ns->fb[0], 0, nullptr, nullptr, nullptr}, lv.n, acc);
+                                rc = node_commit_lanes(ctx, NodeCommit<false>{g, nullptr, 0, t->levels[L - 1].phi, ns->fb[0], 0, nullptr, nullptr, nullptr}, ns->fb_identity, lv.n, acc);
                             else
                                 e = launch_coop<64>((uint32_t)((lanes + 63) / 64), ctx->stream,
                                                     NodeCommitFrCoop<64>{g, t->levels[L - 1].phi, ns->fb[0], lv.n, logB, logH, acc});

@@ -7,7 +7,7 @@ import numpy as np
 
 import tc_inputs
 from oracle import bls12_381 as ec
-from oracle import cbind, tc
+from oracle import cbind, tc, terkle
 
 TAU = tc_inputs.trapdoors()
 TAU_BYTES = tc_inputs.trapdoor_bytes()
@@ -281,3 +281,56 @@ def check_verification(ctx, m):
         assert not ctx.verify(vk, shape, ec.g1_to_bytes(ec.add(C, ec.G1)), kappa, yb, pb), (k, y)
         assert not ctx.verify(vk, shape, Cb, kappa, yb, pb[:-1] + [(1).to_bytes(48, "little") * 2]), (k, y)
         assert not ctx.verify(vk, shape, Cb, kappa, (y + ec.R).to_bytes(32, "little"), pb), (k, y)
+
+
+def check_tree_over_bases(ctx, upload, bases, side, tile):
+    """Every node of an entries tree over `side` x `side` int8 entries, node shape (2, 2), whose four node bases are what
+    `bases` makes of the points of a proper Lagrange SRS.  The entries repeat every `tile` of them, so that the oracle has few
+    distinct nodes to sum term by term."""
+    import paper_2602_12630_amd as T
+
+    srs = ctx.setup_from_trapdoor(TAU_BYTES, (2, 2), T.TC_SRS_SUFFIX | T.TC_SRS_FIXED_BASE)
+    data = bytes(srs.export())
+    srs.close()
+    S = bases([ec.g1_from_bytes(data[56 + 96 * k : 56 + 96 * (k + 1)]) for k in range(4)])
+    srs = ctx.srs_import(data[:56] + b"".join(ec.g1_to_bytes(p) for p in S) + data[56 + 96 * 4 :])
+    X = np.random.default_rng(31).integers(-3, 4, size=(tile, tile)).astype(np.int8)
+    X[:8, :8] = 1
+    X = np.ascontiguousarray(np.tile(X, (side // tile + 1, side // tile + 1))[:side, :side])
+    payload = upload(X)
+    tree = ctx.terkle_build_entries(srs, payload, T.TC_I8, (side, side), (2, 2))
+    try:
+        got = bytes(tree.export())[72:]
+        seen, at = {}, 0
+        below = [[int(v) for v in row] for row in X]
+        while len(below) > 1:
+            n = (len(below) + 1) // 2
+            child = lambda i, j: below[i][j] if i < len(below) and j < len(below) else 0
+            level = []
+            for i in range(n):
+                row = []
+                for j in range(n):
+                    values = tuple(child(2 * i + k // 2, 2 * j + k % 2) for k in range(4))
+                    if values not in seen:
+                        C = ec.INF
+                        for v, p in zip(values, S):
+                            C = ec.add(C, ec.mul(v, p) if v >= 0 else ec.neg(ec.mul(-v, p)))
+                        seen[values] = ec.g1_to_bytes(C), terkle.phi(C)
+                    want, phi = seen[values]
+                    assert got[at : at + 96] == want, (side, n, i, j)
+                    at += 96
+                    row.append(phi)
+                level.append(row)
+            below = level
+        assert at == len(got)
+    finally:
+        tree.close()
+        srs.close()
+
+
+ORDER_THREE = (0, 2)           # on the curve, and no element of the prime-order subgroup: every third multiple is the identity
+NODE_BASES_WITH_IDENTITY = {
+    "one": lambda S: [S[0], S[1], ec.INF, S[3]],
+    "all": lambda S: [ec.INF] * 4,
+    "multiples": lambda S: [ORDER_THREE, S[1], ORDER_THREE, S[3]],
+}

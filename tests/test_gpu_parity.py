@@ -12,7 +12,7 @@ from oracle import bls12_381 as ec
 from oracle import cbind, quantize, tc, terkle
 from oracle.bls12_381 import R
 
-from gpu_util import HOST_THREADS, TAU_BYTES, Stopwatch, check_field_arithmetic, check_wave_inversion, check_one_point_throughout, check_repeated_points, check_verification, fr_bytes_array, oracle_pool, parse_proof, pps, progress, serialize_steps, to_device
+from gpu_util import HOST_THREADS, TAU_BYTES, Stopwatch, check_field_arithmetic, check_wave_inversion, check_one_point_throughout, check_repeated_points, check_tree_over_bases, check_verification, NODE_BASES_WITH_IDENTITY, fr_bytes_array, oracle_pool, parse_proof, pps, progress, serialize_steps, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -1213,6 +1213,15 @@ def test_arity_64_trees(T, ctx, node, grid):
     finally:
         tree.close()
         srs.close()
+
+
+@pytest.mark.parametrize("side", [64, 528])
+@pytest.mark.parametrize("bases", sorted(NODE_BASES_WITH_IDENTITY))
+def test_tree_over_bases_with_the_identity(ctx, bases, side):
+    """Node bases, or multiples of them, that are the identity (an imported SRS may hold such points): all levels by whole
+    waves (64 x 64 entries), and a bottom level by a lane per node (69696 of them) under one by a lane per child
+    (17424 nodes; up to 16384 of this arity the windows of a child are spread over lanes)."""
+    check_tree_over_bases(ctx, to_device, NODE_BASES_WITH_IDENTITY[bases], side, 24)
 
 
 @pytest.mark.parametrize("m", [1, 2, 3, 4])

@@ -25,7 +25,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 import __graft_entry__ as entry  # noqa: E402
 import paper_2602_12630_amd as T  # noqa: E402
-from gpu_util import TAU_BYTES, check_field_arithmetic, check_wave_inversion, check_one_point_throughout, check_repeated_points, check_verification, fr_bytes_array, pps, serialize_steps  # noqa: E402
+from gpu_util import TAU_BYTES, check_field_arithmetic, check_wave_inversion, check_one_point_throughout, check_repeated_points, check_tree_over_bases, check_verification, NODE_BASES_WITH_IDENTITY, fr_bytes_array, pps, serialize_steps  # noqa: E402
 
 EMU = os.path.join(ROOT, "tests", "hostmath", "libtc_hostemu.so")
 
@@ -559,6 +559,14 @@ def test_emulated_tree_over_repeated_bases(emu, node_srs):
     finally:
         tree.close()
         srs.close()
+
+
+@pytest.mark.parametrize("side", [4, 24, 40])
+@pytest.mark.parametrize("bases", sorted(NODE_BASES_WITH_IDENTITY))
+def test_emulated_tree_over_bases_with_the_identity(emu, bases, side):
+    """Node bases, or multiples of them, that are the identity (an imported SRS may hold such points): levels by whole waves
+    (4 x 4 entries) and levels that a lane per node and a lane per child commit (24 x 24 and 40 x 40)."""
+    check_tree_over_bases(emu, lambda a: a, NODE_BASES_WITH_IDENTITY[bases], side, 12)
 
 
 def test_emulated_commit_static(emu):
