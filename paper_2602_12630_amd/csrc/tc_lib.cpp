@@ -343,9 +343,12 @@ static int launch_coop(uint32_t groups, rt::stream_t st, const F& f) {
 #endif
 
 /* ---- the same by whole waves: a phase is a call per wave, its lanes the limbs of what the wave works on (wave28.h) ---- */
+/* a launch has fewer than 2^32 work-items, 64 of them to a wave; more are refused, as by the runtime */
 #if defined(TC_HOST_EMU)
+static const uint64_t LAUNCH_WORK_ITEMS = 1ull << 25;          /* scaled like the sizes at which the CPU build of the tests changes routes */
 template <class F>
-static int launch_wave_groups(uint32_t groups, rt::stream_t, const F& f) {
+static int launch_wave_groups(uint64_t groups, rt::stream_t, const F& f) {
+    if (groups > LAUNCH_WORK_ITEMS / (F::WAVES * 64u)) return 1;
     std::vector<uint8_t> lds(F::LDS_BYTES);
     for (uint32_t g = 0; g < groups; ++g)
         for (int ph = 0; ph < F::PHASES; ++ph)
@@ -362,11 +365,13 @@ __global__ __launch_bounds__(F::WAVES * 64) void wave_kernel(const F f) {
         __syncthreads();
     }
 }
+static const uint64_t LAUNCH_WORK_ITEMS = 0xFFFFFFFFull;
 template <class F>
-static int launch_wave_groups(uint32_t groups, rt::stream_t st, const F& f) {
+static int launch_wave_groups(uint64_t groups, rt::stream_t st, const F& f) {
     static_assert(F::LDS_BYTES <= 64 * 1024, "what a launch may take without asking");
     if (!groups) return 0;
-    hipLaunchKernelGGL((wave_kernel<F>), dim3(groups), dim3(F::WAVES * 64), F::LDS_BYTES, st, f);
+    if (groups > LAUNCH_WORK_ITEMS / (F::WAVES * 64u)) return (int)hipErrorInvalidValue;
+    hipLaunchKernelGGL((wave_kernel<F>), dim3((uint32_t)groups), dim3(F::WAVES * 64), F::LDS_BYTES, st, f);
     return (int)hipGetLastError();
 }
 #endif
@@ -1551,19 +1556,28 @@ static const uint64_t SORT_MIN_BIN_LOAD = SORT_TILE / 4;
  * in a row and 25 to 40 us for the prefix sums between two passes; the lines lie where the two meet.
  * WAVE_ACC_MAX_ITEMS: entries of a launch that are accumulated by waves (AccWave; lanes took 45 us and up whatever there was, and
  * AccFinal 50: commitment of 1024 int8 entries 121 -> 15 us for the two).
+ * WAVE_ACC_MAX_BUCKETS: the same in buckets, each of which then takes a wave of its own in the last pass; above it that pass goes by lanes.  Whole
+ * calls with int16 tensors (32768 buckets each), accumulated and summed by waves / lanes: 16 tensors of 1024 entries 923 / 944 us, 24 of 600
+ * 1043 / 1068, 32 of 32 732 / 534, 96 of 32 1708 / 1053.
  * WAVE_PASS_MAX: partial sums that go straight into the buckets (BucketWave).  Whole calls at 1.93e5 and 1e5 partial sums with
  * the line at 200000 / 110000: 512 x 4096 int16 826 / 769 us, 487 x 11008 1320 / 1241 us; where the pass by lanes that it saves is one over
  * 131072 buckets or more, with three launches of prefix sums, twice as many: four tensors of 64 x 4096 in one call 805 / 1015 us. */
 #if defined(TC_HOST_EMU)
 /* the CPU build of the tests walks both sides with small problems */
 static const uint64_t WAVE_ACC_MAX_ITEMS = 100, WAVE_PASS_MAX = 2048;
+static const uint32_t WAVE_ACC_MAX_BUCKETS = 1u << 17;
 static const uint64_t BUCKET_WAVE_MAX = 16, BUCKET_WAVE_MAX_UNSEEN = 32;
 #else
 static const uint64_t WAVE_ACC_MAX_ITEMS = 16384;
+static const uint32_t WAVE_ACC_MAX_BUCKETS = (1u << 20) - 1;
 static const uint64_t WAVE_PASS_MAX = 110000;          /* partial sums */
 static const uint64_t BUCKET_WAVE_MAX = 64;            /* partial sums in the fullest bucket when the last pass starts */
 static const uint64_t BUCKET_WAVE_MAX_UNSEEN = 256;    /* the same where it is not known but cannot be more */
 #endif
+static const uint64_t BUCKET_ONE_WAVE_MAX = 16;        /* with more than that a bucket takes four waves, not one */
+/* ... and with four waves to every bucket of a launch not to wait for the number costs more than it saves from some buckets on: 64 int8 tensors of
+ * 256 entries (8192 buckets) 244 us, 234 with the wait, 16 of 1024 (2048 buckets) 172 and 176; 16 int16 tensors of 1024 entries 1232 and 923 us */
+static const uint32_t UNSEEN_MAX_BUCKETS = 4096;
 static const uint32_t WAVE_PASS_FANIN = 16;
 
 /* One MSM problem: result = sum_i [e(s_i)] pts[i] over n terms */
@@ -1672,12 +1686,12 @@ static int msm_engine_multi(tc_ctx* ctx, int count, const MsmProblem* prob, int 
      * chains in more passes win (flat commitment of 2^21 terms: 2.74 / 2.70 / 2.59 / 3.08 ms with 16 / 8 / 4 / 2) */
     const uint32_t L2 = ctx->opt[TC_OPT_ACC_FANIN] && !ctx->static_mode ? (uint32_t)ctx->opt[TC_OPT_ACC_FANIN] : nbk <= 65536 ? 4 : 16;
 
-    const bool wave_acc = items <= WAVE_ACC_MAX_ITEMS;
+    const bool wave_acc = items <= WAVE_ACC_MAX_ITEMS && nbk <= WAVE_ACC_MAX_BUCKETS;
     if (wave_acc && !ctx->opt[TC_OPT_ACC_SUBRUN] && !ctx->static_mode) L1 = 4;
     uint32_t totals[2] = {0, 0};   /* sub-runs of the first pass and the largest bucket: which passes are needed */
     /* where even the worst case, every term in one bucket, is a short sum, the fullest bucket is not read back (a wait for the
      * stream in the middle of the call) */
-    const bool planned = ctx->static_mode || (wave_acc && (max_items + L1 - 1) / L1 <= BUCKET_WAVE_MAX_UNSEEN);
+    const bool planned = ctx->static_mode || (wave_acc && (max_items + L1 - 1) / L1 <= (nbk <= UNSEEN_MAX_BUCKETS ? BUCKET_WAVE_MAX_UNSEEN : BUCKET_ONE_WAVE_MAX));
     if ((dtype != TC_FR && dtype != DT_FR128) || ((nbk_pp == 4096 || nbk_pp == 2176) && !ctx->static_mode)) {
         /* small scalars (one or two digits per term), and full-width scalars in 8-bit windows (4096 keys per problem):
          * tile histograms in LDS, no global atomics */
@@ -1900,7 +1914,7 @@ static int msm_engine_multi(tc_ctx* ctx, int count, const MsmProblem* prob, int 
     if (!bucket) return fail(ctx, TC_ERR_NOMEM, "device workspace allocation failed");
     uint32_t* to_raw = by_lanes ? nullptr : (uint32_t*)bucket;
     const WavePoints parts{cur, raw ? WAVE_RAW : WAVE_XYZZ};
-    if (worst > 16) RT(launch_wave_groups(nbk, ctx->stream, BucketWave<4>{parts, cur_start, nbk, to_raw, (g1_xyzz*)bucket}));
+    if (worst > BUCKET_ONE_WAVE_MAX) RT(launch_wave_groups(nbk, ctx->stream, BucketWave<4>{parts, cur_start, nbk, to_raw, (g1_xyzz*)bucket}));
     else RT(launch_wave_groups((nbk + 3u) / 4u, ctx->stream, BucketWave<1>{parts, cur_start, nbk, to_raw, (g1_xyzz*)bucket}));
     return reduce_windows(ctx, WavePoints{bucket, by_lanes ? WAVE_XYZZ : WAVE_RAW}, count, W, c, nb, results);
 }

@@ -272,6 +272,22 @@ def test_commit_where_waves_take_over_from_lanes(T, ctx, n, dtype):
         srs.close()
 
 
+@pytest.mark.parametrize("count", [4, 31, 32, 64, 512])
+def test_commit_of_many_short_int16_tensors(T, ctx, count):
+    """Few entries and many buckets, 32768 to a tensor: accumulated by waves up to 31 tensors a call, by lanes from 32 on (at 512 waves for
+    every bucket would be more than a launch takes).  At most 16384 entries in all, the first tensor long and half of it in one bucket."""
+    lengths = [512] + [15872 // (count - 1) if count < 512 else 31] * (count - 1)
+    srs = {n: ctx.setup_from_trapdoor(TAU_BYTES, (n,), 0) for n in set(lengths)}
+    X = [tc_inputs.int16_uniform((n,), 40 + i, -32768, 32767) for i, n in enumerate(lengths)]
+    X[0][::2] = 32767
+    try:
+        got = ctx.commit_batch([srs[n] for n in lengths], [to_device(x) for x in X], [T.TC_I16] * count)
+        assert got == [ec.g1_to_bytes(cbind.commit(pps(x.shape), x, nthreads=8)) for x in X]
+    finally:
+        for s in srs.values():
+            s.close()
+
+
 def test_degenerate_bucket_loads_in_ordered_launches(T, ctx):
     """The same at 2^26 entries, where the accumulation hands its sub-runs out in the order of their lengths: a
     constant tensor (one bucket with a million sub-runs, all placed by one workgroup), and a tensor whose upper half is

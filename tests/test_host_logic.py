@@ -111,6 +111,23 @@ def test_emulated_commit_open_verify(emu):
     srs.close()
 
 
+@pytest.mark.parametrize("count", [1, 2, 4, 5, 8])
+def test_emulated_batches_of_short_int16_tensors(emu, count):
+    """Few entries and many buckets, 32768 to a tensor: by waves for some tensors a call, by lanes from then on (in this build four
+    and five), where waves for every bucket would be more work-items than a launch has (2^32; 2^25 in this build, whose launcher
+    refuses more, as the runtime does).  One tensor is long enough for the last pass to want four waves to a bucket."""
+    lengths = [66] + [34 // max(1, count - 1)] * (count - 1)
+    srs = [emu.setup_from_trapdoor(TAU_BYTES, (n,), 0) for n in lengths]
+    X = [tc_inputs.int16_uniform((n,), 40 + i, -32768, 32767) for i, n in enumerate(lengths)]
+    X[0][::2] = 32767                                         # the last bucket
+    try:
+        got = emu.commit_batch(srs, X, [T.TC_I16] * count)
+        assert got == [ec.g1_to_bytes(tc.commit(pps(x.shape), x)) for x in X]
+    finally:
+        for s in srs:
+            s.close()
+
+
 @pytest.mark.parametrize("shape", [(48, 131), (24, 85)])
 def test_emulated_int16_commits_over_several_tiles(emu, shape):
     """Tensors of a few thousand 16-bit terms span several ragged tiles of the count / scatter kernels, which read
