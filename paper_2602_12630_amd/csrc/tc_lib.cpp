@@ -376,6 +376,13 @@ static int launch_wave_groups(uint64_t groups, rt::stream_t st, const F& f) {
 }
 #endif
 
+/* Batches of proofs or of verification steps have no bound of their own: this many groups (of up to sixteen waves) a launch, one after the other. */
+#if defined(TC_HOST_EMU)
+static const uint64_t WAVE_GROUPS_AT_ONCE = 64;
+#else
+static const uint64_t WAVE_GROUPS_AT_ONCE = 1ull << 21;
+#endif
+
 /* cooperative launch whose number of phases is known only at run time */
 #if defined(TC_HOST_EMU)
 template <int BLOCK, class F>
@@ -724,7 +731,8 @@ static int normalize(tc_ctx* ctx, const g1_xyzz* d_in, uint64_t n, g1_affine* d_
 static int normalize_sums(tc_ctx* ctx, const uint32_t* d_raw, uint64_t n, uint32_t pieces, g1_affine* d_out, fr_plain* d_phi, uint32_t* d_canonical) {
     if (n > NORMALIZE_WAVES_MAX) {
         WS(sums, g1_xyzz, n);
-        RT(launch_wave_groups((uint32_t)n, ctx->stream, WindowWave{d_raw, pieces, nullptr, sums}));
+        for (uint64_t i = 0; i < n; i += WAVE_GROUPS_AT_ONCE)
+            RT(launch_wave_groups(std::min<uint64_t>(WAVE_GROUPS_AT_ONCE, n - i), ctx->stream, WindowWave{d_raw + i * pieces * WV_POINT_WORDS, pieces, nullptr, sums + i}));
         return normalize(ctx, sums, n, d_out, d_phi, d_canonical);
     }
     const WavePoints in{d_raw, WAVE_RAW};
@@ -1393,7 +1401,7 @@ static int reduce_windows(tc_ctx* ctx, const WavePoints& bucket, int count, int 
     }
     /* bit by bit */
     const uint32_t chains = bitsum_chains(lognb);
-    if ((uint64_t)windows * chains * BITSUM_PARTS > 0x7FFFFFFFull) return fail(ctx, TC_ERR_SHAPE, "too many windows in one launch");
+    if ((uint64_t)windows * chains * BITSUM_PARTS > LAUNCH_WORK_ITEMS / (BitSumWave::WAVES * 64u)) return fail(ctx, TC_ERR_SHAPE, "too many windows in one launch");
     WS(sums, uint32_t, (uint64_t)windows * chains * BITSUM_PARTS * WV_POINT_WORDS);
     WS(scaled, uint32_t, (uint64_t)windows * chains * WV_POINT_WORDS);
     WS(wsum, uint32_t, W > 1 ? (uint64_t)windows * WV_POINT_WORDS : 1u);
@@ -2394,15 +2402,18 @@ static int verify_steps(tc_ctx* ctx, const tc_vk* vk, const std::vector<VerifySt
     RT(rt::launch<256>(n, ctx->stream, Fill32{d_ok, 1u}));
     int mmax = 1;
     for (uint32_t i = 0; i < n; ++i) mmax = steps[i].m > mmax ? steps[i].m : mmax;
-    rt::event_t e0, e1;
-    prof_begin(ctx, TC_PROF_VERIFY_CHAIN, &e0, &e1);
-    int e;
-    if (mmax == 1) e = launch_wave_groups(n, ctx->stream, VerifyWave<1>{d_steps, ctx->gtable, d_ok});
-    else if (mmax == 2) e = launch_wave_groups(n, ctx->stream, VerifyWave<2>{d_steps, ctx->gtable, d_ok});
-    else if (mmax == 3) e = launch_wave_groups(n, ctx->stream, VerifyWave<3>{d_steps, ctx->gtable, d_ok});
-    else e = launch_wave_groups(n, ctx->stream, VerifyWave<4>{d_steps, ctx->gtable, d_ok});
-    prof_end(ctx, TC_PROF_VERIFY_CHAIN, e0, e1);
-    RT(e);
+    for (uint32_t s0 = 0; s0 < n; s0 += (uint32_t)WAVE_GROUPS_AT_ONCE) {
+        const uint64_t sn = std::min<uint64_t>(WAVE_GROUPS_AT_ONCE, n - s0);
+        rt::event_t e0, e1;
+        prof_begin(ctx, TC_PROF_VERIFY_CHAIN, &e0, &e1);
+        int e;
+        if (mmax == 1) e = launch_wave_groups(sn, ctx->stream, VerifyWave<1>{d_steps + s0, ctx->gtable, d_ok + s0});
+        else if (mmax == 2) e = launch_wave_groups(sn, ctx->stream, VerifyWave<2>{d_steps + s0, ctx->gtable, d_ok + s0});
+        else if (mmax == 3) e = launch_wave_groups(sn, ctx->stream, VerifyWave<3>{d_steps + s0, ctx->gtable, d_ok + s0});
+        else e = launch_wave_groups(sn, ctx->stream, VerifyWave<4>{d_steps + s0, ctx->gtable, d_ok + s0});
+        prof_end(ctx, TC_PROF_VERIFY_CHAIN, e0, e1);
+        RT(e);
+    }
     RT(rt::memcpy_d2h(ok.data(), d_ok, 4ull * n, ctx->stream));
     TRY(ctx_sync(ctx));
     return TC_OK;
@@ -3062,7 +3073,6 @@ extern "C" int tc_terkle_open_batch(tc_ctx* ctx, const tc_tree* t, int count, co
                 const uint64_t points = (uint64_t)ns->n[0] * FB_W;
                 const uint32_t per = (uint64_t)jobs * m * ((points + 31) / 32) <= OPEN_WAVES_SHORT ? 4 : 8;
                 const uint32_t pieces = (uint32_t)((points + 8 * per - 1) / (8 * per));
-                if ((uint64_t)jobs * m * pieces > 0x7FFFFFFFull) return fail(ctx, TC_ERR_ARG, "too many openings in one batch");
                 WS(d_q, fr_plain, (uint64_t)jobs * terms);
                 WS(d_sums, uint32_t, (uint64_t)jobs * m * pieces * WV_POINT_WORDS);
                 TRY(h2d(ctx, d_jobs, hj.data(), sizeof(NodeOpenJob) * jobs));
@@ -3072,15 +3082,19 @@ extern "C" int tc_terkle_open_batch(tc_ctx* ctx, const tc_tree* t, int count, co
                 RT(rt::launch<64>((uint64_t)jobs * terms, ctx->stream, k));
                 NodeOpenWave o;
                 memset((void*)&o, 0, sizeof o);
-                o.q = d_q;
                 o.terms_per_job = terms;
                 o.m = (uint32_t)m;
                 o.per = per;
                 o.pieces = pieces;
                 for (int a = 0; a <= 4; ++a) o.axis_first[a] = k.axis_first[a];
                 for (int a = 0; a < m; ++a) o.table[a] = ns->fb[a];
-                o.out = d_sums;
-                RT(launch_wave_groups(jobs * (uint32_t)m * pieces, ctx->stream, o));
+                const uint64_t at_once = std::max<uint64_t>(1, WAVE_GROUPS_AT_ONCE / ((uint64_t)m * pieces));
+                for (uint64_t j = 0; j < jobs; j += at_once) {
+                    const uint64_t jn = std::min<uint64_t>(at_once, jobs - j);
+                    o.q = d_q + j * terms;
+                    o.out = d_sums + j * m * pieces * WV_POINT_WORDS;
+                    RT(launch_wave_groups(jn * m * pieces, ctx->stream, o));
+                }
                 WS(aff, g1_affine, (uint64_t)jobs * m);
                 TRY(normalize_sums(ctx, d_sums, (uint64_t)jobs * m, pieces, aff, nullptr, d_can));
             } else {

@@ -206,6 +206,27 @@ def test_emulated_verification_of_every_order(emu, m):
     check_verification(emu, m)
 
 
+def test_emulated_proofs_in_several_launches(emu, node_srs):
+    """More openings and more verification steps than a launch of this build takes (64 groups of waves; 2^21 on the device): 90 paths of
+    three steps, every proof the oracle's, two wrong values told in their places."""
+    node, grid = (2, 2), (8, 6)
+    X = tc_inputs.int8_uniform(grid, 8)
+    tree = emu.terkle_build_entries(node_srs, X, T.TC_I8, grid, node)
+    try:
+        otree = terkle.build(pps, tc.as_flat_ints(X), grid, node)
+        leaves = [(i % 8, i % 6) for i in range(90)]
+        proofs = tree.open_batch(leaves)
+        for i, leaf in enumerate(leaves[:24]):
+            assert proofs[i] == serialize_steps(terkle.open_path(pps, otree, grid, node, leaf)), leaf
+        assert proofs[24:] == [proofs[i % 24] for i in range(24, 90)]
+        values = [ec.fr_to_bytes((int(X[leaf]) + (i in (3, 88))) % R) for i, leaf in enumerate(leaves)]
+        vk = emu.vk_from_trapdoor(TAU_BYTES)
+        got = emu.verify_paths_batch(vk, [tree.path(leaf) for leaf in leaves], [tree.root] * 90, values, proofs)
+        assert got == [i not in (3, 88) for i in range(90)]
+    finally:
+        tree.close()
+
+
 def test_emulated_entries_tree(emu, node_srs):
     node, grid = (2, 2), (5, 7)
     X = tc_inputs.int16_uniform(grid, 7)
