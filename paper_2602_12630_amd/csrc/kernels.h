@@ -2522,23 +2522,35 @@ struct AnyIdentity {           /* *found = 1 if one of the points is the identit
         if (affine_is_identity(pts[t])) *found = 1u;
     }
 };
+/* The lanes of that list by whole waves, which settle every case.  (Sums of lanes with products as calls went here before: the compiler made a
+ * v_swap_b32 of three moves around a call that returns one of the moved registers, and the doublings came out wrong.) */
 template <bool BOTTOM>
 struct NodeCommitRedo {
+    static constexpr int WAVES = 4;
+    static constexpr int PHASES = 1;
+    static constexpr size_t LDS_BYTES = 0;
     NodeCommit<BOTTOM> n;
-    uint32_t lanes;
-    TC_DEV void operator()(uint32_t lane) const {
-        for (uint32_t j = lane; j < *n.redo_count; j += lanes) {
+    uint32_t waves;             /* of the launch */
+    TC_DEV void phase(int, uint32_t wave, uint32_t wg, uint8_t*) const {
+        const uint32_t count = *n.redo_count;
+        if (wg * (uint32_t)WAVES >= count) return;
+        const wv_consts k = wv_constants();
+        const WavePoints pts{n.table, WAVE_AFFINE};
+        for (uint32_t j = wg * (uint32_t)WAVES + wave; j < count; j += waves) {
             const uint32_t t = n.redo_list[j];
             const uint64_t at = n.first + t;
-            xyzz_acc acc = acc_identity();
+            wv_point acc = wv_identity();
             typename NodeCommit<BOTTOM>::Cursor c;
             n.begin(at, c);
             for (uint32_t i = 0; i < n.terms(); ++i) {
                 uint64_t index;
                 bool negative;
-                if (n.term(at, i, c, index, negative)) acc_madd(acc, n.table[index], negative);
+                if (!n.term(at, i, c, index, negative)) continue;
+                wv_point p = pts.load(index);
+                if (negative) p.v = wv_negate(p.v);
+                wv_accumulate(k, acc, p);
             }
-            n.out[t] = acc_result(acc);
+            wv_store(n.out + t, acc);
         }
     }
 };

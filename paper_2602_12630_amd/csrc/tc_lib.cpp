@@ -2654,6 +2654,7 @@ static int tree_prepare(tc_ctx* ctx, const tc_tree_desc* desc, tc_tree** out) {
 
 /* a level of n nodes by lanes, a lane per node (bottom level) or per child, in chunks that bound the partial sums */
 static const uint64_t NODE_CHUNK_LANES = 1ull << 20;
+static const uint64_t NODE_REDO_GROUPS = 1024;          /* four waves on every SIMD: empty but for degenerate node bases */
 template <bool BOTTOM>
 static int node_commit_lanes(tc_ctx* ctx, NodeCommit<BOTTOM> k, bool identities, uint64_t n, g1_xyzz* out) {
     const uint32_t per = BOTTOM ? 1u : k.g.B;
@@ -2671,13 +2672,13 @@ static int node_commit_lanes(tc_ctx* ctx, NodeCommit<BOTTOM> k, bool identities,
     k.redo_list = redo + COUNTERS;
     for (uint64_t n0 = 0; n0 < n; n0 += chunk) {
         const uint64_t nodes = std::min<uint64_t>(chunk, n - n0), lanes = nodes * per;
-        const uint32_t redo_lanes = (uint32_t)std::min<uint64_t>(lanes, ACC_RESIDENT_LANES);
+        const uint32_t redo_groups = (uint32_t)std::min<uint64_t>((lanes + 3) / 4, NODE_REDO_GROUPS);
         k.first = n0 * per;
         k.out = per > 1 ? part[0] : out + n0;
         RT(rt::launch<64>(COUNTERS, ctx->stream, Fill32{redo, 0u}));
         if (identities) RT(rt::launch<64>(lanes, ctx->stream, ListAll{(uint32_t)lanes, k.redo_count, k.redo_list}));
         else RT((rt::launch_waves<64, 3>(lanes, ctx->stream, k)));
-        RT(rt::launch<64>(redo_lanes, ctx->stream, NodeCommitRedo<BOTTOM>{k, redo_lanes}));
+        RT(launch_wave_groups(redo_groups, ctx->stream, NodeCommitRedo<BOTTOM>{k, redo_groups * (uint32_t)NodeCommitRedo<BOTTOM>::WAVES}));
         /* sums of up to four, as many lanes as there are left; a prime arity above that in one go */
         int from = 0;
         uint32_t step = 0;

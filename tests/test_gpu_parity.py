@@ -1232,6 +1232,13 @@ def test_arity_64_trees(T, ctx, node, grid):
 
 
 @pytest.mark.parametrize("side", [64, 528])
+def test_tree_over_repeated_bases(ctx, side):
+    """Node bases that are one point and its negative: over 528 x 528 entries the lanes of the lowest two levels (69696 and 17424 nodes), and
+    the sums of a node's children, run into doublings and sums that cancel and give themselves up to their lists."""
+    check_tree_over_bases(ctx, to_device, lambda S: [S[0], S[0], ec.neg(S[0]), S[0]], side, 24)
+
+
+@pytest.mark.parametrize("side", [64, 528])
 @pytest.mark.parametrize("bases", sorted(NODE_BASES_WITH_IDENTITY))
 def test_tree_over_bases_with_the_identity(ctx, bases, side):
     """Node bases, or multiples of them, that are the identity (an imported SRS may hold such points): all levels by whole

@@ -47,6 +47,23 @@ def test_header_symbols_are_exported_by_the_product_library():
     assert set(names) == set(lib._tc_signatures), "binding and header disagree"
 
 
+def test_device_code_has_no_register_swaps(tmp_path):
+    """The device code of the product library, disassembled, must not hold a v_swap_b32.  The compiler forms one from three moves that
+    exchange two registers by way of a third; it does not see that a call between them returns its result in that third register
+    (the products of field elements are such calls), and the sum that follows has a wrong limb.  Nothing else here uses the
+    instruction."""
+    import shutil
+    import subprocess
+
+    tools = {t: shutil.which(t) or os.path.join("/opt/rocm/llvm/bin", t) for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-objdump")}
+    fat, code = str(tmp_path / "fat"), str(tmp_path / "code")
+    subprocess.check_call([tools["llvm-objcopy"], "--dump-section", ".hip_fatbin=" + fat, T.library_path(), str(tmp_path / "copy")])
+    subprocess.check_call([tools["clang-offload-bundler"], "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", "--input=" + fat, "--output=" + code])
+    text = subprocess.check_output([tools["llvm-objdump"], "-d", code], text=True)
+    assert text.count("s_swappc_b64") > 100 and "NodeCommitRedo" in text
+    assert text.count("v_swap_b32") == 0
+
+
 def test_product_library_fails_loudly_without_a_gpu():
     import torch
 
