@@ -294,23 +294,6 @@ TC_HD g1_xyzz xyzz_dbl_affine32(const g1_affine& p) {
     return r;
 }
 
-/* 2 P */
-TC_HD g1_xyzz xyzz_dbl32(const g1_xyzz& p) {
-    if (xyzz_is_identity(p) || fe_is_zero(p.Y)) return xyzz_identity();
-    fp_t U = fp_dbl(p.Y);
-    fp_t V = fp_sqr(U);
-    fp_t W = fp_mul(U, V);
-    fp_t S = fp_mul(p.X, V);
-    fp_t X2 = fp_sqr(p.X);
-    fp_t M = fp_add(fp_dbl(X2), X2);
-    g1_xyzz r;
-    r.X = fp_sub(fp_sub(fp_sqr(M), S), S);
-    r.Y = fp_sub(fp_mul(M, fp_sub(S, r.X)), fp_mul(W, p.Y));
-    r.ZZ = fp_mul(V, p.ZZ);
-    r.ZZZ = fp_mul(W, p.ZZZ);
-    return r;
-}
-
 /* acc + q, q affine (chord rule); falls back to the tangent rule / identity when needed */
 TC_HD g1_xyzz xyzz_madd32(const g1_xyzz& a, const g1_affine& q) {
     if (affine_is_identity(q)) return a;

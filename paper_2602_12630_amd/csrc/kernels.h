@@ -2133,24 +2133,25 @@ struct ShiftPoints {
 };
 
 /* ---- normalisation: XYZZ -> affine (batched inversion) and canonical bytes ---------- */
-/* A workgroup is one wave and takes `leaves` (a power of two, at most 64) runs of G consecutive points with ONE field
- * inversion: a lane multiplies the denominators of its run up (the running products parked in out[i] until the
+/* Many points: a workgroup is one wave and takes 64 runs of G consecutive points with ONE field inversion: a lane
+ * multiplies the denominators of its run up (the running products parked in out[i] until the
  * backward sweep overwrites them), the lanes' products are multiplied pairwise up a binary tree in LDS, the root is
  * inverted by the whole wave (fp28_inv_wave) and the inverses come back down the tree, every child taking its parent's
  * inverse times its sibling's product.  phi and the canonical bytes of a point are written along with it where the
  * caller wants them: the point is in registers, and a launch of their own costs as much as their arithmetic.
  * Bound by depth: two products per level of the tree in a lone wave, and the inversion.  131072 points 84 us (phi included), 8192 points
  * 51 us.
- * Phases: 0 run products, 1 .. 6 up (one level each), 7 inversion, 8 .. 13 down, 14 backward sweep; levels above the
- * root of a smaller tree are empty. */
+ * Phases: 0 run products, 1 .. 6 up (one level each), 7 inversion, 8 .. 13 down, 14 backward sweep; a lane without points
+ * takes part with the product 1. */
 struct BatchNormalize {
     static constexpr int BLOCK = 64;
+    static constexpr uint32_t LEAVES = BLOCK;
     static constexpr int PHASES = 15;
     static constexpr size_t NODE_BYTES = sizeof(fp28);
     static constexpr size_t LDS_BYTES = 2 * 128 * NODE_BYTES;      /* products and inverses: node i has children 2 i, 2 i + 1 */
     const g1_xyzz* in;
     uint64_t n;
-    uint32_t G, leaves;
+    uint32_t G;
     g1_affine* out;
     fr_plain* phi;          /* or null */
     uint32_t* canonical;    /* 24 words per point, or null */
@@ -2158,17 +2159,16 @@ struct BatchNormalize {
     TC_DEV void phase(int ph, uint32_t lane, uint32_t wg, uint8_t* lds) const {
         fp28* prod = (fp28*)lds;
         fp28* inv = prod + 128;
-        const uint64_t lo = ((uint64_t)wg * leaves + lane) * G, end = lo + G < n ? lo + G : n, hi = lane < leaves && lo < end ? end : lo;
+        const uint64_t lo = ((uint64_t)wg * LEAVES + lane) * G, end = lo + G < n ? lo + G : n, hi = lo < end ? end : lo;
         if (ph == 0) {
-            if (lane >= leaves) return;
             fp28 run = fp28_one();
             for (uint64_t i = lo; i < hi; ++i) {
                 if (G > 1) *(fp28*)&out[i] = run;                  /* product of the denominators before i */
                 if (!fe_is_zero(in[i].ZZ)) run = G > 1 ? fp28_mul(run, denominator(in[i])) : denominator(in[i]);
             }
-            prod[leaves + lane] = run;
+            prod[LEAVES + lane] = run;
         } else if (ph <= 6) {
-            uint32_t width = leaves >> ph;
+            uint32_t width = LEAVES >> ph;
             if (lane < width) prod[width + lane] = fp28_mul(prod[2 * (width + lane)], prod[2 * (width + lane) + 1]);
         } else if (ph == 7) {
             /* the product of non-zero values is not zero */
@@ -2180,10 +2180,10 @@ struct BatchNormalize {
 #endif
         } else if (ph <= 13) {
             uint32_t width = 2u << (ph - 8);
-            if (width <= leaves && lane < width) inv[width + lane] = fp28_mul(inv[(width + lane) >> 1], prod[(width + lane) ^ 1u]);
+            if (lane < width) inv[width + lane] = fp28_mul(inv[(width + lane) >> 1], prod[(width + lane) ^ 1u]);
         } else {
             if (lo >= hi) return;
-            fp28 rest = inv[leaves + lane];
+            fp28 rest = inv[LEAVES + lane];
             for (uint64_t i = hi; i-- > lo;) {
                 g1_xyzz p = in[i];
                 g1_affine r = affine_identity();

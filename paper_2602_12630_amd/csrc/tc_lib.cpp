@@ -718,13 +718,11 @@ static int normalize(tc_ctx* ctx, const g1_xyzz* d_in, uint64_t n, g1_affine* d_
         return TC_OK;
     }
     /* one point per lane up to four waves per compute unit, then longer runs (of up to 16: past that the tree and the
-     * inversion are a small share); fewer than 64 points take a tree of their own height */
+     * inversion are a small share) */
     uint32_t G = (uint32_t)std::min<uint64_t>(16, (n + 65535) / 65536);
     uint64_t runs = (n + G - 1) / G;
-    uint32_t leaves = 1;
-    while (leaves < 64 && leaves < runs) leaves *= 2;
-    BatchNormalize k{d_in, n, G, leaves, d_out, d_phi, d_canonical};
-    RT((launch_coop<BatchNormalize::BLOCK>((uint32_t)((runs + leaves - 1) / leaves), ctx->stream, k)));
+    BatchNormalize k{d_in, n, G, d_out, d_phi, d_canonical};
+    RT((launch_coop<BatchNormalize::BLOCK>((uint32_t)((runs + BatchNormalize::LEAVES - 1) / BatchNormalize::LEAVES), ctx->stream, k)));
     return TC_OK;
 }
 /* the same for n sums in `pieces` raw points each */
