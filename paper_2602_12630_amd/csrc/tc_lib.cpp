@@ -1565,8 +1565,9 @@ static const uint64_t SORT_MIN_BIN_LOAD = SORT_TILE / 4;
  * WAVE_ACC_MAX_BUCKETS: the same in buckets, each of which then takes a wave of its own in the last pass; above it that pass goes by lanes.  Whole
  * calls with int16 tensors (32768 buckets each), accumulated and summed by waves / lanes: 16 tensors of 1024 entries 923 / 944 us, 24 of 600
  * 1043 / 1068, 32 of 32 732 / 534, 96 of 32 1708 / 1053.
- * WAVE_PASS_MAX: partial sums that go straight into the buckets (BucketWave).  Whole calls at 1.93e5 and 1e5 partial sums with
- * the line at 200000 / 110000: 512 x 4096 int16 826 / 769 us, 487 x 11008 1320 / 1241 us; where the pass by lanes that it saves is one over
+ * WAVE_PASS_MAX: partial sums that go straight into the buckets (BucketWave).  Whole calls, one int16 tensor, after a pass by lanes / straight
+ * away: 400000 terms (67 000 sums) 487 / 397 us, 700000 (109 000) 460 / 464, 2^20 (160 000) 519 / 552, 2^21 (202 000) 749 / 809, 3e6 (200 000)
+ * 854 / 914; where the pass by lanes that it saves is one over
  * 131072 buckets or more, with three launches of prefix sums, twice as many: four tensors of 64 x 4096 in one call 805 / 1015 us. */
 #if defined(TC_HOST_EMU)
 /* the CPU build of the tests walks both sides with small problems */
@@ -1674,10 +1675,12 @@ static int msm_engine_multi(tc_ctx* ctx, int count, const MsmProblem* prob, int 
      * once (the accumulation kernel keeps 3 waves per SIMD), so that the second round evens out what the first left uneven (with 64 entries the
      * LLaMA2-7B-shaped step takes 125.9 ms, and no less with 80 to 128).
      * Others: just as many as the chip holds at once (a bucket's last sub-run is half full on average: an eighth of the buckets for them,
-     * most being empty), as long as that is seven entries or more, since every sub-run is a sum that the passes add up (whole
-     * calls at 6 / 9 / 11 / 14 / 22 entries, int16: 2^21 terms 848 / 781 / 748 / 880 / 768 us; at 14 / 20 / 28 / 30: 5.4e6 terms 1262 / 1398 / 1234 /
-     * 1276 us); from there down seven, or four below 2.6e5 terms, where the chain of a sub-run counts (at 4 / 7 / 11: 2^18 terms 426 / 402 / 408 us,
-     * 2^16 terms 323 / 342 / 375 us).  Not longer than half the average bucket load: longer sub-runs leave the lanes of a wave
+     * most being empty), as long as that is seven entries or more, since every sub-run is a sum that the passes add up; from there down
+     * seven, or four below 2.6e5 terms, where the chain of a sub-run counts.  Whole calls, int16 of a normal distribution, at 4 / 7 / 11 / 14 / 18 /
+     * 28 entries: 2^16 terms 288 / 305 / 341 / 372 / 405 / 406 us, 2^18 terms 360 / 337 / 356 / 380 / 418 / 491, 2^20 terms 594 / 522 / 502 / 523 /
+     * 567 / 519, 2^21 terms 782 / 773 / 745 / 718 / 789 / 769, 5.4e6 terms 1396 / 1274 / 1243 / 1210 / 1272 / 1342, 8e6 terms 1917 / 1821 / 1714 / 1675 /
+     * 1646 / 1751; the rule takes 4, 7, 7, 11, 28 (1330 us) and 42 (1840): within 8 % of the best up to 2^21 terms, 10 to 12 % above it at 5 to 8 million.
+     * The saw of those rows is the last round of lanes.  Not longer than half the average bucket load: longer sub-runs leave the lanes of a wave
      * with very different amounts of work. */
     uint32_t L1 = (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(4, (items + 2 * ACC_RESIDENT_LANES - 1) / (2 * ACC_RESIDENT_LANES)));
     if (ctx->static_mode || items / L1 + nbk + 1 < ORDERED_LANES_MIN) {

@@ -190,8 +190,8 @@ def check_one_point_throughout(ctx, upload, shape):
 def check_repeated_points(ctx, upload, many=512):
     """Commitments over public parameters in which most points repeat or are each other's negatives, with scalars of
     few distinct values: the bucket sums then run into doublings, sums that cancel to the identity and additions to
-    the identity, the cases that the accumulation kernel's fast form of the chord rule hands to the slower routine.
-    Then the same in batches: eight int16 tensors in one call (the row and column sums of their 128 x 256 bucket
+    the identity.  At 4096 entries a call these go by whole waves on the device.
+    Then the same in batches, where lanes accumulate and the fast form of the chord rule hands those cases to the slower routine: eight int16 tensors in one call (the row and column sums of their 128 x 256 bucket
     matrices go one lane per piece, with a list for the sums that meet equal or opposite points) and `many` int8
     tensors in one call (that many windows of 128 buckets, a lane per row and column).
     Expected values: the C oracle's term-by-term sum over the same points.  `upload` puts a numpy array where the

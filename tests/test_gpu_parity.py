@@ -109,8 +109,8 @@ def test_options_do_not_change_results(T, ctx):
 
 
 def test_commit_over_repeated_points(ctx):
-    """Equal and opposite points inside the bucket sums: the sub-runs that the fast accumulation gives up and the
-    second launch redoes with every case of the group law (see check_repeated_points)."""
+    """Equal and opposite points inside the bucket sums (see check_repeated_points): single tensors, which whole waves sum, and batches,
+    where the fast accumulation gives sub-runs up and the second launch redoes them with every case of the group law."""
     check_repeated_points(ctx, to_device)
 
 
@@ -1252,7 +1252,7 @@ def test_verification_of_every_order(ctx, m):
     check_verification(ctx, m)
 
 
-def test_verification_in_chunks(T, ctx, node_srs):
+def test_verification_of_many_steps(T, ctx, node_srs):
     """Thousands of steps in one batch: 1400 paths of 3 steps through a (64, 64) entries tree,
     a few of them with a wrong value or a damaged proof; the verdicts must come out per path, in order."""
     grid, node = (64, 64), tc_inputs.NODE_SHAPE
@@ -1269,7 +1269,7 @@ def test_verification_in_chunks(T, ctx, node_srs):
         paths = [tree.path(l) for l in leaves]
         values = [ec.fr_to_bytes(int(X[l]) % R) for l in leaves]
         want = [True] * len(leaves)
-        for i in (3, 1365, 1366, 1399):                     
+        for i in (3, 1365, 1366, 1399):
             values[i] = ec.fr_to_bytes((int(X[leaves[i]]) + 1) % R)
             want[i] = False
         damaged = bytearray(proofs[1370])
