@@ -124,7 +124,7 @@ int tc_ctx_profile_units(tc_ctx* ctx, int kind, uint64_t* units);
  *   TC_ALU_FP_MUL / TC_ALU_FP_SQR   Fp products / squarings per second of the library's own routines in a chain
  *                     (one product = 300 multiply-adds, one squaring 234);
  *   TC_ALU_FP_MUL_F64 / TC_ALU_FP_SQR_F64   the same for the exact variants on the FP64 pipe;
- *   TC_ALU_FP28_MUL / TC_ALU_FP28_SQR     the same for the carry-free form of the bucket accumulation (14 signed limbs
+ *   TC_ALU_FP28_MUL / TC_ALU_FP28_SQR     the same for the carry-free form of the group law (14 signed limbs
  *                     of 28 bits: 392 multiply-adds a product, 301 a squaring, no carry instructions). */
 #define TC_ALU_MAD 0
 #define TC_ALU_MAD_CARRY 1
@@ -196,7 +196,7 @@ int tc_srs_get_point(tc_ctx* ctx, const tc_srs* srs, int first_axis, uint64_t in
  * the size; a buffer that is too small gives TC_ERR_ARG.
  * Import: builds an SRS equal to the exported one on this context's GPU.  A truncated or overlong buffer, a wrong
  * magic / version / curve, flags, shape or point count that do not fit together give TC_ERR_ARG or TC_ERR_SHAPE; a
- * point that is not canonical or not on the curve gives TC_ERR_RANGE.  (That the points are the powers of a
+ * point that is not canonical or not on the curve gives TC_ERR_RANGE; the identity is taken.  (That the points are the powers of a
  * trapdoor nobody knows is the trusted party's promise; no check here can replace it.) */
 int tc_srs_export(tc_ctx* ctx, const tc_srs* srs, void* host_buf, size_t* len);
 int tc_srs_import(tc_ctx* ctx, const void* host_buf, size_t len, tc_srs** out);

@@ -1,5 +1,5 @@
 /*
- * A second form of Fp for the bucket accumulation: 14 signed limbs of 28 bits, Montgomery radix 2^392.
+ * A second form of Fp, for the group law: 14 signed limbs of 28 bits, Montgomery radix 2^392.
  *
  * Why: in the 12 x 32-bit form every limb product (v_mad_u64_u32) is followed by an addition that carries into the
  * third word of the column sum, and every modular addition is a carry chain with a conditional subtraction.  With

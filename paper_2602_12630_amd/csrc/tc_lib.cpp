@@ -1561,7 +1561,7 @@ static const uint64_t SORT_MIN_BIN_LOAD = SORT_TILE / 4;
 /* Sums by whole waves.  A wave's addition costs the chip about 1 ns (1.6 us in the wave, a thousand SIMDs), a lane's 0.4 ns, but 15 us each
  * in a row and 25 to 40 us for the prefix sums between two passes; the lines lie where the two meet.
  * WAVE_ACC_MAX_ITEMS: entries of a launch that are accumulated by waves (AccWave; lanes took 45 us and up whatever there was, and
- * AccFinal 50: commitment of 1024 int8 entries 121 -> 15 us for the two).
+ * a last pass of theirs 50: commitment of 1024 int8 entries 121 -> 15 us for the two).
  * WAVE_ACC_MAX_BUCKETS: the same in buckets, each of which then takes a wave of its own in the last pass; above it that pass goes by lanes.  Whole
  * calls with int16 tensors (32768 buckets each), accumulated and summed by waves / lanes: 16 tensors of 1024 entries 923 / 944 us, 24 of 600
  * 1043 / 1068, 32 of 32 732 / 534, 96 of 32 1708 / 1053.
